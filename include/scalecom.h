@@ -23,7 +23,7 @@
  *    pointers marked [host] are ordinary process memory, read before the call returns.
  *  - The caller owns every buffer, including the workspace; the library allocates no
  *    device memory.  Per context it keeps pinned host staging for its tile tables
- *    (about numel_max / 256 + 140 * n_tensors_max + 64 KB bytes).
+ *    (about numel_max / 256 + 140 * n_tensors_max + 128 KB bytes).
  *  - The workspace is the caller's allocation but the library's to use: from scalecom_init until
  *    scalecom_destroy it holds the library's tables, counters and threshold predictions, and
  *    the caller must neither write to it nor hand it to anything else.  What it holds never
@@ -78,7 +78,8 @@ typedef enum {
  * Bytes of device workspace needed for up to n_learners_max learners with vectors of up to
  * numel_max elements each, split into at most n_tensors_max segments (1 for whole-vector
  * use), with index sets of at most k_max positions in total per step.  Pure host arithmetic
- * (about 0.8 * numel_max + (4 * n_learners_max + 16) * k_max + 105 KB * n_tensors_max bytes).
+ * (about 0.8 * numel_max + 4 * min(numel_max, 4 M) + (4 * n_learners_max + 16) * k_max +
+ * 170 KB * n_tensors_max bytes).
  * Returns 0 if an argument is out of range (numel_max < 0 or > 2^31 - 1, n_tensors_max < 1,
  * n_learners_max outside 1 .. SCALECOM_MAX_LEARNERS, k_max < 0 or > numel_max).
  */
@@ -126,7 +127,7 @@ scalecom_status scalecom_step(scalecom_ctx* ctx, float* const* mem, const void* 
  * scalecom_step for callers that cannot allocate device memory or pass a workspace along: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  No context and
  * no workspace argument: the scratch memory is a static device array inside the library
- * (about 8.5 MB, held by every GPU the library is used on until the process ends), which bounds
+ * (about 13 MB, held by every GPU the library is used on until the process ends), which bounds
  * the sizes: numel <= SCALECOM_STATIC_NUMEL_MAX, n_learners <= SCALECOM_STATIC_LEARNERS_MAX,
  * k <= SCALECOM_STATIC_K_MAX; anything larger is EINVAL (the detail names the limit) and belongs
  * to scalecom_step.  The call allocates nothing, on the device or through any library: it looks up
@@ -275,10 +276,12 @@ scalecom_status scalecom_layer_ks(int n_tensors, const double* flops_per_gradien
  * context's stream, then copies the counters to the host; nothing in scalecom_step* waits.
  *   counts_out [host] uint64[SCALECOM_N_STATS]:
  *     [SCALECOM_STAT_MISSED]        the threshold fell outside the expected range: two more passes
- *                                   over the leader's vector in that step
+ *                                   over the leader's vector in that step (on short layouts, up to
+ *                                   2 M elements or 4 M in several tensors: a longer search)
  *     [SCALECOM_STAT_NO_PREDICTION] nothing was expected yet (first step of a layout): same cost
  *     [SCALECOM_STAT_FULL_MODE]     so many equal or clustered magnitudes at the threshold that the
  *                                   last two search levels were passes over the leader's vector too
+ *                                   (short layouts: a longer search)
  *     [SCALECOM_STAT_WIDE_RANGE]    the range was wider than 2^19 magnitudes and held the threshold:
  *                                   one more pass over the listed magnitudes, none over the vector
  *     [SCALECOM_STAT_STEPS]         calls of scalecom_step / scalecom_step_layers counted

@@ -67,6 +67,20 @@ struct ChunkDesc {        // one per scan chunk: up to kChunk consecutive supert
     int32_t pad;
 };
 
+struct PartDesc {         // short layouts: one block's consecutive positions of ONE segment (four per thread)
+    int32_t seg;
+    int32_t a0;           // first position, a multiple of 4 (may lie up to 3 before begin)
+    int32_t begin, end;   // the segment's positions [begin, end)
+    int32_t k;            // size of the segment's index set
+    int32_t out_base;     // first output slot of the segment
+    int32_t part_first;   // the segment's first part
+    int32_t n_parts;      // number of its parts, at most kShortSegParts
+};
+
+constexpr int kShortPartMax = 8192;              // positions of a part (blocks of 256, 512 or 1024 threads, four or eight positions each)
+constexpr int kShortSegParts = 256;              // parts of one segment
+constexpr int kShortPartsMax = 1280;             // parts of a layout
+
 struct SegState {         // selection state of one segment after a level; every field is rewritten by k_level0 each step
     uint32_t prefix;      // key bits fixed so far (level 0: 12 bits, level 1: 24 bits)
     uint32_t k_rem;       // members still to be found inside the current bucket
@@ -128,6 +142,8 @@ __host__ __device__ constexpr uint32_t clamp_width(uint32_t w)
 constexpr int kPredWords = 8;                    // [0] 1 if there is one, [1] top 24 bits of the last threshold, [2] w,
                                                  // [3] steps in a row in which the threshold fell into the range's middle half,
                                                  // [4] (float) by how much the last leader's threshold grew since its previous turn
+                                                 // [5] short layouts: log2 of the keys per narrow column (0: no prediction), [6] calm steps
+constexpr int kPredShortWidth = 5, kPredShortCalm = 6;
 constexpr uint32_t kCalmSteps = 8;               // so many of those before the range is made narrower
 // Counts of the predicted pass, per segment: [0] keys above the range, [1] keys inside it.
 // Blocks add into one of kPartSlots copies (same-address atomics from thousands of blocks would

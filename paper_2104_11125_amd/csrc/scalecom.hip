@@ -44,6 +44,8 @@
 // done, never what is selected.  The output is ascending by position and deterministic.
 // Nothing here is a dense contraction, so there is no MFMA; the kernels are bound by HBM traffic
 // (update, predicted) and by launch latency (the small ones).
+// Short layouts (see short_parts) take two kernels instead: `short_collect` sorts the leader's keys by their
+// distance from the expected threshold, `short_step` searches, updates and sums (short_kernels.h).
 // The chunk-wise selector (scalecom_step_chunked, scalecom_step_layers_chunked) replaces everything
 // before `update` by chunk_select + chunk_marks.
 
@@ -66,6 +68,7 @@
 #include "select_kernels.h"
 #include "update_kernels.h"
 #include "chunk_kernels.h"
+#include "short_kernels.h"
 #include "aux_kernels.h"
 
 namespace {
@@ -87,12 +90,18 @@ constexpr int64_t max_chunks(int64_t numel_max, int n_tensors_max)
 
 struct WsLayout {
     size_t segs, sts, chunks, hblocks, small, preds, stats, state, wt_cnt, st_sum, st_prefix, chunk_tot, st_cand_cnt, cand, sel_mask,
-        eq_mask, tile_slot, vals, best, total;
+        eq_mask, tile_slot, vals, best, parts, short_used, short_counts, short_keys, total;
+    int64_t short_numel;   // positions that the short path's key array is made for
+    size_t short_words;    // and its words
     // per-step counters and histograms: one zone, all zero between steps (offsets inside the zone)
     size_t zone, zone_bytes, z_overflow, z_p_used, z_full_flag, z_part, z_hist0, z_hist1, z_hist1_spec, z_hist2;
 };
 
-constexpr WsLayout layout_for(int64_t numel_max, int n_tensors_max, int n_learners_max, int64_t k_max)
+// Layouts of at most this many positions may take the short path (see short_parts).
+constexpr int64_t kShortNumelMax = 4 * 1024 * 1024;
+
+constexpr WsLayout layout_for(int64_t numel_max, int n_tensors_max, int n_learners_max, int64_t k_max,
+                              int64_t short_numel_max = kShortNumelMax)
 {
     const size_t nt = static_cast<size_t>(n_tensors_max);
     const size_t nst = static_cast<size_t>(max_supertiles(numel_max, n_tensors_max));
@@ -143,6 +152,14 @@ constexpr WsLayout layout_for(int64_t numel_max, int n_tensors_max, int n_learne
     l.tile_slot = take(ntile * sizeof(uint32_t));
     l.vals = take(static_cast<size_t>(n_learners_max) * static_cast<size_t>(k_max) * sizeof(float));
     l.best = take(static_cast<size_t>(k_max) * sizeof(unsigned long long));       // chunk-wise selector: a word per chunk
+    // short path: the parts, what each segment's list starts from, counts and keys per part
+    l.parts = take(kShortPartsMax * sizeof(PartDesc));
+    l.short_used = take(nt * sizeof(uint4));
+    l.short_counts = take(static_cast<size_t>(kShortPartsMax) * kShortCols * sizeof(uint16_t));
+    l.short_numel = numel_max < short_numel_max ? numel_max : short_numel_max;
+    // a segment's first and last part may be partly empty
+    l.short_words = static_cast<size_t>(l.short_numel) + 2 * (nt < 256 ? nt : 256) * static_cast<size_t>(kShortPartMax);
+    l.short_keys = take(l.short_words * sizeof(uint32_t));
     l.total = o;
     return l;
 }
@@ -168,6 +185,7 @@ struct scalecom_ctx {
     // tables of the layout used last, kept on the device until the layout changes
     std::vector<int64_t> cached_offsets, cached_ks, cached_chunks;
     int n_st = 0, n_chunks = 0, n_hblocks = 0, n_small = 0;
+    int short_threads = 0, short_rows = 0, n_parts = 0;   // the layout's ShortPlan
     // segments of one supertile are searched by a kernel of their own, on a second stream beside the
     // leader pass (contexts for more than one tensor only)
     hipStream_t side = nullptr;
@@ -227,7 +245,42 @@ size_t pinned_bytes_for(int64_t numel_max, int n_tensors_max)
            align_up(sizeof(StDesc) * static_cast<size_t>(max_supertiles(numel_max, n_tensors_max)), 256) +
            align_up(sizeof(ChunkDesc) * static_cast<size_t>(max_chunks(numel_max, n_tensors_max)), 256) +
            align_up(sizeof(HistBlock) * (kHistGridMax + static_cast<size_t>(n_tensors_max)), 256) +
-           sizeof(HistBlock) * static_cast<size_t>(n_tensors_max);
+           align_up(sizeof(HistBlock) * static_cast<size_t>(n_tensors_max), 256) + sizeof(PartDesc) * kShortPartsMax;
+}
+
+// Does a layout take the short path (k_short_collect, k_short_step), and with how many threads per block
+// and rows of four positions per thread?  Every block of that path does the search for its segment, whose
+// cost grows with the segment's parts, so the smallest part is taken with which no segment has more than 256
+// (up to there one vector of 1 M positions takes 25 us a step either way, and the long path 42 us) and all
+// segments together 1280.  Beyond 2 M positions in one vector the update of all learners by one block at a time
+// (5.5 to 6 TB/s against 6.5) costs what the launches saved (2.05 M x 8 learners, bf16: 56 us against 62 us;
+// 3.5 M x 8, f32: 96 against 92); a layout of several tensors has more to save (60 tensors, 2.4 M x 4
+// learners, bf16: 45 us against 91 us).
+struct ShortPlan {
+    int threads = 0, rows = 0, n_parts = 0;      // threads 0: the long path
+    int64_t part() const { return static_cast<int64_t>(threads) * rows * kVec; }
+};
+
+ShortPlan short_parts(const WsLayout& l, int n_tensors, const int64_t* offsets)
+{
+    const int64_t total = offsets[n_tensors] - offsets[0];
+    if (total > l.short_numel || (n_tensors == 1 && total > kShortNumelMax / 2)) return ShortPlan{};
+    for (ShortPlan p : {ShortPlan{256, 1}, ShortPlan{512, 1}, ShortPlan{1024, 1}, ShortPlan{1024, 2}}) {
+        int64_t n = 0;
+        bool fits = true;
+        for (int s = 0; s < n_tensors; ++s) {
+            const int64_t b = offsets[s], e = offsets[s + 1];
+            if (e == b) continue;
+            const int64_t count = (e - (b & ~static_cast<int64_t>(kVec - 1)) + p.part() - 1) / p.part();
+            fits = fits && count <= kShortSegParts;
+            n += count;
+        }
+        if (fits && n <= kShortPartsMax && static_cast<size_t>(n * p.part()) <= l.short_words) {
+            p.n_parts = static_cast<int>(n);
+            return p;
+        }
+    }
+    return ShortPlan{};
 }
 
 // Rebuild and upload the segment, supertile, chunk and block tables if the layout differs from the cached one.
@@ -299,6 +352,24 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
         // a segment of one supertile with a non-empty index set: searched by one block of k_small
         if (count == 1 && ks[s] > 0 && ctx->side) small[n_small++] = hblocks[n_hb - 1];
     }
+    const ShortPlan plan = sel_chunks ? ShortPlan{} : short_parts(ctx->lay, n_tensors, offsets);
+    if (plan.threads > 0) {
+        PartDesc* parts = reinterpret_cast<PartDesc*>(
+            ctx->pinned + sm_off + align_up(sizeof(HistBlock) * static_cast<size_t>(ctx->n_tensors_max), 256));
+        const int64_t part = plan.part();
+        int32_t n = 0;
+        for (int s = 0; s < n_tensors; ++s) {
+            if (segs[s].end == segs[s].begin) continue;
+            const int64_t a_first = segs[s].begin & ~(kVec - 1);
+            const int32_t count = static_cast<int32_t>((segs[s].end - a_first + part - 1) / part);
+            for (int32_t j = 0; j < count; ++j)
+                parts[n + j] = PartDesc{s, static_cast<int32_t>(a_first + j * part), segs[s].begin, segs[s].end,
+                                        segs[s].k, segs[s].out_base, n, count};
+            n += count;
+        }
+        SC_HIP(ctx, hipMemcpyAsync(ctx->ws + ctx->lay.parts, parts, sizeof(PartDesc) * plan.n_parts, hipMemcpyHostToDevice,
+                                   ctx->stream));
+    }
     SC_HIP(ctx, hipMemcpyAsync(ctx->ws + ctx->lay.segs, segs, sizeof(SegDesc) * n_tensors, hipMemcpyHostToDevice,
                                ctx->stream));
     if (n_st > 0) {
@@ -328,6 +399,9 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
     ctx->n_chunks = static_cast<int>(n_ch);
     ctx->n_hblocks = static_cast<int>(n_hb);
     ctx->n_small = static_cast<int>(n_small);
+    ctx->short_threads = plan.threads;
+    ctx->short_rows = plan.rows;
+    ctx->n_parts = plan.n_parts;
     ctx->cached_offsets.assign(offsets, offsets + n_tensors + 1);
     ctx->cached_ks.assign(ks, ks + n_tensors);
     ctx->cached_chunks = ch;
@@ -470,6 +544,41 @@ void launch_select(scalecom_ctx* ctx, const float* memL, const G* gradL, float l
     }
 }
 
+// The exact step on a short layout: two launches, nothing of the scratch zone is used.
+template <typename G, int T, int R, typename Mark>
+void launch_short_as(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learners, float beta, float lr, int leader,
+                  uint32_t* preds, uint32_t* lead_mine, int32_t* idx_out, float* red_out, Mark&& mark)
+{
+    char* ws = ctx->ws;
+    const WsLayout& l = ctx->lay;
+    const PartDesc* parts = reinterpret_cast<const PartDesc*>(ws + l.parts);
+    uint4* used = reinterpret_cast<uint4*>(ws + l.short_used);
+    uint16_t* counts = reinterpret_cast<uint16_t*>(ws + l.short_counts);
+    uint32_t* keys = reinterpret_cast<uint32_t*>(ws + l.short_keys);
+    unsigned long long* stats = reinterpret_cast<unsigned long long*>(ws + l.stats);
+    k_short_collect<G, T, R><<<ctx->n_parts, T, 0, ctx->stream>>>(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), lr,
+                                                               parts, preds, lead_mine, used, counts, keys, stats);
+    mark(1);
+    mark(2);
+    mark(3);
+    k_short_step<G, T, R><<<ctx->n_parts, T, 0, ctx->stream>>>(lp, n_learners, leader, lr, beta, 1.0f - beta, parts, preds,
+                                                            lead_mine, used, counts, keys, idx_out, red_out, stats);
+    mark(4);
+}
+
+template <typename G, typename... Args>
+void launch_short(scalecom_ctx* ctx, Args&&... args)
+{
+    if (ctx->short_threads == 256)
+        launch_short_as<G, 256, 1>(ctx, args...);
+    else if (ctx->short_threads == 512)
+        launch_short_as<G, 512, 1>(ctx, args...);
+    else if (ctx->short_rows == 1)
+        launch_short_as<G, 1024, 1>(ctx, args...);
+    else
+        launch_short_as<G, 1024, 2>(ctx, args...);
+}
+
 template <typename G>
 scalecom_status launch_step(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learners, int n_tensors, int64_t k_total,
                             float beta, float lr, int leader, int32_t* idx_out, float* red_out)
@@ -487,6 +596,13 @@ scalecom_status launch_step(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_lear
         // this leader's own last thresholds, kept behind the per-segment predictions
         uint32_t* lead_mine = preds + (static_cast<size_t>(kPredWords) + static_cast<size_t>(leader)) *
                                           static_cast<size_t>(ctx->n_tensors_max);
+        if (ctx->short_threads > 0) {
+            launch_short<G>(ctx, lp, n_learners, beta, lr, leader, preds, lead_mine, idx_out, red_out, mark);
+            mark(5);
+            if (timed) ++ctx->prof_steps;
+            SC_HIP(ctx, hipGetLastError());
+            return SCALECOM_OK;
+        }
         launch_select<G>(ctx, lp.mem[leader], static_cast<const G*>(lp.grad[leader]), lr, n_tensors, preds, lead_mine,
                          reinterpret_cast<unsigned long long*>(ctx->ws + ctx->lay.stats), false, mark);
         mark(3);
@@ -684,7 +800,8 @@ scalecom_status launch_hamming(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
 constexpr int64_t kStaticNumelMax = SCALECOM_STATIC_NUMEL_MAX;
 constexpr int kStaticLearnersMax = SCALECOM_STATIC_LEARNERS_MAX;
 constexpr int64_t kStaticKMax = SCALECOM_STATIC_K_MAX;
-constexpr WsLayout kStaticLayout = layout_for(kStaticNumelMax, 1, kStaticLearnersMax, kStaticKMax);
+constexpr int64_t kStaticShortMax = 1 << 20;      // longer vectors take the long path: four bytes per position are kept for the short one
+constexpr WsLayout kStaticLayout = layout_for(kStaticNumelMax, 1, kStaticLearnersMax, kStaticKMax, kStaticShortMax);
 constexpr size_t kStaticBytes = kStaticLayout.total;
 static_assert(kStaticBytes <= (size_t{16} << 20), "the static workspace stays modest");
 
@@ -712,8 +829,8 @@ scalecom_status static_fail(scalecom_status st, const std::string& msg)
 // written by the GPU: what ensure_tables builds on the host and uploads for offsets = {0, numel}.
 __global__ void __launch_bounds__(kBlock)
 k_flat_tables(SegDesc* __restrict__ segs, StDesc* __restrict__ sts, ChunkDesc* __restrict__ chunks,
-              HistBlock* __restrict__ hblocks, int32_t numel, int32_t k, int32_t n_st, int32_t n_ch, int32_t per_block,
-              int32_t n_hb)
+              HistBlock* __restrict__ hblocks, PartDesc* __restrict__ parts, int32_t numel, int32_t k, int32_t n_st,
+              int32_t n_ch, int32_t per_block, int32_t n_hb, int32_t n_parts, int32_t part)
 {
     const int32_t i = blockIdx.x * kBlock + threadIdx.x;
     if (i == 0) segs[0] = SegDesc{0, numel, k, 0, 0, n_st, 0, n_ch, 0, 0};
@@ -723,6 +840,7 @@ k_flat_tables(SegDesc* __restrict__ segs, StDesc* __restrict__ sts, ChunkDesc* _
         const int32_t lo = i * per_block, hi = lo + per_block < n_st ? lo + per_block : n_st;
         hblocks[i] = HistBlock{0, lo, hi, i == 0 ? 1 : 0, lo * kSuper, 0, numel, 0};
     }
+    if (i < n_parts) parts[i] = PartDesc{0, i * part, 0, numel, k, 0, 0, n_parts};
 }
 
 
@@ -855,10 +973,13 @@ scalecom_status scalecom_step_static(int device, void* hip_stream, float* const*
         const int32_t n_ch = (n_st + kChunk - 1) / kChunk;
         const int32_t per_block = std::max<int32_t>(1, (n_st + kHistGridMax - 1) / kHistGridMax);
         const int32_t n_hb = (n_st + per_block - 1) / per_block;
-        k_flat_tables<<<(n_st + kBlock - 1) / kBlock, kBlock, 0, ctx->stream>>>(
+        const int64_t offsets[2] = {0, numel};
+        const ShortPlan plan = short_parts(l, 1, offsets);
+        k_flat_tables<<<(std::max<int32_t>(n_st, plan.n_parts) + kBlock - 1) / kBlock, kBlock, 0, ctx->stream>>>(
             reinterpret_cast<SegDesc*>(slot.ptr + l.segs), reinterpret_cast<StDesc*>(slot.ptr + l.sts),
             reinterpret_cast<ChunkDesc*>(slot.ptr + l.chunks), reinterpret_cast<HistBlock*>(slot.ptr + l.hblocks),
-            static_cast<int32_t>(numel), static_cast<int32_t>(k), n_st, n_ch, per_block, n_hb);
+            reinterpret_cast<PartDesc*>(slot.ptr + l.parts), static_cast<int32_t>(numel), static_cast<int32_t>(k), n_st, n_ch,
+            per_block, n_hb, plan.n_parts, static_cast<int32_t>(plan.part()));
         k_init<<<1, kBlock, 0, ctx->stream>>>(reinterpret_cast<uint32_t*>(slot.ptr + l.preds),
                                               (kPredWords + static_cast<size_t>(kStaticLearnersMax)));
         k_init<<<1, kBlock, 0, ctx->stream>>>(reinterpret_cast<uint32_t*>(slot.ptr + l.stats),
@@ -868,6 +989,9 @@ scalecom_status scalecom_step_static(int device, void* hip_stream, float* const*
         ctx->n_st = n_st;
         ctx->n_chunks = n_ch;
         ctx->n_hblocks = n_hb;
+        ctx->short_threads = plan.threads;
+        ctx->short_rows = plan.rows;
+        ctx->n_parts = plan.n_parts;
         slot.numel = slot.k = -1;                               // until the step below has been enqueued
         slot.gdt = -1;
     }

@@ -1,0 +1,94 @@
+"""The exact step on short layouts (two launches, every block searches for itself), against the oracle, bit for
+bit: lengths around the edges of its parts (1024, 2048, 4096 and 8192 positions, at most 256 of them per
+segment) and around the lengths where it gives way to the long path, segments that start anywhere, index sets
+from one position to all of them, columns with one key and with thousands of equal ones, expectations that
+hold and that miss in both directions.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2104_11125_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gu():
+    import gpu_util
+    return gpu_util
+
+
+def _normal(n, seed, scale=1e-3):
+    return (torch.randn(n, generator=torch.Generator(device="cpu").manual_seed(seed)) * scale)
+
+
+@pytest.mark.parametrize("numel,ks", [
+    (1, [1]), (3, [0, 1, 3]), (1023, [1, 1023]), (1024, [10]), (1025, [1, 512]), (5000, [50]),
+    (262_144, [2621]), (262_145, [2621, 87_381]),               # 256 parts of 1024, then parts of 2048
+    (524_288, [10_485]), (524_289, [1, 524_289]),               # parts of 4096
+    (1_048_576, [10_485]), (1_048_577, [41_943]),               # parts of 8192
+    (2_097_152, [20_971, 699_050]), (2_097_153, [20_971]),      # the last one takes the long path
+])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_lengths_around_the_parts(gu, numel, ks, dtype):
+    n = 2
+    for k in ks:
+        ctx = binding.scalecom_init(numel, n, dtype, 1, gu.DEV)
+        mem = [(_normal(numel, 7 * i + 1, 2e-4)).to(gu.DEV) for i in range(n)]
+        ref = [m.cpu().numpy().copy() for m in mem]
+        for step in range(4):
+            grad = [_normal(numel, 100 * step + i).to(gu.DEV).to(dtype) for i in range(n)]
+            print(f"[short] numel={numel} k={k} {dtype} step={step}", flush=True)
+            gu.compare_step(ctx, mem, grad, ref, step, 0.3, 0.5, k=k, what=f"numel={numel} k={k}")
+        ctx.close()
+
+
+def test_segments_anywhere(gu):
+    """Segments of one part and of many, at starts that are no multiple of four, empty ones and full ones, and
+    elements outside all of them; learner counts below, at and above the number that is loaded at once."""
+    sizes = [1, 4, 1023, 0, 1024, 1025, 7, 40_961, 300_001, 3, 9_000]
+    ks = [1, 0, 11, 0, 1024, 1, 3, 410, 3_001, 3, 4_500]
+    offsets = [5]
+    for s in sizes:
+        offsets.append(offsets[-1] + s)
+    numel = offsets[-1] + 9
+    for n in (1, 4, 5, 9):
+        ctx = binding.scalecom_init(numel, n, torch.float32, len(ks), gu.DEV)
+        mem = [_normal(numel, 31 * i + n, 1.0).to(gu.DEV) for i in range(n)]
+        ref = [m.cpu().numpy().copy() for m in mem]
+        for step in range(3):
+            grad = [_normal(numel, 1000 * n + 50 * step + i, 1.0).to(gu.DEV) for i in range(n)]
+            print(f"[short] segments n={n} step={step}", flush=True)
+            gu.compare_step(ctx, mem, grad, ref, step, 0.5, 0.25, offsets=offsets, ks=ks, what=f"segments n={n}")
+        ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["equal", "half_zero", "two_values", "dense", "jumps"])
+def test_columns_of_any_size(gu, kind):
+    """More keys in the threshold's column than one thread each can rank (256), than one wave can search
+    (1024), all of them; and thresholds that leave the columns around the expected one."""
+    numel, n = 300_007, 2
+    rng = np.random.default_rng(11)
+    ctx = binding.scalecom_init(numel, n, torch.float32, 1, gu.DEV)
+    mem = [torch.zeros(numel, device=gu.DEV) for _ in range(n)]
+    ref = [np.zeros(numel, np.float32) for _ in range(n)]
+    ks = [300, 3_000, 100_000, 150_000, 299_000, 299_999]
+    for step in range(12):
+        k = ks[step // 2]
+        if kind == "equal":
+            x = np.full(numel, 0.25, np.float32)
+        elif kind == "half_zero":                               # the threshold is 0 from k = 150 000 on
+            x = rng.standard_normal(numel).astype(np.float32) * (rng.random(numel) < 0.49)
+        elif kind == "two_values":
+            x = np.where(rng.random(numel) < 0.01, np.float32(2.0), np.float32(1.0)).astype(np.float32)
+        elif kind == "dense":                                   # magnitudes a few units in the last place apart
+            x = (np.float32(1.0) + rng.integers(0, 2_000, numel).astype(np.float32) * np.float32(2.0 ** -23)).astype(np.float32)
+        else:                                                   # by 2 to 1000 from step to step, up and down
+            x = rng.standard_normal(numel).astype(np.float32) * np.float32([1, 2, 0.5, 30, 1, 1e-3, 1e3, 1, 8, 9, 1.2, 0.9][step])
+        grad = [torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).to(gu.DEV),
+                torch.from_numpy(rng.permutation(x).astype(np.float32)).to(gu.DEV)]
+        print(f"[short] {kind} k={k} step={step}", flush=True)
+        gu.compare_step(ctx, mem, grad, ref, step, 0.5 if kind == "jumps" else 1.0, 1.0, k=k if kind != "jumps" else 3_000,
+                        what=f"{kind} k={k}")
+    ctx.close()
