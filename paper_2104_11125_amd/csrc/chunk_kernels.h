@@ -9,6 +9,300 @@
 
 namespace {
 
+// The chunks that a group of the kernels below owns: group u of a supertile takes G = (256 * Q - 3) / chunk chunks
+// from the supertile's u * G-th on (a chunk belongs to the supertile in which it starts; the group's first
+// position may lie up to 3 behind a multiple of 4).
+template <int Q>
+struct ChunkGroup {
+    uint32_t begin, end, ch, recip;     // segment, elements per chunk; rel / ch = rel * recip >> 22 for rel < 1024
+    uint32_t first, n;                  // first chunk (counted in the segment) and number of chunks
+    uint32_t lo, hi, base;              // positions [lo, hi); lo rounded down to a multiple of 4
+    int32_t out_base;
+    __device__ __forceinline__ bool find(const StDesc& d, uint32_t u)   // false: no chunk left
+    {
+        // positions and chunk sizes are below 2^31 + 8192: 32-bit arithmetic throughout
+        begin = static_cast<uint32_t>(d.begin);
+        end = static_cast<uint32_t>(d.end);
+        ch = static_cast<uint32_t>(d.sel_chunk);
+        out_base = d.out_base;
+        // 2^22 / ch rounded up, or a little more (the factor makes up for the reciprocal's last bit)
+        recip = static_cast<uint32_t>(4194308.0f * __builtin_amdgcn_rcpf(static_cast<float>(ch))) + 1u;
+        const uint32_t per_group = ((256u * Q - 3u) * recip) >> 22;
+        const uint32_t a0 = static_cast<uint32_t>(d.a0), st_end = a0 + kSuper < end ? a0 + kSuper : end;
+        first = static_cast<uint32_t>(d.chunk_first) + u * per_group;
+        lo = begin + first * ch;
+        if (lo >= st_end) return false;
+        const uint32_t starts = st_end - 1u - lo;           // the last position at which a chunk of mine may start, from lo
+        n = starts >= per_group * ch ? per_group : ((starts * recip) >> 22) + 1u;
+        hi = n * ch < end - lo ? lo + n * ch : end;
+        base = lo & ~static_cast<uint32_t>(kVec - 1);
+        return true;
+    }
+};
+
+// The whole chunk-wise step in one launch, for chunks of up to 509 elements.  What the step cannot do without is
+// one read of (mem, grad) and one write of mem per learner; the kernels below read the leader twice, and
+// a chunk's winner depends on nothing outside the chunk.  So a block takes whole chunks, at most
+// 256 * Q - 3 positions, and all learners: one wave per learner and wave tile (the access pattern of the
+// all-learner pass: one wave moves 256 consecutive positions of one learner; several tiles per wave or
+// several learners per thread cost 5 to 20 % of the rate), the leader's first.  Winners and the members' values
+// go through LDS.  Blocks share no chunk, so the memories can be updated in place.
+constexpr int kChunkStepWaves = 16;              // waves of a block at most: further (learner, tile) pairs take turns
+
+template <typename G, int Q>
+__global__ void __launch_bounds__(kChunkStepWaves * kLanes)
+k_chunk_step(const LearnerPtrs lp, int n_learners, int leader, float lr, float beta, float one_minus_beta,
+             const StDesc* __restrict__ sts, int n_st, int max_chunks, int32_t* __restrict__ idx_out,
+             float* __restrict__ red_out)
+{
+    // per chunk the largest word (magnitude key << 32 | ~position), then [chunk][learner] the learners' values there
+    extern __shared__ unsigned long long chunk_lds[];
+    unsigned long long* best = chunk_lds;
+    float* xs = reinterpret_cast<float*>(chunk_lds + max_chunks);
+    const int st = static_cast<int>(blockIdx.y + blockIdx.z * gridDim.y);
+    if (st >= n_st) return;                                 // padding of the 3-d grid (whole block)
+    const StDesc d = sts[st];
+    ChunkGroup<Q> grp;
+    if (!grp.find(d, blockIdx.x)) return;                   // whole block
+    const uint32_t begin = grp.begin, end = grp.end, recip = grp.recip, cf = grp.first, n_ch = grp.n;
+    const uint32_t lo = grp.lo, hi = grp.hi, base = grp.base;
+
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes), lane = threadIdx.x % kLanes;
+    const int n_waves = blockDim.x / kLanes;
+    const int n_pairs = n_learners * Q;
+    float4 m, g;
+    // pair p: tile p % Q of learner (leader + p / Q) mod n.  Four positions that straddle the block's ends are
+    // loaded whole where they lie inside the segment; what other blocks write there meanwhile is not used.
+    auto place = [&](int p, int& l, uint32_t& p0) {
+        l = leader + p / Q;
+        if (l >= n_learners) l -= n_learners;
+        p0 = base + static_cast<uint32_t>(p % Q) * kWaveTile + static_cast<uint32_t>(lane) * kVec;
+    };
+    auto fetch = [&](int l, uint32_t p0) {
+        m = make_float4(0, 0, 0, 0);
+        g = m;
+        if (p0 >= hi) return;
+        const bool whole = p0 >= begin && p0 + 3 < end;
+        m = load_guarded(lp.mem[l], p0, begin, end, whole);
+        g = load_guarded(static_cast<const G*>(lp.grad[l]), p0, begin, end, whole);
+    };
+    int l;
+    uint32_t p0;
+    place(wave, l, p0);
+    if (wave < n_pairs) fetch(l, p0);
+    for (uint32_t j = threadIdx.x; j < n_ch; j += blockDim.x) best[j] = 0ull;
+    if (Q > 1) __syncthreads();                             // (of one tile wave 0 clears and uses all: at most 63 chunks)
+    if (wave < Q) {                                         // the leader's tiles: the largest word of every chunk
+        const float4 x = accumulate4(m, g, lr);
+        const uint32_t key[4] = {magnitude_key(x.x), magnitude_key(x.y), magnitude_key(x.z), magnitude_key(x.w)};
+        // a lane's elements lie in one chunk or, around a boundary, in two or more: one atomic per run
+        unsigned long long word = 0ull;
+        uint32_t cur = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t p = p0 + c;
+            if (p < lo || p >= hi) continue;
+            const uint32_t j = ((p - lo) * recip) >> 22;
+            const unsigned long long w = (static_cast<unsigned long long>(key[c]) << 32) | (0xffffffffu - p);
+            if (word != 0ull && j != cur) {
+                atomicMax(&best[cur], word);
+                word = 0ull;
+            }
+            cur = j;
+            word = w > word ? w : word;
+        }
+        if (word != 0ull) atomicMax(&best[cur], word);
+    }
+    __syncthreads();
+    for (int p = wave; p < n_pairs; p += n_waves) {
+        if (p != wave) {
+            place(p, l, p0);
+            fetch(l, p0);
+        }
+        if (p0 >= hi) continue;
+        const float4 x = accumulate4(m, g, lr);
+        const float xv[4] = {x.x, x.y, x.z, x.w}, mv[4] = {m.x, m.y, m.z, m.w};
+        float out[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t pos = p0 + c;
+            const uint32_t rel = pos >= lo ? pos - lo : 0u;
+            const uint32_t j = (rel * recip) >> 22;
+            const bool in = pos >= lo && pos < hi;
+            const bool sel = in && static_cast<uint32_t>(best[in ? j : 0u]) == 0xffffffffu - pos;
+            if (sel) xs[j * n_learners + l] = xv[c];
+            out[c] = fmaf(beta, sel ? 0.0f : xv[c], one_minus_beta * mv[c]);   // Eq. 5
+        }
+        store_guarded(lp.mem[l], p0, lo, hi, p0 >= lo && p0 + 3 < hi, make_float4(out[0], out[1], out[2], out[3]));
+    }
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < n_ch; j += blockDim.x) {   // Alg. 1 line 10, learner 0 first
+        const uint32_t slot = static_cast<uint32_t>(d.out_base) + cf + j;
+        float s = xs[j * n_learners];
+        for (int i = 1; i < n_learners; ++i) s = s + xs[j * n_learners + i];
+        idx_out[slot] = static_cast<int32_t>(0xffffffffu - static_cast<uint32_t>(best[j]));
+        red_out[slot] = s;
+    }
+}
+
+// The same for layouts with more data, where reading the leader once more costs less than blocks whose positions do not
+// start on whole kilobytes: the winners first, one wave per group of whole chunks (at most 256 * Q - 3 positions,
+// the same groups as above), straight to idx_out; no atomics in memory and nothing to clear.  Bound by the vector ALU
+// before memory, so the reduction is left to LDS: a maximum per chunk, then the lowest position among the holders (one
+// atomic per lane and run each, in words of the wave's own).  A reduction inside the ALU per chunk took 43 us at
+// 25.6 M elements and chunk 112, and 52 us at 19.6 M with chunks of 25, 50 and 400; a scan over the lanes 41 and 39.
+constexpr int kChunkGroupMax = 256;              // chunks of a group at most (1021 positions, chunks of 4)
+
+template <typename G, int Q>
+__global__ void __launch_bounds__(kBlock)
+k_chunk_winners(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const StDesc* __restrict__ sts, int n_st,
+                int32_t* __restrict__ idx_out)
+{
+    constexpr int kMost = Q == 4 ? kChunkGroupMax : 64 * Q;
+    __shared__ uint32_t key_max[kWaves][kMost], pos_min[kWaves][kMost];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes), lane = threadIdx.x % kLanes;
+    const int st = static_cast<int>(blockIdx.y + blockIdx.z * gridDim.y);
+    if (st >= n_st) return;
+    const StDesc d = sts[st];
+    ChunkGroup<Q> c;
+    if (!c.find(d, blockIdx.x * kWaves + wave)) return;     // whole wave
+    float4 m[Q], g[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint32_t p0 = c.base + static_cast<uint32_t>(q * kWaveTile + lane * kVec);
+        m[q] = make_float4(0, 0, 0, 0);
+        g[q] = m[q];
+        if (p0 < c.hi) {
+            const bool whole = p0 >= c.begin && p0 + 3 < c.end;
+            m[q] = load_guarded(mem, p0, c.begin, c.end, whole);
+            g[q] = load_guarded(grad, p0, c.begin, c.end, whole);
+        }
+    }
+    for (uint32_t j = lane; j < c.n; j += kLanes) {
+        key_max[wave][j] = 0u;
+        pos_min[wave][j] = 0xffffffffu;
+    }
+    wave_lds_fence();
+    // A lane's elements belong to chunk j0 up to element nb, then to the next one.  Keys fit 31 bits, so -1 stands for
+    // an element outside the group.
+    int32_t key[Q][4];
+    uint32_t j0[Q], nb[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint32_t p0 = c.base + static_cast<uint32_t>(q * kWaveTile + lane * kVec);
+        const float4 x = accumulate4(m[q], g[q], lr);
+        const float xv[4] = {x.x, x.y, x.z, x.w};
+        const uint32_t rel = p0 > c.lo ? p0 - c.lo : 0u;
+        j0[q] = (rel * c.recip) >> 22;
+        nb[q] = c.lo + (j0[q] + 1u) * c.ch - p0;            // (at least 1; lane 0 may begin up to 3 before lo)
+        int32_t head = -1, tail = -1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool in = p0 + e >= c.lo && p0 + e < c.hi;
+            key[q][e] = in ? static_cast<int32_t>(magnitude_key(xv[e])) : -1;
+            if (static_cast<uint32_t>(e) < nb[q])
+                head = key[q][e] > head ? key[q][e] : head;
+            else
+                tail = key[q][e] > tail ? key[q][e] : tail;
+        }
+        if (head >= 0) atomicMax(&key_max[wave][j0[q]], static_cast<uint32_t>(head));
+        if (tail >= 0) atomicMax(&key_max[wave][j0[q] + 1u], static_cast<uint32_t>(tail));
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint32_t p0 = c.base + static_cast<uint32_t>(q * kWaveTile + lane * kVec);
+        const bool two = nb[q] < 4u && p0 + nb[q] < c.hi;
+        const int32_t best0 = p0 < c.hi ? static_cast<int32_t>(key_max[wave][j0[q]]) : 0;
+        const int32_t best1 = two ? static_cast<int32_t>(key_max[wave][j0[q] + 1u]) : 0;
+        uint32_t at0 = 0xffffffffu, at1 = 0xffffffffu;
+#pragma unroll
+        for (int e = 3; e >= 0; --e) {
+            if (static_cast<uint32_t>(e) < nb[q])
+                at0 = key[q][e] == best0 ? p0 + e : at0;
+            else
+                at1 = key[q][e] == best1 ? p0 + e : at1;
+        }
+        if (at0 != 0xffffffffu) atomicMin(&pos_min[wave][j0[q]], at0);
+        if (at1 != 0xffffffffu) atomicMin(&pos_min[wave][j0[q] + 1u], at1);
+    }
+    wave_lds_fence();
+    for (uint32_t j = lane; j < c.n; j += kLanes)
+        idx_out[static_cast<uint32_t>(c.out_base) + c.first + j] = static_cast<int32_t>(pos_min[wave][j]);
+}
+
+// The all-learner pass with the winners at hand: k_update's blocks and order, but an element is a member if
+// its chunk's entry of idx_out names it, and the chunk is the slot.  (The masks and slots per wave tile that
+// k_update reads would take one more launch.)  For chunks of 4 to 1021 elements.
+template <typename G>
+__global__ void __launch_bounds__(kBlock)
+k_update_chunks(LearnerPtrs lp, float lr, float beta, float one_minus_beta, const StDesc* __restrict__ sts, int n_st,
+                const int32_t* __restrict__ idx, float* __restrict__ vals, int64_t k_total, int learner0)
+{
+    const int learner = learner0 + blockIdx.x;
+    const int group = blockIdx.y + blockIdx.z * gridDim.y;
+    const int st = group / kUpdateBlocksPerSuper;
+    if (st >= n_st) return;                                 // padding of the 3-d grid (whole block)
+    const StDesc d = sts[st];
+    const uint32_t begin = static_cast<uint32_t>(d.begin), end = static_cast<uint32_t>(d.end);
+    const uint32_t blk0 = static_cast<uint32_t>(d.a0) + static_cast<uint32_t>(group % kUpdateBlocksPerSuper) * kWaves * kWaveTile;
+    const uint32_t v_lo = blk0 > begin ? blk0 : begin;      // the block's positions of the segment
+    const uint32_t v_hi = blk0 + kWaves * kWaveTile < end ? blk0 + kWaves * kWaveTile : end;
+    if (v_lo >= v_hi) return;                               // whole block
+    const uint32_t p0 = blk0 + threadIdx.x * kVec;
+    const bool inside = blk0 >= begin && blk0 + kWaves * kWaveTile <= end;     // block-uniform
+    const bool full = inside || (p0 >= begin && p0 + 3 < end), any = inside || (p0 + 3 >= begin && p0 < end);
+    float* mem = lp.mem[learner];
+    const G* grad = static_cast<const G*>(lp.grad[learner]);
+    float4 m = make_float4(0, 0, 0, 0), g = m;
+    if (inside) {
+        m = load4(mem + p0);
+        g = load4(grad + p0);
+    } else if (any) {
+        m = load_guarded(mem, p0, begin, end, full);
+        g = load_guarded(grad, p0, begin, end, full);
+    }
+    // chunk numbers from the supertile's first one on; x / ch for x < 16384 and ch < 1024 by a product: the
+    // reciprocal is 2^32 / ch rounded up, or more by at most its float's last bits (one element per chunk: x is 0)
+    const uint32_t ch = static_cast<uint32_t>(d.sel_chunk);
+    const uint32_t recip = static_cast<uint32_t>(4294968320.0f * __builtin_amdgcn_rcpf(static_cast<float>(ch > 1u ? ch : 2u))) + 1u;
+    auto over_ch = [&](uint32_t x) { return __umulhi(x, recip); };
+    const uint32_t c0 = static_cast<uint32_t>(d.chunk_first), start0 = begin + c0 * ch;   // (at most a0 + ch)
+    // the chunk that holds the block's first position: the one before c0, or one from c0 on
+    const uint32_t j_lo = v_lo < start0 ? c0 - 1u : c0 + over_ch(v_lo - start0);
+    const uint32_t lo_pos = begin + j_lo * ch;
+    const uint32_t n_j = over_ch(v_hi - 1u - lo_pos) + 1u;  // chunks that the block has a part of
+    const int32_t* my_idx = idx + d.out_base + j_lo;
+    const uint32_t q0 = p0 > v_lo ? p0 : v_lo, q3 = p0 + 3 < v_hi ? p0 + 3 : v_hi - 1u;
+    const uint32_t r0 = any ? over_ch(q0 - lo_pos) : 0u, r3 = any ? over_ch(q3 - lo_pos) : 0u;
+    const uint32_t w0 = static_cast<uint32_t>(my_idx[r0]), w3 = static_cast<uint32_t>(my_idx[r3]);
+    __shared__ float stage[kWaves * kWaveTile / 4 + 2];
+    const uint32_t win_t = threadIdx.x < n_j ? static_cast<uint32_t>(my_idx[threadIdx.x]) : 0xffffffffu;
+    const float4 x = accumulate4(m, g, lr);
+    const float xv[4] = {x.x, x.y, x.z, x.w}, mv[4] = {m.x, m.y, m.z, m.w};
+    float out[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const uint32_t p = p0 + c;
+        const bool sel = (p == w0 || p == w3) && p >= v_lo && p < v_hi;
+        if (sel) stage[p == w0 ? r0 : r3] = xv[c];
+        out[c] = fmaf(beta, sel ? 0.0f : xv[c], one_minus_beta * mv[c]);       // Eq. 5
+    }
+    const float4 o = make_float4(out[0], out[1], out[2], out[3]);
+    if (inside)
+        store4(mem + p0, o);
+    else if (any)
+        store_guarded(mem, p0, begin, end, full, o);
+    __syncthreads();
+    float* my_vals = vals + static_cast<size_t>(learner) * static_cast<size_t>(k_total) + d.out_base + j_lo;
+    if (win_t >= v_lo && win_t < v_hi) my_vals[threadIdx.x] = stage[threadIdx.x];
+    for (uint32_t j = kBlock + threadIdx.x; j < n_j; j += kBlock) {            // (chunks of 4: up to 257)
+        const uint32_t w = static_cast<uint32_t>(my_idx[j]);
+        if (w >= v_lo && w < v_hi) my_vals[j] = stage[j];
+    }
+}
+
+// Chunks beyond those sizes: maxima per chunk by atomics, then masks and slots for k_update.
 // Leader pass of the chunk-wise selector, one wave per wave tile: every element becomes the word
 // (magnitude key << 32 | ~position), so that the largest word of a chunk is its largest
 // magnitude at the lowest position; for each chunk of the tile's segment that overlaps the tile

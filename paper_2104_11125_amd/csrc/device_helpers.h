@@ -213,6 +213,14 @@ __device__ __forceinline__ void refine_t24(uint32_t* pred, uint32_t* lead_mine, 
     if (lead_mine) lead_mine[seg] = t24;
 }
 
+// Orders one wave's LDS accesses: what its lanes wrote or added before is seen by its lanes after.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 // Membership bitmask layout: per wave tile four 64-bit words; bit l of word c belongs to
 // position tile0 + 4*l + c, i.e. word c is the wave ballot of "element c of my lane is a member".
 __device__ __forceinline__ void store_tile_masks(uint64_t* mask, size_t tile, const uint64_t b[4])

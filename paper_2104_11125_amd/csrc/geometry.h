@@ -48,7 +48,9 @@ struct StDesc {           // one per supertile; carries what the streaming kerne
     int32_t a0;           // first position, a multiple of 4 (may lie up to 3 before begin)
     int32_t begin, end;   // the segment's positions [begin, end)
     int32_t slot_end;     // one past the segment's last output slot
-    int32_t pad[3];
+    int32_t sel_chunk;    // chunk-wise selector: elements per chunk of the segment (0 in exact mode)
+    int32_t out_base;     // first output slot of the segment
+    int32_t chunk_first;  // chunk-wise selector: first chunk of the segment that starts in this supertile
 };
 
 struct HistBlock {        // one block of the kernels of the search levels: consecutive supertiles of ONE segment

@@ -172,6 +172,15 @@ bool sizes_ok(int64_t numel_max, int n_tensors_max, int n_learners_max, int64_t 
 
 }  // namespace
 
+// How a layout's chunk-wise step runs (elements per chunk clamped to the segment's length):
+// with groups of whole chunks of at most 256 * tiles - 3 positions, per_st of them per supertile, in one
+// launch (k_chunk_step, up to two tiles) or two and the sum over learners (k_chunk_winners); tiles = 0: chunks too
+// long or too short for that, one more launch.
+struct ChunkPlan {
+    int tiles = 0, per_st = 0;
+    int max_chunks = 0;          // chunks of a group at most
+};
+
 struct scalecom_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
@@ -186,6 +195,7 @@ struct scalecom_ctx {
     std::vector<int64_t> cached_offsets, cached_ks, cached_chunks;
     int n_st = 0, n_chunks = 0, n_hblocks = 0, n_small = 0;
     int short_threads = 0, short_rows = 0, n_parts = 0;   // the layout's ShortPlan
+    ChunkPlan chunk;
     // segments of one supertile are searched by a kernel of their own, on a second stream beside the
     // leader pass (contexts for more than one tensor only)
     hipStream_t side = nullptr;
@@ -283,6 +293,28 @@ ShortPlan short_parts(const WsLayout& l, int n_tensors, const int64_t* offsets)
     return ShortPlan{};
 }
 
+// (the smallest number of tiles that takes all chunks: more make no difference to k_chunk_winners)
+ChunkPlan chunk_plan(int n_tensors, const SegDesc* segs)
+{
+    for (int tiles = 1; tiles <= 4; tiles *= 2) {
+        const int64_t positions = 256 * tiles - 3;
+        int64_t per_st = 1, max_chunks = 1;
+        bool fits = true;
+        for (int s = 0; s < n_tensors && fits; ++s) {
+            if (segs[s].end == segs[s].begin) continue;
+            const int64_t ch = segs[s].sel_chunk, per_group = positions / ch;
+            // (a segment of fewer than four elements is one chunk or has chunks of 1 to 3)
+            fits = per_group >= 1 && (ch >= 4 || segs[s].k == 1);
+            const int64_t in_st = std::min<int64_t>((kSuper + ch - 1) / ch, segs[s].k);   // chunks that start in a supertile
+            if (!fits) break;
+            per_st = std::max(per_st, (in_st + per_group - 1) / per_group);
+            max_chunks = std::max(max_chunks, std::min(per_group, in_st));
+        }
+        if (fits) return ChunkPlan{tiles, static_cast<int>(per_st), static_cast<int>(max_chunks)};
+    }
+    return ChunkPlan{};
+}
+
 // Rebuild and upload the segment, supertile, chunk and block tables if the layout differs from the cached one.
 scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* offsets, const int64_t* ks,
                               const int64_t* sel_chunks = nullptr)
@@ -324,9 +356,13 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
         segs[s] = SegDesc{static_cast<int32_t>(b),    static_cast<int32_t>(e),     static_cast<int32_t>(ks[s]),
                           static_cast<int32_t>(out),  static_cast<int32_t>(n_st),  static_cast<int32_t>(count),
                           static_cast<int32_t>(n_ch), static_cast<int32_t>(n_chunks), static_cast<int32_t>(sel_chunk), 0};
-        for (int64_t j = 0; j < count; ++j)
+        for (int64_t j = 0; j < count; ++j) {
+            const int64_t before = std::max<int64_t>(a_first + j * kSuper - b, 0);   // the segment's positions before the supertile
             sts[n_st + j] = StDesc{s, static_cast<int32_t>(a_first + j * kSuper), static_cast<int32_t>(b),
-                                   static_cast<int32_t>(e), static_cast<int32_t>(out + ks[s]), {0, 0, 0}};
+                                   static_cast<int32_t>(e), static_cast<int32_t>(out + ks[s]),
+                                   static_cast<int32_t>(sel_chunk), static_cast<int32_t>(out),
+                                   static_cast<int32_t>(sel_chunk > 0 ? (before + sel_chunk - 1) / sel_chunk : 0)};
+        }
         for (int64_t c = 0; c < n_chunks; ++c)
             chunks[n_ch + c] = ChunkDesc{s, static_cast<int32_t>(n_st + c * kChunk),
                                          static_cast<int32_t>(std::min<int64_t>(kChunk, count - c * kChunk)), 0};
@@ -402,6 +438,7 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
     ctx->short_threads = plan.threads;
     ctx->short_rows = plan.rows;
     ctx->n_parts = plan.n_parts;
+    ctx->chunk = sel_chunks ? chunk_plan(n_tensors, segs) : ChunkPlan{};
     ctx->cached_offsets.assign(offsets, offsets + n_tensors + 1);
     ctx->cached_ks.assign(ks, ks + n_tensors);
     ctx->cached_chunks = ch;
@@ -617,6 +654,18 @@ scalecom_status launch_step(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_lear
     return SCALECOM_OK;
 }
 
+// Is the whole chunk-wise step in one launch the faster way?  It reads the leader once instead of twice and saves two
+// launches, but moves the rest at 4.9 TB/s instead of 6.5.  One launch against three, us: 4 x 5.3 M elements 57
+// against 74 with the four launches of old; 8 x 3.3 M 76 against 69; 6 x 5.1 M 85 against 80; 4 x 11.4 M 111 against
+// 116; 3 x 30 M bf16 207 against 201; 8 x 25.6 M 489 against 422.
+bool chunks_in_one_launch(int tiles, int n_learners, int64_t numel, int grad_bytes)
+{
+    if (tiles < 1 || tiles > 2) return false;
+    const double all = static_cast<double>(n_learners) * static_cast<double>(numel) * (8 + grad_bytes);
+    const double leader = static_cast<double>(numel) * (4 + grad_bytes);
+    return all * (1.0 / 4.9 - 1.0 / 6.5) * 1e-6 < leader / 4.8 * 1e-6 + 5.0;
+}
+
 // One step with the chunk-wise selector: leader pass (per-chunk maxima), marks, then the same
 // all-learner pass and reduction as the exact path.
 template <typename G>
@@ -641,6 +690,58 @@ scalecom_status launch_chunked(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
         return dim3(gx, static_cast<unsigned>((blocks + gx - 1) / gx));
     };
     mark(0);
+    const int64_t extent = ctx->cached_offsets[n_tensors] - ctx->cached_offsets[0];
+    const int gb = sizeof(G);
+    if (chunks_in_one_launch(ctx->chunk.tiles, n_learners, extent, gb)) {
+        mark(1);
+        mark(2);
+        mark(3);
+        const unsigned gz = static_cast<unsigned>((ctx->n_st + 65534) / 65535);
+        const dim3 grid(ctx->chunk.per_st, (ctx->n_st + gz - 1) / gz, gz);
+        const int waves = std::min(n_learners * ctx->chunk.tiles, kChunkStepWaves);
+        const size_t lds = static_cast<size_t>(ctx->chunk.max_chunks) * (sizeof(unsigned long long) + sizeof(float) * n_learners);
+        if (ctx->chunk.tiles == 1)
+            k_chunk_step<G, 1><<<grid, waves * kLanes, lds, s>>>(lp, n_learners, leader, lr, beta, 1.0f - beta, sts,
+                                                                 ctx->n_st, ctx->chunk.max_chunks, idx_out, red_out);
+        else
+            k_chunk_step<G, 2><<<grid, waves * kLanes, lds, s>>>(lp, n_learners, leader, lr, beta, 1.0f - beta, sts,
+                                                                 ctx->n_st, ctx->chunk.max_chunks, idx_out, red_out);
+        mark(4);
+        mark(5);
+        if (timed) ++ctx->prof_steps;
+        SC_HIP(ctx, hipGetLastError());
+        return SCALECOM_OK;
+    }
+    if (ctx->chunk.tiles > 0) {
+        const unsigned sz = static_cast<unsigned>((ctx->n_st + 65534) / 65535);
+        const dim3 groups((ctx->chunk.per_st + kWaves - 1) / kWaves, (ctx->n_st + sz - 1) / sz, sz);
+        const float* memL = lp.mem[leader];
+        const G* gradL = static_cast<const G*>(lp.grad[leader]);
+        if (ctx->chunk.tiles == 1)
+            k_chunk_winners<G, 1><<<groups, kBlock, 0, s>>>(memL, gradL, lr, sts, ctx->n_st, idx_out);
+        else if (ctx->chunk.tiles == 2)
+            k_chunk_winners<G, 2><<<groups, kBlock, 0, s>>>(memL, gradL, lr, sts, ctx->n_st, idx_out);
+        else
+            k_chunk_winners<G, 4><<<groups, kBlock, 0, s>>>(memL, gradL, lr, sts, ctx->n_st, idx_out);
+        mark(1);
+        mark(2);
+        mark(3);
+        float* vals = reinterpret_cast<float*>(ws + l.vals);
+        const int64_t blocks = static_cast<int64_t>(ctx->n_st) * kUpdateBlocksPerSuper;
+        const unsigned gz = static_cast<unsigned>((blocks + 65534) / 65535);
+        const unsigned gy = static_cast<unsigned>((blocks + gz - 1) / gz);
+        for (int l0 = 0; l0 < n_learners; l0 += kUpdateLearnersPerLaunch) {
+            const int nl = std::min(kUpdateLearnersPerLaunch, n_learners - l0);
+            k_update_chunks<G><<<dim3(nl, gy, gz), kBlock, 0, s>>>(lp, lr, beta, 1.0f - beta, sts, ctx->n_st, idx_out, vals,
+                                                                  k_total, l0);
+        }
+        mark(4);
+        k_reduce<<<static_cast<unsigned>((k_total + kBlock - 1) / kBlock), kBlock, 0, s>>>(vals, n_learners, k_total, red_out);
+        mark(5);
+        if (timed) ++ctx->prof_steps;
+        SC_HIP(ctx, hipGetLastError());
+        return SCALECOM_OK;
+    }
     if (!ctx->best_clean) {             // first chunked step of this context, or one that failed half-way
         const size_t words = 2 * static_cast<size_t>(ctx->k_max);   // 2 words per entry
         const int grid = static_cast<int>(std::min<size_t>((words + kBlock - 1) / kBlock, 4096));
@@ -834,7 +935,7 @@ k_flat_tables(SegDesc* __restrict__ segs, StDesc* __restrict__ sts, ChunkDesc* _
 {
     const int32_t i = blockIdx.x * kBlock + threadIdx.x;
     if (i == 0) segs[0] = SegDesc{0, numel, k, 0, 0, n_st, 0, n_ch, 0, 0};
-    if (i < n_st) sts[i] = StDesc{0, i * kSuper, 0, numel, k, {0, 0, 0}};
+    if (i < n_st) sts[i] = StDesc{0, i * kSuper, 0, numel, k, 0, 0, 0};
     if (i < n_ch) chunks[i] = ChunkDesc{0, i * kChunk, n_st - i * kChunk < kChunk ? n_st - i * kChunk : kChunk, 0};
     if (i < n_hb) {
         const int32_t lo = i * per_block, hi = lo + per_block < n_st ? lo + per_block : n_st;

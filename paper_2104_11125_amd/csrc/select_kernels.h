@@ -1039,14 +1039,6 @@ __device__ __forceinline__ uint32_t find_threshold(uint32_t h_lo, uint32_t h_hi,
     return T;
 }
 
-// Orders one wave's LDS accesses: what its lanes wrote or added before is seen by its lanes after.
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
 // Per wave tile of the leader's vector: number of keys above the threshold (low half of the
 // packed counter) and equal to it (high half), and the two bitmasks that go with them.
 // Full-pass mode recomputes every key; candidate mode adds the listed keys to what the collecting

@@ -92,3 +92,41 @@ def test_columns_of_any_size(gu, kind):
         gu.compare_step(ctx, mem, grad, ref, step, 0.5 if kind == "jumps" else 1.0, 1.0, k=k if kind != "jumps" else 3_000,
                         what=f"{kind} k={k}")
     ctx.close()
+
+
+@pytest.mark.parametrize("chunk", [1, 3, 4, 7, 8, 25, 50, 63, 84, 100, 112, 126, 127, 155, 252, 253, 254, 400, 509, 510, 3000])
+def test_chunks_in_one_launch(gu, chunk):
+    """Chunk sizes around the edges of the one-launch step (253 and 509 positions per block, 64 chunks per
+    block), lengths with one position in the last chunk and with a full one, learner counts with fewer, as many and
+    more (learner, tile) pairs than a block has waves, equal magnitudes inside a chunk."""
+    rng = np.random.default_rng(chunk)
+    for n, numel, dtype in [(1, 8 * chunk + 1, torch.float32), (3, 40_003, torch.bfloat16), (8, 8192 + chunk, torch.float32),
+                            (9, 3 * 8192 - 1, torch.float32), (17, 5 * chunk + 777, torch.bfloat16)]:
+        ctx = binding.scalecom_init(numel, n, dtype, 1, gu.DEV)
+        mem = [torch.from_numpy(np.round(rng.standard_normal(numel) * 4).astype(np.float32)).to(gu.DEV) for _ in range(n)]
+        ref = [m.cpu().numpy().copy() for m in mem]
+        for step in range(2):
+            grad = [torch.from_numpy(np.round(rng.standard_normal(numel) * 8).astype(np.float32)).to(gu.DEV).to(dtype)
+                    for _ in range(n)]
+            print(f"[chunk] chunk={chunk} n={n} numel={numel} step={step}", flush=True)
+            gu.compare_step(ctx, mem, grad, ref, step + n // 2, 0.25, 0.5, chunk=chunk, what=f"chunk={chunk} n={n} numel={numel}")
+        ctx.close()
+
+
+def test_chunks_per_layer_in_one_launch(gu):
+    """Chunk sizes that differ from tensor to tensor, tensors shorter than a chunk, at starts that are no
+    multiple of four; elements outside the tensors keep their bits."""
+    sizes = [64, 3, 20_000, 0, 1, 8_193, 401, 30_011, 7]
+    for chunks in ([25, 50, 400, 25, 400, 100, 400, 112, 8], [9, 11, 250, 8, 509, 60, 1000, 13, 20_000]):
+        offsets = [3]
+        for s in sizes:
+            offsets.append(offsets[-1] + s)
+        numel, n = offsets[-1] + 6, 5
+        ctx = binding.scalecom_init(numel, n, torch.float32, len(sizes), gu.DEV)
+        mem = [_normal(numel, 13 * i, 1.0).to(gu.DEV) for i in range(n)]
+        ref = [m.cpu().numpy().copy() for m in mem]
+        for step in range(3):
+            grad = [_normal(numel, 77 * step + i, 1.0).to(gu.DEV) for i in range(n)]
+            print(f"[chunk] per layer step={step}", flush=True)
+            gu.compare_step(ctx, mem, grad, ref, step, 0.5, 0.25, offsets=offsets, chunks=chunks, what="chunks per layer")
+        ctx.close()
