@@ -245,8 +245,8 @@ scalecom_status scalecom_hamming_distance(scalecom_ctx* ctx, float* const* mem, 
  * learners' memories with it), accumulated in binary64.
  *   a, b   [device] float[numel]
  *   out    [device] double[4], 8-byte aligned: out[0] the distance, out[1..3] = a.b, a.a, b.b
- * The order of the partial sums is not fixed: results agree to a few ulp of binary64 between
- * runs.  A zero vector gives NaN.  Asynchronous on the context's stream.
+ * The partial sums are added in one order for one pair of pointers' alignment; other orders agree to
+ * a few ulp of binary64.  A zero vector gives NaN.  Asynchronous on the context's stream.
  */
 scalecom_status scalecom_cosine_distance(scalecom_ctx* ctx, const float* a, const float* b, int64_t numel, double* out);
 

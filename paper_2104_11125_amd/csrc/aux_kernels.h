@@ -24,53 +24,170 @@ k_apply_update(float* __restrict__ theta, int64_t numel, const int32_t* __restri
 // Similarity diagnostics (Sec. 3) --------------------------------------------------------------
 // y[p] = sum over learners 0..n-1, left to right, of x_i[p] = fma(lr, grad_i[p], mem_i[p]): the
 // all-reduced error-feedback gradient whose top-k is the "true top-k" (times n, which does not
-// change the order of magnitudes).
+// change the order of magnitudes).  Bound by the read of all (mem, grad): a block takes one wave tile, one wave per
+// learner (the pattern that moves most bytes, see k_update), and adds the learners up through LDS; one thread per
+// four positions and all learners took 303 us at 8 x 25.6 M, one per position 333 us.
+// The first threads zero `clear_words` words from `clear_from` on the way: the selection's scratch
+// zone, which the selection before this kernel has used and the one after it expects clean.
+constexpr int kSumWaves = 16;                    // waves of a block at most: further learners take turns
+
 template <typename G>
-__global__ void __launch_bounds__(kBlock)
-k_sum_x(const LearnerPtrs lp, int n_learners, float lr, int64_t begin, int64_t end, float* __restrict__ y)
+__global__ void __launch_bounds__(kSumWaves * kLanes)
+k_sum_x(const LearnerPtrs lp, int n_learners, float lr, int64_t begin, int64_t end, int64_t n_tiles, float* __restrict__ y,
+        uint32_t* __restrict__ clear_from, size_t clear_words)
 {
-    const int64_t p = begin + (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * kBlock + threadIdx.x;
-    if (p >= end) return;
-    float acc = fmaf(lr, widen(static_cast<const G*>(lp.grad[0])[p]), lp.mem[0][p]);
-    for (int i = 1; i < n_learners; ++i) acc += fmaf(lr, widen(static_cast<const G*>(lp.grad[i])[p]), lp.mem[i][p]);
-    y[p] = acc;
+    extern __shared__ float4 sum_lds[];                     // [learner][lane]
+    const int64_t tile = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+    for (size_t i = static_cast<size_t>(tile) * blockDim.x + threadIdx.x; i < clear_words;
+         i += static_cast<size_t>(gridDim.x) * gridDim.y * blockDim.x)
+        clear_from[i] = 0u;
+    if (tile >= n_tiles) return;                            // whole block
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes), lane = threadIdx.x % kLanes;
+    const int64_t p0 = (begin & ~static_cast<int64_t>(kVec - 1)) + tile * kWaveTile + lane * kVec;
+    const bool full = p0 >= begin && p0 + 3 < end;
+    for (int i = wave; i < n_learners; i += static_cast<int>(blockDim.x) / kLanes) {
+        float4 m, g;
+        if (full) {
+            m = load4(lp.mem[i] + p0);
+            g = load4(static_cast<const G*>(lp.grad[i]) + p0);
+        } else {
+            leader_load(lp.mem[i], static_cast<const G*>(lp.grad[i]), p0, begin, end, m, g);
+        }
+        sum_lds[i * kLanes + lane] = accumulate4(m, g, lr);
+    }
+    __syncthreads();
+    if (wave != 0 || p0 >= end) return;
+    float4 acc = sum_lds[lane];
+    for (int i = 1; i < n_learners; ++i) {
+        const float4 x = sum_lds[i * kLanes + lane];
+        acc.x += x.x;
+        acc.y += x.y;
+        acc.z += x.z;
+        acc.w += x.w;
+    }
+    if (full)                                               // (kept in the caches: the selection that follows reads it)
+        *reinterpret_cast<float4*>(y + p0) = acc;
+    else
+        store_guarded(y, p0, begin, end, false, acc);
 }
 
-__global__ void __launch_bounds__(kBlock) k_set_ks(const SegDesc* __restrict__ segs, int n_tensors, int32_t* __restrict__ d)
+// What the diagnostic's two selections start from, per tensor: d = k; for the leader's vector the prediction
+// that the steps keep, if they have one, otherwise what this diagnostic's last call left.  (The steps' own
+// predictions are only read.)
+__global__ void __launch_bounds__(kBlock)
+k_diag_begin(const SegDesc* __restrict__ segs, int n_tensors, const uint32_t* __restrict__ preds,
+             const uint32_t* __restrict__ lead_mine, uint32_t* __restrict__ diag_preds, uint32_t* __restrict__ diag_lead,
+             int32_t* __restrict__ d)
 {
     const int s = blockIdx.x * kBlock + threadIdx.x;
-    if (s < n_tensors) d[s] = segs[s].k;
+    if (s >= n_tensors) return;
+    d[s] = segs[s].k;
+    const uint32_t* src = preds + static_cast<size_t>(s) * kPredWords;
+    if (src[0] == 0u) return;
+    for (int j = 0; j < kPredWords; ++j) diag_preds[static_cast<size_t>(s) * kPredWords + j] = src[j];
+    diag_lead[s] = lead_mine[s];
 }
 
 // d[seg] -= |A and B| over the membership masks of two selections: with d preset to k, what is
 // left is the number of positions of one index set that the other one lacks (Eq. 6: the binarised
-// vectors differ in 2d places).  One wave per supertile.
+// vectors differ in 2d places).  A wave takes consecutive supertiles, and a block adds its waves up where they end
+// in the same segment: an atomic per supertile on the one word of a flat vector took 37 us at 25.6 M.
+// Zeroes the scratch zone as k_sum_x does.
+constexpr int kOverlapBlocks = 256;
+
 __global__ void __launch_bounds__(kBlock)
 k_mask_overlap(const StDesc* __restrict__ sts, int n_st, const uint64_t* __restrict__ mask_a,
-               const uint64_t* __restrict__ mask_b, int32_t* __restrict__ d)
+               const uint64_t* __restrict__ mask_b, int32_t* __restrict__ d, uint32_t* __restrict__ clear_from, size_t clear_words)
 {
-    const int st = blockIdx.x * kWaves + threadIdx.x / kLanes;
-    if (st >= n_st) return;
-    const int lane = threadIdx.x % kLanes;
-    const size_t w0 = static_cast<size_t>(st) * kTilesPerSuper * 4;   // 4 words per wave tile
-    uint32_t both = 0;
-    for (int w = lane; w < kTilesPerSuper * 4; w += kLanes) both += __popcll(mask_a[w0 + w] & mask_b[w0 + w]);
-    both = wave_sum(both);
-    if (lane == 0 && both) atomicSub(&d[sts[st].seg], static_cast<int32_t>(both));
+    for (size_t i = blockIdx.x * static_cast<size_t>(kBlock) + threadIdx.x; i < clear_words;
+         i += static_cast<size_t>(gridDim.x) * kBlock)
+        clear_from[i] = 0u;
+    const int lane = threadIdx.x % kLanes, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
+    const int64_t n_waves = static_cast<int64_t>(gridDim.x) * kWaves, w_id = static_cast<int64_t>(blockIdx.x) * kWaves + wave;
+    const int lo = static_cast<int>(n_st * w_id / n_waves), hi = static_cast<int>(n_st * (w_id + 1) / n_waves);
+    static_assert(kTilesPerSuper * 4 == 2 * kLanes, "one 16-byte access per lane and supertile");
+    int seg = -1;
+    uint32_t both = 0;                                      // this lane's share of the members of both in `seg`
+    auto flush = [&]() {
+        const uint32_t n = wave_sum(both);
+        if (lane == 0 && n) atomicSub(&d[seg], static_cast<int32_t>(n));
+        both = 0;
+    };
+    for (int st = lo; st < hi; ++st) {
+        const int here = sts[st].seg;
+        const ulonglong2 a = reinterpret_cast<const ulonglong2*>(mask_a + static_cast<size_t>(st) * kTilesPerSuper * 4)[lane];
+        const ulonglong2 b = reinterpret_cast<const ulonglong2*>(mask_b + static_cast<size_t>(st) * kTilesPerSuper * 4)[lane];
+        if (here != seg) {                                  // wave-uniform
+            if (seg >= 0) flush();
+            seg = here;
+        }
+        both += __popcll(a.x & b.x) + __popcll(a.y & b.y);
+    }
+    __shared__ uint32_t part[kWaves];
+    __shared__ int part_seg[kWaves];
+    const uint32_t n = wave_sum(both);
+    if (lane == 0) {
+        part[wave] = n;
+        part_seg[wave] = seg;
+    }
+    __syncthreads();
+    if (threadIdx.x < kWaves && part_seg[threadIdx.x] >= 0) {
+        // the first of the block's waves that ended in this segment adds them all up
+        uint32_t sum = 0;
+        for (int w = 0; w < kWaves; ++w) {
+            if (part_seg[w] != part_seg[threadIdx.x]) continue;
+            if (w < static_cast<int>(threadIdx.x)) return;
+            sum += part[w];
+        }
+        if (sum) atomicSub(&d[part_seg[threadIdx.x]], static_cast<int32_t>(sum));
+    }
 }
 
-// Partial sums of a.b, a.a and b.b in binary64, added into acc[1..3].
+// Partial sums of a.b, a.a and b.b in binary64, three per block.  Bound by the read of a and b: 16 bytes per
+// access and thread with four accesses in flight, if both vectors start on 16 bytes (VEC); one element at a time
+// took 57 us at 25.6 M, 3.6 TB/s.
+constexpr int kDotsBlocks = 2048;
+
+template <bool VEC>
 __global__ void __launch_bounds__(kBlock)
-k_dots(const float* __restrict__ a, const float* __restrict__ b, int64_t numel, double* __restrict__ acc)
+k_dots(const float* __restrict__ a, const float* __restrict__ b, int64_t numel, double* __restrict__ partial)
 {
     double ab = 0.0, aa = 0.0, bb = 0.0;
-    for (int64_t j = blockIdx.x * static_cast<int64_t>(kBlock) + threadIdx.x; j < numel;
-         j += static_cast<int64_t>(gridDim.x) * kBlock) {
-        const double x = a[j], y = b[j];
+    auto add = [&](float fx, float fy) {
+        const double x = fx, y = fy;
         ab += x * y;
         aa += x * x;
         bb += y * y;
+    };
+    const int64_t t = blockIdx.x * static_cast<int64_t>(kBlock) + threadIdx.x, stride = static_cast<int64_t>(gridDim.x) * kBlock;
+    const int64_t groups = VEC ? numel / kVec : 0;
+    if (VEC) {
+        constexpr int kAhead = 2;
+        int64_t g = t;
+        for (; g + (kAhead - 1) * stride < groups; g += kAhead * stride) {
+            float4 x[kAhead], y[kAhead];
+#pragma unroll
+            for (int j = 0; j < kAhead; ++j) {
+                x[j] = load4(a + (g + j * stride) * kVec);
+                y[j] = load4(b + (g + j * stride) * kVec);
+            }
+#pragma unroll
+            for (int j = 0; j < kAhead; ++j) {
+                add(x[j].x, y[j].x);
+                add(x[j].y, y[j].y);
+                add(x[j].z, y[j].z);
+                add(x[j].w, y[j].w);
+            }
+        }
+        for (; g < groups; g += stride) {
+            const float4 x = load4(a + g * kVec), y = load4(b + g * kVec);
+            add(x.x, y.x);
+            add(x.y, y.y);
+            add(x.z, y.z);
+            add(x.w, y.w);
+        }
     }
+    for (int64_t j = groups * kVec + t; j < numel; j += stride) add(a[j], b[j]);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         ab += __shfl_xor(ab, off, kLanes);
@@ -85,16 +202,39 @@ k_dots(const float* __restrict__ a, const float* __restrict__ b, int64_t numel, 
     }
     __syncthreads();
     if (threadIdx.x < 3) {
-        double t = 0.0;
-        for (int w = 0; w < kWaves; ++w) t += part[threadIdx.x][w];
-        atomicAdd(&acc[1 + threadIdx.x], t);
+        double s = 0.0;
+        for (int w = 0; w < kWaves; ++w) s += part[threadIdx.x][w];
+        partial[threadIdx.x * static_cast<size_t>(kDotsBlocks) + blockIdx.x] = s;
     }
 }
 
-// acc[0] = 1 - a.b / (|a| |b|)
-__global__ void k_cosine_final(double* __restrict__ acc)
+// out[1..3] = the sums over n_blocks blocks, out[0] = 1 - a.b / (|a| |b|), by one block.
+__global__ void __launch_bounds__(kBlock) k_cosine_final(const double* __restrict__ partial, int n_blocks, double* __restrict__ out)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) acc[0] = 1.0 - acc[1] / (sqrt(acc[2]) * sqrt(acc[3]));
+    double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int j = 0; j < kDotsBlocks / kBlock; ++j) {
+            const int i = j * kBlock + static_cast<int>(threadIdx.x);
+            s[c] += i < n_blocks ? partial[c * static_cast<size_t>(kDotsBlocks) + i] : 0.0;
+        }
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) s[c] += __shfl_xor(s[c], off, kLanes);
+    __shared__ double part[3][kWaves];
+    if (threadIdx.x % kLanes == 0)
+        for (int c = 0; c < 3; ++c) part[c][threadIdx.x / kLanes] = s[c];
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    double tot[3];
+    for (int c = 0; c < 3; ++c) {
+        tot[c] = 0.0;
+        for (int w = 0; w < kWaves; ++w) tot[c] += part[c][w];
+        out[1 + c] = tot[c];
+    }
+    out[0] = 1.0 - tot[0] / (sqrt(tot[1]) * sqrt(tot[2]));
 }
 
 // Plain streaming copy, one 16-byte nontemporal load and store per thread: the yardstick the

@@ -90,7 +90,7 @@ constexpr int64_t max_chunks(int64_t numel_max, int n_tensors_max)
 
 struct WsLayout {
     size_t segs, sts, chunks, hblocks, small, preds, stats, state, wt_cnt, st_sum, st_prefix, chunk_tot, st_cand_cnt, cand, sel_mask,
-        eq_mask, tile_slot, vals, best, parts, short_used, short_counts, short_keys, total;
+        eq_mask, tile_slot, vals, best, parts, short_used, short_counts, short_keys, diag_preds, dots, total;
     int64_t short_numel;   // positions that the short path's key array is made for
     size_t short_words;    // and its words
     // per-step counters and histograms: one zone, all zero between steps (offsets inside the zone)
@@ -152,6 +152,10 @@ constexpr WsLayout layout_for(int64_t numel_max, int n_tensors_max, int n_learne
     l.tile_slot = take(ntile * sizeof(uint32_t));
     l.vals = take(static_cast<size_t>(n_learners_max) * static_cast<size_t>(k_max) * sizeof(float));
     l.best = take(static_cast<size_t>(k_max) * sizeof(unsigned long long));       // chunk-wise selector: a word per chunk
+    // similarity diagnostics: predictions for the leader's vector and for the sum over learners, and per learner and
+    // segment that leader's last threshold (kept like the steps' own); partial sums of the cosine distance
+    l.diag_preds = take((2 * kPredWords + static_cast<size_t>(n_learners_max)) * nt * sizeof(uint32_t));
+    l.dots = take(3 * static_cast<size_t>(kDotsBlocks) * sizeof(double));
     // short path: the parts, what each segment's list starts from, counts and keys per part
     l.parts = take(kShortPartsMax * sizeof(PartDesc));
     l.short_used = take(nt * sizeof(uint4));
@@ -423,6 +427,9 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
     k_init<<<1, kBlock, 0, ctx->stream>>>(reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.preds),
                                           (kPredWords + static_cast<size_t>(ctx->n_learners_max)) *
                                               static_cast<size_t>(ctx->n_tensors_max));
+    k_init<<<1, kBlock, 0, ctx->stream>>>(reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.diag_preds),
+                                          (2 * kPredWords + static_cast<size_t>(ctx->n_learners_max)) *
+                                              static_cast<size_t>(ctx->n_tensors_max));
     if (!ctx->stats_ready) {
         k_init<<<1, kBlock, 0, ctx->stream>>>(reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.stats),
                                               kStatWords * sizeof(unsigned long long) / sizeof(uint32_t));
@@ -486,13 +493,13 @@ void launch_update_reduce(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learne
 // The exact selection on one vector x = fma(lr, grad, mem) (Eq. 2): every kernel from the first
 // look at the vector to the output slot of every wave tile.  Leaves the membership mask, the
 // tile slots and the threshold behind.  `preds` holds one bucket prediction per segment (read and
-// rewritten), `stats` the context's selection counters (null: nothing is counted).  Expects the scratch zone zeroed (clears it first if the context says it is not) and
-// leaves it used: nothing reads the zone after this function's last kernel, and the caller has
-// it cleared (the all-learner pass does that on the way, see launch_update_reduce), or, with
-// `clear_after`, a clearing kernel is enqueued here.
+// rewritten), `stats` the context's selection counters (null: nothing is counted), `sel_mask` the membership mask.
+// Expects the scratch zone zeroed (clears it first if the context says it is not) and leaves it used: nothing reads
+// the zone after this function's last kernel, and the caller has it cleared by a kernel that follows (the
+// all-learner pass does that on the way, see launch_update_reduce).
 template <typename G, typename Mark>
 void launch_select(scalecom_ctx* ctx, const float* memL, const G* gradL, float lr, int n_tensors, uint32_t* preds,
-                   uint32_t* lead_mine, unsigned long long* stats, bool clear_after, Mark&& mark)
+                   uint32_t* lead_mine, unsigned long long* stats, uint64_t* sel_mask, Mark&& mark)
 {
     char* ws = ctx->ws;
     const WsLayout& l = ctx->lay;
@@ -525,7 +532,6 @@ void launch_select(scalecom_ctx* ctx, const float* memL, const G* gradL, float l
     uint2* chunk_tot = reinterpret_cast<uint2*>(ws + l.chunk_tot);
     uint32_t* st_cand_cnt = reinterpret_cast<uint32_t*>(ws + l.st_cand_cnt);
     uint2* cand = reinterpret_cast<uint2*>(ws + l.cand);
-    uint64_t* sel_mask = reinterpret_cast<uint64_t*>(ws + l.sel_mask);
     uint64_t* eq_mask = reinterpret_cast<uint64_t*>(ws + l.eq_mask);
     uint32_t* tile_slot = reinterpret_cast<uint32_t*>(ws + l.tile_slot);
     const int n_st = ctx->n_st;
@@ -574,10 +580,6 @@ void launch_select(scalecom_ctx* ctx, const float* memL, const G* gradL, float l
             k_slots<false><<<(n_st + kWaves - 1) / kWaves, kBlock, 0, s>>>(segs, sts, n_st, state, wt_cnt, st_sum, st_prefix,
                                                                            chunk_tot, sel_mask, eq_mask, tile_slot,
                                                                            n_tensors == 1);
-    }
-    if (clear_after) {
-        clear_zone();
-        if (hipPeekAtLastError() == hipSuccess) ctx->scratch_clean = true;
     }
 }
 
@@ -641,7 +643,8 @@ scalecom_status launch_step(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_lear
             return SCALECOM_OK;
         }
         launch_select<G>(ctx, lp.mem[leader], static_cast<const G*>(lp.grad[leader]), lr, n_tensors, preds, lead_mine,
-                         reinterpret_cast<unsigned long long*>(ctx->ws + ctx->lay.stats), false, mark);
+                         reinterpret_cast<unsigned long long*>(ctx->ws + ctx->lay.stats),
+                         reinterpret_cast<uint64_t*>(ctx->ws + ctx->lay.sel_mask), mark);
         mark(3);
         launch_update_reduce<G>(ctx, lp, n_learners, k_total, beta, lr, idx_out, red_out,
                                 reinterpret_cast<uint32_t*>(ctx->ws + ctx->lay.zone), ctx->lay.zone_bytes / sizeof(uint32_t),
@@ -839,10 +842,9 @@ scalecom_status step_common(scalecom_ctx* ctx, float* const* mem, const void* co
     return launch_step<float>(ctx, lp, n_learners, n_tensors, k_total, beta, lr, leader, idx_out, red_out);
 }
 
-// Scratch of scalecom_hamming_distance: the summed vector, a copy of the leader's membership
-// mask, and bucket predictions of its own (so the step's predictions stay untouched).
+// Scratch of scalecom_hamming_distance: the summed vector and the leader's membership mask.
 struct DiagLayout {
-    size_t y, mask, preds, total;
+    size_t y, mask, total;
 };
 
 DiagLayout diag_layout(int64_t numel_max, int n_tensors_max)
@@ -851,8 +853,7 @@ DiagLayout diag_layout(int64_t numel_max, int n_tensors_max)
     const size_t ntile = static_cast<size_t>(max_supertiles(numel_max, n_tensors_max)) * kTilesPerSuper;
     d.y = 0;
     d.mask = align_up(static_cast<size_t>(numel_max) * sizeof(float), 256);
-    d.preds = d.mask + align_up(ntile * 4 * sizeof(uint64_t), 256);
-    d.total = d.preds + align_up(kPredWords * static_cast<size_t>(n_tensors_max) * sizeof(uint32_t), 256);
+    d.total = d.mask + align_up(ntile * 4 * sizeof(uint64_t), 256);
     return d;
 }
 
@@ -863,33 +864,40 @@ scalecom_status launch_hamming(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
     const WsLayout& l = ctx->lay;
     hipStream_t s = ctx->stream;
     const DiagLayout dl = diag_layout(ctx->numel_max, ctx->n_tensors_max);
+    const size_t nt = static_cast<size_t>(ctx->n_tensors_max);
     float* y = reinterpret_cast<float*>(scratch + dl.y);
     uint64_t* mask_a = reinterpret_cast<uint64_t*>(scratch + dl.mask);
-    uint32_t* preds = reinterpret_cast<uint32_t*>(scratch + dl.preds);
+    uint64_t* mask_b = reinterpret_cast<uint64_t*>(ctx->ws + l.sel_mask);
+    const uint32_t* preds = reinterpret_cast<const uint32_t*>(ctx->ws + l.preds);
+    uint32_t* preds_a = reinterpret_cast<uint32_t*>(ctx->ws + l.diag_preds);
+    uint32_t* preds_b = preds_a + kPredWords * nt;
+    uint32_t* lead_a = preds_b + (kPredWords + static_cast<size_t>(leader)) * nt;
     const SegDesc* segs = reinterpret_cast<const SegDesc*>(ctx->ws + l.segs);
     const StDesc* sts = reinterpret_cast<const StDesc*>(ctx->ws + l.sts);
-    const uint64_t* sel_mask = reinterpret_cast<const uint64_t*>(ctx->ws + l.sel_mask);
-    const size_t mask_bytes = static_cast<size_t>(ctx->n_st) * kTilesPerSuper * 4 * sizeof(uint64_t);
+    uint32_t* zone = reinterpret_cast<uint32_t*>(ctx->ws + l.zone);
+    const size_t zone_words = l.zone_bytes / sizeof(uint32_t);
     auto no_mark = [](int) {};
 
-    k_set_ks<<<(n_tensors + kBlock - 1) / kBlock, kBlock, 0, s>>>(segs, n_tensors, d_out);
+    k_diag_begin<<<(n_tensors + kBlock - 1) / kBlock, kBlock, 0, s>>>(
+        segs, n_tensors, preds, preds + (kPredWords + static_cast<size_t>(leader)) * nt, preds_a, lead_a, d_out);
     if (ctx->n_st > 0) {
         // the leader's index set (Eq. 3)
-        k_init<<<1, kBlock, 0, s>>>(preds, kPredWords * static_cast<size_t>(n_tensors));
-        launch_select<G>(ctx, lp.mem[leader], static_cast<const G*>(lp.grad[leader]), lr, n_tensors, preds, nullptr, nullptr,
-                         true, no_mark);
-        SC_HIP(ctx, hipMemcpyAsync(mask_a, sel_mask, mask_bytes, hipMemcpyDeviceToDevice, s));
+        launch_select<G>(ctx, lp.mem[leader], static_cast<const G*>(lp.grad[leader]), lr, n_tensors, preds_a, lead_a, nullptr,
+                         mask_a, no_mark);
         // the top-k of the summed error-feedback gradients
-        const int64_t blocks = (end - begin + kBlock - 1) / kBlock;
-        const unsigned gx = static_cast<unsigned>(std::min<int64_t>(blocks, 1 << 20));
-        const dim3 grid(gx, static_cast<unsigned>((blocks + gx - 1) / gx));
-        k_sum_x<G><<<grid, kBlock, 0, s>>>(lp, n_learners, lr, begin, end, y);
-        k_init<<<1, kBlock, 0, s>>>(preds, kPredWords * static_cast<size_t>(n_tensors));
-        launch_select<NoGrad>(ctx, y, static_cast<const NoGrad*>(nullptr), 0.0f, n_tensors, preds, nullptr, nullptr, true,
+        const int64_t tiles = (end - (begin & ~static_cast<int64_t>(kVec - 1)) + kWaveTile - 1) / kWaveTile;
+        const unsigned gx = static_cast<unsigned>(std::min<int64_t>(tiles, 1 << 20));
+        const dim3 grid(gx, static_cast<unsigned>((tiles + gx - 1) / gx));
+        k_sum_x<G><<<grid, std::min(n_learners, kSumWaves) * kLanes, sizeof(float4) * kLanes * n_learners, s>>>(
+            lp, n_learners, lr, begin, end, tiles, y, zone, zone_words);
+        ctx->scratch_clean = hipPeekAtLastError() == hipSuccess;
+        launch_select<NoGrad>(ctx, y, static_cast<const NoGrad*>(nullptr), 0.0f, n_tensors, preds_b, nullptr, nullptr, mask_b,
                               no_mark);
-        k_mask_overlap<<<(ctx->n_st + kWaves - 1) / kWaves, kBlock, 0, s>>>(sts, ctx->n_st, mask_a, sel_mask, d_out);
+        k_mask_overlap<<<std::min(kOverlapBlocks, (ctx->n_st + kWaves - 1) / kWaves), kBlock, 0, s>>>(
+            sts, ctx->n_st, mask_a, mask_b, d_out, zone, zone_words);
     }
     SC_HIP(ctx, hipGetLastError());
+    if (ctx->n_st > 0) ctx->scratch_clean = true;
     return SCALECOM_OK;
 }
 
@@ -1211,12 +1219,16 @@ scalecom_status scalecom_cosine_distance(scalecom_ctx* ctx, const float* a, cons
     if (reinterpret_cast<uintptr_t>(out) % 8) return fail(ctx, SCALECOM_EINVAL, "out is not aligned");
     DeviceGuard guard;
     SC_HIP(ctx, guard.enter(ctx->device));
-    k_init<<<1, kBlock, 0, ctx->stream>>>(reinterpret_cast<uint32_t*>(out), 8);
-    if (numel > 0) {
-        const int grid = static_cast<int>(std::min<int64_t>((numel + kBlock - 1) / kBlock, 2048));
-        k_dots<<<grid, kBlock, 0, ctx->stream>>>(a, b, numel, out);
+    double* partial = reinterpret_cast<double*>(ctx->ws + ctx->lay.dots);
+    const int64_t per_block = static_cast<int64_t>(kBlock) * kVec;
+    const int grid = static_cast<int>(std::min<int64_t>((numel + per_block - 1) / per_block, kDotsBlocks));
+    if (grid > 0) {
+        if (reinterpret_cast<uintptr_t>(a) % 16 == 0 && reinterpret_cast<uintptr_t>(b) % 16 == 0)
+            k_dots<true><<<grid, kBlock, 0, ctx->stream>>>(a, b, numel, partial);
+        else
+            k_dots<false><<<grid, kBlock, 0, ctx->stream>>>(a, b, numel, partial);
     }
-    k_cosine_final<<<1, kLanes, 0, ctx->stream>>>(out);
+    k_cosine_final<<<1, kBlock, 0, ctx->stream>>>(partial, grid, out);
     SC_HIP(ctx, hipGetLastError());
     return SCALECOM_OK;
 }

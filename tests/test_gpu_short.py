@@ -130,3 +130,46 @@ def test_chunks_per_layer_in_one_launch(gu):
             print(f"[chunk] per layer step={step}", flush=True)
             gu.compare_step(ctx, mem, grad, ref, step, 0.5, 0.25, offsets=offsets, chunks=chunks, what="chunks per layer")
         ctx.close()
+
+
+@pytest.mark.parametrize("numel", [1, 3, 1023, 4096, 2048 * 1024 + 5, 2 * 2048 * 1024 + 1029])
+def test_cosine_distance_at_any_alignment(gu, numel):
+    """Vectors that start on 16 bytes and vectors that do not, fewer elements than a block has threads and more
+    than one round of the grid."""
+    ctx = binding.scalecom_init(16, 1, torch.float32, 1, gu.DEV)
+    a, b = _normal(numel + 4, 1, 1.0).to(gu.DEV), _normal(numel + 4, 2, 1.0).to(gu.DEV)
+    for da, db in ((0, 0), (1, 0), (2, 3), (0, 4)):
+        x, y = a[da:da + numel], b[db:db + numel]
+        out = ctx.scalecom_cosine_distance(x, y).cpu().numpy()
+        xd, yd = x.double(), y.double()
+        ab, aa, bb = float((xd * yd).sum()), float((xd * xd).sum()), float((yd * yd).sum())
+        np.testing.assert_allclose(out[2:], [aa, bb], rtol=1e-13)
+        assert abs(out[1] - ab) <= 1e-13 * (aa * bb) ** 0.5 and abs(out[0] - (1.0 - ab / (aa * bb) ** 0.5)) <= 1e-13
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 16, 17])
+def test_hamming_distance_repeated(gu, n):
+    """The diagnostic keeps thresholds of its own: called again and again between steps, with gradients whose
+    scale jumps, on a flat vector and on tensors at odd starts, with more learners than a block has waves."""
+    import oracle
+    for offsets, ks in (([0, 50_001], [500]), ([3, 20_000, 20_000, 20_007, 61_003], [200, 0, 7, 410])):
+        numel = offsets[-1] + 2
+        ctx = binding.scalecom_init(numel, n, torch.float32, len(ks), gu.DEV)
+        mem = [_normal(numel, 5 * i, 1.0).to(gu.DEV) for i in range(n)]
+        ref = [m.cpu().numpy().copy() for m in mem]
+        for step in range(6):
+            scale = [1.0, 1.0, 40.0, 1.0, 0.01, 1.0][step]
+            grad = [(_normal(numel, 900 + step, scale) + _normal(numel, 40 * step + i, 0.5 * scale)).to(gu.DEV) for i in range(n)]
+            for rep in range(2):
+                print(f"[hamming] n={n} tensors={len(ks)} step={step}", flush=True)
+                d = ctx.scalecom_hamming_distance(mem, grad, offsets, ks, 0.7, step)
+                torch.cuda.synchronize()
+                host = [g.cpu().numpy() for g in grad]
+                for s, k in enumerate(ks):
+                    a, b = offsets[s], offsets[s + 1]
+                    want = 0 if a == b else oracle.hamming_distance([np.ascontiguousarray(m[a:b]) for m in ref],
+                                                                    [np.ascontiguousarray(g[a:b]) for g in host], k, 0.7, step)
+                    assert int(d[s]) == want, (step, rep, s)
+            gu.compare_step(ctx, mem, grad, ref, step, 0.5, 0.7, offsets=offsets, ks=ks, what="between diagnostics")
+        ctx.close()
