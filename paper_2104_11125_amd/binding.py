@@ -6,6 +6,7 @@ there is no fallback.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 from typing import Optional, Sequence
@@ -86,8 +87,37 @@ def scalecom_workspace_bytes(numel_max: int, n_tensors_max: int, n_learners_max:
     return int(lib().scalecom_workspace_bytes(numel_max, n_tensors_max, n_learners_max, k_max))
 
 
-def _ptrs(tensors: Sequence[torch.Tensor]):
-    return (ctypes.c_void_p * len(tensors))(*[t.data_ptr() for t in tensors])
+def _ptr_array(addresses):
+    return (ctypes.c_void_p * len(addresses))(*addresses)
+
+
+def _int64_array(values):
+    """Values as an int64 array (anything int() takes) whose memory the C-ABI can read."""
+    try:
+        return array.array("q", values)
+    except TypeError:
+        return array.array("q", [int(v) for v in values])
+
+
+def _address(a: array.array):
+    return ctypes.c_void_p(a.buffer_info()[0])
+
+
+def _checked_ptrs(mem, grad, mem_dtype, grad_dtype, device, type_error, place_error):
+    """Every learner's buffers: one dtype, contiguous, on one device and of one length.  Returns the length
+    and the two pointer tables.  (One walk over the tensors: the attribute look-ups are most of what a call costs.)"""
+    numel = mem[0].numel()
+    mem_ptrs, grad_ptrs = [], []
+    for m, g in zip(mem, grad):
+        if m.dtype is not mem_dtype or g.dtype is not grad_dtype:
+            raise TypeError(type_error)
+        if not (m.is_contiguous() and g.is_contiguous() and m.device == device and g.device == device):
+            raise ValueError(place_error)
+        if m.numel() != numel or g.numel() != numel:
+            raise ValueError("every learner's mem and grad must have the same number of elements")
+        mem_ptrs.append(m.data_ptr())
+        grad_ptrs.append(g.data_ptr())
+    return numel, _ptr_array(mem_ptrs), _ptr_array(grad_ptrs)
 
 
 def scalecom_layer_ks(flops_per_gradient: Sequence[float], sizes: Sequence[int],
@@ -113,22 +143,19 @@ def scalecom_step_static(mem: Sequence[torch.Tensor], grad: Sequence[torch.Tenso
     """``scalecom_step_static`` of the C-ABI: no context, no workspace, nothing allocated (so the
     outputs must be passed in).  Marshalling only; sizes beyond the static limits raise."""
     dev = mem[0].device
-    numel = mem[0].numel()
-    for m, g in zip(mem, grad):
-        if m.dtype != torch.float32 or g.dtype not in (torch.float32, torch.bfloat16) or g.dtype != grad[0].dtype:
-            raise TypeError("mem must be float32 and grad float32 or bfloat16")
-        if not (m.is_contiguous() and g.is_contiguous() and m.device == dev and g.device == dev):
-            raise ValueError("buffers must be contiguous tensors on one device")
-        if m.numel() != numel or g.numel() != numel:
-            raise ValueError("every learner's mem and grad must have the same number of elements")
+    gd = grad[0].dtype
+    if gd not in (torch.float32, torch.bfloat16):
+        raise TypeError("mem must be float32 and grad float32 or bfloat16")
+    numel, c_mem, c_grad = _checked_ptrs(mem, grad, torch.float32, gd, dev, "mem must be float32 and grad float32 or bfloat16",
+                                         "buffers must be contiguous tensors on one device")
     if idx_out.dtype != torch.int32 or reduced_vals_out.dtype != torch.float32 or \
             idx_out.numel() < k or reduced_vals_out.numel() < k:
         raise TypeError("idx_out must be int32[k] and reduced_vals_out float32[k]")
     s = stream if stream is not None else torch.cuda.current_stream(dev)
     index = dev.index if dev.index is not None else torch.cuda.current_device()
-    st = lib().scalecom_step_static(index, ctypes.c_void_p(s.cuda_stream), _ptrs(mem), _ptrs(grad), len(mem), numel, k,
+    st = lib().scalecom_step_static(index, ctypes.c_void_p(s.cuda_stream), c_mem, c_grad, len(mem), numel, k,
                                     beta, lr, step,
-                                    SCALECOM_GRAD_BF16 if grad[0].dtype == torch.bfloat16 else SCALECOM_GRAD_F32,
+                                    SCALECOM_GRAD_BF16 if gd == torch.bfloat16 else SCALECOM_GRAD_F32,
                                     ctypes.c_void_p(idx_out.data_ptr()), ctypes.c_void_p(reduced_vals_out.data_ptr()))
     if st != SCALECOM_OK:
         raise ScaleComError(st, lib().scalecom_last_error(None).decode())
@@ -171,28 +198,23 @@ class ScaleCom:
         """Every learner's buffers have one length (and reach `extent`, the end of the last segment)."""
         if len(mem) != len(grad) or len(mem) == 0:
             raise ValueError("one mem and one grad buffer per learner")
-        numel = mem[0].numel()
-        for m, g in zip(mem, grad):
-            if m.dtype != torch.float32 or g.dtype != self.grad_dtype:
-                raise TypeError("mem must be float32 and grad must have the context's grad_dtype")
-            if not (m.is_contiguous() and g.is_contiguous() and m.device == self.device and g.device == self.device):
-                raise ValueError("buffers must be contiguous tensors on the context's device")
-            if m.numel() != numel or g.numel() != numel:
-                raise ValueError("every learner's mem and grad must have the same number of elements")
+        numel, c_mem, c_grad = _checked_ptrs(mem, grad, torch.float32, self.grad_dtype, self.device,
+                                             "mem must be float32 and grad must have the context's grad_dtype",
+                                             "buffers must be contiguous tensors on the context's device")
         if extent is not None and int(extent) > numel:
             raise ValueError("the last segment ends beyond the learners' buffers")
+        return numel, c_mem, c_grad
 
     def scalecom_step(self, mem: Sequence[torch.Tensor], grad: Sequence[torch.Tensor], k: int, beta: float,
                       lr: float, step: int, idx_out: Optional[torch.Tensor] = None,
                       reduced_vals_out: Optional[torch.Tensor] = None):
         """``scalecom_step`` of the C-ABI; allocates the two outputs if they are not given."""
-        self._check_buffers(mem, grad)
-        numel = mem[0].numel()
+        numel, c_mem, c_grad = self._check_buffers(mem, grad)
         if idx_out is None:
             idx_out = torch.empty(max(k, 0), dtype=torch.int32, device=self.device)
         if reduced_vals_out is None:
             reduced_vals_out = torch.empty(max(k, 0), dtype=torch.float32, device=self.device)
-        st = lib().scalecom_step(self._ctx, _ptrs(mem), _ptrs(grad), len(mem), numel, k, beta, lr, step,
+        st = lib().scalecom_step(self._ctx, c_mem, c_grad, len(mem), numel, k, beta, lr, step,
                                  ctypes.c_void_p(idx_out.data_ptr()), ctypes.c_void_p(reduced_vals_out.data_ptr()))
         self._check(st)
         return idx_out, reduced_vals_out
@@ -201,14 +223,13 @@ class ScaleCom:
                               beta: float, lr: float, step: int, idx_out: Optional[torch.Tensor] = None,
                               reduced_vals_out: Optional[torch.Tensor] = None):
         """``scalecom_step_chunked`` of the C-ABI: one position per chunk of ``chunk`` elements."""
-        self._check_buffers(mem, grad)
-        numel = mem[0].numel()
+        numel, c_mem, c_grad = self._check_buffers(mem, grad)
         k = -(-numel // chunk) if chunk >= 1 else 0
         if idx_out is None:
             idx_out = torch.empty(k, dtype=torch.int32, device=self.device)
         if reduced_vals_out is None:
             reduced_vals_out = torch.empty(k, dtype=torch.float32, device=self.device)
-        st = lib().scalecom_step_chunked(self._ctx, _ptrs(mem), _ptrs(grad), len(mem), numel, chunk, beta, lr, step,
+        st = lib().scalecom_step_chunked(self._ctx, c_mem, c_grad, len(mem), numel, chunk, beta, lr, step,
                                          ctypes.c_void_p(idx_out.data_ptr()),
                                          ctypes.c_void_p(reduced_vals_out.data_ptr()))
         self._check(st)
@@ -219,19 +240,19 @@ class ScaleCom:
                              idx_out: Optional[torch.Tensor] = None,
                              reduced_vals_out: Optional[torch.Tensor] = None):
         """``scalecom_step_layers`` of the C-ABI."""
-        self._check_buffers(mem, grad, offsets[-1] if len(offsets) else None)
+        _, c_mem, c_grad = self._check_buffers(mem, grad, offsets[-1] if len(offsets) else None)
         n_tensors = len(ks)
         if len(offsets) != n_tensors + 1:
             raise ValueError("offsets must have len(ks) + 1 entries")
-        c_off = (ctypes.c_int64 * (n_tensors + 1))(*[int(o) for o in offsets])
-        c_ks = (ctypes.c_int64 * n_tensors)(*[int(v) for v in ks])
-        total = max(int(sum(int(v) for v in ks)), 0)
+        c_off, c_ks = _int64_array(offsets), _int64_array(ks)
+        if idx_out is None or reduced_vals_out is None:
+            total = max(sum(c_ks), 0)
         if idx_out is None:
             idx_out = torch.empty(total, dtype=torch.int32, device=self.device)
         if reduced_vals_out is None:
             reduced_vals_out = torch.empty(total, dtype=torch.float32, device=self.device)
-        st = lib().scalecom_step_layers(self._ctx, _ptrs(mem), _ptrs(grad), len(mem), n_tensors, c_off, c_ks, beta,
-                                        lr, step, ctypes.c_void_p(idx_out.data_ptr()),
+        st = lib().scalecom_step_layers(self._ctx, c_mem, c_grad, len(mem), n_tensors, _address(c_off),
+                                        _address(c_ks), beta, lr, step, ctypes.c_void_p(idx_out.data_ptr()),
                                         ctypes.c_void_p(reduced_vals_out.data_ptr()))
         self._check(st)
         return idx_out, reduced_vals_out
@@ -241,20 +262,19 @@ class ScaleCom:
                                      idx_out: Optional[torch.Tensor] = None,
                                      reduced_vals_out: Optional[torch.Tensor] = None):
         """``scalecom_step_layers_chunked`` of the C-ABI: one position per chunk, a chunk size per tensor."""
-        self._check_buffers(mem, grad, offsets[-1] if len(offsets) else None)
+        _, c_mem, c_grad = self._check_buffers(mem, grad, offsets[-1] if len(offsets) else None)
         n_tensors = len(chunks)
         if len(offsets) != n_tensors + 1:
             raise ValueError("offsets must have len(chunks) + 1 entries")
-        c_off = (ctypes.c_int64 * (n_tensors + 1))(*[int(o) for o in offsets])
-        c_ch = (ctypes.c_int64 * n_tensors)(*[int(v) for v in chunks])
-        total = sum(-(-(int(b) - int(a)) // int(c)) for a, b, c in zip(offsets[:-1], offsets[1:], chunks)
-                    if int(c) >= 1 and int(b) >= int(a))
+        c_off, c_ch = _int64_array(offsets), _int64_array(chunks)
+        if idx_out is None or reduced_vals_out is None:
+            total = sum(-(-(b - a) // c) for a, b, c in zip(c_off[:-1], c_off[1:], c_ch) if c >= 1 and b >= a)
         if idx_out is None:
             idx_out = torch.empty(total, dtype=torch.int32, device=self.device)
         if reduced_vals_out is None:
             reduced_vals_out = torch.empty(total, dtype=torch.float32, device=self.device)
-        st = lib().scalecom_step_layers_chunked(self._ctx, _ptrs(mem), _ptrs(grad), len(mem), n_tensors, c_off, c_ch,
-                                                beta, lr, step, ctypes.c_void_p(idx_out.data_ptr()),
+        st = lib().scalecom_step_layers_chunked(self._ctx, c_mem, c_grad, len(mem), n_tensors, _address(c_off),
+                                                _address(c_ch), beta, lr, step, ctypes.c_void_p(idx_out.data_ptr()),
                                                 ctypes.c_void_p(reduced_vals_out.data_ptr()))
         self._check(st)
         return idx_out, reduced_vals_out
@@ -290,12 +310,11 @@ class ScaleCom:
                                   offsets: Sequence[int], ks: Sequence[int], lr: float, step: int,
                                   d_out: Optional[torch.Tensor] = None) -> torch.Tensor:
         """``scalecom_hamming_distance`` of the C-ABI; the scratch buffer is allocated on first use and kept."""
-        self._check_buffers(mem, grad, offsets[-1] if len(offsets) else None)
+        _, c_mem, c_grad = self._check_buffers(mem, grad, offsets[-1] if len(offsets) else None)
         n_tensors = len(ks)
         if len(offsets) != n_tensors + 1:
             raise ValueError("offsets must have len(ks) + 1 entries")
-        c_off = (ctypes.c_int64 * (n_tensors + 1))(*[int(o) for o in offsets])
-        c_ks = (ctypes.c_int64 * n_tensors)(*[int(v) for v in ks])
+        c_off, c_ks = _int64_array(offsets), _int64_array(ks)
         if self._diag_scratch is None:
             nbytes = lib().scalecom_hamming_scratch_bytes(self.numel_max, self.n_tensors_max)
             self._diag_scratch = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
@@ -303,8 +322,8 @@ class ScaleCom:
             d_out = torch.empty(n_tensors, dtype=torch.int32, device=self.device)
         elif d_out.dtype != torch.int32 or d_out.numel() < n_tensors:
             raise TypeError("d_out must be int32 with one entry per tensor")
-        st = lib().scalecom_hamming_distance(self._ctx, _ptrs(mem), _ptrs(grad), len(mem), n_tensors, c_off, c_ks, lr,
-                                             step, ctypes.c_void_p(self._diag_scratch.data_ptr()),
+        st = lib().scalecom_hamming_distance(self._ctx, c_mem, c_grad, len(mem), n_tensors, _address(c_off),
+                                             _address(c_ks), lr, step, ctypes.c_void_p(self._diag_scratch.data_ptr()),
                                              self._diag_scratch.numel(), ctypes.c_void_p(d_out.data_ptr()))
         self._check(st)
         return d_out

@@ -197,6 +197,7 @@ struct scalecom_ctx {
     WsLayout lay{};
     // tables of the layout used last, kept on the device until the layout changes
     std::vector<int64_t> cached_offsets, cached_ks, cached_chunks;
+    bool cached_chunked = false;
     int n_st = 0, n_chunks = 0, n_hblocks = 0, n_small = 0;
     int short_threads = 0, short_rows = 0, n_parts = 0;   // the layout's ShortPlan
     ChunkPlan chunk;
@@ -325,12 +326,14 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
 {
     // chunk sizes of the chunk-wise selector (0: exact selection) are part of the layout: two
     // chunk sizes can give the same number of chunks
-    std::vector<int64_t> ch(static_cast<size_t>(n_tensors), 0);
-    if (sel_chunks) ch.assign(sel_chunks, sel_chunks + n_tensors);
     const bool same = ctx->cached_ks.size() == static_cast<size_t>(n_tensors) &&
                       std::memcmp(ctx->cached_offsets.data(), offsets, sizeof(int64_t) * (n_tensors + 1)) == 0 &&
-                      std::memcmp(ctx->cached_ks.data(), ks, sizeof(int64_t) * n_tensors) == 0 && ctx->cached_chunks == ch;
+                      std::memcmp(ctx->cached_ks.data(), ks, sizeof(int64_t) * n_tensors) == 0 &&
+                      ctx->cached_chunked == (sel_chunks != nullptr) &&
+                      (!sel_chunks || std::memcmp(ctx->cached_chunks.data(), sel_chunks, sizeof(int64_t) * n_tensors) == 0);
     if (same) return SCALECOM_OK;
+    std::vector<int64_t> ch(static_cast<size_t>(n_tensors), 0);
+    if (sel_chunks) ch.assign(sel_chunks, sel_chunks + n_tensors);
 
     if (ctx->upload_pending) {   // staging memory may still be read by an earlier copy
         SC_HIP(ctx, hipEventSynchronize(ctx->upload_done));
@@ -449,6 +452,7 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
     ctx->cached_offsets.assign(offsets, offsets + n_tensors + 1);
     ctx->cached_ks.assign(ks, ks + n_tensors);
     ctx->cached_chunks = ch;
+    ctx->cached_chunked = sel_chunks != nullptr;
     return SCALECOM_OK;
 }
 
