@@ -83,7 +83,7 @@ k_diag_begin(const SegDesc* __restrict__ segs, int n_tensors, const uint32_t* __
     if (s >= n_tensors) return;
     d[s] = segs[s].k;
     const uint32_t* src = preds + static_cast<size_t>(s) * kPredWords;
-    if (src[0] == 0u) return;
+    if (src[0] == 0u && src[kPredShortWidth] == 0u) return;   // (a layout has one kind or the other)
     for (int j = 0; j < kPredWords; ++j) diag_preds[static_cast<size_t>(s) * kPredWords + j] = src[j];
     diag_lead[s] = lead_mine[s];
 }

@@ -90,7 +90,8 @@ constexpr int64_t max_chunks(int64_t numel_max, int n_tensors_max)
 
 struct WsLayout {
     size_t segs, sts, chunks, hblocks, small, preds, stats, state, wt_cnt, st_sum, st_prefix, chunk_tot, st_cand_cnt, cand, sel_mask,
-        eq_mask, tile_slot, vals, best, parts, short_used, short_counts, short_keys, diag_preds, dots, total;
+        eq_mask, tile_slot, vals, best, parts, short_used, short_counts, short_keys, diag_preds, diag_used, diag_counts,
+        diag_keys, dots, total;
     int64_t short_numel;   // positions that the short path's key array is made for
     size_t short_words;    // and its words
     // per-step counters and histograms: one zone, all zero between steps (offsets inside the zone)
@@ -101,7 +102,7 @@ struct WsLayout {
 constexpr int64_t kShortNumelMax = 4 * 1024 * 1024;
 
 constexpr WsLayout layout_for(int64_t numel_max, int n_tensors_max, int n_learners_max, int64_t k_max,
-                              int64_t short_numel_max = kShortNumelMax)
+                              int64_t short_numel_max = kShortNumelMax, bool diagnostics = true)
 {
     const size_t nt = static_cast<size_t>(n_tensors_max);
     const size_t nst = static_cast<size_t>(max_supertiles(numel_max, n_tensors_max));
@@ -152,10 +153,6 @@ constexpr WsLayout layout_for(int64_t numel_max, int n_tensors_max, int n_learne
     l.tile_slot = take(ntile * sizeof(uint32_t));
     l.vals = take(static_cast<size_t>(n_learners_max) * static_cast<size_t>(k_max) * sizeof(float));
     l.best = take(static_cast<size_t>(k_max) * sizeof(unsigned long long));       // chunk-wise selector: a word per chunk
-    // similarity diagnostics: predictions for the leader's vector and for the sum over learners, and per learner and
-    // segment that leader's last threshold (kept like the steps' own); partial sums of the cosine distance
-    l.diag_preds = take((2 * kPredWords + static_cast<size_t>(n_learners_max)) * nt * sizeof(uint32_t));
-    l.dots = take(3 * static_cast<size_t>(kDotsBlocks) * sizeof(double));
     // short path: the parts, what each segment's list starts from, counts and keys per part
     l.parts = take(kShortPartsMax * sizeof(PartDesc));
     l.short_used = take(nt * sizeof(uint4));
@@ -164,6 +161,16 @@ constexpr WsLayout layout_for(int64_t numel_max, int n_tensors_max, int n_learne
     // a segment's first and last part may be partly empty
     l.short_words = static_cast<size_t>(l.short_numel) + 2 * (nt < 256 ? nt : 256) * static_cast<size_t>(kShortPartMax);
     l.short_keys = take(l.short_words * sizeof(uint32_t));
+    // similarity diagnostics: predictions for the leader's vector and for the sum over learners, and per learner and
+    // segment that leader's last threshold (kept like the steps' own); the short path's words for the sum; partial
+    // sums of the cosine distance
+    if (diagnostics) {
+        l.diag_preds = take((2 * kPredWords + static_cast<size_t>(n_learners_max)) * nt * sizeof(uint32_t));
+        l.diag_used = take(nt * sizeof(uint4));
+        l.diag_counts = take(static_cast<size_t>(kShortPartsMax) * kShortCols * sizeof(uint16_t));
+        l.diag_keys = take(l.short_words * sizeof(uint32_t));
+        l.dots = take(3 * static_cast<size_t>(kDotsBlocks) * sizeof(double));
+    }
     l.total = o;
     return l;
 }
@@ -861,6 +868,15 @@ DiagLayout diag_layout(int64_t numel_max, int n_tensors_max)
     return d;
 }
 
+template <typename G, int T, int R>
+void launch_short_overlap(scalecom_ctx* ctx, const float* memL, const G* gradL, float lr, const float* y, const ShortVector& a,
+                          const ShortVector& b, int32_t* d_out)
+{
+    const PartDesc* parts = reinterpret_cast<const PartDesc*>(ctx->ws + ctx->lay.parts);
+    k_short_collect_two<G, T, R><<<dim3(ctx->n_parts, 2), T, 0, ctx->stream>>>(memL, gradL, lr, y, parts, a, b);
+    k_short_overlap<G, T, R><<<ctx->n_parts, T, 0, ctx->stream>>>(memL, gradL, lr, y, parts, a, b, d_out);
+}
+
 template <typename G>
 scalecom_status launch_hamming(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learners, int n_tensors, int64_t begin,
                                int64_t end, float lr, int leader, char* scratch, int32_t* d_out)
@@ -884,16 +900,38 @@ scalecom_status launch_hamming(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
 
     k_diag_begin<<<(n_tensors + kBlock - 1) / kBlock, kBlock, 0, s>>>(
         segs, n_tensors, preds, preds + (kPredWords + static_cast<size_t>(leader)) * nt, preds_a, lead_a, d_out);
+    auto sum_x = [&](size_t clear_words) {
+        const int64_t tiles = (end - (begin & ~static_cast<int64_t>(kVec - 1)) + kWaveTile - 1) / kWaveTile;
+        const unsigned gx = static_cast<unsigned>(std::min<int64_t>(tiles, 1 << 20));
+        const dim3 grid(gx, static_cast<unsigned>((tiles + gx - 1) / gx));
+        k_sum_x<G><<<grid, std::min(n_learners, kSumWaves) * kLanes, sizeof(float4) * kLanes * n_learners, s>>>(
+            lp, n_learners, lr, begin, end, tiles, y, zone, clear_words);
+    };
+    if (ctx->n_st > 0 && ctx->short_threads > 0) {
+        sum_x(0);
+        const ShortVector a{preds_a, lead_a, reinterpret_cast<uint4*>(ctx->ws + l.short_used),
+                            reinterpret_cast<uint16_t*>(ctx->ws + l.short_counts), reinterpret_cast<uint32_t*>(ctx->ws + l.short_keys)};
+        const ShortVector b{preds_b, nullptr, reinterpret_cast<uint4*>(ctx->ws + l.diag_used),
+                            reinterpret_cast<uint16_t*>(ctx->ws + l.diag_counts), reinterpret_cast<uint32_t*>(ctx->ws + l.diag_keys)};
+        const float* memL = lp.mem[leader];
+        const G* gradL = static_cast<const G*>(lp.grad[leader]);
+        if (ctx->short_threads == 256)
+            launch_short_overlap<G, 256, 1>(ctx, memL, gradL, lr, y, a, b, d_out);
+        else if (ctx->short_threads == 512)
+            launch_short_overlap<G, 512, 1>(ctx, memL, gradL, lr, y, a, b, d_out);
+        else if (ctx->short_rows == 1)
+            launch_short_overlap<G, 1024, 1>(ctx, memL, gradL, lr, y, a, b, d_out);
+        else
+            launch_short_overlap<G, 1024, 2>(ctx, memL, gradL, lr, y, a, b, d_out);
+        SC_HIP(ctx, hipGetLastError());
+        return SCALECOM_OK;
+    }
     if (ctx->n_st > 0) {
         // the leader's index set (Eq. 3)
         launch_select<G>(ctx, lp.mem[leader], static_cast<const G*>(lp.grad[leader]), lr, n_tensors, preds_a, lead_a, nullptr,
                          mask_a, no_mark);
         // the top-k of the summed error-feedback gradients
-        const int64_t tiles = (end - (begin & ~static_cast<int64_t>(kVec - 1)) + kWaveTile - 1) / kWaveTile;
-        const unsigned gx = static_cast<unsigned>(std::min<int64_t>(tiles, 1 << 20));
-        const dim3 grid(gx, static_cast<unsigned>((tiles + gx - 1) / gx));
-        k_sum_x<G><<<grid, std::min(n_learners, kSumWaves) * kLanes, sizeof(float4) * kLanes * n_learners, s>>>(
-            lp, n_learners, lr, begin, end, tiles, y, zone, zone_words);
+        sum_x(zone_words);
         ctx->scratch_clean = hipPeekAtLastError() == hipSuccess;
         launch_select<NoGrad>(ctx, y, static_cast<const NoGrad*>(nullptr), 0.0f, n_tensors, preds_b, nullptr, nullptr, mask_b,
                               no_mark);
@@ -914,7 +952,7 @@ constexpr int64_t kStaticNumelMax = SCALECOM_STATIC_NUMEL_MAX;
 constexpr int kStaticLearnersMax = SCALECOM_STATIC_LEARNERS_MAX;
 constexpr int64_t kStaticKMax = SCALECOM_STATIC_K_MAX;
 constexpr int64_t kStaticShortMax = 1 << 20;      // longer vectors take the long path: four bytes per position are kept for the short one
-constexpr WsLayout kStaticLayout = layout_for(kStaticNumelMax, 1, kStaticLearnersMax, kStaticKMax, kStaticShortMax);
+constexpr WsLayout kStaticLayout = layout_for(kStaticNumelMax, 1, kStaticLearnersMax, kStaticKMax, kStaticShortMax, false);
 constexpr size_t kStaticBytes = kStaticLayout.total;
 static_assert(kStaticBytes <= (size_t{16} << 20), "the static workspace stays modest");
 

@@ -168,10 +168,10 @@ __device__ __forceinline__ uint32_t short_sample(const float* __restrict__ mem, 
 // One block per part: R rows of four consecutive positions per thread.  The loads of the part are
 // requested before anything else is looked at.
 template <typename G, int T, int R>
-__global__ void __launch_bounds__(T)
-k_short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const PartDesc* __restrict__ parts,
-                const uint32_t* __restrict__ preds, const uint32_t* __restrict__ lead_mine, uint4* __restrict__ used,
-                uint16_t* __restrict__ counts, uint32_t* __restrict__ keys, unsigned long long* __restrict__ stats)
+__device__ __forceinline__ void
+short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const PartDesc* __restrict__ parts,
+              const uint32_t* __restrict__ preds, const uint32_t* __restrict__ lead_mine, uint4* __restrict__ used,
+              uint16_t* __restrict__ counts, uint32_t* __restrict__ keys, unsigned long long* __restrict__ stats)
 {
     constexpr int W = T / kLanes, P = T * kVec * R;
     // the sample's counts, then the part's keys in the order in which they leave
@@ -267,6 +267,36 @@ k_short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float
     }
 }
 
+template <typename G, int T, int R>
+__global__ void __launch_bounds__(T)
+k_short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const PartDesc* __restrict__ parts,
+                const uint32_t* __restrict__ preds, const uint32_t* __restrict__ lead_mine, uint4* __restrict__ used,
+                uint16_t* __restrict__ counts, uint32_t* __restrict__ keys, unsigned long long* __restrict__ stats)
+{
+    short_collect<G, T, R>(mem, grad, lr, parts, preds, lead_mine, used, counts, keys, stats);
+}
+
+// What k_short_collect leaves of one vector, and where its expectations are kept.
+struct ShortVector {
+    uint32_t* preds;
+    uint32_t* lead_mine;         // null: no record per leader
+    uint4* used;
+    uint16_t* counts;
+    uint32_t* keys;
+};
+
+// For the similarity diagnostic: the leader's vector (blocks with y = 0) and the sum over learners.
+template <typename G, int T, int R>
+__global__ void __launch_bounds__(T)
+k_short_collect_two(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const float* __restrict__ sum,
+                    const PartDesc* __restrict__ parts, ShortVector a, ShortVector b)
+{
+    if (blockIdx.y == 0)
+        short_collect<G, T, R>(mem, grad, lr, parts, a.preds, a.lead_mine, a.used, a.counts, a.keys, nullptr);
+    else
+        short_collect<NoGrad, T, R>(sum, nullptr, 0.0f, parts, b.preds, b.lead_mine, b.used, b.counts, b.keys, nullptr);
+}
+
 // The listed keys of a segment's parts [0, n_parts), words [from[p], to[p]) of part p's slice, to `f`
 // (key, part).  One wave per part, AHEAD parts requested at once: the loads come from the L2 or from
 // the memory-side cache, half a microsecond away, and nothing else hides that.
@@ -346,32 +376,44 @@ __device__ __forceinline__ uint32_t sum_of_every_eighth(uint32_t v)
     return b[0] + b[1];
 }
 
-// One block per part: search, output slots, update of all learners, sums (see the top of the file).
-// The update walks the learners one after the other with one position group per thread: at these
-// sizes that is as fast as one learner per block (4 M elements in all: 16 us either way; 28 M: 57 us
-// against 53 us), and the sums over learners stay in registers.
-template <typename G, int T, int R>
-__global__ void __launch_bounds__(T)
-k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, float one_minus_beta,
-             const PartDesc* __restrict__ parts, uint32_t* __restrict__ preds, uint32_t* __restrict__ lead_mine,
-             const uint4* __restrict__ used, const uint16_t* __restrict__ counts, const uint32_t* __restrict__ keys,
-             int32_t* __restrict__ idx_out, float* __restrict__ red_out, unsigned long long* __restrict__ stats)
+// LDS of a block's search, and what the search finds.
+template <int T>
+struct ShortLds {
+    static constexpr int W = T / kLanes;
+    alignas(16) uint32_t hist[kShortGeneral];               // bins of the general search, or the column's keys
+    alignas(16) uint32_t list[kShortListMax];
+    unsigned long long found[kShortListMax / kLanes];       // per wave: threshold key, members among its holders
+    uint32_t sums[W][kShortCols];
+    uint32_t wave_tot[W];
+    uint32_t res[4];                                        // found, bin, its count, keys above it
+    uint32_t n_list, n_over;
+    uint32_t own[3][W];                                     // members for sure / ties in earlier parts, largest share of a part
+    uint16_t from[kShortSegParts], to[kShortSegParts];
+};
+static_assert(kShortGeneral >= kShortColumnMax, "a column fits");
+
+struct ShortFound {
+    uint32_t T_key, q;           // threshold (all bits set: no member), members among its holders
+    uint32_t gt_before, eq_before;   // members for sure / ties in the parts before the block's own
+    uint32_t n_bins, n_col, n_valid; // keys of the narrow columns, of the threshold's column; positions of the segment
+    int col;
+    bool missed;
+};
+
+// The search for the segment of a block's part, by all T threads; ends with a barrier.  `request` is called
+// once the counts have been requested, for loads that nothing here waits for.
+template <int T, int P, typename F>
+__device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartDesc& d, const uint4* __restrict__ used,
+                                                   const uint16_t* __restrict__ counts, const uint32_t* __restrict__ keys,
+                                                   F&& request)
 {
-    constexpr int W = T / kLanes, P = T * kVec * R;
-    __shared__ __align__(16) uint32_t hist[kShortGeneral];  // bins of the general search, or the column's keys
-    static_assert(kShortGeneral >= kShortColumnMax, "a column fits");
-    __shared__ uint32_t sums[W][kShortCols];
-    __shared__ uint32_t wave_tot[W];
-    __shared__ uint32_t res[4];                             // found, bin, its count, keys above it
-    __shared__ uint16_t from[kShortSegParts], to[kShortSegParts];
-    __shared__ __align__(16) uint32_t list[kShortListMax];
-    __shared__ uint32_t n_list, n_over;
-    __shared__ unsigned long long found[kShortListMax / kLanes];   // per wave: threshold key, members among its holders
-    __shared__ uint32_t own[3][W];                          // members for sure / ties in earlier parts, largest share of a part
-    __shared__ uint32_t in_row[2][2][W];                    // of two rows in turn: members for sure / ties
-    const PartDesc d = parts[blockIdx.x];
+    constexpr int W = T / kLanes;
+    uint32_t* hist = lds.hist;
+    uint32_t* list = lds.list;
+    uint32_t* wave_tot = lds.wave_tot;
+    uint32_t* res = lds.res;
+    unsigned long long* found = lds.found;
     const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
-    const int64_t begin = d.begin, end = d.end;
     const int mine = static_cast<int>(blockIdx.x) - d.part_first, n_parts = d.n_parts;
     const uint32_t k = static_cast<uint32_t>(d.k);
 
@@ -387,8 +429,7 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
         if (r < n_parts) row[i] = reinterpret_cast<const uint4*>(my_counts + static_cast<size_t>(r) * kShortCols)[lane % 8];
     }
     const uint4 u = used[d.seg];
-    float4 lm, lg;
-    leader_load(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), static_cast<int64_t>(d.a0) + t * kVec, begin, end, lm, lg);
+    request();
     uint32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int i = 0; i < kTurns; ++i) {
@@ -405,12 +446,12 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
     if (t < static_cast<int>(kShortListMax) / kLanes) found[t] = ~0ull;
     if (lane < 8) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) sums[wave][lane * 8 + j] = acc[j];
+        for (int j = 0; j < 8; ++j) lds.sums[wave][lane * 8 + j] = acc[j];
     }
     __syncthreads();
     uint32_t total = 0;                                     // lane j: running count of column j over the segment
 #pragma unroll
-    for (int w = 0; w < W; ++w) total += sums[w][lane];
+    for (int w = 0; w < W; ++w) total += lds.sums[w][lane];
     const uint32_t n_listed = __builtin_amdgcn_readlane(static_cast<int>(total), kShortListed);
     const uint32_t n_valid = __builtin_amdgcn_readlane(static_cast<int>(total), kShortValid);
     // the first column with which k keys are listed
@@ -436,7 +477,7 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
             eq_mine = mc[kShortValid] - gt_mine;
         }
     }
-    // every branch up to the update is block-uniform: k, the totals and `used` are the same in all threads
+    // every branch from here on is block-uniform: k, the totals and `used` are the same in all threads
     bool missed = false;
     if (k == 0) {
         // no member
@@ -521,8 +562,8 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
         if (col > 0) span = 32u - static_cast<uint32_t>(__clz(static_cast<int>(cols.end(col - 1) - base)));   // (not empty: at least 1)
         if (span > 31u) span = 31u;
         if (has_part) {
-            from[t] = static_cast<uint16_t>(lo_c);
-            to[t] = static_cast<uint16_t>(hi_c);
+            lds.from[t] = static_cast<uint16_t>(lo_c);
+            lds.to[t] = static_cast<uint16_t>(hi_c);
         }
         const uint32_t* slices = keys + static_cast<size_t>(d.part_first) * P;
         bool by_list = false;
@@ -531,10 +572,10 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
             const uint32_t shift = span > kShortGeneralLog ? span - kShortGeneralLog : 0u;
             __syncthreads();                                // everybody has read what is cleared here
             for (int b = t; b < kShortGeneral; b += T) hist[b] = 0u;
-            if (t == 0) n_over = n_list = res[0] = 0u;
+            if (t == 0) lds.n_over = lds.n_list = res[0] = 0u;
             __syncthreads();
             uint32_t over = 0;
-            short_for_keys<T, P>(slices, from, to, n_parts, [&](uint32_t key, int) {
+            short_for_keys<T, P>(slices, lds.from, lds.to, n_parts, [&](uint32_t key, int) {
                 const uint32_t rel = key - base;
                 if (key < base) return;
                 if (rel >> span)
@@ -543,9 +584,9 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
                     atomicAdd(&hist[rel >> shift], 1u);
             });
             over = wave_sum(over);
-            if (lane == 0 && over) atomicAdd(&n_over, over);
+            if (lane == 0 && over) atomicAdd(&lds.n_over, over);
             __syncthreads();
-            over = sure + n_over;
+            over = sure + lds.n_over;
             if (over >= k) {                                // the threshold lies above the counted range
                 base += 1u << span;
                 span = 31u;                                 // everything above
@@ -575,17 +616,17 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
         }
         if (by_list) {
             // the bin's few keys (lowest bit: from a part before mine), ranked against each other
-            short_for_keys<T, P>(slices, from, to, n_parts, [&](uint32_t key, int p) {
+            short_for_keys<T, P>(slices, lds.from, lds.to, n_parts, [&](uint32_t key, int p) {
                 if (key < base) return;
                 if ((key - base) >> span) {
                     gt_mine += p < mine ? 1u : 0u;
                 } else {
-                    const uint32_t at = atomicAdd(&n_list, 1u);
+                    const uint32_t at = atomicAdd(&lds.n_list, 1u);
                     if (at < kShortListMax) list[at] = (key << 1) | (p < mine ? 1u : 0u);
                 }
             });
             __syncthreads();
-            const uint32_t n = n_list < kShortListMax ? n_list : kShortListMax;
+            const uint32_t n = lds.n_list < kShortListMax ? lds.n_list : kShortListMax;
             short_rank<T, true>(list, n, rem, found);
             __syncthreads();
             const unsigned long long best = short_least(found);
@@ -597,7 +638,7 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
                 eq_mine += v == T_key ? 1u : 0u;
             }
         } else if (T_key != 0xffffffffu) {
-            short_for_keys<T, P>(slices, from, to, n_parts, [&](uint32_t key, int p) {
+            short_for_keys<T, P>(slices, lds.from, lds.to, n_parts, [&](uint32_t key, int p) {
                 gt_mine += p < mine && key > T_key ? 1u : 0u;
                 eq_mine += p < mine && key == T_key ? 1u : 0u;
             });
@@ -606,8 +647,8 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
     {
         const uint32_t g = wave_sum(gt_mine), e = wave_sum(eq_mine);
         if (lane == 0) {
-            own[0][wave] = g;
-            own[1][wave] = e;
+            lds.own[0][wave] = g;
+            lds.own[1][wave] = e;
         }
         if (mine == 0 && k != 0) {                          // the largest share of a part in the narrow columns
             uint32_t most = 0;
@@ -616,50 +657,86 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
                 most = mc[kShortBelow - 1] - mc[kShortFirstBin - 1];
             }
             most = wave_max_u32(most);
-            if (lane == 0) own[2][wave] = most;
+            if (lane == 0) lds.own[2][wave] = most;
         }
     }
 
     __syncthreads();
-    uint32_t gt_run = 0, eq_run = 0;                        // members for sure / ties before the row
+    ShortFound f{T_key, q, 0u, 0u, n_bins, n_col, n_valid, col, missed};
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-        gt_run += own[0][w];
-        eq_run += own[1][w];
+        f.gt_before += lds.own[0][w];
+        f.eq_before += lds.own[1][w];
     }
-    // what the next steps expect, and the counters: by the segment's first block
-    if (mine == 0 && t == 0 && k != 0 && T_key != 0xffffffffu) {
-        uint32_t* pred = preds + static_cast<size_t>(d.seg) * kPredWords;
-        // The narrow columns: wider at once if the threshold left their middle half or if they held few keys,
-        // narrower after some calm steps if they held many more than an index set's worth (and enough for the
-        // spread of an order statistic of rank k).
-        uint32_t want = static_cast<uint32_t>(16.0f * sqrtf(static_cast<float>(k)));
-        want = want > k ? want : k;
-        want = want > 64u ? want : 64u;
-        const bool middle = col >= kShortFirstBin + kShortBins / 4 && col < kShortBelow - kShortBins / 4;
-        uint32_t width = u.y, calm = middle ? u.w + 1u : 0u;
-        if (!middle || 5u * n_bins < 3u * want) {
-            ++width;
-            calm = 0u;
-        } else if (calm >= kShortCalm && 2u * n_bins > 3u * want) {
-            --width;
-            calm = 0u;
-        }
-        width = width < kShortWidthMin ? kShortWidthMin : (width > kShortWidthMax ? kShortWidthMax : width);
-        pred[kPredShortWidth] = width;
-        pred[kPredShortCalm] = calm;
-        record_t24(pred, lead_mine, d.seg, T_key >> kBits2);
-        if (stats && n_valid > static_cast<uint32_t>(kSuper)) {
-            if (u.z == 0u)                                  // the threshold came from a sample
-                atomicAdd(&stats[kStatNoPrediction], 1ull);
-            else if (missed)
-                atomicAdd(&stats[kStatMissed], 1ull);
-            uint32_t most = 0;                              // a quarter of a part: clustered in one place
-            for (int w = 0; w < W; ++w) most = own[2][w] > most ? own[2][w] : most;
-            if (n_col > kShortColumnMax || 4u * most > static_cast<uint32_t>(P)) atomicAdd(&stats[kStatFullMode], 1ull);
-        }
-    }
+    return f;
+}
 
+// What the next steps expect, and the counters (stats: null for none): by the segment's first block.
+template <int T, int P>
+__device__ __forceinline__ void short_record(const ShortLds<T>& lds, const PartDesc& d, const uint4& u, const ShortFound& f,
+                                             uint32_t* __restrict__ preds, uint32_t* __restrict__ lead_mine,
+                                             unsigned long long* __restrict__ stats)
+{
+    constexpr int W = T / kLanes;
+    const uint32_t k = static_cast<uint32_t>(d.k);
+    const int mine = static_cast<int>(blockIdx.x) - d.part_first, col = f.col;
+    if (mine != 0 || threadIdx.x != 0 || k == 0 || f.T_key == 0xffffffffu) return;
+    uint32_t* pred = preds + static_cast<size_t>(d.seg) * kPredWords;
+    // The narrow columns: wider at once if the threshold left their middle half or if they held few keys,
+    // narrower after some calm steps if they held many more than an index set's worth (and enough for the
+    // spread of an order statistic of rank k).
+    uint32_t want = static_cast<uint32_t>(16.0f * sqrtf(static_cast<float>(k)));
+    want = want > k ? want : k;
+    want = want > 64u ? want : 64u;
+    const bool middle = col >= kShortFirstBin + kShortBins / 4 && col < kShortBelow - kShortBins / 4;
+    uint32_t width = u.y, calm = middle ? u.w + 1u : 0u;
+    if (!middle || 5u * f.n_bins < 3u * want) {
+        ++width;
+        calm = 0u;
+    } else if (calm >= kShortCalm && 2u * f.n_bins > 3u * want) {
+        --width;
+        calm = 0u;
+    }
+    width = width < kShortWidthMin ? kShortWidthMin : (width > kShortWidthMax ? kShortWidthMax : width);
+    pred[kPredShortWidth] = width;
+    pred[kPredShortCalm] = calm;
+    record_t24(pred, lead_mine, d.seg, f.T_key >> kBits2);
+    if (stats && f.n_valid > static_cast<uint32_t>(kSuper)) {
+        if (u.z == 0u)                                  // the threshold came from a sample
+            atomicAdd(&stats[kStatNoPrediction], 1ull);
+        else if (f.missed)
+            atomicAdd(&stats[kStatMissed], 1ull);
+        uint32_t most = 0;                              // a quarter of a part: clustered in one place
+        for (int w = 0; w < W; ++w) most = lds.own[2][w] > most ? lds.own[2][w] : most;
+        if (f.n_col > kShortColumnMax || 4u * most > static_cast<uint32_t>(P)) atomicAdd(&stats[kStatFullMode], 1ull);
+    }
+}
+
+// One block per part: search, output slots, update of all learners, sums (see the top of the file).
+// The update walks the learners one after the other with one position group per thread: at these
+// sizes that is as fast as one learner per block (4 M elements in all: 16 us either way; 28 M: 57 us
+// against 53 us), and the sums over learners stay in registers.
+template <typename G, int T, int R>
+__global__ void __launch_bounds__(T)
+k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, float one_minus_beta,
+             const PartDesc* __restrict__ parts, uint32_t* __restrict__ preds, uint32_t* __restrict__ lead_mine,
+             const uint4* __restrict__ used, const uint16_t* __restrict__ counts, const uint32_t* __restrict__ keys,
+             int32_t* __restrict__ idx_out, float* __restrict__ red_out, unsigned long long* __restrict__ stats)
+{
+    constexpr int W = T / kLanes, P = T * kVec * R;
+    __shared__ ShortLds<T> lds;
+    __shared__ uint32_t in_row[2][2][W];                    // of two rows in turn: members for sure / ties
+    const PartDesc d = parts[blockIdx.x];
+    const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
+    const int64_t begin = d.begin, end = d.end;
+    const uint32_t k = static_cast<uint32_t>(d.k);
+    float4 lm, lg;
+    const ShortFound f = short_search<T, P>(lds, d, used, counts, keys, [&]() {
+        leader_load(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), static_cast<int64_t>(d.a0) + t * kVec, begin, end, lm, lg);
+    });
+    short_record<T, P>(lds, d, used[d.seg], f, preds, lead_mine, stats);
+    const uint32_t T_key = f.T_key, q = f.q;
+    uint32_t gt_run = f.gt_before, eq_run = f.eq_before;    // members for sure / ties before the row
 #pragma unroll 1
     for (int r = 0; r < R; ++r) {
         // membership and output slots of my four positions (ties in position order until q are taken)
@@ -753,6 +830,77 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
                 red_out[slot[c]] = s4[c];
             }
         }
+    }
+}
+
+// The similarity diagnostic on a short layout: the searches for the leader's vector and for the sum over learners,
+// then the positions that both index sets hold, taken off d (preset to k).
+template <typename G, int T, int R>
+__global__ void __launch_bounds__(T)
+k_short_overlap(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const float* __restrict__ sum,
+                const PartDesc* __restrict__ parts, ShortVector a, ShortVector b, int32_t* __restrict__ d_out)
+{
+    constexpr int W = T / kLanes, P = T * kVec * R;
+    __shared__ ShortLds<T> lds;
+    __shared__ uint32_t in_row[2][2][W];                    // of two rows in turn: ties of the two sets
+    const PartDesc d = parts[blockIdx.x];
+    if (d.k == 0) return;                                   // whole block: nothing in common
+    const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
+    const int64_t begin = d.begin, end = d.end;
+    const ShortFound fa = short_search<T, P>(lds, d, a.used, a.counts, a.keys, []() {});
+    short_record<T, P>(lds, d, a.used[d.seg], fa, a.preds, a.lead_mine, nullptr);
+    __syncthreads();                                        // the search's words are used again
+    const ShortFound fb = short_search<T, P>(lds, d, b.used, b.counts, b.keys, []() {});
+    short_record<T, P>(lds, d, b.used[d.seg], fb, b.preds, b.lead_mine, nullptr);
+    uint32_t run_a = fa.eq_before, run_b = fb.eq_before, both = 0;
+#pragma unroll 1
+    for (int r = 0; r < R; ++r) {
+        const int64_t p0 = static_cast<int64_t>(d.a0) + (r * T + t) * kVec;
+        uint32_t ka[4], kb[4];
+        bool ok[4];
+        leader_keys(mem, grad, lr, p0, begin, end, ka, ok);
+        leader_keys(sum, static_cast<const NoGrad*>(nullptr), 0.0f, p0, begin, end, kb, ok);
+        uint32_t rank_a = run_a, rank_b = run_b, n_a = 0, n_b = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint64_t ba = __builtin_amdgcn_ballot_w64(ok[c] && ka[c] == fa.T_key);
+            const uint64_t bb = __builtin_amdgcn_ballot_w64(ok[c] && kb[c] == fb.T_key);
+            rank_a += lanes_below(ba);
+            rank_b += lanes_below(bb);
+            n_a += __popcll(ba);
+            n_b += __popcll(bb);
+        }
+        if (lane == 0) {
+            in_row[r & 1][0][wave] = n_a;
+            in_row[r & 1][1][wave] = n_b;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t x = in_row[r & 1][0][w], y = in_row[r & 1][1][w];
+            run_a += x;
+            run_b += y;
+            rank_a += w < wave ? x : 0u;
+            rank_b += w < wave ? y : 0u;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const bool ea = ok[c] && ka[c] == fa.T_key, eb = ok[c] && kb[c] == fb.T_key;
+            const bool in_a = ok[c] && (ka[c] > fa.T_key || (ea && rank_a < fa.q));   // (no member: T_key is above every key)
+            const bool in_b = ok[c] && (kb[c] > fb.T_key || (eb && rank_b < fb.q));
+            both += in_a && in_b ? 1u : 0u;
+            rank_a += ea ? 1u : 0u;
+            rank_b += eb ? 1u : 0u;
+        }
+    }
+    both = wave_sum(both);
+    __syncthreads();
+    if (lane == 0) lds.wave_tot[wave] = both;
+    __syncthreads();
+    if (t == 0) {
+        uint32_t n = 0;
+        for (int w = 0; w < W; ++w) n += lds.wave_tot[w];
+        if (n) atomicSub(&d_out[d.seg], static_cast<int32_t>(n));
     }
 }
 

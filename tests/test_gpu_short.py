@@ -153,7 +153,10 @@ def test_hamming_distance_repeated(gu, n):
     """The diagnostic keeps thresholds of its own: called again and again between steps, with gradients whose
     scale jumps, on a flat vector and on tensors at odd starts, with more learners than a block has waves."""
     import oracle
-    for offsets, ks in (([0, 50_001], [500]), ([3, 20_000, 20_000, 20_007, 61_003], [200, 0, 7, 410])):
+    layouts = [([0, 50_001], [500]), ([3, 20_000, 20_000, 20_007, 61_003], [200, 0, 7, 410])]
+    if n == 2:                                                  # too long for the short path
+        layouts += [([0, 2_200_003], [22_000]), ([1, 2_300_000, 4_300_001, 4_300_300], [23_000, 5_000, 3])]
+    for offsets, ks in layouts:
         numel = offsets[-1] + 2
         ctx = binding.scalecom_init(numel, n, torch.float32, len(ks), gu.DEV)
         mem = [_normal(numel, 5 * i, 1.0).to(gu.DEV) for i in range(n)]
