@@ -304,7 +304,7 @@ template <int T, int P, typename F>
 __device__ __forceinline__ void short_for_keys(const uint32_t* __restrict__ slices, const uint16_t* from, const uint16_t* to,
                                                int n_parts, F&& f)
 {
-    constexpr int W = T / kLanes, AHEAD = 8;
+    constexpr int W = T / kLanes, AHEAD = 4;
     const int lane = threadIdx.x % kLanes, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     for (int p0 = wave; p0 < n_parts; p0 += AHEAD * W) {
         uint32_t s[AHEAD], e[AHEAD], longest = 0;
@@ -683,10 +683,11 @@ __device__ __forceinline__ void short_record(const ShortLds<T>& lds, const PartD
     if (mine != 0 || threadIdx.x != 0 || k == 0 || f.T_key == 0xffffffffu) return;
     uint32_t* pred = preds + static_cast<size_t>(d.seg) * kPredWords;
     // The narrow columns: wider at once if the threshold left their middle half or if they held few keys,
-    // narrower after some calm steps if they held many more than an index set's worth (and enough for the
-    // spread of an order statistic of rank k).
-    uint32_t want = static_cast<uint32_t>(16.0f * sqrtf(static_cast<float>(k)));
-    want = want > k ? want : k;
+    // narrower after some calm steps if they held many more than a quarter of an index set's worth (and enough for
+    // the spread of an order statistic of rank k): few keys to search, and a threshold that leaves the narrow
+    // columns lands in one that is not much larger.  (As many as the index set: 24.5 us a step at 4 x 1 M, now 22.6.)
+    uint32_t want = static_cast<uint32_t>(8.0f * sqrtf(static_cast<float>(k)));
+    want = want > k / 4u ? want : k / 4u;
     want = want > 64u ? want : 64u;
     const bool middle = col >= kShortFirstBin + kShortBins / 4 && col < kShortBelow - kShortBins / 4;
     uint32_t width = u.y, calm = middle ? u.w + 1u : 0u;
@@ -715,9 +716,10 @@ __device__ __forceinline__ void short_record(const ShortLds<T>& lds, const PartD
 // One block per part: search, output slots, update of all learners, sums (see the top of the file).
 // The update walks the learners one after the other with one position group per thread: at these
 // sizes that is as fast as one learner per block (4 M elements in all: 16 us either way; 28 M: 57 us
-// against 53 us), and the sums over learners stay in registers.
+// against 53 us), and the sums over learners stay in registers.  Registers for six waves per SIMD: layouts of several
+// tensors have more blocks than the chip runs at once (60 tensors, 1213 blocks: 46 us a step with 99 registers, 42).
 template <typename G, int T, int R>
-__global__ void __launch_bounds__(T)
+__global__ void __launch_bounds__(T, T == 1024 ? 4 : 6)
 k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, float one_minus_beta,
              const PartDesc* __restrict__ parts, uint32_t* __restrict__ preds, uint32_t* __restrict__ lead_mine,
              const uint4* __restrict__ used, const uint16_t* __restrict__ counts, const uint32_t* __restrict__ keys,
