@@ -716,10 +716,12 @@ __device__ __forceinline__ void short_record(const ShortLds<T>& lds, const PartD
 // One block per part: search, output slots, update of all learners, sums (see the top of the file).
 // The update walks the learners one after the other with one position group per thread: at these
 // sizes that is as fast as one learner per block (4 M elements in all: 16 us either way; 28 M: 57 us
-// against 53 us), and the sums over learners stay in registers.  Registers for six waves per SIMD: layouts of several
-// tensors have more blocks than the chip runs at once (60 tensors, 1213 blocks: 46 us a step with 99 registers, 42).
-template <typename G, int T, int R>
-__global__ void __launch_bounds__(T, T == 1024 ? 4 : 6)
+// against 53 us), and the sums over learners stay in registers.
+//   OCC: waves per SIMD that the registers are kept for, 4 or 6.  Layouts of several tensors have more blocks than the chip runs at once (60 tensors, 1213 blocks
+// of 512 threads: 46 us a step with 99 registers, 42 with 79); with fewer blocks the registers hold more
+// loads in flight (8 x 262 147, 129 blocks: 18.4 us against 19.3).
+template <typename G, int T, int R, int OCC>
+__global__ void __launch_bounds__(T, OCC)
 k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, float one_minus_beta,
              const PartDesc* __restrict__ parts, uint32_t* __restrict__ preds, uint32_t* __restrict__ lead_mine,
              const uint4* __restrict__ used, const uint16_t* __restrict__ counts, const uint32_t* __restrict__ keys,
