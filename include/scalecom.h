@@ -78,8 +78,8 @@ typedef enum {
  * Bytes of device workspace needed for up to n_learners_max learners with vectors of up to
  * numel_max elements each, split into at most n_tensors_max segments (1 for whole-vector
  * use), with index sets of at most k_max positions in total per step.  Pure host arithmetic
- * (about 0.8 * numel_max + 4 * min(numel_max, 4 M) + (4 * n_learners_max + 16) * k_max +
- * 170 KB * n_tensors_max bytes).
+ * (about 0.8 * numel_max + 8 * min(numel_max, 2 M; with several tensors 8 M) + (4 * n_learners_max + 16) * k_max +
+ * 235 KB * n_tensors_max bytes).
  * Returns 0 if an argument is out of range (numel_max < 0 or > 2^31 - 1, n_tensors_max < 1,
  * n_learners_max outside 1 .. SCALECOM_MAX_LEARNERS, k_max < 0 or > numel_max).
  */
@@ -277,7 +277,7 @@ scalecom_status scalecom_layer_ks(int n_tensors, const double* flops_per_gradien
  *   counts_out [host] uint64[SCALECOM_N_STATS]:
  *     [SCALECOM_STAT_MISSED]        the threshold fell outside the expected range: two more passes
  *                                   over the leader's vector in that step (on short layouts, up to
- *                                   2 M elements or 4 M in several tensors: a longer search)
+ *                                   2 M elements or 8 M in several tensors: a longer search)
  *     [SCALECOM_STAT_NO_PREDICTION] nothing was expected yet (first step of a layout): same cost
  *     [SCALECOM_STAT_FULL_MODE]     so many equal or clustered magnitudes at the threshold that the
  *                                   last two search levels were passes over the leader's vector too

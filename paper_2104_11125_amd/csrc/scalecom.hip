@@ -98,8 +98,8 @@ struct WsLayout {
     size_t zone, zone_bytes, z_overflow, z_p_used, z_full_flag, z_part, z_hist0, z_hist1, z_hist1_spec, z_hist2;
 };
 
-// Layouts of at most this many positions may take the short path (see short_parts).
-constexpr int64_t kShortNumelMax = 4 * 1024 * 1024;
+// Layouts of at most this many positions may take the short path (see short_parts): one vector, several tensors.
+constexpr int64_t kShortNumelFlat = 2 * 1024 * 1024, kShortNumelMax = 8 * 1024 * 1024;
 
 constexpr WsLayout layout_for(int64_t numel_max, int n_tensors_max, int n_learners_max, int64_t k_max,
                               int64_t short_numel_max = kShortNumelMax, bool diagnostics = true)
@@ -157,6 +157,7 @@ constexpr WsLayout layout_for(int64_t numel_max, int n_tensors_max, int n_learne
     l.parts = take(kShortPartsMax * sizeof(PartDesc));
     l.short_used = take(nt * sizeof(uint4));
     l.short_counts = take(static_cast<size_t>(kShortPartsMax) * kShortCols * sizeof(uint16_t));
+    if (nt == 1 && short_numel_max > kShortNumelFlat) short_numel_max = kShortNumelFlat;
     l.short_numel = numel_max < short_numel_max ? numel_max : short_numel_max;
     // a segment's first and last part may be partly empty
     l.short_words = static_cast<size_t>(l.short_numel) + 2 * (nt < 256 ? nt : 256) * static_cast<size_t>(kShortPartMax);
@@ -277,7 +278,8 @@ size_t pinned_bytes_for(int64_t numel_max, int n_tensors_max)
 // segments together 1280.  Beyond 2 M positions in one vector the update of all learners by one block at a time
 // (5.5 to 6 TB/s against 6.5) costs what the launches saved (2.05 M x 8 learners, bf16: 56 us against 62 us;
 // 3.5 M x 8, f32: 96 against 92); a layout of several tensors has more to save (60 tensors, 2.4 M x 4
-// learners, bf16: 45 us against 91 us).
+// learners, bf16: 42 us against 91 us; 193 tensors, 5.2 M x 8: 134 against 160; 101 tensors, 7.1 M x 6: 155 against 171;
+// 75 tensors, 8.1 M x 6: even), see also short_step.
 struct ShortPlan {
     int threads = 0, rows = 0, n_parts = 0;      // threads 0: the long path
     int64_t part() const { return static_cast<int64_t>(threads) * rows * kVec; }
@@ -286,7 +288,7 @@ struct ShortPlan {
 ShortPlan short_parts(const WsLayout& l, int n_tensors, const int64_t* offsets)
 {
     const int64_t total = offsets[n_tensors] - offsets[0];
-    if (total > l.short_numel || (n_tensors == 1 && total > kShortNumelMax / 2)) return ShortPlan{};
+    if (total > l.short_numel || (n_tensors == 1 && total > kShortNumelFlat)) return ShortPlan{};
     for (ShortPlan p : {ShortPlan{256, 1}, ShortPlan{512, 1}, ShortPlan{1024, 1}, ShortPlan{1024, 2}}) {
         int64_t n = 0;
         bool fits = true;
@@ -594,6 +596,13 @@ void launch_select(scalecom_ctx* ctx, const float* memL, const G* gradL, float l
     }
 }
 
+// Does a call on the tables' layout take the short path?  Not with so many learners that the update outweighs the
+// launches (98 tensors, 7.7 M x 16: 370 us against 328 on the long path).
+bool short_step(const scalecom_ctx* ctx, int n_learners, int64_t numel)
+{
+    return ctx->short_threads > 0 && n_learners * numel <= (int64_t{48} << 20);
+}
+
 // The exact step on a short layout: two launches, nothing of the scratch zone is used.
 template <typename G, int T, int R, typename Mark>
 void launch_short_as(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learners, float beta, float lr, int leader,
@@ -637,8 +646,8 @@ void launch_short(scalecom_ctx* ctx, Args&&... args)
 }
 
 template <typename G>
-scalecom_status launch_step(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learners, int n_tensors, int64_t k_total,
-                            float beta, float lr, int leader, int32_t* idx_out, float* red_out)
+scalecom_status launch_step(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learners, int n_tensors, int64_t numel,
+                            int64_t k_total, float beta, float lr, int leader, int32_t* idx_out, float* red_out)
 {
     hipStream_t s = ctx->stream;
     // phase boundaries for scalecom_timing_*: one event before the first kernel, one after each phase
@@ -653,7 +662,7 @@ scalecom_status launch_step(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_lear
         // this leader's own last thresholds, kept behind the per-segment predictions
         uint32_t* lead_mine = preds + (static_cast<size_t>(kPredWords) + static_cast<size_t>(leader)) *
                                           static_cast<size_t>(ctx->n_tensors_max);
-        if (ctx->short_threads > 0) {
+        if (short_step(ctx, n_learners, numel)) {
             launch_short<G>(ctx, lp, n_learners, beta, lr, leader, preds, lead_mine, idx_out, red_out, mark);
             mark(5);
             if (timed) ++ctx->prof_steps;
@@ -856,8 +865,8 @@ scalecom_status step_common(scalecom_ctx* ctx, float* const* mem, const void* co
         return launch_chunked<float>(ctx, lp, n_learners, n_tensors, k_total, beta, lr, leader, idx_out, red_out);
     }
     if (ctx->gdt == SCALECOM_GRAD_BF16)
-        return launch_step<uint16_t>(ctx, lp, n_learners, n_tensors, k_total, beta, lr, leader, idx_out, red_out);
-    return launch_step<float>(ctx, lp, n_learners, n_tensors, k_total, beta, lr, leader, idx_out, red_out);
+        return launch_step<uint16_t>(ctx, lp, n_learners, n_tensors, offsets[n_tensors] - offsets[0], k_total, beta, lr, leader, idx_out, red_out);
+    return launch_step<float>(ctx, lp, n_learners, n_tensors, offsets[n_tensors] - offsets[0], k_total, beta, lr, leader, idx_out, red_out);
 }
 
 // Scratch of scalecom_hamming_distance: the summed vector and the leader's membership mask.
@@ -914,7 +923,7 @@ scalecom_status launch_hamming(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
         k_sum_x<G><<<grid, std::min(n_learners, kSumWaves) * kLanes, sizeof(float4) * kLanes * n_learners, s>>>(
             lp, n_learners, lr, begin, end, tiles, y, zone, clear_words);
     };
-    if (ctx->n_st > 0 && ctx->short_threads > 0) {
+    if (ctx->n_st > 0 && short_step(ctx, n_learners, end - begin)) {
         sum_x(0);
         const ShortVector a{preds_a, lead_a, reinterpret_cast<uint4*>(ctx->ws + l.short_used),
                             reinterpret_cast<uint16_t*>(ctx->ws + l.short_counts), reinterpret_cast<uint32_t*>(ctx->ws + l.short_keys)};
@@ -1156,8 +1165,8 @@ scalecom_status scalecom_step_static(int device, void* hip_stream, float* const*
     const int leader = static_cast<int>(step % n_learners);    // Alg. 1 line 6: CLT-k of learner mod(t, n)
     const scalecom_status st =
         grad_dtype == SCALECOM_GRAD_BF16
-            ? launch_step<uint16_t>(ctx, lp, n_learners, 1, k, beta, lr, leader, idx_out, reduced_vals_out)
-            : launch_step<float>(ctx, lp, n_learners, 1, k, beta, lr, leader, idx_out, reduced_vals_out);
+            ? launch_step<uint16_t>(ctx, lp, n_learners, 1, numel, k, beta, lr, leader, idx_out, reduced_vals_out)
+            : launch_step<float>(ctx, lp, n_learners, 1, numel, k, beta, lr, leader, idx_out, reduced_vals_out);
     if (st != SCALECOM_OK) return static_fail(st, ctx->last_error);
     slot.numel = numel;
     slot.k = k;

@@ -176,3 +176,27 @@ def test_hamming_distance_repeated(gu, n):
                     assert int(d[s]) == want, (step, rep, s)
             gu.compare_step(ctx, mem, grad, ref, step, 0.5, 0.7, offsets=offsets, ks=ks, what="between diagnostics")
         ctx.close()
+
+
+@pytest.mark.parametrize("n,sizes", [
+    (2, [2_097_152, 3, 2_097_149, 900_001, 8_192]),              # 256 parts of 8192 in one segment
+    (2, [2_097_153, 1_000_000]),                                 # one more: the long path
+    (16, [1_500_001, 700_003, 900_000]),                         # the last learner count with which 3.1 M positions are short
+    (17, [1_500_001, 700_003, 900_000]),
+])
+def test_layouts_at_the_limits(gu, n, sizes):
+    """Several tensors up to the sizes and learner counts at which the long path takes over."""
+    offsets = [1]
+    for s in sizes:
+        offsets.append(offsets[-1] + s)
+    ks = [-(-s // 100) for s in sizes]
+    numel = offsets[-1]
+    ctx = binding.scalecom_init(numel, n, torch.bfloat16, len(ks), gu.DEV, k_max=sum(ks))
+    gen = torch.Generator(device=gu.DEV).manual_seed(n)
+    mem = [torch.randn(numel, device=gu.DEV, generator=gen) * 2e-4 for _ in range(n)]
+    ref = [m.cpu().numpy().copy() for m in mem]
+    for step in range(2):
+        grad = [(torch.randn(numel, device=gu.DEV, generator=gen) * 1e-3).to(torch.bfloat16) for _ in range(n)]
+        print(f"[short] limits n={n} numel={numel} step={step}", flush=True)
+        gu.compare_step(ctx, mem, grad, ref, step, 0.2, 0.1, offsets=offsets, ks=ks, what=f"limits n={n}")
+    ctx.close()
