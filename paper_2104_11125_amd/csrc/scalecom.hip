@@ -186,8 +186,8 @@ bool sizes_ok(int64_t numel_max, int n_tensors_max, int n_learners_max, int64_t 
 
 // How a layout's chunk-wise step runs (elements per chunk clamped to the segment's length):
 // with groups of whole chunks of at most 256 * tiles - 3 positions, per_st of them per supertile, in one
-// launch (k_chunk_step, up to two tiles) or two and the sum over learners (k_chunk_winners); tiles = 0: chunks too
-// long or too short for that, one more launch.
+// launch (k_chunk_step, up to two tiles) or two and the sum over learners (k_chunk_winners); tiles = 0: chunks of
+// no suitable size for that, one more launch.
 struct ChunkPlan {
     int tiles = 0, per_st = 0;
     int max_chunks = 0;          // chunks of a group at most
@@ -208,7 +208,7 @@ struct scalecom_ctx {
     bool cached_chunked = false;
     int n_st = 0, n_chunks = 0, n_hblocks = 0, n_small = 0;
     int short_threads = 0, short_rows = 0, n_parts = 0;   // the layout's ShortPlan
-    ChunkPlan chunk;
+    ChunkPlan chunk_one, chunk_two;          // the layout's chunk-wise step in one launch, and the winners first
     // segments of one supertile are searched by a kernel of their own, on a second stream beside the
     // leader pass (contexts for more than one tensor only)
     hipStream_t side = nullptr;
@@ -307,12 +307,17 @@ ShortPlan short_parts(const WsLayout& l, int n_tensors, const int64_t* offsets)
     return ShortPlan{};
 }
 
-// (the smallest number of tiles that takes all chunks: more make no difference to k_chunk_winners)
-ChunkPlan chunk_plan(int n_tensors, const SegDesc* segs)
+// The number of tiles, up to tiles_max, with which the groups' positions leave the fewest lanes of their tiles idle
+// (25 positions per chunk fill 98 % of one tile, 100 fill 78 % of one and 98 % of two, 400 fill 78 % of two or four),
+// and none if that is less than `enough` of them.
+ChunkPlan chunk_plan(int n_tensors, const SegDesc* segs, int tiles_max, double enough)
 {
-    for (int tiles = 1; tiles <= 4; tiles *= 2) {
+    ChunkPlan best{};
+    double best_use = enough;
+    for (int tiles = 1; tiles <= tiles_max; tiles *= 2) {
         const int64_t positions = 256 * tiles - 3;
         int64_t per_st = 1, max_chunks = 1;
+        double used = 0.0, lanes = 0.0;                      // positions, and those that their groups' tiles have room for
         bool fits = true;
         for (int s = 0; s < n_tensors && fits; ++s) {
             if (segs[s].end == segs[s].begin) continue;
@@ -323,10 +328,16 @@ ChunkPlan chunk_plan(int n_tensors, const SegDesc* segs)
             if (!fits) break;
             per_st = std::max(per_st, (in_st + per_group - 1) / per_group);
             max_chunks = std::max(max_chunks, std::min(per_group, in_st));
+            const double len = segs[s].end - segs[s].begin;
+            used += len;
+            lanes += len * (256.0 * tiles) / static_cast<double>(per_group * ch);
         }
-        if (fits) return ChunkPlan{tiles, static_cast<int>(per_st), static_cast<int>(max_chunks)};
+        if (fits && lanes > 0.0 && used / lanes > best_use + (best.tiles > 0 ? 0.03 : 0.0)) {
+            best = ChunkPlan{tiles, static_cast<int>(per_st), static_cast<int>(max_chunks)};
+            best_use = used / lanes;
+        }
     }
-    return ChunkPlan{};
+    return best;
 }
 
 // Rebuild and upload the segment, supertile, chunk and block tables if the layout differs from the cached one.
@@ -457,7 +468,10 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
     ctx->short_threads = plan.threads;
     ctx->short_rows = plan.rows;
     ctx->n_parts = plan.n_parts;
-    ctx->chunk = sel_chunks ? chunk_plan(n_tensors, segs) : ChunkPlan{};
+    // (with fewer lanes in use the winners' pass is slower than maxima by atomics: 8 x 10^9 elements, chunk 400, 14.2 ms a
+    // step against 13.6)
+    ctx->chunk_one = sel_chunks ? chunk_plan(n_tensors, segs, 2, 0.0) : ChunkPlan{};
+    ctx->chunk_two = sel_chunks ? chunk_plan(n_tensors, segs, 4, 0.85) : ChunkPlan{};
     ctx->cached_offsets.assign(offsets, offsets + n_tensors + 1);
     ctx->cached_ks.assign(ks, ks + n_tensors);
     ctx->cached_chunks = ch;
@@ -722,34 +736,34 @@ scalecom_status launch_chunked(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
     mark(0);
     const int64_t extent = ctx->cached_offsets[n_tensors] - ctx->cached_offsets[0];
     const int gb = sizeof(G);
-    if (chunks_in_one_launch(ctx->chunk.tiles, n_learners, extent, gb)) {
+    if (chunks_in_one_launch(ctx->chunk_one.tiles, n_learners, extent, gb)) {
         mark(1);
         mark(2);
         mark(3);
         const unsigned gz = static_cast<unsigned>((ctx->n_st + 65534) / 65535);
-        const dim3 grid(ctx->chunk.per_st, (ctx->n_st + gz - 1) / gz, gz);
-        const int waves = std::min(n_learners * ctx->chunk.tiles, kChunkStepWaves);
-        const size_t lds = static_cast<size_t>(ctx->chunk.max_chunks) * (sizeof(unsigned long long) + sizeof(float) * n_learners);
-        if (ctx->chunk.tiles == 1)
+        const dim3 grid(ctx->chunk_one.per_st, (ctx->n_st + gz - 1) / gz, gz);
+        const int waves = std::min(n_learners * ctx->chunk_one.tiles, kChunkStepWaves);
+        const size_t lds = static_cast<size_t>(ctx->chunk_one.max_chunks) * (sizeof(unsigned long long) + sizeof(float) * n_learners);
+        if (ctx->chunk_one.tiles == 1)
             k_chunk_step<G, 1><<<grid, waves * kLanes, lds, s>>>(lp, n_learners, leader, lr, beta, 1.0f - beta, sts,
-                                                                 ctx->n_st, ctx->chunk.max_chunks, idx_out, red_out);
+                                                                 ctx->n_st, ctx->chunk_one.max_chunks, idx_out, red_out);
         else
             k_chunk_step<G, 2><<<grid, waves * kLanes, lds, s>>>(lp, n_learners, leader, lr, beta, 1.0f - beta, sts,
-                                                                 ctx->n_st, ctx->chunk.max_chunks, idx_out, red_out);
+                                                                 ctx->n_st, ctx->chunk_one.max_chunks, idx_out, red_out);
         mark(4);
         mark(5);
         if (timed) ++ctx->prof_steps;
         SC_HIP(ctx, hipGetLastError());
         return SCALECOM_OK;
     }
-    if (ctx->chunk.tiles > 0) {
+    if (ctx->chunk_two.tiles > 0) {
         const unsigned sz = static_cast<unsigned>((ctx->n_st + 65534) / 65535);
-        const dim3 groups((ctx->chunk.per_st + kWaves - 1) / kWaves, (ctx->n_st + sz - 1) / sz, sz);
+        const dim3 groups((ctx->chunk_two.per_st + kWaves - 1) / kWaves, (ctx->n_st + sz - 1) / sz, sz);
         const float* memL = lp.mem[leader];
         const G* gradL = static_cast<const G*>(lp.grad[leader]);
-        if (ctx->chunk.tiles == 1)
+        if (ctx->chunk_two.tiles == 1)
             k_chunk_winners<G, 1><<<groups, kBlock, 0, s>>>(memL, gradL, lr, sts, ctx->n_st, idx_out);
-        else if (ctx->chunk.tiles == 2)
+        else if (ctx->chunk_two.tiles == 2)
             k_chunk_winners<G, 2><<<groups, kBlock, 0, s>>>(memL, gradL, lr, sts, ctx->n_st, idx_out);
         else
             k_chunk_winners<G, 4><<<groups, kBlock, 0, s>>>(memL, gradL, lr, sts, ctx->n_st, idx_out);
