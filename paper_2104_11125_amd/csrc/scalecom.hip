@@ -46,8 +46,9 @@
 // (update, predicted) and by launch latency (the small ones).
 // Short layouts (see short_parts) take two kernels instead: `short_collect` sorts the leader's keys by their
 // distance from the expected threshold, `short_step` searches, updates and sums (short_kernels.h).
-// The chunk-wise selector (scalecom_step_chunked, scalecom_step_layers_chunked) replaces everything
-// before `update` by chunk_select + chunk_marks.
+// The chunk-wise selector (scalecom_step_chunked, scalecom_step_layers_chunked) needs no search: the whole step in
+// one launch (chunk_step), or the winners (chunk_winners, then update_chunks and reduce), or chunk_select +
+// chunk_marks in place of everything before `update` (see chunk_plan, chunks_in_one_launch).
 
 #include <hip/hip_runtime.h>
 
@@ -700,7 +701,7 @@ scalecom_status launch_step(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_lear
 
 // Is the whole chunk-wise step in one launch the faster way?  It reads the leader once instead of twice and saves two
 // launches, but moves the rest at 4.9 TB/s instead of 6.5.  One launch against three, us: 4 x 5.3 M elements 57
-// against 74 with the four launches of old; 8 x 3.3 M 76 against 69; 6 x 5.1 M 85 against 80; 4 x 11.4 M 111 against
+// against 74 (that side with the maxima by atomics, four launches); 8 x 3.3 M 76 against 69; 6 x 5.1 M 85 against 80; 4 x 11.4 M 111 against
 // 116; 3 x 30 M bf16 207 against 201; 8 x 25.6 M 489 against 422.
 bool chunks_in_one_launch(int tiles, int n_learners, int64_t numel, int grad_bytes)
 {
