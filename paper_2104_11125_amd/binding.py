@@ -142,6 +142,8 @@ def scalecom_step_static(mem: Sequence[torch.Tensor], grad: Sequence[torch.Tenso
                          stream: Optional[torch.cuda.Stream] = None) -> None:
     """``scalecom_step_static`` of the C-ABI: no context, no workspace, nothing allocated (so the
     outputs must be passed in).  Marshalling only; sizes beyond the static limits raise."""
+    if len(grad) < len(mem):        # (the pointer tables have one entry per learner)
+        raise ValueError("one mem and one grad buffer per learner")
     dev = mem[0].device
     gd = grad[0].dtype
     if gd not in (torch.float32, torch.bfloat16):

@@ -4,6 +4,9 @@ import ctypes
 import os
 import re
 
+import pytest
+import torch
+
 from paper_2104_11125_amd import binding
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -103,6 +106,30 @@ def test_static_entry_point_checks_that_need_no_device():
     assert call(numel=0, k=0) == binding.SCALECOM_OK          # nothing to do, nothing touched
     assert L.scalecom_last_error(None) == b""
     assert L.scalecom_selection_stats(None, None, 0) == binding.SCALECOM_EINVAL
+
+
+def test_static_binding_refuses_learners_without_a_gradient(monkeypatch):
+    """Fewer gradients than memories: refused before anything is handed to the library, whose pointer tables
+    would otherwise end before the learner count that goes with them.  (Further gradients are ignored.)"""
+    handed = []
+
+    class Lib:
+        def scalecom_step_static(self, index, stream, mem, grad, n, *rest):
+            handed.append((len(mem), len(grad), n))
+            return binding.SCALECOM_OK
+
+    class Stream:
+        cuda_stream = 0
+
+    monkeypatch.setattr(binding, "lib", lambda: Lib())
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    bufs = [torch.zeros(8) for _ in range(3)]
+    idx, red = torch.zeros(2, dtype=torch.int32), torch.zeros(2)
+    with pytest.raises(ValueError):
+        binding.scalecom_step_static(bufs, bufs[:1], 2, 0.5, 0.1, 0, idx, red, stream=Stream())
+    assert handed == []
+    binding.scalecom_step_static(bufs[:2], bufs, 2, 0.5, 0.1, 0, idx, red, stream=Stream())
+    assert handed == [(2, 2, 2)]
 
 
 def test_workloads_match_the_benchmark_table():
