@@ -192,6 +192,8 @@ bool sizes_ok(int64_t numel_max, int n_tensors_max, int n_learners_max, int64_t 
 struct ChunkPlan {
     int tiles = 0, per_st = 0;
     int max_chunks = 0;          // chunks of a group at most
+    double use = 0.0;            // share of the tiles' lanes that hold a position
+    bool crowded = false;        // most positions lie in groups of so few chunks that their maxima wait for each other
 };
 
 struct scalecom_ctx {
@@ -209,7 +211,7 @@ struct scalecom_ctx {
     bool cached_chunked = false;
     int n_st = 0, n_chunks = 0, n_hblocks = 0, n_small = 0;
     int short_threads = 0, short_rows = 0, n_parts = 0;   // the layout's ShortPlan
-    ChunkPlan chunk_one, chunk_two;          // the layout's chunk-wise step in one launch, and the winners first
+    ChunkPlan chunk_one, chunk_two[2];       // the layout's chunk-wise step in one launch; the winners first, up to four tiles and up to two
     // segments of one supertile are searched by a kernel of their own, on a second stream beside the
     // leader pass (contexts for more than one tensor only)
     hipStream_t side = nullptr;
@@ -317,8 +319,9 @@ ChunkPlan chunk_plan(int n_tensors, const SegDesc* segs, int tiles_max, double e
     double best_use = enough;
     for (int tiles = 1; tiles <= tiles_max; tiles *= 2) {
         const int64_t positions = 256 * tiles - 3;
+        const int64_t few = tiles == 4 ? 8 : tiles;          // (see winners_first)
         int64_t per_st = 1, max_chunks = 1;
-        double used = 0.0, lanes = 0.0;                      // positions, and those that their groups' tiles have room for
+        double used = 0.0, lanes = 0.0, in_few = 0.0;        // positions, those that their groups' tiles have room for, those in groups of few chunks
         bool fits = true;
         for (int s = 0; s < n_tensors && fits; ++s) {
             if (segs[s].end == segs[s].begin) continue;
@@ -332,9 +335,10 @@ ChunkPlan chunk_plan(int n_tensors, const SegDesc* segs, int tiles_max, double e
             const double len = segs[s].end - segs[s].begin;
             used += len;
             lanes += len * (256.0 * tiles) / static_cast<double>(per_group * ch);
+            if (per_group < few) in_few += len;
         }
         if (fits && lanes > 0.0 && used / lanes > best_use + (best.tiles > 0 ? 0.03 : 0.0)) {
-            best = ChunkPlan{tiles, static_cast<int>(per_st), static_cast<int>(max_chunks)};
+            best = ChunkPlan{tiles, static_cast<int>(per_st), static_cast<int>(max_chunks), used / lanes, 2.0 * in_few > used};
             best_use = used / lanes;
         }
     }
@@ -469,10 +473,8 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
     ctx->short_threads = plan.threads;
     ctx->short_rows = plan.rows;
     ctx->n_parts = plan.n_parts;
-    // (with fewer lanes in use the winners' pass is slower than maxima by atomics: 8 x 10^9 elements, chunk 400, 14.2 ms a
-    // step against 13.6)
     ctx->chunk_one = sel_chunks ? chunk_plan(n_tensors, segs, 2, 0.0) : ChunkPlan{};
-    ctx->chunk_two = sel_chunks ? chunk_plan(n_tensors, segs, 4, 0.85) : ChunkPlan{};
+    for (int m = 0; m < 2; ++m) ctx->chunk_two[m] = sel_chunks ? chunk_plan(n_tensors, segs, m == 0 ? 4 : 2, 0.85) : ChunkPlan{};
     ctx->cached_offsets.assign(offsets, offsets + n_tensors + 1);
     ctx->cached_ks.assign(ks, ks + n_tensors);
     ctx->cached_chunks = ch;
@@ -700,15 +702,29 @@ scalecom_status launch_step(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_lear
 }
 
 // Is the whole chunk-wise step in one launch the faster way?  It reads the leader once instead of twice and saves two
-// launches, but moves the rest at 4.9 TB/s instead of 6.5.  One launch against three, us: 4 x 5.3 M elements 57
-// against 74 (that side with the maxima by atomics, four launches); 8 x 3.3 M 76 against 69; 6 x 5.1 M 85 against 80; 4 x 11.4 M 111 against
-// 116; 3 x 30 M bf16 207 against 201; 8 x 25.6 M 489 against 422.
-bool chunks_in_one_launch(int tiles, int n_learners, int64_t numel, int grad_bytes)
+// launches and, beyond eight learners, one per further eight, but moves everything at a rate that falls with the idle lanes of its
+// tiles: 5.0 to 5.2 TB/s where 88 to 98 % of one tile are in use (chunks of 25, 84, 112), 4.6 to 5.1 with two (100, 155), 4.5 to 4.9 at 78 %
+// (200, 400), 3.9 at 66 % (170, 340), 3.0 at 50 % (255), against 6.5 of the all-learner pass.  One launch against the best of the others, us:
+// 3 x 30 M elements, chunk 25 208 against 226, 155 235 / 225, 200 224 / 223, 255 363 / 221; 4 x 11.4 M, 112 105 / 113, 155 112 / 112;
+// 6 x 5.1 M, 25 87 / 78; 8 x 3.3 M, 25 73 / 65; 8 x 1 M, 25 23 / 25, 200 25 / 27, 255 35 / 27; 2 x 100 M, 155 460 / 526, 170 615 / 515;
+// 64 x 0.2 M, 25 46 / 75.
+bool chunks_in_one_launch(const ChunkPlan& plan, int n_learners, int64_t numel, int grad_bytes)
 {
-    if (tiles < 1 || tiles > 2) return false;
+    if (plan.tiles < 1) return false;
+    const double rate = plan.tiles == 1 ? std::min(5.1, 5.9 * plan.use) : std::min(4.8, 5.7 * plan.use);
     const double all = static_cast<double>(n_learners) * static_cast<double>(numel) * (8 + grad_bytes);
     const double leader = static_cast<double>(numel) * (4 + grad_bytes);
-    return all * (1.0 / 4.9 - 1.0 / 6.5) * 1e-6 < leader / 4.8 * 1e-6 + 5.0;
+    const int more_launches = (n_learners - 1) / kUpdateLearnersPerLaunch;
+    return all * (1.0 / rate - 1.0 / 6.5) * 1e-6 < leader / 4.8 * 1e-6 + 7.0 + 3.0 * more_launches;
+}
+
+// If not, are the winners first, in groups of up to `tiles_max` tiles, faster than the maxima by atomics (one launch more)?  With less
+// than 85 % of the lanes in use they are not (8 x 10^9 elements, chunk 400, 14.2 ms a step against 13.6), nor with few chunks per
+// group, whose words in LDS all lanes then wait for (four tiles: 30 M, chunk 255 113 us against 103, 1000 112 / 98, but 112 107 / 110;
+// two tiles: 4 x 5.3 M, 450 58.0 / 57.2) -- except where a launch counts for more than the pass (8 x 0.3 M, 1000 17.2 / 20.5; 1 x 3 M 19.7 / 18.1).
+bool winners_first(const ChunkPlan& plan, int n_learners, int64_t numel)
+{
+    return plan.tiles > 0 && (!plan.crowded || (numel <= 1'000'000 && n_learners * numel <= 3'000'000));
 }
 
 // One step with the chunk-wise selector: leader pass (per-chunk maxima), marks, then the same
@@ -737,7 +753,7 @@ scalecom_status launch_chunked(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
     mark(0);
     const int64_t extent = ctx->cached_offsets[n_tensors] - ctx->cached_offsets[0];
     const int gb = sizeof(G);
-    if (chunks_in_one_launch(ctx->chunk_one.tiles, n_learners, extent, gb)) {
+    if (chunks_in_one_launch(ctx->chunk_one, n_learners, extent, gb)) {
         mark(1);
         mark(2);
         mark(3);
@@ -757,14 +773,15 @@ scalecom_status launch_chunked(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
         SC_HIP(ctx, hipGetLastError());
         return SCALECOM_OK;
     }
-    if (ctx->chunk_two.tiles > 0) {
+    const ChunkPlan& two = winners_first(ctx->chunk_two[0], n_learners, extent) ? ctx->chunk_two[0] : ctx->chunk_two[1];
+    if (winners_first(two, n_learners, extent)) {
         const unsigned sz = static_cast<unsigned>((ctx->n_st + 65534) / 65535);
-        const dim3 groups((ctx->chunk_two.per_st + kWaves - 1) / kWaves, (ctx->n_st + sz - 1) / sz, sz);
+        const dim3 groups((two.per_st + kWaves - 1) / kWaves, (ctx->n_st + sz - 1) / sz, sz);
         const float* memL = lp.mem[leader];
         const G* gradL = static_cast<const G*>(lp.grad[leader]);
-        if (ctx->chunk_two.tiles == 1)
+        if (two.tiles == 1)
             k_chunk_winners<G, 1><<<groups, kBlock, 0, s>>>(memL, gradL, lr, sts, ctx->n_st, idx_out);
-        else if (ctx->chunk_two.tiles == 2)
+        else if (two.tiles == 2)
             k_chunk_winners<G, 2><<<groups, kBlock, 0, s>>>(memL, gradL, lr, sts, ctx->n_st, idx_out);
         else
             k_chunk_winners<G, 4><<<groups, kBlock, 0, s>>>(memL, gradL, lr, sts, ctx->n_st, idx_out);

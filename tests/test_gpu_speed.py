@@ -1,0 +1,57 @@
+"""Calls beside those that the benchmark times, against a call of the same size whose time is known to be near its bound: rules
+of the dispatch that are off show as factors here.  Both calls of a pair run in turn on the same GPU, and the smallest of
+several means of each counts; the factors leave room for twice the scatter of those (about 2 %)."""
+import pytest
+import torch
+
+from paper_2104_11125_amd import binding
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+def _normal(numel, seed):
+    return torch.randn(numel, generator=torch.Generator(device=DEV).manual_seed(seed), device=DEV)
+
+
+def _times(calls, rounds=7, least_us=3000.0):
+    """Smallest mean time of each call in us; a call takes the number of its turn."""
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    turn, reps, best = [0] * len(calls), [8] * len(calls), [float("inf")] * len(calls)
+    for r in range(rounds + 2):                                 # (two to warm up and to find the number of repetitions)
+        for c, call in enumerate(calls):
+            ev[0].record()
+            for _ in range(reps[c]):
+                call(turn[c])
+                turn[c] += 1
+            ev[1].record()
+            torch.cuda.synchronize()
+            us = ev[0].elapsed_time(ev[1]) * 1e3 / reps[c]
+            if r < 2:
+                reps[c] = max(8, min(400, int(least_us / us)))
+            else:
+                best[c] = min(best[c], us)
+    return best
+
+
+@pytest.mark.parametrize("n,numel,chunk,factor", [
+    (3, 8_000_000, 255, 1.12), (2, 30_000_000, 255, 1.12),      # half of the lanes idle in one launch
+    (1, 30_000_000, 1000, 1.07),                                # one chunk per group: maxima that wait for each other
+    (8, 1_000_000, 255, 1.10),
+])
+def test_chunk_sizes_that_leave_lanes_idle(n, numel, chunk, factor):
+    """No slower than chunks of 600, which always take the maxima by atomics."""
+    calls, keep = [], []
+    grad = [_normal(numel, i) for i in range(n)]
+    for ch in (chunk, 600):
+        k = -(-numel // ch)
+        ctx = binding.scalecom_init(numel, n, torch.float32, 1, DEV, k_max=k)
+        mem = [torch.zeros(numel, device=DEV) for _ in range(n)]
+        idx, red = torch.empty(k, dtype=torch.int32, device=DEV), torch.empty(k, device=DEV)
+        keep.append(ctx)
+        calls.append(lambda t, ctx=ctx, mem=mem, ch=ch, idx=idx, red=red: ctx.scalecom_step_chunked(mem, grad, ch, 0.1, 0.1, t, idx, red))
+    got, base = _times(calls)
+    print(f"[speed] chunk {chunk}: {got:.1f} us, 600: {base:.1f} us", flush=True)
+    assert got <= factor * base
+    for ctx in keep:
+        ctx.close()
