@@ -279,10 +279,10 @@ size_t pinned_bytes_for(int64_t numel_max, int n_tensors_max)
 // cost grows with the segment's parts, so the smallest part is taken with which no segment has more than 256
 // (up to there one vector of 1 M positions takes 25 us a step either way, and the long path 42 us) and all
 // segments together 1280.  Beyond 2 M positions in one vector the update of all learners by one block at a time
-// (5.5 to 6 TB/s against 6.5) costs what the launches saved (2.05 M x 8 learners, bf16: 56 us against 62 us;
-// 3.5 M x 8, f32: 96 against 92); a layout of several tensors has more to save (60 tensors, 2.4 M x 4
-// learners, bf16: 42 us against 91 us; 193 tensors, 5.2 M x 8: 134 against 160; 101 tensors, 7.1 M x 6: 155 against 171;
-// 75 tensors, 8.1 M x 6: even), see also short_step.
+// (5.5 to 6 TB/s against 6.5) costs what the launches saved (one vector, f32, us against the long path: 1.5 M x 1 to 32 learners 25 / 38 to 128 / 140,
+// 2 M x 2 33 / 47, x 8 54 / 66, x 16 90 / 101; 3.5 M x 8: 96 / 92); a layout of several tensors with small ones among them has more to
+// save (64 to 4 M positions: 60 tensors, 2.4 M x 4 learners, bf16: 42 us against 91 us; 193 tensors, 5.2 M x 8: 134 against 160; 101 tensors,
+// 7.1 M x 6: 155 against 171; 75 tensors, 8.1 M x 6: even), see short_step.
 struct ShortPlan {
     int threads = 0, rows = 0, n_parts = 0;      // threads 0: the long path
     int64_t part() const { return static_cast<int64_t>(threads) * rows * kVec; }
@@ -614,10 +614,31 @@ void launch_select(scalecom_ctx* ctx, const float* memL, const G* gradL, float l
 }
 
 // Does a call on the tables' layout take the short path?  Not with so many learners that the update outweighs the
-// launches (98 tensors, 7.7 M x 16: 370 us against 328 on the long path).
-bool short_step(const scalecom_ctx* ctx, int n_learners, int64_t numel)
+// launches (98 tensors, 7.7 M x 16: 370 us against 328 on the long path).  Beyond 2 M positions in all it is the
+// search for segments of one supertile that makes the long path slow (k_small: 30 to 40 us a step whatever their number), so without
+// such segments the line lies at 2 M, or 3 M with few learners.  Short against long, us: 64 tensors of equal size, 2 M x 8 56 against 71, 2.5 M x 4 44 / 59,
+// 2.5 M x 16 125 / 125, 3 M x 4 56 / 62, 4 M x 2 55 / 51, 5 M x 8 140 / 119, 8 M x 2 94 / 74; with one more tensor of 500 positions: 2.5 M x 16 120 / 149,
+// 4 M x 8 104 / 126, 8 M x 4 127 / 132.
+constexpr int64_t kShortNumelFew = 3'000'000, kShortWorkFew = 12'000'000;
+
+bool short_work(const scalecom_ctx* ctx, int n_learners, int64_t numel)
 {
     return ctx->short_threads > 0 && n_learners * numel <= (int64_t{48} << 20);
+}
+
+bool short_step(const scalecom_ctx* ctx, int n_learners, int64_t numel)
+{
+    return short_work(ctx, n_learners, numel) &&
+           (ctx->n_small > 0 || numel <= kShortNumelFlat || (numel <= kShortNumelFew && n_learners * numel <= kShortWorkFew));
+}
+
+// The same for the similarity diagnostic, which has two searches to save (64 tensors of equal size, us: 4 M x 8 117 against 127, 6.5 M x 4
+// 161 / 130, and 163 / 255 with small tensors).
+constexpr int64_t kShortNumelDiag = 4'000'000;
+
+bool short_diagnostic(const scalecom_ctx* ctx, int n_learners, int64_t numel)
+{
+    return short_work(ctx, n_learners, numel) && (ctx->n_small > 0 || numel <= kShortNumelDiag);
 }
 
 // The exact step on a short layout: two launches, nothing of the scratch zone is used.
@@ -955,7 +976,7 @@ scalecom_status launch_hamming(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
         k_sum_x<G><<<grid, std::min(n_learners, kSumWaves) * kLanes, sizeof(float4) * kLanes * n_learners, s>>>(
             lp, n_learners, lr, begin, end, tiles, y, zone, clear_words);
     };
-    if (ctx->n_st > 0 && short_step(ctx, n_learners, end - begin)) {
+    if (ctx->n_st > 0 && short_diagnostic(ctx, n_learners, end - begin)) {
         sum_x(0);
         const ShortVector a{preds_a, lead_a, reinterpret_cast<uint4*>(ctx->ws + l.short_used),
                             reinterpret_cast<uint16_t*>(ctx->ws + l.short_counts), reinterpret_cast<uint32_t*>(ctx->ws + l.short_keys)};

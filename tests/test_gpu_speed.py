@@ -55,3 +55,28 @@ def test_chunk_sizes_that_leave_lanes_idle(n, numel, chunk, factor):
     assert got <= factor * base
     for ctx in keep:
         ctx.close()
+
+
+@pytest.mark.parametrize("n,tensors,size,factor", [(2, 64, 125_000, 1.12), (8, 98, 60_000, 1.12), (2, 4, 1_250_000, 1.15)])
+def test_tensors_of_equal_size_against_one_vector(n, tensors, size, factor):
+    """Several million positions in tensors that are all larger than a supertile (8192): no slower than one vector of
+    that length beyond the tables and searches per tensor."""
+    numel = tensors * size
+    offsets, ks = [t * size for t in range(tensors + 1)], [size // 100] * tensors
+    grad = [_normal(numel, i) for i in range(n)]
+    calls, keep = [], []
+    for layered in (True, False):
+        k = sum(ks)
+        ctx = binding.scalecom_init(numel, n, torch.float32, tensors if layered else 1, DEV, k_max=k)
+        mem = [torch.zeros(numel, device=DEV) for _ in range(n)]
+        idx, red = torch.empty(k, dtype=torch.int32, device=DEV), torch.empty(k, device=DEV)
+        keep.append(ctx)
+        if layered:
+            calls.append(lambda t, c=ctx, m=mem, i=idx, r=red: c.scalecom_step_layers(m, grad, offsets, ks, 0.1, 0.1, t, i, r))
+        else:
+            calls.append(lambda t, c=ctx, m=mem, i=idx, r=red: c.scalecom_step(m, grad, k, 0.1, 0.1, t, i, r))
+    got, base = _times(calls)
+    print(f"[speed] {tensors} x {size}: {got:.1f} us, one vector: {base:.1f} us", flush=True)
+    assert got <= factor * base
+    for ctx in keep:
+        ctx.close()
