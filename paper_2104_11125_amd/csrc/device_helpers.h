@@ -51,6 +51,16 @@ __device__ __forceinline__ void store4(float* p, const float4& v)
 struct NoGrad {};
 __device__ __forceinline__ float4 load4(const NoGrad*) { return make_float4(0.0f, 0.0f, 0.0f, 0.0f); }
 
+// The same without the hint, for the few positions that many waves read.
+__device__ __forceinline__ float4 cached4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ float4 cached4(const uint16_t* p)
+{
+    const uint2 v = *reinterpret_cast<const uint2*>(p);
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+                       __uint_as_float(v.y & 0xffff0000u));
+}
+__device__ __forceinline__ float4 cached4(const NoGrad*) { return make_float4(0.0f, 0.0f, 0.0f, 0.0f); }
+
 // number of set bits of a wave-wide ballot that belong to lanes below the calling lane
 __device__ __forceinline__ uint32_t lanes_below(uint64_t ballot)
 {
@@ -139,12 +149,16 @@ template <typename G>
 __device__ __forceinline__ void leader_load(const float* mem, const G* grad, int64_t p0, int64_t begin, int64_t end,
                                             float4& m, float4& g)
 {
+    if (p0 >= begin && p0 + 3 < end) {                      // (one branch for both: they are in flight together)
+        m = load4(mem + p0);
+        g = load4(grad + p0);
+        return;
+    }
     m = make_float4(0, 0, 0, 0);
     g = m;
     if (p0 >= end || p0 + 3 < begin) return;
-    const bool full = p0 >= begin && p0 + 3 < end;
-    m = load_guarded(mem, p0, begin, end, full);
-    g = load_guarded(grad, p0, begin, end, full);
+    m = load_guarded(mem, p0, begin, end, false);
+    g = load_guarded(grad, p0, begin, end, false);
 }
 
 // Magnitude keys of x = fma(lr, grad, mem) (Alg. 1 line 6) for those 4 positions; ok[c] tells
@@ -175,18 +189,18 @@ __device__ __forceinline__ void leader_keys(const float* mem, const G* grad, flo
 // (lead_mine[seg], 0 before its first turn) and moved on by the growth the last leader saw over
 // its cycle; without it, the last step's threshold.  Only a prediction: it decides how much work
 // a step does, never what it selects.
+__device__ __forceinline__ uint32_t predicted_t24(uint32_t last, uint32_t growth_bits, uint32_t mine)
+{
+    if (mine == 0u) return last;
+    const float growth = growth_bits != 0u ? __uint_as_float(growth_bits) : 1.0f;
+    const float f = __uint_as_float(mine << kBits2) * growth;
+    return (__float_as_uint(f) & 0x7fffffffu) >> kBits2;
+}
+
 __device__ __forceinline__ uint32_t predicted_t24(const uint32_t* pred, const uint32_t* lead_mine, int seg)
 {
-    uint32_t t24 = pred[1];
-    if (lead_mine) {
-        const uint32_t mine = lead_mine[seg];
-        if (mine != 0u) {
-            const float growth = pred[4] != 0u ? __uint_as_float(pred[4]) : 1.0f;
-            const float f = __uint_as_float(mine << kBits2) * growth;
-            t24 = (__float_as_uint(f) & 0x7fffffffu) >> kBits2;
-        }
-    }
-    return t24;
+    const uint32_t mine = lead_mine ? lead_mine[seg] : 0u;
+    return predicted_t24(pred[1], mine != 0u ? pred[4] : 0u, mine);
 }
 
 // Records the threshold a step found (by one thread, for the next steps' predictions).

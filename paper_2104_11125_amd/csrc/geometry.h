@@ -79,6 +79,8 @@ struct PartDesc {         // short layouts: one block's consecutive positions of
     int32_t n_parts;      // number of its parts, at most kShortSegParts
 };
 
+// Layouts of at most this many positions may take the short path: one vector, several tensors.
+constexpr int64_t kShortNumelFlat = 2 * 1024 * 1024, kShortNumelMax = 8 * 1024 * 1024;
 constexpr int kShortPartMax = 8192;              // positions of a part (blocks of 256, 512 or 1024 threads, four or eight positions each)
 constexpr int kShortSegParts = 256;              // parts of one segment
 constexpr int kShortPartsMax = 1280;             // parts of a layout
@@ -144,8 +146,9 @@ __host__ __device__ constexpr uint32_t clamp_width(uint32_t w)
 constexpr int kPredWords = 8;                    // [0] 1 if there is one, [1] top 24 bits of the last threshold, [2] w,
                                                  // [3] steps in a row in which the threshold fell into the range's middle half,
                                                  // [4] (float) by how much the last leader's threshold grew since its previous turn
-                                                 // [5] short layouts: log2 of the keys per narrow column (0: no prediction), [6] calm steps
-constexpr int kPredShortWidth = 5, kPredShortCalm = 6;
+                                                 // [5] short layouts: log2 of the keys per narrow column (0: no prediction), [6] calm steps,
+                                                 // [7] whether the expectation is trusted; of 64 keys, those not far below the threshold
+constexpr int kPredShortWidth = 5, kPredShortCalm = 6, kPredShortTrust = 7;
 constexpr uint32_t kCalmSteps = 8;               // so many of those before the range is made narrower
 // Counts of the predicted pass, per segment: [0] keys above the range, [1] keys inside it.
 // Blocks add into one of kPartSlots copies (same-address atomics from thousands of blocks would

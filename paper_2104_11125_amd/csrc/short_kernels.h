@@ -25,8 +25,13 @@ namespace {
 //                    those keys, in the parts before its own, give the block's first output slot.  Then the
 //                    block updates its positions for all learners, sums its members' values and writes them
 //
-// No kernel reads what another block of the same launch wrote, and a wrong expectation costs a longer
-// column to search, not another pass.  The price is that every block does the search.
+// No kernel reads what another block of the same launch wrote.  The price is that every block does the search: keys of
+// the threshold's column beyond the first thousand are read by all blocks of the segment, several times (all keys of 2 M positions
+// after a jump of the gradients by 64: 1.2 ms, where the long path takes 65 us).  So columns are kept small: the expectation is checked on a few
+// keys before it is used (short_far_off), after a long search a sample takes its place until it would have held for a while (ShortTrust),
+// columns that are crowded get narrower, and a part's keys of one column that are all equal count as one key with a weight (`pure`).
+// A step of 2 x 2 M positions, us, against the long path: normal values 32 / 47, all magnitudes equal 36 / 121, two of them 71 / 154, a jump by
+// 64 every third step 56 / 66, one jump 50 / 64 and the step after it 167 / 68.
 
 constexpr int kShortCols = 64;                   // words of a row of running counts (16 bits each)
 constexpr int kShortAbove = 3, kShortBins = 48;  // columns 0..2; 3..50 around the expected threshold, highest keys first
@@ -81,6 +86,36 @@ struct ShortCols {
 };
 static_assert(kShortBelow + 8 == kShortBulk && kShortBulk + 1 == kShortListed && kShortListed < kShortValid && kShortValid < kShortCols,
               "a row holds them all");
+
+// What a segment's columns were laid around (the low two bits of word z of `used`; above them the trust as the step found it, which
+// saves the step's first block a trip to memory).
+constexpr uint32_t kShortNone = 0, kShortExpected = 1, kShortDoubted = 2;   // sample: nothing expected / expectation; sample: expectation not trusted
+
+// How far a segment's expectation is trusted, packed into 24 bits: `count` steps in a row in which it held, or would have, of the
+// 2^need that are asked for before it is used again (0: it is used), and a level that rises with every long search, so that searches by
+// data that jump again and again get rarer (8 to 1024 steps), and falls in quiet times.  The sample costs 4 to 9 us a step, a long search
+// 20 to 130.
+struct ShortTrust {
+    uint32_t count, need, level;
+    __device__ __forceinline__ explicit ShortTrust(uint32_t w) : count(w & 0xffffu), need((w >> 16) & 0xfu), level((w >> 20) & 0xfu) {}
+    __device__ __forceinline__ bool sampling() const { return need != 0u; }
+    __device__ __forceinline__ uint32_t next(bool held, bool long_search)
+    {
+        if (!sampling() && !held && long_search) {
+            level = level < 8u ? level + 1u : 8u;
+            need = level + 2u;
+            count = 0u;
+        } else if (sampling()) {
+            count = held ? count + 1u : 0u;
+            if (count >> need) need = count = 0u;
+        } else if (level != 0u && (++count >> (level + 4u)) != 0u) {
+            --level;
+            count = 0u;
+        }
+        return count | need << 16 | level << 20;
+    }
+};
+constexpr uint32_t kShortLong = 8 * 1024;        // keys read by every block of a segment that make a search a long one
 
 // The bin of h[0 .. NB) that holds the rem-th largest key counted there (rem >= 1), by all T
 // threads of a block; wave_tot is T / 64 words of LDS.  The thread that owns the bin returns true.
@@ -165,39 +200,83 @@ __device__ __forceinline__ uint32_t short_sample(const float* __restrict__ mem, 
     return res[0];
 }
 
+// Is the expectation far off?  Every wave looks at the same 16 groups of four positions, one in each of 16 equal stretches of the
+// segment (at equal distances they would share a memory channel), so all waves of all blocks come to the same answer without a word
+// between them.  Far off: many more of the 64 keys above the near columns than the index set's share, or hardly any down to the
+// end of column kShortBulk, where the last step had `below`.  m, g: every group in four lanes.  Costs 0.2 us a step.
+constexpr int kShortCheckGroups = 16, kShortCheckParts = 4;   // (segments of few parts do without: a long column is short there)
+
+__device__ __forceinline__ bool short_far_off(const float4& m, const float4& g, float lr, const PartDesc& d, const ShortCols& cols,
+                                              uint32_t below)
+{
+    const float4 x = accumulate4(m, g, lr);
+    const uint32_t key[4] = {magnitude_key(x.x), magnitude_key(x.y), magnitude_key(x.z), magnitude_key(x.w)};
+    const uint32_t high = cols.end(1), low = cols.end(kShortBulk);
+    uint32_t above = 0, near = 0;                           // four times as many: every key is in four lanes
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        above += __popcll(__builtin_amdgcn_ballot_w64(key[c] >= high));
+        near += __popcll(__builtin_amdgcn_ballot_w64(key[c] >= low));
+    }
+    const float share = 64.0f * static_cast<float>(d.k) * __builtin_amdgcn_rcpf(static_cast<float>(d.end - d.begin));
+    return static_cast<float>(above) > 4.0f * (2.0f * share + 8.0f) || 8u * near < 4u * below;
+}
+
 // One block per part: R rows of four consecutive positions per thread.  The loads of the part are
 // requested before anything else is looked at.
 template <typename G, int T, int R>
 __device__ __forceinline__ void
 short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const PartDesc* __restrict__ parts,
               const uint32_t* __restrict__ preds, const uint32_t* __restrict__ lead_mine, uint4* __restrict__ used,
-              uint16_t* __restrict__ counts, uint32_t* __restrict__ keys, unsigned long long* __restrict__ stats)
+              uint16_t* __restrict__ counts, uint64_t* __restrict__ pure, uint32_t* __restrict__ keys,
+              unsigned long long* __restrict__ stats)
 {
     constexpr int W = T / kLanes, P = T * kVec * R;
     // the sample's counts, then the part's keys in the order in which they leave
     __shared__ __align__(16) uint32_t stage[(1 << kShortSampleLog) > P ? (1 << kShortSampleLog) : P];
     __shared__ uint32_t wave_tot[W];
     __shared__ uint32_t res[2];
-    __shared__ uint32_t cnt[kShortCols], first[kShortCols];
+    __shared__ uint32_t cnt[kShortCols], first[kShortCols], mixed[kShortCols];
+    __shared__ uint64_t heavy;
     const PartDesc d = parts[blockIdx.x];
     const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
     const int64_t begin = d.begin, end = d.end;
+    // (without a branch, or the compiler waits for these loads before it requests the part's; any valid address where they are not used)
+    const bool check = d.n_parts > kShortCheckParts;        // block-uniform
+    const float* s_mem = reinterpret_cast<const float*>(parts);
+    const G* s_grad = reinterpret_cast<const G*>(parts);
+    if (check) {
+        const uint32_t up = (static_cast<uint32_t>(d.begin) + kVec - 1) & ~static_cast<uint32_t>(kVec - 1);
+        const uint32_t stretch = (static_cast<uint32_t>(d.end) - up) / (kVec * kShortCheckGroups);   // whole groups, at least 63
+        const uint32_t j = static_cast<uint32_t>(lane) % kShortCheckGroups;
+        const int64_t p0 = up + static_cast<int64_t>(j * stretch + __umulhi(j * 0x9e3779b1u, stretch)) * kVec;
+        s_mem = mem + p0;
+        s_grad = grad + p0;
+    }
+    const float4 sm = cached4(s_mem), sg = cached4(s_grad);
     float4 m[R], g[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) leader_load(mem, grad, static_cast<int64_t>(d.a0) + (r * T + t) * kVec, begin, end, m[r], g[r]);
-    const uint32_t* pred = preds + static_cast<size_t>(d.seg) * kPredWords;
-    uint32_t width = pred[kPredShortWidth], mid;            // 0: nothing to go by
-    const uint32_t have = width != 0u ? 1u : 0u;
-    if (t < kShortCols) cnt[t] = 0u;
-    if (have) {                                             // block-uniform
-        mid = (predicted_t24(pred, lead_mine, d.seg) << kBits2) | (kBins2 / 2);
+    // the prediction's words in one access (a trip for each of them took as long as the part's loads)
+    static_assert(kPredWords == 8 && kPredShortWidth == 5 && kPredShortCalm == 6 && kPredShortTrust == 7, "two groups of four");
+    const uint4* pred = reinterpret_cast<const uint4*>(preds + static_cast<size_t>(d.seg) * kPredWords);
+    const uint4 pred_lo = pred[0], pred_hi = pred[1];
+    const uint32_t lead = lead_mine ? lead_mine[d.seg] : 0u;
+    uint32_t width = pred_hi.y, mid = 0u;                   // 0: nothing to go by
+    const uint32_t trust = pred_hi.w & 0xffffffu;
+    uint32_t have = width == 0u ? kShortNone : (ShortTrust(trust).sampling() ? kShortDoubted : kShortExpected);
+    if (t < kShortCols) cnt[t] = mixed[t] = 0u;
+    if (have == kShortExpected) {                           // block-uniform
+        mid = (predicted_t24(pred_lo.y, pred_hi.x, lead) << kBits2) | (kBins2 / 2);
         width = width < kShortWidthMin ? kShortWidthMin : (width > kShortWidthMax ? kShortWidthMax : width);
-    } else {
+        if (check && short_far_off(sm, sg, lr, d, ShortCols(mid, width), pred_hi.w >> 24)) have = kShortDoubted;   // in all blocks
+    }
+    if (have != kShortExpected) {
         width = kShortWidthFirst;
         mid = d.k > 0 ? short_sample<G, T>(mem, grad, lr, d, stage, wave_tot, res) : 0u;
     }
     if (blockIdx.x == static_cast<uint32_t>(d.part_first) && t == 0)
-        used[d.seg] = make_uint4(mid, width, have, pred[kPredShortCalm]);
+        used[d.seg] = make_uint4(mid, width, have | trust << 2, pred_hi.z);
     if (stats && blockIdx.x == 0 && t == 0) atomicAdd(&stats[kStatSteps], 1ull);
 
     const ShortCols cols(mid, width);
@@ -250,6 +329,13 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
             if (lane >= off) run += v;
         }
         first[lane] = run - (lane <= kShortListed ? n : 0u);
+        // columns with so many keys that it pays to know whether they are equal (not the last ones, wide and full as a rule:
+        // a sample's threshold is at most 0.9 spans below the narrow columns)
+        const uint64_t many = __builtin_amdgcn_ballot_w64(lane < kShortBelow + 6 && n >= static_cast<uint32_t>(P / 32));
+        if (lane == 0) {
+            heavy = many;
+            if (many == 0) pure[blockIdx.x] = 0;
+        }
         counts[static_cast<size_t>(blockIdx.x) * kShortCols + lane] = static_cast<uint16_t>(lane <= kShortListed ? run : n);
     }
     __syncthreads();
@@ -258,6 +344,7 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
     for (int c = 0; c < 4 * R; ++c)
         if (col[c] < static_cast<uint32_t>(kShortCols)) stage[first[col[c]] + rank[c]] = key[c];
     const uint32_t n_listed = first[kShortListed + 1];
+    const uint64_t many = heavy;
     __syncthreads();
     uint32_t* slice = keys + static_cast<size_t>(blockIdx.x) * P;
 #pragma unroll
@@ -265,15 +352,25 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
         const uint32_t at = static_cast<uint32_t>(r * T + t) * kVec;
         if (at < n_listed) *reinterpret_cast<uint4*>(slice + at) = *reinterpret_cast<const uint4*>(stage + at);
     }
+    if (many == 0) return;                                  // whole block
+#pragma unroll
+    for (int c = 0; c < 4 * R; ++c)
+        if (col[c] < static_cast<uint32_t>(kShortBulk) && stage[first[col[c]]] != key[c]) mixed[col[c]] = 1u;
+    __syncthreads();
+    if (wave == 0) {
+        const uint64_t same = __builtin_amdgcn_ballot_w64(mixed[lane] == 0u) & many;
+        if (lane == 0) pure[blockIdx.x] = same;
+    }
 }
 
 template <typename G, int T, int R>
 __global__ void __launch_bounds__(T)
 k_short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const PartDesc* __restrict__ parts,
                 const uint32_t* __restrict__ preds, const uint32_t* __restrict__ lead_mine, uint4* __restrict__ used,
-                uint16_t* __restrict__ counts, uint32_t* __restrict__ keys, unsigned long long* __restrict__ stats)
+                uint16_t* __restrict__ counts, uint64_t* __restrict__ pure, uint32_t* __restrict__ keys,
+                unsigned long long* __restrict__ stats)
 {
-    short_collect<G, T, R>(mem, grad, lr, parts, preds, lead_mine, used, counts, keys, stats);
+    short_collect<G, T, R>(mem, grad, lr, parts, preds, lead_mine, used, counts, pure, keys, stats);
 }
 
 // What k_short_collect leaves of one vector, and where its expectations are kept.
@@ -282,6 +379,7 @@ struct ShortVector {
     uint32_t* lead_mine;         // null: no record per leader
     uint4* used;
     uint16_t* counts;
+    uint64_t* pure;              // per part: the columns whose keys are all equal
     uint32_t* keys;
 };
 
@@ -292,27 +390,28 @@ k_short_collect_two(const float* __restrict__ mem, const G* __restrict__ grad, f
                     const PartDesc* __restrict__ parts, ShortVector a, ShortVector b)
 {
     if (blockIdx.y == 0)
-        short_collect<G, T, R>(mem, grad, lr, parts, a.preds, a.lead_mine, a.used, a.counts, a.keys, nullptr);
+        short_collect<G, T, R>(mem, grad, lr, parts, a.preds, a.lead_mine, a.used, a.counts, a.pure, a.keys, nullptr);
     else
-        short_collect<NoGrad, T, R>(sum, nullptr, 0.0f, parts, b.preds, b.lead_mine, b.used, b.counts, b.keys, nullptr);
+        short_collect<NoGrad, T, R>(sum, nullptr, 0.0f, parts, b.preds, b.lead_mine, b.used, b.counts, b.pure, b.keys, nullptr);
 }
 
 // The listed keys of a segment's parts [0, n_parts), words [from[p], to[p]) of part p's slice, to `f`
-// (key, part).  One wave per part, AHEAD parts requested at once: the loads come from the L2 or from
+// (key, part, how many keys it stands for).  One wave per part, AHEAD parts requested at once: the loads come from the L2 or from
 // the memory-side cache, half a microsecond away, and nothing else hides that.
 template <int T, int P, typename F>
 __device__ __forceinline__ void short_for_keys(const uint32_t* __restrict__ slices, const uint16_t* from, const uint16_t* to,
-                                               int n_parts, F&& f)
+                                               const uint16_t* weight, int n_parts, F&& f)
 {
     constexpr int W = T / kLanes, AHEAD = 4;
     const int lane = threadIdx.x % kLanes, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
     for (int p0 = wave; p0 < n_parts; p0 += AHEAD * W) {
-        uint32_t s[AHEAD], e[AHEAD], longest = 0;
+        uint32_t s[AHEAD], e[AHEAD], w[AHEAD], longest = 0;
 #pragma unroll
         for (int j = 0; j < AHEAD; ++j) {
             const int p = p0 + j * W;
             s[j] = p < n_parts ? from[p] : 0u;
             e[j] = p < n_parts ? to[p] : 0u;
+            w[j] = p < n_parts ? weight[p] : 0u;
             const uint32_t len = e[j] - s[j];
             longest = len > longest ? len : longest;
         }
@@ -324,7 +423,7 @@ __device__ __forceinline__ void short_for_keys(const uint32_t* __restrict__ slic
                 key[j] = s[j] + r < e[j] ? slices[static_cast<size_t>(p0 + j * W) * P + s[j] + r] : 0u;
 #pragma unroll
             for (int j = 0; j < AHEAD; ++j)
-                if (s[j] + r < e[j]) f(key[j], p0 + j * W);
+                if (s[j] + r < e[j]) f(key[j], p0 + j * W, w[j]);
         }
     }
 }
@@ -386,9 +485,9 @@ struct ShortLds {
     uint32_t sums[W][kShortCols];
     uint32_t wave_tot[W];
     uint32_t res[4];                                        // found, bin, its count, keys above it
-    uint32_t n_list, n_over;
+    uint32_t n_list, n_over, n_scan;
     uint32_t own[3][W];                                     // members for sure / ties in earlier parts, largest share of a part
-    uint16_t from[kShortSegParts], to[kShortSegParts];
+    uint16_t from[kShortSegParts], to[kShortSegParts], weight[kShortSegParts];
 };
 static_assert(kShortGeneral >= kShortColumnMax, "a column fits");
 
@@ -396,6 +495,8 @@ struct ShortFound {
     uint32_t T_key, q;           // threshold (all bits set: no member), members among its holders
     uint32_t gt_before, eq_before;   // members for sure / ties in the parts before the block's own
     uint32_t n_bins, n_col, n_valid; // keys of the narrow columns, of the threshold's column; positions of the segment
+    uint32_t n_near;                 // keys down to the end of column kShortBulk
+    uint32_t n_scan, n_same;         // keys that the whole block had to read, several times; how many of them are the threshold itself (if many)
     int col;
     bool missed;
 };
@@ -404,8 +505,8 @@ struct ShortFound {
 // once the counts have been requested, for loads that nothing here waits for.
 template <int T, int P, typename F>
 __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartDesc& d, const uint4* __restrict__ used,
-                                                   const uint16_t* __restrict__ counts, const uint32_t* __restrict__ keys,
-                                                   F&& request)
+                                                   const uint16_t* __restrict__ counts, const uint64_t* __restrict__ pure,
+                                                   const uint32_t* __restrict__ keys, F&& request)
 {
     constexpr int W = T / kLanes;
     uint32_t* hist = lds.hist;
@@ -461,8 +562,9 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
     const uint32_t n_col = __builtin_amdgcn_readlane(static_cast<int>(total), col) - sure;
     const uint32_t n_bins = __builtin_amdgcn_readlane(static_cast<int>(total), kShortBelow - 1) -
                             __builtin_amdgcn_readlane(static_cast<int>(total), kShortFirstBin - 1);
+    const uint32_t n_near = __builtin_amdgcn_readlane(static_cast<int>(total), kShortBulk);
     const ShortCols cols(u.x, u.y);
-    uint32_t T_key = 0xffffffffu, q = 0;                    // no member
+    uint32_t T_key = 0xffffffffu, q = 0, n_scan = 0, n_same = 0;                    // no member
     uint32_t gt_mine = 0, eq_mine = 0;                      // this thread's share of the members for sure / ties in earlier parts
     // one part per thread from here on: what it lists before and in the column
     uint32_t lo_c = 0, hi_c = 0;
@@ -561,10 +663,15 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
         uint32_t span = 24u;                                // log2 of the keys counted in bins
         if (col > 0) span = 32u - static_cast<uint32_t>(__clz(static_cast<int>(cols.end(col - 1) - base)));   // (not empty: at least 1)
         if (span > 31u) span = 31u;
-        if (has_part) {
+        if (has_part) {                                     // equal keys: the first one for all of them
+            const bool one = hi_c > lo_c && ((pure[d.part_first + t] >> col) & 1u) != 0u;
             lds.from[t] = static_cast<uint16_t>(lo_c);
-            lds.to[t] = static_cast<uint16_t>(hi_c);
+            lds.to[t] = static_cast<uint16_t>(one ? lo_c + 1u : hi_c);
+            lds.weight[t] = static_cast<uint16_t>(one ? hi_c - lo_c : 1u);
+            n_scan = one ? 1u : hi_c - lo_c;
         }
+        if (t == 0) lds.n_scan = 0u;
+        n_scan = wave_sum(n_scan);
         const uint32_t* slices = keys + static_cast<size_t>(d.part_first) * P;
         bool by_list = false;
         uint32_t rem = 0;                                   // rank of the threshold inside the bin that was found
@@ -573,15 +680,23 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
             __syncthreads();                                // everybody has read what is cleared here
             for (int b = t; b < kShortGeneral; b += T) hist[b] = 0u;
             if (t == 0) lds.n_over = lds.n_list = res[0] = 0u;
+            if (level == 0 && lane == 0 && n_scan) atomicAdd(&lds.n_scan, n_scan);
             __syncthreads();
             uint32_t over = 0;
-            short_for_keys<T, P>(slices, lds.from, lds.to, n_parts, [&](uint32_t key, int) {
+            short_for_keys<T, P>(slices, lds.from, lds.to, lds.weight, n_parts, [&](uint32_t key, int, uint32_t w) {
                 const uint32_t rel = key - base;
                 if (key < base) return;
-                if (rel >> span)
-                    ++over;
-                else
-                    atomicAdd(&hist[rel >> shift], 1u);
+                if (rel >> span) {
+                    over += w;
+                    return;
+                }
+                // the lanes that share the first one's bin add once (few-valued data would wait for one word 64 times)
+                const uint32_t bin = rel >> shift, lead = __builtin_amdgcn_readfirstlane(static_cast<int>(bin));
+                const uint64_t same = __builtin_amdgcn_ballot_w64(bin == lead);
+                if (bin != lead)
+                    atomicAdd(&hist[bin], w);
+                else if (lanes_below(same) == 0u)
+                    atomicAdd(&hist[bin], w * static_cast<uint32_t>(__popcll(same)));
             });
             over = wave_sum(over);
             if (lane == 0 && over) atomicAdd(&lds.n_over, over);
@@ -607,6 +722,7 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
             if (shift == 0u) {                              // one key per bin
                 T_key = base;
                 q = rem;
+                n_same = res[2];
                 break;
             }
             if (res[2] <= kShortListMax) {
@@ -616,13 +732,14 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
         }
         if (by_list) {
             // the bin's few keys (lowest bit: from a part before mine), ranked against each other
-            short_for_keys<T, P>(slices, lds.from, lds.to, n_parts, [&](uint32_t key, int p) {
+            short_for_keys<T, P>(slices, lds.from, lds.to, lds.weight, n_parts, [&](uint32_t key, int p, uint32_t w) {
                 if (key < base) return;
                 if ((key - base) >> span) {
-                    gt_mine += p < mine ? 1u : 0u;
+                    gt_mine += p < mine ? w : 0u;
                 } else {
-                    const uint32_t at = atomicAdd(&lds.n_list, 1u);
-                    if (at < kShortListMax) list[at] = (key << 1) | (p < mine ? 1u : 0u);
+                    uint32_t at = atomicAdd(&lds.n_list, w);
+                    for (const uint32_t past = at + w; at < past && at < kShortListMax; ++at)
+                        list[at] = (key << 1) | (p < mine ? 1u : 0u);
                 }
             });
             __syncthreads();
@@ -638,11 +755,12 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
                 eq_mine += v == T_key ? 1u : 0u;
             }
         } else if (T_key != 0xffffffffu) {
-            short_for_keys<T, P>(slices, lds.from, lds.to, n_parts, [&](uint32_t key, int p) {
-                gt_mine += p < mine && key > T_key ? 1u : 0u;
-                eq_mine += p < mine && key == T_key ? 1u : 0u;
+            short_for_keys<T, P>(slices, lds.from, lds.to, lds.weight, n_parts, [&](uint32_t key, int p, uint32_t w) {
+                gt_mine += p < mine && key > T_key ? w : 0u;
+                eq_mine += p < mine && key == T_key ? w : 0u;
             });
         }
+        n_scan = lds.n_scan;                                // (added up behind the first level's barrier)
     }
     {
         const uint32_t g = wave_sum(gt_mine), e = wave_sum(eq_mine);
@@ -662,7 +780,7 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
     }
 
     __syncthreads();
-    ShortFound f{T_key, q, 0u, 0u, n_bins, n_col, n_valid, col, missed};
+    ShortFound f{T_key, q, 0u, 0u, n_bins, n_col, n_valid, n_near, n_scan, n_same, col, missed};
 #pragma unroll
     for (int w = 0; w < W; ++w) {
         f.gt_before += lds.own[0][w];
@@ -682,8 +800,16 @@ __device__ __forceinline__ void short_record(const ShortLds<T>& lds, const PartD
     const int mine = static_cast<int>(blockIdx.x) - d.part_first, col = f.col;
     if (mine != 0 || threadIdx.x != 0 || k == 0 || f.T_key == 0xffffffffu) return;
     uint32_t* pred = preds + static_cast<size_t>(d.seg) * kPredWords;
-    // The narrow columns: wider at once if the threshold left their middle half or if they held few keys,
-    // narrower after some calm steps if they held many more than a quarter of an index set's worth (and enough for
+    const uint32_t have = u.z & 3u;
+    bool held = !f.missed;
+    if (have == kShortDoubted) {                             // would the expectation have held?
+        const ShortCols cols((predicted_t24(pred, lead_mine, d.seg) << kBits2) | (kBins2 / 2), kShortWidthFirst);
+        held = f.T_key < cols.end(1) && f.T_key >= cols.end(kShortBulk - 1);
+    }
+    pred[kPredShortTrust] = ShortTrust(u.z >> 2).next(held, f.n_scan > kShortLong && have == kShortExpected) |
+                            static_cast<uint32_t>(64.0f * static_cast<float>(f.n_near) / static_cast<float>(f.n_valid)) << 24;
+    // The narrow columns: wider at once if the threshold left their middle half or if they held few keys, narrower at once if
+    // the threshold's own held too many different ones, and after some calm steps if they all held many more than a quarter of an index set's worth (and enough for
     // the spread of an order statistic of rank k): few keys to search, and a threshold that leaves the narrow
     // columns lands in one that is not much larger.  (As many as the index set: 24.5 us a step at 4 x 1 M, now 22.6.)
     uint32_t want = static_cast<uint32_t>(8.0f * sqrtf(static_cast<float>(k)));
@@ -691,7 +817,13 @@ __device__ __forceinline__ void short_record(const ShortLds<T>& lds, const PartD
     want = want > 64u ? want : 64u;
     const bool middle = col >= kShortFirstBin + kShortBins / 4 && col < kShortBelow - kShortBins / 4;
     uint32_t width = u.y, calm = middle ? u.w + 1u : 0u;
-    if (!middle || 5u * f.n_bins < 3u * want) {
+    const uint32_t crowd = f.n_scan > f.n_same ? f.n_scan - f.n_same : 0u;
+    if (middle && crowd > kShortColumnMax) {
+        uint32_t less = 32u - static_cast<uint32_t>(__clz(static_cast<int>(crowd / kShortColumnMax)));
+        less = less < 4u ? less : 4u;
+        width = width > less + kShortWidthMin ? width - less : kShortWidthMin;
+        calm = 0u;
+    } else if (!middle || 5u * f.n_bins < 3u * want) {
         ++width;
         calm = 0u;
     } else if (calm >= kShortCalm && 2u * f.n_bins > 3u * want) {
@@ -703,9 +835,9 @@ __device__ __forceinline__ void short_record(const ShortLds<T>& lds, const PartD
     pred[kPredShortCalm] = calm;
     record_t24(pred, lead_mine, d.seg, f.T_key >> kBits2);
     if (stats && f.n_valid > static_cast<uint32_t>(kSuper)) {
-        if (u.z == 0u)                                  // the threshold came from a sample
+        if (have == kShortNone)
             atomicAdd(&stats[kStatNoPrediction], 1ull);
-        else if (f.missed)
+        else if (!held)
             atomicAdd(&stats[kStatMissed], 1ull);
         uint32_t most = 0;                              // a quarter of a part: clustered in one place
         for (int w = 0; w < W; ++w) most = lds.own[2][w] > most ? lds.own[2][w] : most;
@@ -724,8 +856,8 @@ template <typename G, int T, int R, int OCC>
 __global__ void __launch_bounds__(T, OCC)
 k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, float one_minus_beta,
              const PartDesc* __restrict__ parts, uint32_t* __restrict__ preds, uint32_t* __restrict__ lead_mine,
-             const uint4* __restrict__ used, const uint16_t* __restrict__ counts, const uint32_t* __restrict__ keys,
-             int32_t* __restrict__ idx_out, float* __restrict__ red_out, unsigned long long* __restrict__ stats)
+             const uint4* __restrict__ used, const uint16_t* __restrict__ counts, const uint64_t* __restrict__ pure,
+             const uint32_t* __restrict__ keys, int32_t* __restrict__ idx_out, float* __restrict__ red_out, unsigned long long* __restrict__ stats)
 {
     constexpr int W = T / kLanes, P = T * kVec * R;
     __shared__ ShortLds<T> lds;
@@ -735,7 +867,7 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
     const int64_t begin = d.begin, end = d.end;
     const uint32_t k = static_cast<uint32_t>(d.k);
     float4 lm, lg;
-    const ShortFound f = short_search<T, P>(lds, d, used, counts, keys, [&]() {
+    const ShortFound f = short_search<T, P>(lds, d, used, counts, pure, keys, [&]() {
         leader_load(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), static_cast<int64_t>(d.a0) + t * kVec, begin, end, lm, lg);
     });
     short_record<T, P>(lds, d, used[d.seg], f, preds, lead_mine, stats);
@@ -851,10 +983,10 @@ k_short_overlap(const float* __restrict__ mem, const G* __restrict__ grad, float
     if (d.k == 0) return;                                   // whole block: nothing in common
     const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
     const int64_t begin = d.begin, end = d.end;
-    const ShortFound fa = short_search<T, P>(lds, d, a.used, a.counts, a.keys, []() {});
+    const ShortFound fa = short_search<T, P>(lds, d, a.used, a.counts, a.pure, a.keys, []() {});
     short_record<T, P>(lds, d, a.used[d.seg], fa, a.preds, a.lead_mine, nullptr);
     __syncthreads();                                        // the search's words are used again
-    const ShortFound fb = short_search<T, P>(lds, d, b.used, b.counts, b.keys, []() {});
+    const ShortFound fb = short_search<T, P>(lds, d, b.used, b.counts, b.pure, b.keys, []() {});
     short_record<T, P>(lds, d, b.used[d.seg], fb, b.preds, b.lead_mine, nullptr);
     uint32_t run_a = fa.eq_before, run_b = fb.eq_before, both = 0;
 #pragma unroll 1

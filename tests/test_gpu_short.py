@@ -94,6 +94,68 @@ def test_columns_of_any_size(gu, kind):
     ctx.close()
 
 
+@pytest.mark.parametrize("numel", [60_001, 300_007, 700_001, 1_300_003])   # parts of 1024, 2048, 4096 and 8192 positions
+@pytest.mark.parametrize("kind", ["per_part", "runs", "mixed", "far"])
+def test_columns_of_equal_keys(gu, numel, kind):
+    """Parts whose keys of one column are all equal count as one key with a weight: another value in every stretch of
+    positions, runs of equal keys that share a column with thousands of different ones (so that the threshold's bin holds few keys
+    but some with a weight), parts with one value and parts with several; thresholds inside, at the ends of and between the
+    runs; and, in "far", in the columns next to the narrow ones."""
+    rng = np.random.default_rng(numel)
+    n, ulp = 2, np.float32(2.0 ** -23)
+    part = {60_001: 1024, 300_007: 2048, 700_001: 4096, 1_300_003: 8192}[numel]
+    pos = np.arange(numel)
+    if kind == "per_part":                                      # few values, each constant over a stretch
+        x = 1.0 + ((pos // (part * 3 + 7)) % 5 * 40).astype(np.float32) * ulp
+        ks = [1, numel // 100, numel // 5, numel // 2, numel - 1]
+    elif kind == "runs":
+        x = rng.random(numel).astype(np.float32) * 0.5
+        x[rng.choice(numel, 3_000, replace=False)] = 1.0 + rng.permutation(3_000).astype(np.float32) * 8 * ulp   # all different
+        for r in range(6):                                      # six parts with a run of equal keys among them
+            at = (3 + 7 * r) * part % (numel - part)
+            x[at:at + part // 12] = 1.0 + np.float32(4 + 8 * 400 * r) * ulp
+        order = np.sort(x)[::-1]
+        edge = [int(np.searchsorted(-order, -np.float32(1.0 + np.float32(4 + 8 * 400 * r) * ulp))) for r in (1, 3, 5)]
+        ks = [edge[0] + 1, edge[1], edge[1] + part // 24, edge[2] + part // 12, edge[2] + part // 12 + 1]
+    elif kind == "mixed":
+        x = np.where((pos // part) % 3 == 0, np.float32(1.0), 1.0 + rng.integers(0, 3, numel).astype(np.float32) * ulp)
+        ks = [5, numel // 100, numel // 3, numel // 2, numel - 3]
+    else:                                                       # nine tenths equal, the threshold jumps there from a narrow column
+        x = np.where(rng.random(numel) < 0.9, np.float32(0.97), 1.0 + rng.random(numel).astype(np.float32) * 0.01)
+        ks = [numel // 100, numel // 100, numel // 2, numel // 20, numel // 5]
+    x = np.ascontiguousarray(x, dtype=np.float32)
+    grad = [torch.from_numpy(x).to(gu.DEV), torch.from_numpy(x[::-1].copy()).to(gu.DEV)]
+    ctx = binding.scalecom_init(numel, n, torch.float32, 1, gu.DEV)
+    same_k = kind == "far"                                      # (expectations are kept for one k only)
+    for k in ks[:1] if same_k else ks:
+        mem = [torch.zeros(numel, device=gu.DEV) for _ in range(n)]
+        ref = [np.zeros(numel, np.float32) for _ in range(n)]
+        for step in range(12 if same_k else 3):
+            # memories start from zero each time, but for "far": there the scale moves the threshold over the run and back
+            lr = [1.0, 1.0, 0.97, 1.02, 1.0, 0.5, 64.0, 1.0, 1.0, 1.0, 1.03, 0.98][step] if same_k else 1.0
+            print(f"[short] equal keys {kind} numel={numel} k={k} step={step}", flush=True)
+            gu.compare_step(ctx, mem, grad, ref, step, 0.25, lr, k=k, what=f"{kind} numel={numel} k={k}")
+    ctx.close()
+
+
+@pytest.mark.parametrize("numel", [150_001, 1_100_003])
+def test_expectations_that_are_not_trusted(gu, numel):
+    """After a threshold far from where it was expected, a sample takes the expectation's place until that would have held for
+    several steps: jumps in both directions, alone and again and again, then quiet steps until it is used again, then a jump."""
+    n, k = 2, numel // 100
+    x = [_normal(numel, 1, 1.0), _normal(numel, 2, 1.0)]
+    ctx = binding.scalecom_init(numel, n, torch.float32, 1, gu.DEV)
+    mem = [torch.zeros(numel, device=gu.DEV) for _ in range(n)]
+    ref = [np.zeros(numel, np.float32) for _ in range(n)]
+    grad = [g.to(gu.DEV) for g in x]
+    scales = [1, 1, 1, 1, 50, 1, 1, 0.02, 0.02, 3, 1 / 3, 1, 7, 1] + [1] * 44 + [0.01, 0.01, 1, 1, 100, 100, 1]
+    for step, sc in enumerate(scales):
+        gu.compare_step(ctx, mem, grad, ref, step, 0.01, float(sc), k=k, what=f"trust numel={numel} scale {sc}")
+    missed = ctx.scalecom_selection_stats()["missed"]
+    assert 4 <= missed <= len(scales) // 2
+    ctx.close()
+
+
 @pytest.mark.parametrize("chunk", [1, 3, 4, 7, 8, 25, 50, 63, 84, 100, 112, 126, 127, 155, 252, 253, 254, 400, 509, 510, 3000])
 def test_chunks_in_one_launch(gu, chunk):
     """Chunk sizes around the edges of the one-launch step (253 and 509 positions per block, 64 chunks per
