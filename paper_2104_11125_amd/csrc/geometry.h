@@ -162,7 +162,7 @@ constexpr int kStatWords = 8;
 enum : int {
     kStatMissed = 0,        // had a prediction and its range did not hold the threshold: two more leader passes
     kStatNoPrediction = 1,  // had no prediction (first step with a layout, or the step after a miss)
-    kStatFullMode = 2,      // the threshold bucket did not fit the candidate list: refinement by full leader passes
+    kStatFullMode = 2,      // the threshold bucket did not fit the candidate list: refinement by full leader passes (short layouts: a search by whole blocks)
     kStatWideRange = 3,     // hit with a range wider than 2^19 keys: one more pass over the listed keys
     kStatSteps = 4          // selections enqueued (one per step, whatever the number of tensors)
 };

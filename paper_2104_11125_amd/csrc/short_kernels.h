@@ -486,7 +486,7 @@ struct ShortLds {
     uint32_t wave_tot[W];
     uint32_t res[4];                                        // found, bin, its count, keys above it
     uint32_t n_list, n_over, n_scan;
-    uint32_t own[3][W];                                     // members for sure / ties in earlier parts, largest share of a part
+    uint32_t own[2][W];                                     // members for sure / ties in earlier parts
     uint16_t from[kShortSegParts], to[kShortSegParts], weight[kShortSegParts];
 };
 static_assert(kShortGeneral >= kShortColumnMax, "a column fits");
@@ -768,15 +768,6 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
             lds.own[0][wave] = g;
             lds.own[1][wave] = e;
         }
-        if (mine == 0 && k != 0) {                          // the largest share of a part in the narrow columns
-            uint32_t most = 0;
-            if (has_part) {
-                const uint16_t* mc = my_counts + static_cast<size_t>(t) * kShortCols;
-                most = mc[kShortBelow - 1] - mc[kShortFirstBin - 1];
-            }
-            most = wave_max_u32(most);
-            if (lane == 0) lds.own[2][wave] = most;
-        }
     }
 
     __syncthreads();
@@ -790,12 +781,9 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
 }
 
 // What the next steps expect, and the counters (stats: null for none): by the segment's first block.
-template <int T, int P>
-__device__ __forceinline__ void short_record(const ShortLds<T>& lds, const PartDesc& d, const uint4& u, const ShortFound& f,
-                                             uint32_t* __restrict__ preds, uint32_t* __restrict__ lead_mine,
-                                             unsigned long long* __restrict__ stats)
+__device__ __forceinline__ void short_record(const PartDesc& d, const uint4& u, const ShortFound& f, uint32_t* __restrict__ preds,
+                                             uint32_t* __restrict__ lead_mine, unsigned long long* __restrict__ stats)
 {
-    constexpr int W = T / kLanes;
     const uint32_t k = static_cast<uint32_t>(d.k);
     const int mine = static_cast<int>(blockIdx.x) - d.part_first, col = f.col;
     if (mine != 0 || threadIdx.x != 0 || k == 0 || f.T_key == 0xffffffffu) return;
@@ -839,9 +827,7 @@ __device__ __forceinline__ void short_record(const ShortLds<T>& lds, const PartD
             atomicAdd(&stats[kStatNoPrediction], 1ull);
         else if (!held)
             atomicAdd(&stats[kStatMissed], 1ull);
-        uint32_t most = 0;                              // a quarter of a part: clustered in one place
-        for (int w = 0; w < W; ++w) most = lds.own[2][w] > most ? lds.own[2][w] : most;
-        if (f.n_col > kShortColumnMax || 4u * most > static_cast<uint32_t>(P)) atomicAdd(&stats[kStatFullMode], 1ull);
+        if (f.n_scan != 0u) atomicAdd(&stats[kStatFullMode], 1ull);   // searched by the whole block
     }
 }
 
@@ -870,7 +856,7 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
     const ShortFound f = short_search<T, P>(lds, d, used, counts, pure, keys, [&]() {
         leader_load(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), static_cast<int64_t>(d.a0) + t * kVec, begin, end, lm, lg);
     });
-    short_record<T, P>(lds, d, used[d.seg], f, preds, lead_mine, stats);
+    short_record(d, used[d.seg], f, preds, lead_mine, stats);
     const uint32_t T_key = f.T_key, q = f.q;
     uint32_t gt_run = f.gt_before, eq_run = f.eq_before;    // members for sure / ties before the row
 #pragma unroll 1
@@ -984,10 +970,10 @@ k_short_overlap(const float* __restrict__ mem, const G* __restrict__ grad, float
     const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
     const int64_t begin = d.begin, end = d.end;
     const ShortFound fa = short_search<T, P>(lds, d, a.used, a.counts, a.pure, a.keys, []() {});
-    short_record<T, P>(lds, d, a.used[d.seg], fa, a.preds, a.lead_mine, nullptr);
+    short_record(d, a.used[d.seg], fa, a.preds, a.lead_mine, nullptr);
     __syncthreads();                                        // the search's words are used again
     const ShortFound fb = short_search<T, P>(lds, d, b.used, b.counts, b.pure, b.keys, []() {});
-    short_record<T, P>(lds, d, b.used[d.seg], fb, b.preds, b.lead_mine, nullptr);
+    short_record(d, b.used[d.seg], fb, b.preds, b.lead_mine, nullptr);
     uint32_t run_a = fa.eq_before, run_b = fb.eq_before, both = 0;
 #pragma unroll 1
     for (int r = 0; r < R; ++r) {

@@ -138,6 +138,27 @@ def test_columns_of_equal_keys(gu, numel, kind):
     ctx.close()
 
 
+def test_counter_of_long_searches(gu):
+    """Counted are searches by whole blocks, and nothing else: not an ordinary search on a vector whose keys around the
+    threshold happen to sit in one part."""
+    numel, n, k = 200_003, 2, 1_000                             # k: no column above the threshold's can hold more than 1024 keys
+    x = np.sort(np.abs(_normal(numel, 5, 1.0).numpy()))
+    ctx = binding.scalecom_init(numel, n, torch.float32, 1, gu.DEV)
+    mem = [torch.zeros(numel, device=gu.DEV) for _ in range(n)]
+    ref = [np.zeros(numel, np.float32) for _ in range(n)]
+    grad = [torch.from_numpy(x).to(gu.DEV) for _ in range(n)]
+    for step in range(12):
+        gu.compare_step(ctx, mem, grad, ref, step, 1e-3, 1.0, k=k, what="sorted")
+    assert ctx.scalecom_selection_stats(reset=True)["full_mode"] == 0
+    equal = [torch.where(g > 1.0, 1.0, g) for g in grad]        # 60 000 equal keys at the threshold
+    for m, r in zip(mem, ref):
+        m.zero_()
+        r[:] = 0
+    gu.compare_step(ctx, mem, equal, ref, 12, 1e-3, 1.0, k=k, what="equal")
+    assert ctx.scalecom_selection_stats()["full_mode"] == 1
+    ctx.close()
+
+
 @pytest.mark.parametrize("numel", [150_001, 1_100_003])
 def test_expectations_that_are_not_trusted(gu, numel):
     """After a threshold far from where it was expected, a sample takes the expectation's place until that would have held for
