@@ -72,18 +72,19 @@ k_sum_x(const LearnerPtrs lp, int n_learners, float lr, int64_t begin, int64_t e
 }
 
 // What the diagnostic's two selections start from, per tensor: d = k; for the leader's vector the prediction
-// that the steps keep, if they have one, otherwise what this diagnostic's last call left.  (The steps' own
+// that the steps keep, if they have one for the route this call takes (`is_short`; the learner count decides, so steps and
+// diagnostics on one layout may go different ways), otherwise what this diagnostic's last call left.  (The steps' own
 // predictions are only read.)
 __global__ void __launch_bounds__(kBlock)
 k_diag_begin(const SegDesc* __restrict__ segs, int n_tensors, const uint32_t* __restrict__ preds,
              const uint32_t* __restrict__ lead_mine, uint32_t* __restrict__ diag_preds, uint32_t* __restrict__ diag_lead,
-             int32_t* __restrict__ d)
+             int32_t* __restrict__ d, bool is_short)
 {
     const int s = blockIdx.x * kBlock + threadIdx.x;
     if (s >= n_tensors) return;
     d[s] = segs[s].k;
     const uint32_t* src = preds + static_cast<size_t>(s) * kPredWords;
-    if (src[0] == 0u && src[kPredShortWidth] == 0u) return;   // (a layout has one kind or the other)
+    if (src[is_short ? kPredShortWidth : 0] == 0u) return;
     for (int j = 0; j < kPredWords; ++j) diag_preds[static_cast<size_t>(s) * kPredWords + j] = src[j];
     diag_lead[s] = lead_mine[s];
 }

@@ -967,8 +967,9 @@ scalecom_status launch_hamming(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
     const size_t zone_words = l.zone_bytes / sizeof(uint32_t);
     auto no_mark = [](int) {};
 
+    const bool is_short = ctx->n_st > 0 && short_diagnostic(ctx, n_learners, end - begin);
     k_diag_begin<<<(n_tensors + kBlock - 1) / kBlock, kBlock, 0, s>>>(
-        segs, n_tensors, preds, preds + (kPredWords + static_cast<size_t>(leader)) * nt, preds_a, lead_a, d_out);
+        segs, n_tensors, preds, preds + (kPredWords + static_cast<size_t>(leader)) * nt, preds_a, lead_a, d_out, is_short);
     auto sum_x = [&](size_t clear_words) {
         const int64_t tiles = (end - (begin & ~static_cast<int64_t>(kVec - 1)) + kWaveTile - 1) / kWaveTile;
         const unsigned gx = static_cast<unsigned>(std::min<int64_t>(tiles, 1 << 20));
@@ -976,7 +977,7 @@ scalecom_status launch_hamming(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
         k_sum_x<G><<<grid, std::min(n_learners, kSumWaves) * kLanes, sizeof(float4) * kLanes * n_learners, s>>>(
             lp, n_learners, lr, begin, end, tiles, y, zone, clear_words);
     };
-    if (ctx->n_st > 0 && short_diagnostic(ctx, n_learners, end - begin)) {
+    if (is_short) {
         sum_x(0);
         const ShortVector a{preds_a, lead_a, reinterpret_cast<uint4*>(ctx->ws + l.short_used),
                             reinterpret_cast<uint16_t*>(ctx->ws + l.short_counts),

@@ -283,3 +283,32 @@ def test_layouts_at_the_limits(gu, n, sizes):
         print(f"[short] limits n={n} numel={numel} step={step}", flush=True)
         gu.compare_step(ctx, mem, grad, ref, step, 0.2, 0.1, offsets=offsets, ks=ks, what=f"limits n={n}")
     ctx.close()
+
+
+def test_diagnostic_beside_steps_on_the_other_route(gu):
+    """Steps with so many learners that they take the long path, the diagnostic with few on the short one: the steps' predictions
+    are of another kind and must not displace what the diagnostic itself expects.  What a short search started from is read
+    from the workspace: the expected threshold's top 24 bits in the middle of their range, a width, and the mark of an expectation."""
+    sizes = [1_500_001, 700_003, 900_000]
+    offsets = [0, sizes[0], sizes[0] + sizes[1], sum(sizes)]
+    ks = [s // 100 for s in sizes]
+    numel, many = offsets[-1], 17                               # 17 x 3.1 M: the long path
+    ctx = binding.scalecom_init(numel, many, torch.float32, len(ks), gu.DEV, k_max=sum(ks))
+    x = _normal(numel, 3, 1.0).to(gu.DEV)
+    mem = [torch.zeros(numel, device=gu.DEV) for _ in range(many)]
+    ctx.scalecom_step_layers(mem, [x] * many, offsets, ks, 0.5, 1.0, 0)
+    zeros = [torch.zeros(numel, device=gu.DEV) for _ in range(2)]
+    keys = [int(torch.topk(x[a:b].abs(), k).values[-1].view(torch.int32)) for a, b, k in zip(offsets, offsets[1:], ks)]
+    want = [(t >> 7 << 7) | 64 for t in keys]
+
+    def started_from_the_expectation():
+        torch.cuda.synchronize()
+        w = ctx.workspace.view(torch.int32)
+        w = w[:w.numel() // 4 * 4].view(-1, 4)
+        return [bool(((w[:, 0] == t) & (w[:, 1] >= 2) & (w[:, 1] <= 15) & (w[:, 2] & 3 == 1)).any()) for t in want]
+
+    for call in range(3):
+        d = ctx.scalecom_hamming_distance(zeros, [x, x], offsets, ks, 1.0, 0)
+        assert d.cpu().tolist() == [0, 0, 0]
+        assert started_from_the_expectation() == [call > 0] * len(ks), call
+    ctx.close()
