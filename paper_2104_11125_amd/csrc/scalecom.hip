@@ -91,8 +91,8 @@ constexpr int64_t max_chunks(int64_t numel_max, int n_tensors_max)
 
 struct WsLayout {
     size_t segs, sts, chunks, hblocks, small, preds, stats, state, wt_cnt, st_sum, st_prefix, chunk_tot, st_cand_cnt, cand, sel_mask,
-        eq_mask, tile_slot, vals, best, parts, short_used, short_counts, short_pure, short_keys, diag_preds, diag_used, diag_counts,
-        diag_pure, diag_keys, dots, total;
+        eq_mask, tile_slot, vals, best, parts, short_used, short_counts, short_keys, diag_preds, diag_used, diag_counts,
+        diag_keys, dots, total;
     int64_t short_numel;   // positions that the short path's key array is made for
     size_t short_words;    // and its words
     // per-step counters and histograms: one zone, all zero between steps (offsets inside the zone)
@@ -155,7 +155,6 @@ constexpr WsLayout layout_for(int64_t numel_max, int n_tensors_max, int n_learne
     l.parts = take(kShortPartsMax * sizeof(PartDesc));
     l.short_used = take(nt * sizeof(uint4));
     l.short_counts = take(static_cast<size_t>(kShortPartsMax) * kShortCols * sizeof(uint16_t));
-    l.short_pure = take(kShortPartsMax * sizeof(uint64_t));
     if (nt == 1 && short_numel_max > kShortNumelFlat) short_numel_max = kShortNumelFlat;
     l.short_numel = numel_max < short_numel_max ? numel_max : short_numel_max;
     // a segment's first and last part may be partly empty
@@ -168,7 +167,6 @@ constexpr WsLayout layout_for(int64_t numel_max, int n_tensors_max, int n_learne
         l.diag_preds = take((2 * kPredWords + static_cast<size_t>(n_learners_max)) * nt * sizeof(uint32_t));
         l.diag_used = take(nt * sizeof(uint4));
         l.diag_counts = take(static_cast<size_t>(kShortPartsMax) * kShortCols * sizeof(uint16_t));
-        l.diag_pure = take(kShortPartsMax * sizeof(uint64_t));
         l.diag_keys = take(l.short_words * sizeof(uint32_t));
         l.dots = take(3 * static_cast<size_t>(kDotsBlocks) * sizeof(double));
     }
@@ -650,17 +648,16 @@ void launch_short_as(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learners, f
     const PartDesc* parts = reinterpret_cast<const PartDesc*>(ws + l.parts);
     uint4* used = reinterpret_cast<uint4*>(ws + l.short_used);
     uint16_t* counts = reinterpret_cast<uint16_t*>(ws + l.short_counts);
-    uint64_t* pure = reinterpret_cast<uint64_t*>(ws + l.short_pure);
     uint32_t* keys = reinterpret_cast<uint32_t*>(ws + l.short_keys);
     unsigned long long* stats = reinterpret_cast<unsigned long long*>(ws + l.stats);
     k_short_collect<G, T, R><<<ctx->n_parts, T, 0, ctx->stream>>>(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), lr,
-                                                               parts, preds, lead_mine, used, counts, pure, keys, stats);
+                                                               parts, preds, lead_mine, used, counts, keys, stats);
     mark(1);
     mark(2);
     mark(3);
     auto step = [&](auto kernel) {
         kernel<<<ctx->n_parts, T, 0, ctx->stream>>>(lp, n_learners, leader, lr, beta, 1.0f - beta, parts, preds, lead_mine, used,
-                                                    counts, pure, keys, idx_out, red_out, stats);
+                                                    counts, keys, idx_out, red_out, stats);
     };
     // more waves than four per SIMD on 256 compute units: registers for six (blocks of 1024 threads are few)
     if (T < 1024 && ctx->n_parts * (T / kLanes) > 256 * 4 * 4)
@@ -980,11 +977,9 @@ scalecom_status launch_hamming(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
     if (is_short) {
         sum_x(0);
         const ShortVector a{preds_a, lead_a, reinterpret_cast<uint4*>(ctx->ws + l.short_used),
-                            reinterpret_cast<uint16_t*>(ctx->ws + l.short_counts),
-                            reinterpret_cast<uint64_t*>(ctx->ws + l.short_pure), reinterpret_cast<uint32_t*>(ctx->ws + l.short_keys)};
+                            reinterpret_cast<uint16_t*>(ctx->ws + l.short_counts), reinterpret_cast<uint32_t*>(ctx->ws + l.short_keys)};
         const ShortVector b{preds_b, nullptr, reinterpret_cast<uint4*>(ctx->ws + l.diag_used),
-                            reinterpret_cast<uint16_t*>(ctx->ws + l.diag_counts),
-                            reinterpret_cast<uint64_t*>(ctx->ws + l.diag_pure), reinterpret_cast<uint32_t*>(ctx->ws + l.diag_keys)};
+                            reinterpret_cast<uint16_t*>(ctx->ws + l.diag_counts), reinterpret_cast<uint32_t*>(ctx->ws + l.diag_keys)};
         const float* memL = lp.mem[leader];
         const G* gradL = static_cast<const G*>(lp.grad[leader]);
         if (ctx->short_threads == 256)

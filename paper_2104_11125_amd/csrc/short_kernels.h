@@ -29,7 +29,7 @@ namespace {
 // the threshold's column beyond the first thousand are read by all blocks of the segment, several times (all keys of 2 M positions
 // after a jump of the gradients by 64: 1.2 ms, where the long path takes 65 us).  So columns are kept small: the expectation is checked on a few
 // keys before it is used (short_far_off), after a long search a sample takes its place until it would have held for a while (ShortTrust),
-// columns that are crowded get narrower, and a part's keys of one column that are all equal count as one key with a weight (`pure`).
+// columns that are crowded get narrower, and a part's keys of one column that are all equal count as one key with a weight (kShortEqual).
 // A step of 2 x 2 M positions, us, against the long path: normal values 32 / 47, all magnitudes equal 36 / 121, two of them 71 / 154, a jump by
 // 64 every third step 56 / 66, one jump 50 / 64 and the step after it 167 / 68.
 
@@ -39,6 +39,7 @@ constexpr int kShortFirstBin = kShortAbove, kShortBelow = kShortAbove + kShortBi
 constexpr int kShortListed = 60;                 // running count of everything that is listed (all but zeros)
 constexpr int kShortBulk = kShortListed - 1;     // the last two columns, where most keys are
 constexpr int kShortValid = 61;                  // the part's positions inside the segment (not a running count)
+constexpr int kShortEqual = 62;                  // two words, four bytes: columns whose keys are all equal, plus 1 (0: none)
 constexpr int kShortSampleLog = 12;              // bins of the sample: the key's top twelve bits
 constexpr int kShortGeneralLog = 11, kShortGeneral = 1 << kShortGeneralLog;   // bins of the general search
 constexpr uint32_t kShortColumnMax = 1024;       // keys that one wave searches, 16 per lane
@@ -84,7 +85,8 @@ struct ShortCols {
         return c;
     }
 };
-static_assert(kShortBelow + 8 == kShortBulk && kShortBulk + 1 == kShortListed && kShortListed < kShortValid && kShortValid < kShortCols,
+static_assert(kShortBelow + 8 == kShortBulk && kShortBulk + 1 == kShortListed && kShortListed < kShortValid &&
+                  kShortValid < kShortEqual && kShortEqual % 2 == 0 && kShortEqual + 2 == kShortCols,
               "a row holds them all");
 
 // What a segment's columns were laid around (the low two bits of word z of `used`; above them the trust as the step found it, which
@@ -204,7 +206,7 @@ __device__ __forceinline__ uint32_t short_sample(const float* __restrict__ mem, 
 // segment (at equal distances they would share a memory channel), so all waves of all blocks come to the same answer without a word
 // between them.  Far off: many more of the 64 keys above the near columns than the index set's share, or hardly any down to the
 // end of column kShortBulk, where the last step had `below`.  m, g: every group in four lanes.  Costs 0.2 us a step.
-constexpr int kShortCheckGroups = 16, kShortCheckParts = 4;   // (segments of few parts do without: a long column is short there)
+constexpr int kShortCheckGroups = 16, kShortCheckParts = 32;  // (segments of few parts do without: a long column is read by few blocks)
 
 __device__ __forceinline__ bool short_far_off(const float4& m, const float4& g, float lr, const PartDesc& d, const ShortCols& cols,
                                               uint32_t below)
@@ -228,8 +230,7 @@ template <typename G, int T, int R>
 __device__ __forceinline__ void
 short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const PartDesc* __restrict__ parts,
               const uint32_t* __restrict__ preds, const uint32_t* __restrict__ lead_mine, uint4* __restrict__ used,
-              uint16_t* __restrict__ counts, uint64_t* __restrict__ pure, uint32_t* __restrict__ keys,
-              unsigned long long* __restrict__ stats)
+              uint16_t* __restrict__ counts, uint32_t* __restrict__ keys, unsigned long long* __restrict__ stats)
 {
     constexpr int W = T / kLanes, P = T * kVec * R;
     // the sample's counts, then the part's keys in the order in which they leave
@@ -247,7 +248,7 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
     const G* s_grad = reinterpret_cast<const G*>(parts);
     if (check) {
         const uint32_t up = (static_cast<uint32_t>(d.begin) + kVec - 1) & ~static_cast<uint32_t>(kVec - 1);
-        const uint32_t stretch = (static_cast<uint32_t>(d.end) - up) / (kVec * kShortCheckGroups);   // whole groups, at least 63
+        const uint32_t stretch = (static_cast<uint32_t>(d.end) - up) / (kVec * kShortCheckGroups);   // whole groups, at least 512
         const uint32_t j = static_cast<uint32_t>(lane) % kShortCheckGroups;
         const int64_t p0 = up + static_cast<int64_t>(j * stretch + __umulhi(j * 0x9e3779b1u, stretch)) * kVec;
         s_mem = mem + p0;
@@ -332,10 +333,7 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
         // columns with so many keys that it pays to know whether they are equal (not the last ones, wide and full as a rule:
         // a sample's threshold is at most 0.9 spans below the narrow columns)
         const uint64_t many = __builtin_amdgcn_ballot_w64(lane < kShortBelow + 6 && n >= static_cast<uint32_t>(P / 32));
-        if (lane == 0) {
-            heavy = many;
-            if (many == 0) pure[blockIdx.x] = 0;
-        }
+        if (lane == 0) heavy = many;
         counts[static_cast<size_t>(blockIdx.x) * kShortCols + lane] = static_cast<uint16_t>(lane <= kShortListed ? run : n);
     }
     __syncthreads();
@@ -359,7 +357,11 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
     __syncthreads();
     if (wave == 0) {
         const uint64_t same = __builtin_amdgcn_ballot_w64(mixed[lane] == 0u) & many;
-        if (lane == 0) pure[blockIdx.x] = same;
+        uint64_t left = same;                               // the highest four (scalar)
+        uint32_t four = 0;
+        for (int j = 0; j < 32 && left != 0; j += 8, left &= left - 1) four |= static_cast<uint32_t>(__ffsll(static_cast<long long>(left))) << j;
+        if (lane == 0)
+            *reinterpret_cast<uint32_t*>(counts + static_cast<size_t>(blockIdx.x) * kShortCols + kShortEqual) = four;
     }
 }
 
@@ -367,10 +369,9 @@ template <typename G, int T, int R>
 __global__ void __launch_bounds__(T)
 k_short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const PartDesc* __restrict__ parts,
                 const uint32_t* __restrict__ preds, const uint32_t* __restrict__ lead_mine, uint4* __restrict__ used,
-                uint16_t* __restrict__ counts, uint64_t* __restrict__ pure, uint32_t* __restrict__ keys,
-                unsigned long long* __restrict__ stats)
+                uint16_t* __restrict__ counts, uint32_t* __restrict__ keys, unsigned long long* __restrict__ stats)
 {
-    short_collect<G, T, R>(mem, grad, lr, parts, preds, lead_mine, used, counts, pure, keys, stats);
+    short_collect<G, T, R>(mem, grad, lr, parts, preds, lead_mine, used, counts, keys, stats);
 }
 
 // What k_short_collect leaves of one vector, and where its expectations are kept.
@@ -379,7 +380,6 @@ struct ShortVector {
     uint32_t* lead_mine;         // null: no record per leader
     uint4* used;
     uint16_t* counts;
-    uint64_t* pure;              // per part: the columns whose keys are all equal
     uint32_t* keys;
 };
 
@@ -390,9 +390,9 @@ k_short_collect_two(const float* __restrict__ mem, const G* __restrict__ grad, f
                     const PartDesc* __restrict__ parts, ShortVector a, ShortVector b)
 {
     if (blockIdx.y == 0)
-        short_collect<G, T, R>(mem, grad, lr, parts, a.preds, a.lead_mine, a.used, a.counts, a.pure, a.keys, nullptr);
+        short_collect<G, T, R>(mem, grad, lr, parts, a.preds, a.lead_mine, a.used, a.counts, a.keys, nullptr);
     else
-        short_collect<NoGrad, T, R>(sum, nullptr, 0.0f, parts, b.preds, b.lead_mine, b.used, b.counts, b.pure, b.keys, nullptr);
+        short_collect<NoGrad, T, R>(sum, nullptr, 0.0f, parts, b.preds, b.lead_mine, b.used, b.counts, b.keys, nullptr);
 }
 
 // The listed keys of a segment's parts [0, n_parts), words [from[p], to[p]) of part p's slice, to `f`
@@ -505,8 +505,8 @@ struct ShortFound {
 // once the counts have been requested, for loads that nothing here waits for.
 template <int T, int P, typename F>
 __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartDesc& d, const uint4* __restrict__ used,
-                                                   const uint16_t* __restrict__ counts, const uint64_t* __restrict__ pure,
-                                                   const uint32_t* __restrict__ keys, F&& request)
+                                                   const uint16_t* __restrict__ counts, const uint32_t* __restrict__ keys,
+                                                   F&& request)
 {
     constexpr int W = T / kLanes;
     uint32_t* hist = lds.hist;
@@ -664,7 +664,10 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
         if (col > 0) span = 32u - static_cast<uint32_t>(__clz(static_cast<int>(cols.end(col - 1) - base)));   // (not empty: at least 1)
         if (span > 31u) span = 31u;
         if (has_part) {                                     // equal keys: the first one for all of them
-            const bool one = hi_c > lo_c && ((pure[d.part_first + t] >> col) & 1u) != 0u;
+            const uint32_t four = *reinterpret_cast<const uint32_t*>(my_counts + static_cast<size_t>(t) * kShortCols + kShortEqual);
+            bool one = false;
+#pragma unroll
+            for (int j = 0; j < 32; j += 8) one = one || ((four >> j) & 0xffu) == static_cast<uint32_t>(col) + 1u;
             lds.from[t] = static_cast<uint16_t>(lo_c);
             lds.to[t] = static_cast<uint16_t>(one ? lo_c + 1u : hi_c);
             lds.weight[t] = static_cast<uint16_t>(one ? hi_c - lo_c : 1u);
@@ -842,8 +845,8 @@ template <typename G, int T, int R, int OCC>
 __global__ void __launch_bounds__(T, OCC)
 k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, float one_minus_beta,
              const PartDesc* __restrict__ parts, uint32_t* __restrict__ preds, uint32_t* __restrict__ lead_mine,
-             const uint4* __restrict__ used, const uint16_t* __restrict__ counts, const uint64_t* __restrict__ pure,
-             const uint32_t* __restrict__ keys, int32_t* __restrict__ idx_out, float* __restrict__ red_out, unsigned long long* __restrict__ stats)
+             const uint4* __restrict__ used, const uint16_t* __restrict__ counts, const uint32_t* __restrict__ keys,
+             int32_t* __restrict__ idx_out, float* __restrict__ red_out, unsigned long long* __restrict__ stats)
 {
     constexpr int W = T / kLanes, P = T * kVec * R;
     __shared__ ShortLds<T> lds;
@@ -853,7 +856,7 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
     const int64_t begin = d.begin, end = d.end;
     const uint32_t k = static_cast<uint32_t>(d.k);
     float4 lm, lg;
-    const ShortFound f = short_search<T, P>(lds, d, used, counts, pure, keys, [&]() {
+    const ShortFound f = short_search<T, P>(lds, d, used, counts, keys, [&]() {
         leader_load(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), static_cast<int64_t>(d.a0) + t * kVec, begin, end, lm, lg);
     });
     short_record(d, used[d.seg], f, preds, lead_mine, stats);
@@ -958,7 +961,7 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
 // The similarity diagnostic on a short layout: the searches for the leader's vector and for the sum over learners,
 // then the positions that both index sets hold, taken off d (preset to k).
 template <typename G, int T, int R>
-__global__ void __launch_bounds__(T)
+__global__ void __launch_bounds__(T, T < 1024 ? 6 : 4)
 k_short_overlap(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const float* __restrict__ sum,
                 const PartDesc* __restrict__ parts, ShortVector a, ShortVector b, int32_t* __restrict__ d_out)
 {
@@ -969,10 +972,10 @@ k_short_overlap(const float* __restrict__ mem, const G* __restrict__ grad, float
     if (d.k == 0) return;                                   // whole block: nothing in common
     const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
     const int64_t begin = d.begin, end = d.end;
-    const ShortFound fa = short_search<T, P>(lds, d, a.used, a.counts, a.pure, a.keys, []() {});
+    const ShortFound fa = short_search<T, P>(lds, d, a.used, a.counts, a.keys, []() {});
     short_record(d, a.used[d.seg], fa, a.preds, a.lead_mine, nullptr);
     __syncthreads();                                        // the search's words are used again
-    const ShortFound fb = short_search<T, P>(lds, d, b.used, b.counts, b.pure, b.keys, []() {});
+    const ShortFound fb = short_search<T, P>(lds, d, b.used, b.counts, b.keys, []() {});
     short_record(d, b.used[d.seg], fb, b.preds, b.lead_mine, nullptr);
     uint32_t run_a = fa.eq_before, run_b = fb.eq_before, both = 0;
 #pragma unroll 1
