@@ -79,7 +79,7 @@ typedef enum {
  * numel_max elements each, split into at most n_tensors_max segments (1 for whole-vector
  * use), with index sets of at most k_max positions in total per step.  Pure host arithmetic
  * (about 0.8 * numel_max + 8 * min(numel_max, 2 M; with several tensors 8 M) + (4 * n_learners_max + 16) * k_max +
- * 235 KB * n_tensors_max bytes).
+ * 170 KB * n_tensors_max + 600 KB).
  * Returns 0 if an argument is out of range (numel_max < 0 or > 2^31 - 1, n_tensors_max < 1,
  * n_learners_max outside 1 .. SCALECOM_MAX_LEARNERS, k_max < 0 or > numel_max).
  */

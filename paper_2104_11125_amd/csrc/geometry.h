@@ -81,7 +81,7 @@ struct PartDesc {         // short layouts: one block's consecutive positions of
 
 // Layouts of at most this many positions may take the short path: one vector, several tensors.
 constexpr int64_t kShortNumelFlat = 2 * 1024 * 1024, kShortNumelMax = 8 * 1024 * 1024;
-constexpr int kShortPartMax = 8192;              // positions of a part (blocks of 256, 512 or 1024 threads, four or eight positions each)
+constexpr int kShortPartMin = 1024, kShortPartMax = 8192;              // positions of a part (blocks of 256, 512 or 1024 threads, four or eight positions each)
 constexpr int kShortSegParts = 256;              // parts of one segment
 constexpr int kShortPartsMax = 1280;             // parts of a layout
 

@@ -89,12 +89,44 @@ constexpr int64_t max_chunks(int64_t numel_max, int n_tensors_max)
     return max_supertiles(numel_max, n_tensors_max) / kChunk + static_cast<int64_t>(n_tensors_max) + 1;
 }
 
+// What k_short_collect leaves of one vector (offsets): what each segment's columns start from, counts and keys per part.
+struct ShortWords {
+    size_t used, counts, keys, end;
+    int64_t numel;         // positions that the key array is made for
+    size_t words;          // and its words
+};
+
+constexpr ShortWords short_words_for(int64_t numel_max, int n_tensors_max, int64_t short_numel_max, size_t begin)
+{
+    const size_t nt = static_cast<size_t>(n_tensors_max);
+    ShortWords w{};
+    size_t o = begin;
+    auto take = [&](size_t bytes) {
+        const size_t at = o;
+        o = align_up(o + bytes, 256);
+        return at;
+    };
+    if (nt == 1 && short_numel_max > kShortNumelFlat) short_numel_max = kShortNumelFlat;
+    w.numel = numel_max < short_numel_max ? numel_max : short_numel_max;
+    w.used = take(nt * sizeof(uint4));
+    w.counts = take(static_cast<size_t>(kShortPartsMax) * kShortCols * sizeof(uint16_t));
+    // A segment's first part may begin up to 3 positions early and its last one may be partly empty.  Parts of p positions are taken only
+    // if a segment is too long for 256 parts of p / 2 or all segments together for 1280 (see short_parts).
+    for (int64_t p = kShortPartMin; p <= kShortPartMax; p *= 2) {
+        const int64_t n = static_cast<int64_t>(nt), half = p / 2;
+        if (p > kShortPartMin && w.numel + 3 <= kShortSegParts * half && n + (w.numel + 3 * n) / half <= kShortPartsMax) break;
+        const int64_t room = w.numel + n * (p + 2), most = kShortPartsMax * p;
+        w.words = static_cast<size_t>(room < most ? room : most);
+    }
+    w.keys = take(w.words * sizeof(uint32_t));
+    w.end = o;
+    return w;
+}
+
 struct WsLayout {
     size_t segs, sts, chunks, hblocks, small, preds, stats, state, wt_cnt, st_sum, st_prefix, chunk_tot, st_cand_cnt, cand, sel_mask,
-        eq_mask, tile_slot, vals, best, parts, short_used, short_counts, short_keys, diag_preds, diag_used, diag_counts,
-        diag_keys, dots, total;
-    int64_t short_numel;   // positions that the short path's key array is made for
-    size_t short_words;    // and its words
+        eq_mask, tile_slot, vals, best, parts, diag_preds, dots, total;
+    ShortWords short_path, diag_path;   // what k_short_collect leaves, of the leader's vector and of the diagnostic's sum
     // per-step counters and histograms: one zone, all zero between steps (offsets inside the zone)
     size_t zone, zone_bytes, z_overflow, z_p_used, z_full_flag, z_part, z_hist0, z_hist1, z_hist1_spec, z_hist2;
 };
@@ -151,23 +183,17 @@ constexpr WsLayout layout_for(int64_t numel_max, int n_tensors_max, int n_learne
     l.tile_slot = take(ntile * sizeof(uint32_t));
     l.vals = take(static_cast<size_t>(n_learners_max) * static_cast<size_t>(k_max) * sizeof(float));
     l.best = take(static_cast<size_t>(k_max) * sizeof(unsigned long long));       // chunk-wise selector: a word per chunk
-    // short path: the parts, what each segment's list starts from, counts and keys per part
+    // short path: the parts, and what k_short_collect leaves
     l.parts = take(kShortPartsMax * sizeof(PartDesc));
-    l.short_used = take(nt * sizeof(uint4));
-    l.short_counts = take(static_cast<size_t>(kShortPartsMax) * kShortCols * sizeof(uint16_t));
-    if (nt == 1 && short_numel_max > kShortNumelFlat) short_numel_max = kShortNumelFlat;
-    l.short_numel = numel_max < short_numel_max ? numel_max : short_numel_max;
-    // a segment's first and last part may be partly empty
-    l.short_words = static_cast<size_t>(l.short_numel) + 2 * (nt < 256 ? nt : 256) * static_cast<size_t>(kShortPartMax);
-    l.short_keys = take(l.short_words * sizeof(uint32_t));
+    l.short_path = short_words_for(numel_max, n_tensors_max, short_numel_max, o);
+    o = l.short_path.end;
     // similarity diagnostics: predictions for the leader's vector and for the sum over learners, and per learner and
-    // segment that leader's last threshold (kept like the steps' own); the short path's words for the sum; partial
-    // sums of the cosine distance
+    // segment that leader's last threshold (kept like the steps' own); the short path's words for the sum (the call's own
+    // scratch holds the sum and a mask, at most 5 bytes per position); partial sums of the cosine distance
     if (diagnostics) {
         l.diag_preds = take((2 * kPredWords + static_cast<size_t>(n_learners_max)) * nt * sizeof(uint32_t));
-        l.diag_used = take(nt * sizeof(uint4));
-        l.diag_counts = take(static_cast<size_t>(kShortPartsMax) * kShortCols * sizeof(uint16_t));
-        l.diag_keys = take(l.short_words * sizeof(uint32_t));
+        l.diag_path = short_words_for(numel_max, n_tensors_max, short_numel_max, o);
+        o = l.diag_path.end;
         l.dots = take(3 * static_cast<size_t>(kDotsBlocks) * sizeof(double));
     }
     l.total = o;
@@ -288,7 +314,7 @@ struct ShortPlan {
 ShortPlan short_parts(const WsLayout& l, int n_tensors, const int64_t* offsets)
 {
     const int64_t total = offsets[n_tensors] - offsets[0];
-    if (total > l.short_numel || (n_tensors == 1 && total > kShortNumelFlat)) return ShortPlan{};
+    if (total > l.short_path.numel || (n_tensors == 1 && total > kShortNumelFlat)) return ShortPlan{};
     for (ShortPlan p : {ShortPlan{256, 1}, ShortPlan{512, 1}, ShortPlan{1024, 1}, ShortPlan{1024, 2}}) {
         int64_t n = 0;
         bool fits = true;
@@ -299,7 +325,7 @@ ShortPlan short_parts(const WsLayout& l, int n_tensors, const int64_t* offsets)
             fits = fits && count <= kShortSegParts;
             n += count;
         }
-        if (fits && n <= kShortPartsMax && static_cast<size_t>(n * p.part()) <= l.short_words) {
+        if (fits && n <= kShortPartsMax && static_cast<size_t>(n * p.part()) <= l.short_path.words) {
             p.n_parts = static_cast<int>(n);
             return p;
         }
@@ -646,9 +672,9 @@ void launch_short_as(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learners, f
     char* ws = ctx->ws;
     const WsLayout& l = ctx->lay;
     const PartDesc* parts = reinterpret_cast<const PartDesc*>(ws + l.parts);
-    uint4* used = reinterpret_cast<uint4*>(ws + l.short_used);
-    uint16_t* counts = reinterpret_cast<uint16_t*>(ws + l.short_counts);
-    uint32_t* keys = reinterpret_cast<uint32_t*>(ws + l.short_keys);
+    uint4* used = reinterpret_cast<uint4*>(ws + l.short_path.used);
+    uint16_t* counts = reinterpret_cast<uint16_t*>(ws + l.short_path.counts);
+    uint32_t* keys = reinterpret_cast<uint32_t*>(ws + l.short_path.keys);
     unsigned long long* stats = reinterpret_cast<unsigned long long*>(ws + l.stats);
     k_short_collect<G, T, R><<<ctx->n_parts, T, 0, ctx->stream>>>(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), lr,
                                                                parts, preds, lead_mine, used, counts, keys, stats);
@@ -934,6 +960,12 @@ DiagLayout diag_layout(int64_t numel_max, int n_tensors_max)
     return d;
 }
 
+ShortVector short_vector(char* base, const ShortWords& w, uint32_t* preds, uint32_t* lead_mine)
+{
+    return ShortVector{preds, lead_mine, reinterpret_cast<uint4*>(base + w.used), reinterpret_cast<uint16_t*>(base + w.counts),
+                       reinterpret_cast<uint32_t*>(base + w.keys)};
+}
+
 template <typename G, int T, int R>
 void launch_short_overlap(scalecom_ctx* ctx, const float* memL, const G* gradL, float lr, const float* y, const ShortVector& a,
                           const ShortVector& b, int32_t* d_out)
@@ -976,10 +1008,8 @@ scalecom_status launch_hamming(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
     };
     if (is_short) {
         sum_x(0);
-        const ShortVector a{preds_a, lead_a, reinterpret_cast<uint4*>(ctx->ws + l.short_used),
-                            reinterpret_cast<uint16_t*>(ctx->ws + l.short_counts), reinterpret_cast<uint32_t*>(ctx->ws + l.short_keys)};
-        const ShortVector b{preds_b, nullptr, reinterpret_cast<uint4*>(ctx->ws + l.diag_used),
-                            reinterpret_cast<uint16_t*>(ctx->ws + l.diag_counts), reinterpret_cast<uint32_t*>(ctx->ws + l.diag_keys)};
+        const ShortVector a = short_vector(ctx->ws, l.short_path, preds_a, lead_a);
+        const ShortVector b = short_vector(ctx->ws, l.diag_path, preds_b, nullptr);
         const float* memL = lp.mem[leader];
         const G* gradL = static_cast<const G*>(lp.grad[leader]);
         if (ctx->short_threads == 256)

@@ -66,6 +66,17 @@ def test_workspace_bytes_is_host_arithmetic():
     assert binding.scalecom_workspace_bytes(10, 1, 1, 11) == 0
 
 
+def test_workspace_size_as_the_header_states_it():
+    """No more than the header's formula: the parts of a short layout are counted once, and a part that is partly empty only with
+    as many positions as a layout of that length can give it."""
+    for numel, tensors, learners in [(1_048_576, 1, 4), (25_557_032, 1, 8), (60_000, 60, 4), (2_400_000, 60, 4), (8_000_000, 1_000, 4),
+                                     (120_000_000, 200, 8), (1_000_000_000, 1, 8), (0, 1, 1)]:
+        k = numel // 100
+        short = 8 * min(numel, (2 if tensors == 1 else 8) << 20)
+        got = binding.scalecom_workspace_bytes(numel, tensors, learners, k)
+        assert 0 < got <= 0.8 * numel + short + (4 * learners + 16) * k + 170 * 1024 * tensors + 600 * 1024, (numel, tensors)
+
+
 def test_argument_checks_that_need_no_device():
     L = binding.lib()
     out = ctypes.c_void_p()

@@ -261,6 +261,25 @@ def test_hamming_distance_repeated(gu, n):
         ctx.close()
 
 
+@pytest.mark.parametrize("sizes", [[200_003], [2_097_152], [1] * 300 + [1_100_000], [700] * 1270, [60_000, 30, 2_000_001]])
+def test_scratch_of_the_diagnostic_is_enough(gu, sizes):
+    """Scratch of exactly scalecom_hamming_scratch_bytes: nothing behind them is touched, on layouts with as many and as empty parts as there can be."""
+    offsets = [0]
+    for s in sizes:
+        offsets.append(offsets[-1] + s)
+    ks, n, numel = [-(-s // 100) for s in sizes], 2, offsets[-1]
+    ctx = binding.scalecom_init(numel, n, torch.float32, len(sizes), gu.DEV, k_max=sum(ks))
+    nbytes = binding.lib().scalecom_hamming_scratch_bytes(numel, len(sizes))
+    buf = torch.full((nbytes + (1 << 20),), 0x5a, dtype=torch.uint8, device=gu.DEV)
+    ctx._diag_scratch = buf[:nbytes]
+    x = _normal(numel, 2, 1.0).to(gu.DEV)
+    mem = [torch.zeros(numel, device=gu.DEV) for _ in range(n)]
+    for step in range(3):
+        assert int(ctx.scalecom_hamming_distance(mem, [x, x], offsets, ks, 1.0, step).abs().sum()) == 0
+    assert bool((buf[nbytes:] == 0x5a).all())
+    ctx.close()
+
+
 @pytest.mark.parametrize("n,sizes", [
     (2, [2_097_152, 3, 2_097_149, 900_001, 8_192]),              # 256 parts of 8192 in one segment
     (2, [2_097_153, 1_000_000]),                                 # one more: the long path
