@@ -19,8 +19,8 @@
 //               counts)?  Then the top 24 bits of the threshold follow from the range's counts
 //               (Eq. 2; of a wide range the bin, whose open bits level 1 then resolves on the
 //               listed keys).  Otherwise (no prediction, or a miss): histogram of the top 12 key bits
-//               of the leader's vector.  A segment of one supertile is finished here by its one
-//               block, without prediction
+//               of the leader's vector.  A segment of one supertile is finished by a block of its own
+//               (k_small), without prediction
 //   level<1>    a histogram of level0 is searched by every block that needs the result; then the
 //               next 12 key bits, histogrammed over the candidate list -- nothing to do if they
 //               are known already; for segments that went through the level-0 histogram this is
@@ -608,8 +608,8 @@ void launch_select(scalecom_ctx* ctx, const float* memL, const G* gradL, float l
     k_predicted<G><<<n_st, kBlock, 0, s>>>(memL, gradL, lr, segs, sts, cand, st_cand_cnt, preds, wt_cnt, sel_mask, eq_mask,
                                            part, overflow, p_used, hist1_spec, lead_mine);
     if (fork) (void)hipStreamWaitEvent(s, ctx->join_ev, 0);
-    k_level0<G><<<hgrid, kBlock, 0, s>>>(memL, gradL, lr, segs, hblocks, states, fork, hist0, preds, p_used, part, overflow,
-                                         hist1_spec, lead_mine, wt_cnt, sel_mask, eq_mask, st_sum, stats);
+    k_level0<G><<<hgrid, kBlock, 0, s>>>(memL, gradL, lr, segs, hblocks, states, hist0, preds, p_used, part, overflow, hist1_spec,
+                                         lead_mine, stats);
     mark(1);
     const CollectOut collect_out{wt_cnt, sel_mask, eq_mask, cand, st_cand_cnt, full_flag};
     k_level<G, 1><<<hgrid, kBlock, 0, s>>>(memL, gradL, lr, segs, hblocks, state0, state1, hist0, hist1, preds, lead_mine,
@@ -1140,7 +1140,7 @@ scalecom_status scalecom_init(scalecom_ctx** out, int device, void* hip_stream, 
     if (hipHostMalloc(reinterpret_cast<void**>(&ctx->pinned), ctx->pinned_bytes, hipHostMallocDefault) != hipSuccess)
         return bail(SCALECOM_ENOMEM);
     if (hipEventCreateWithFlags(&ctx->upload_done, hipEventDisableTiming) != hipSuccess) return bail(SCALECOM_EHIP);
-    if (n_tensors_max > 1) {                // (a whole vector of one supertile is handled in the main chain)
+    if (n_tensors_max > 1) {                // (one vector of one supertile takes the short path)
         if (hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking) != hipSuccess ||
             hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming) != hipSuccess ||
             hipEventCreateWithFlags(&ctx->join_ev, hipEventDisableTiming) != hipSuccess)

@@ -216,7 +216,7 @@ k_predicted(const float* __restrict__ mem, const G* __restrict__ grad, float lr,
     const uint32_t w = clamp_width(pred[2]);                // (whatever the memory holds, the counts stay in their words)
     const uint32_t t24 = predicted_t24(pred, lead_mine, d.seg);
     const SegDesc sd = segs[d.seg];
-    if (have == 0 || sd.k == 0 || sd.st_count == 1) return;   // (one supertile: k_level0 searches it directly)
+    if (have == 0 || sd.k == 0 || sd.st_count == 1) return;   // (one supertile: k_small searches it directly)
     // the range: 2^w keys centred on the middle of the expected threshold's 128 keys, aligned to 128,
     // cut off at key 0 and at 2^31
     const uint32_t span = 1u << w;
@@ -592,11 +592,10 @@ __device__ __forceinline__ void select_one_supertile(const float* __restrict__ m
 template <typename G>
 __global__ void __launch_bounds__(kBlock)
 k_level0(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const SegDesc* __restrict__ segs,
-         const HistBlock* __restrict__ hblocks, StateCopies states, bool small_elsewhere, uint32_t* __restrict__ hist,
+         const HistBlock* __restrict__ hblocks, StateCopies states, uint32_t* __restrict__ hist,
          uint32_t* __restrict__ preds, const uint32_t* __restrict__ p_used, const uint32_t* __restrict__ part,
          const uint32_t* __restrict__ overflow, const uint32_t* __restrict__ hist1_spec, uint32_t* __restrict__ lead_mine,
-         uint32_t* __restrict__ wt_cnt, uint64_t* __restrict__ sel_mask, uint64_t* __restrict__ eq_mask,
-         uint2* __restrict__ st_sum, unsigned long long* __restrict__ stats)
+         unsigned long long* __restrict__ stats)
 {
     __shared__ uint32_t lh[kBins0];
     __shared__ uint32_t tot_s[kPartWords];
@@ -632,13 +631,7 @@ k_level0(const float* __restrict__ mem, const G* __restrict__ grad, float lr, co
         }
         return;
     }
-    if (sd.st_count == 1) {                                 // block-uniform
-        // (a context for several tensors has k_small do this beside the leader pass)
-        if (!small_elsewhere)
-            select_one_supertile(mem, grad, lr, hb, k, s, states, pred, lead_mine, wt_cnt, sel_mask, eq_mask, st_sum, lh,
-                                 tot_s, res, above);
-        return;
-    }
+    if (sd.st_count == 1) return;                           // block-uniform: k_small does it beside the leader pass
     if (t == 0) flag = 0u;
     bool hit = false;
     if (have != 0) {                                        // block-uniform: sum the slotted copies of the counters
