@@ -48,6 +48,16 @@ def assert_same(kind, got: np.ndarray, want: np.ndarray, rtol=None, what=""):
     raise AssertionError(f"{kind} {what}: within rtol={rtol} but not bit-exact (the arithmetic is meant to be pinned)")
 
 
+# More parts than a short layout may have: with so many one-element tensors behind it (no members), any layout takes the
+# long path, whatever its size.
+BALLAST = 1281
+
+
+def long_layout(offsets, ks):
+    """The tensors of a layout followed by the ballast; the learners' buffers need BALLAST more elements."""
+    return list(offsets) + [int(offsets[-1]) + i + 1 for i in range(BALLAST)], list(ks) + [0] * BALLAST
+
+
 def compare_step(ctx, mem_dev, grad_dev, mem_ref, step, beta, lr, k=None, offsets=None, ks=None, what="", chunk=None,
                  chunks=None):
     """Run one step on both sides; mem_dev / mem_ref are updated in place."""

@@ -18,10 +18,11 @@ from paper_2104_11125_amd import binding
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("chunk,layered", [(None, False), (100, False), (None, True)])
+@pytest.mark.parametrize("chunk,layered", [(None, False), (100, False), (None, True), (None, "long"), (None, "flat_long")])
 def test_graph_replay_of_single_steps(chunk, layered):
-    """layered: per-tensor index sets, with tensors of one supertile among them (their search runs
-    on the context's second stream, which the capture has to follow)."""
+    """layered: per-tensor index sets, on the short path; "long": with so many tensors that they take the long one,
+    where tensors of one supertile are searched on the context's second stream, which the capture has to follow; "flat_long": one
+    vector beyond the short path's 2 M positions."""
     import gpu_util as gu
 
     dev = gu.DEV
@@ -31,6 +32,11 @@ def test_graph_replay_of_single_steps(chunk, layered):
     offsets = np.concatenate([[0], np.cumsum(sizes)]).tolist()
     ks = [-(-sz // 100) for sz in sizes]
     assert offsets[-1] == numel
+    if layered == "flat_long":
+        layered, numel = False, 2_100_007
+    if layered == "long":
+        offsets, ks = gu.long_layout(offsets, ks)
+        numel += gu.BALLAST
     if layered:
         k = sum(ks)
     n_out = k if chunk is None else -(-numel // chunk)
@@ -41,7 +47,7 @@ def test_graph_replay_of_single_steps(chunk, layered):
         return [((shared + 0.5 * rng.standard_normal(numel)) * 1e-3).astype(np.float32) for _ in range(n)]
 
     with torch.cuda.stream(side):
-        ctx = binding.scalecom_init(numel, n, torch.float32, len(sizes) if layered else 1, dev, stream=side, k_max=n_out)
+        ctx = binding.scalecom_init(numel, n, torch.float32, len(ks) if layered else 1, dev, stream=side, k_max=n_out)
         mem = [torch.zeros(numel, device=dev) for _ in range(n)]
         grads = [torch.zeros(numel, device=dev) for _ in range(n)]
         idx = torch.zeros(n_out, dtype=torch.int32, device=dev)

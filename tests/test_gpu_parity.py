@@ -101,30 +101,54 @@ def _adversarial(numel, kind, rng):
     raise ValueError(kind)
 
 
+@pytest.mark.parametrize("route", ["short", "long"])
 @pytest.mark.parametrize("kind", ["all_equal", "two_valued", "zeros", "signed_zeros", "denormals", "few_levels",
                                   "nonfinite"])
-def test_adversarial_values(gu, kind):
+def test_adversarial_values(gu, kind, route):
+    """route: one vector of these lengths takes the short path; as a tensor among many, the long one."""
     rng = np.random.default_rng(hash(kind) % 1000)
     n = 3
     for numel in (1, 3, 255, 256, 257, 8191, 8192, 8193, 40_003):
         ks = sorted({0, 1, numel // 3, numel - 1, numel} - {-1})
-        ctx = binding.scalecom_init(numel, n, torch.float32, 1, gu.DEV)
+        length = numel + (gu.BALLAST if route == "long" else 0)
+        ctx = binding.scalecom_init(length, n, torch.float32, 1 + (gu.BALLAST if route == "long" else 0), gu.DEV)
         for k in ks:
-            grads = [_adversarial(numel, kind, rng) for _ in range(n)]
-            mems = [_adversarial(numel, kind, rng) if kind != "nonfinite" else np.zeros(numel, np.float32)
+            grads = [_adversarial(length, kind, rng) for _ in range(n)]
+            mems = [_adversarial(length, kind, rng) if kind != "nonfinite" else np.zeros(length, np.float32)
                     for _ in range(n)]
             mem = [torch.from_numpy(m.copy()).to(gu.DEV) for m in mems]
             grad = [torch.from_numpy(g).to(gu.DEV) for g in grads]
             ref = [m.copy() for m in mems]
             for step in range(2):
-                gu.compare_step(ctx, mem, grad, ref, step, 0.25, 1.0, k=k, what=f"{kind} numel={numel} k={k}")
+                if route == "long":
+                    offsets, all_ks = gu.long_layout([0, numel], [k])
+                    gu.compare_step(ctx, mem, grad, ref, step, 0.25, 1.0, offsets=offsets, ks=all_ks, what=f"{kind} numel={numel} k={k}")
+                else:
+                    gu.compare_step(ctx, mem, grad, ref, step, 0.25, 1.0, k=k, what=f"{kind} numel={numel} k={k}")
         ctx.close()
 
 
-def test_threshold_ties_across_tiles(gu):
+@pytest.mark.parametrize("kind", ["all_equal", "signed_zeros", "denormals", "few_levels", "nonfinite"])
+def test_adversarial_values_in_one_long_vector(gu, kind):
+    """The same values in one vector beyond the short path's 2 M positions."""
+    rng = np.random.default_rng(len(kind))
+    n, numel = 2, 2_097_152 + 4_097
+    ctx = binding.scalecom_init(numel, n, torch.float32, 1, gu.DEV)
+    for k in (1, numel // 3):
+        grads = [_adversarial(numel, kind, rng) for _ in range(n)]
+        mem = [torch.zeros(numel, device=gu.DEV) for _ in range(n)]
+        grad = [torch.from_numpy(g).to(gu.DEV) for g in grads]
+        ref = [np.zeros(numel, np.float32) for _ in range(n)]
+        for step in range(3):
+            gu.compare_step(ctx, mem, grad, ref, step, 0.25, 1.0, k=k, what=f"{kind} long k={k}")
+    ctx.close()
+
+
+@pytest.mark.parametrize("numel", [3 * 8192 + 777, 2_097_152 + 777])
+def test_threshold_ties_across_tiles(gu, numel):
     """The threshold value repeated in every wave tile and supertile: members among the equal
     keys are the lowest positions, wherever the tile boundaries fall."""
-    numel, n = 3 * 8192 + 777, 2
+    n = 2
     x = np.full(numel, 1.0, np.float32)
     x[::5] = 2.0                                   # above the threshold
     x[3::7] = 0.5                                  # below
@@ -160,12 +184,13 @@ def test_bucket_keys_clustered_in_one_place(gu, supertiles):
     ctx.close()
 
 
-def test_threshold_jumps_between_steps(gu):
+@pytest.mark.parametrize("numel", [300_007, 2_200_007])     # the short path and the long one
+def test_threshold_jumps_between_steps(gu, numel):
     """The library predicts each step's threshold bucket from the previous step (same context,
     same layout) to save a pass over the leader; the prediction must never change the result.
     Gradient scale and lr jump by orders of magnitude from step to step, so predictions miss,
     hit, and land just inside / outside their window."""
-    w = workloads.scaled(workloads.by_name("resnet50_sized"), 300_007, n_learners=3, steps=1)
+    w = workloads.scaled(workloads.by_name("resnet50_sized"), numel, n_learners=3, steps=1)
     ctx = binding.scalecom_init(w.numel, w.n_learners, torch.float32, 1, gu.DEV)
     mem = workloads.zero_memories(w, gu.DEV)
     ref = [m.cpu().numpy().copy() for m in mem]
@@ -178,12 +203,13 @@ def test_threshold_jumps_between_steps(gu):
     ctx.close()
 
 
-def test_selection_stats_count_misses(gu):
+@pytest.mark.parametrize("numel", [300_007, 2_200_007])     # the short path and the long one
+def test_selection_stats_count_misses(gu, numel):
     """The device counters behind scalecom_selection_stats: the first step of a layout has no
     prediction, a gradient scale that jumps by 100 is a sure miss (the widest range spans two
     binades), and a step repeated on the same inputs from the same state must hit the third time
     (the leader's own last threshold is the centre of its range).  Results are compared as ever."""
-    w = workloads.scaled(workloads.by_name("resnet50_sized"), 300_007, n_learners=3, steps=1)
+    w = workloads.scaled(workloads.by_name("resnet50_sized"), numel, n_learners=3, steps=1)
     ctx = binding.scalecom_init(w.numel, w.n_learners, torch.float32, 1, gu.DEV)
     assert ctx.scalecom_selection_stats() == {"missed": 0, "no_prediction": 0, "full_mode": 0, "wide_range": 0, "steps": 0}
     mem = workloads.zero_memories(w, gu.DEV)
@@ -215,24 +241,28 @@ def test_selection_stats_count_misses(gu):
     ctx.close()
 
 
-def test_per_layer_predictions(gu):
+@pytest.mark.parametrize("route", ["short", "long"])
+def test_per_layer_predictions(gu, route):
     """Per-tensor mode keeps one prediction per tensor; tensors' thresholds move independently."""
     w = workloads.per_layer_workload(name="per_layer_pred", n_learners=3, n_tensors=25, lo=8, hi=60_000, rate=50,
                                      steps=1, seed=78)
-    ctx = binding.scalecom_init(w.numel, w.n_learners, torch.float32, w.n_tensors, gu.DEV)
-    mem = workloads.zero_memories(w, gu.DEV)
+    offsets, ks, pad = w.offsets, w.ks, 0
+    if route == "long":
+        (offsets, ks), pad = gu.long_layout(offsets, ks), gu.BALLAST
+    ctx = binding.scalecom_init(w.numel + pad, w.n_learners, torch.float32, len(ks), gu.DEV)
+    mem = [torch.zeros(w.numel + pad, device=gu.DEV) for _ in range(w.n_learners)]
     ref = [m.cpu().numpy().copy() for m in mem]
-    base = workloads.gradients(w, 0, gu.DEV)
+    base = [torch.nn.functional.pad(b, (0, pad)) for b in workloads.gradients(w, 0, gu.DEV)]
     g = torch.Generator(device="cpu").manual_seed(3)
     for step in range(6):
         # every tensor gets its own scale factor each step
         factors = torch.exp(torch.randn(w.n_tensors, generator=g) * (0.05 if step % 2 else 2.0))
-        scale = torch.ones(w.numel)
+        scale = torch.ones(w.numel + pad)
         for t in range(w.n_tensors):
             scale[w.offsets[t]:w.offsets[t + 1]] = factors[t]
         scale = scale.to(gu.DEV)
         grad = [b * scale for b in base]
-        gu.compare_step(ctx, mem, grad, ref, step, 0.3, 0.5, offsets=w.offsets, ks=w.ks, what=f"step {step}")
+        gu.compare_step(ctx, mem, grad, ref, step, 0.3, 0.5, offsets=offsets, ks=ks, what=f"step {step}")
     ctx.close()
 
 
@@ -357,7 +387,9 @@ def _oracle_d(gu, mem, grad, offsets, ks, lr, step):
     return np.array(out, np.int32)
 
 
-@pytest.mark.parametrize("recipe,numel", [("resnet50_sized", 300_001), ("large_bf16", 150_002)])
+@pytest.mark.parametrize("recipe,numel", [("resnet50_sized", 300_001), ("large_bf16", 150_002),
+                                          ("resnet50_sized", 800_003), ("large_bf16", 1_900_001),     # parts of 4096 and 8192 positions
+                                          ("large_bf16", 2_200_002)])                                # the long path
 def test_hamming_distance_between_steps(gu, recipe, numel):
     """d between the leader's set and the true top-k, asked for between ordinary steps: exact,
     leaves the memories alone and does not disturb the steps that follow."""
@@ -379,11 +411,14 @@ def test_hamming_distance_between_steps(gu, recipe, numel):
     ctx.close()
 
 
-def test_hamming_distance_per_layer_and_extremes(gu):
+@pytest.mark.parametrize("route", ["short", "long"])
+def test_hamming_distance_per_layer_and_extremes(gu, route):
     n = 3
     sizes = [0, 1, 7, 8192, 8193, 300, 2, 0, 40_000]
     ks = [0, 1, 3, 100, 8193, 0, 1, 0, 400]
     offsets = np.concatenate([[4], 4 + np.cumsum(sizes)]).tolist()
+    if route == "long":                                        # (the calls on one vector below stay on the short path)
+        offsets, ks = gu.long_layout(offsets, ks)
     numel = offsets[-1] + 3
     g = torch.Generator(device="cpu").manual_seed(15)
     mem = [torch.randn(numel, generator=g).to(gu.DEV) for _ in range(n)]
@@ -434,8 +469,9 @@ def test_cosine_distance(gu):
 
 
 # ------------------------------------------------------------------ randomized layouts and values
+@pytest.mark.parametrize("route", ["short", "long"])
 @pytest.mark.parametrize("seed", range(32))
-def test_randomized_layouts_values_and_modes(gu, seed):
+def test_randomized_layouts_values_and_modes(gu, seed, route):
     """Seeded random problems: learner count, tensor layout (gaps, empty tensors, unaligned starts),
     set sizes from 0 to everything, value distributions with heavy ties, both gradient types, and
     exact, chunk-wise and diagnostic calls mixed on one context.  Every output is compared."""
@@ -450,6 +486,11 @@ def test_randomized_layouts_values_and_modes(gu, seed):
         pos += sz
     offsets.append(pos)                                        # tensors are back to back; a gap only in front
     numel = pos + gaps[-1]
+    ballast = 0
+    if route == "long":                                        # the exact steps and diagnostics beyond the short path
+        sizes, ballast = sizes + [1] * gu.BALLAST, gu.BALLAST
+        offsets = offsets + [pos + i + 1 for i in range(gu.BALLAST)]
+        numel, n_tensors = numel + gu.BALLAST, n_tensors + gu.BALLAST
     bf16 = bool(seed % 2)
     kind = ["normal", "rounded", "few_levels", "sparse"][seed % 4]
     def draw(scale):
@@ -467,7 +508,7 @@ def test_randomized_layouts_values_and_modes(gu, seed):
         grad = [g.to(torch.bfloat16) for g in grad]
     ref = [m.cpu().numpy().copy() for m in mem]
     ctx = binding.scalecom_init(max(numel, 1), n, torch.bfloat16 if bf16 else torch.float32, n_tensors, gu.DEV)
-    what = f"seed {seed}: n={n} sizes={sizes} kind={kind} bf16={bf16}"
+    what = f"seed {seed}: n={n} sizes={sizes[:len(sizes) - ballast]} kind={kind} bf16={bf16} {route}"
     print("[random]", what, flush=True)
     for step in range(5):
         beta = float(rng.choice([1.0, 0.5, 0.1]))
@@ -475,11 +516,11 @@ def test_randomized_layouts_values_and_modes(gu, seed):
         mode = int(rng.integers(0, 4))
         if mode == 0:                                          # per-tensor exact sets, sizes from 0 to everything
             ks = [int(rng.choice([0, 1, sz // 100, sz // 2, sz])) if sz else 0 for sz in sizes]
-            gu.compare_step(ctx, mem, grad, ref, step, beta, lr, offsets=offsets, ks=ks, what=what + f" ks={ks}")
+            gu.compare_step(ctx, mem, grad, ref, step, beta, lr, offsets=offsets, ks=ks, what=what + f" ks={ks[:12]}")
         elif mode == 1:                                        # per-tensor chunk sizes
             chunks = [int(rng.choice([1, 2, 7, 100, 112, 400, 100_000])) for _ in sizes]
             gu.compare_step(ctx, mem, grad, ref, step, beta, lr, offsets=offsets, chunks=chunks,
-                            what=what + f" chunks={chunks}")
+                            what=what + f" chunks={chunks[:12]}")
         elif mode == 2 and numel > 0:                          # the whole vector as one tensor
             k = int(rng.choice([0, 1, numel // 100, numel]))
             gu.compare_step(ctx, mem, grad, ref, step, beta, lr, k=k, what=what + f" flat k={k}")
@@ -493,8 +534,9 @@ def test_randomized_layouts_values_and_modes(gu, seed):
     ctx.close()
 
 
+@pytest.mark.parametrize("route", ["short", "long"])
 @pytest.mark.parametrize("seed", range(12))
-def test_randomized_prediction_walk(gu, seed):
+def test_randomized_prediction_walk(gu, seed, route):
     """One layout kept for many steps while the gradients' scale drifts, jumps and collapses into
     ties: the predicted single pass hits, misses and overflows, and every step stays exact."""
     rng = np.random.default_rng(2000 + seed)
@@ -504,6 +546,9 @@ def test_randomized_prediction_walk(gu, seed):
     offsets = np.concatenate([[seed % 4], (seed % 4) + np.cumsum(sizes)]).tolist()
     numel = offsets[-1] + 2
     ks = [max(1, sz // int(rng.choice([25, 100, 400]))) for sz in sizes]
+    if route == "long":
+        offsets, ks = gu.long_layout(offsets, ks)
+        numel, n_tensors = numel + gu.BALLAST, n_tensors + gu.BALLAST
     bf16 = seed % 3 == 0
     ctx = binding.scalecom_init(numel, n, torch.bfloat16 if bf16 else torch.float32, n_tensors, gu.DEV)
     mem = [torch.zeros(numel, device=gu.DEV) for _ in range(n)]
@@ -525,7 +570,7 @@ def test_randomized_prediction_walk(gu, seed):
                 g = np.sign(g) * np.float32(scale)             # two magnitudes only: the bucket overflows every list
             t = torch.from_numpy(np.ascontiguousarray(g, dtype=np.float32)).to(gu.DEV)
             grads.append(t.to(torch.bfloat16) if bf16 else t)
-        what = f"seed {seed} step {step} {move} sizes={sizes} ks={ks} bf16={bf16}"
+        what = f"seed {seed} step {step} {move} sizes={sizes} ks={ks[:8]} bf16={bf16} {route}"
         if n_tensors == 1 and offsets[0] == 0:
             gu.compare_step(ctx, mem, grads, ref, step, 0.3, 1.0, k=ks[0], what=what)
         else:
@@ -533,15 +578,19 @@ def test_randomized_prediction_walk(gu, seed):
     ctx.close()
 
 
+@pytest.mark.parametrize("route", ["short", "long"])
 @pytest.mark.parametrize("scale", [1e-44, 3e-39, 1e-30, 1.0, 1e30, 5e36])
-def test_prediction_at_the_ends_of_the_key_range(gu, scale):
+def test_prediction_at_the_ends_of_the_key_range(gu, scale, route):
     """The same scale for several steps, so that the prediction and the finely counted keys around
     the previous threshold are in use, with thresholds among the subnormals (the counted range is
     cut off at key 0, and few distinct values exist), at the smallest normal numbers and close to
     the largest finite ones."""
     rng = np.random.default_rng(77)
     numel, n, k = 50_021, 3, 500
-    ctx = binding.scalecom_init(numel, n, torch.float32, 1, gu.DEV)
+    offsets, ks = gu.long_layout([0, numel], [k]) if route == "long" else (None, None)
+    if route == "long":
+        numel += gu.BALLAST
+    ctx = binding.scalecom_init(numel, n, torch.float32, len(ks) if ks else 1, gu.DEV)
     mem = [torch.zeros(numel, device=gu.DEV) for _ in range(n)]
     ref = [np.zeros(numel, np.float32) for _ in range(n)]
     shared = rng.standard_normal(numel)
@@ -550,11 +599,12 @@ def test_prediction_at_the_ends_of_the_key_range(gu, scale):
         for i in range(n):
             g = ((shared + 0.5 * rng.standard_normal(numel)) * scale).astype(np.float32)
             grads.append(torch.from_numpy(g).to(gu.DEV))
-        gu.compare_step(ctx, mem, grads, ref, step, 0.3, 1.0, k=k, what=f"scale {scale} step {step}")
+        gu.compare_step(ctx, mem, grads, ref, step, 0.3, 1.0, k=k, offsets=offsets, ks=ks, what=f"scale {scale} step {step}")
     ctx.close()
 
 
-def test_long_run_into_the_piled_up_state(gu):
+@pytest.mark.parametrize("route", ["short", "long"])
+def test_long_run_into_the_piled_up_state(gu, route):
     """Several hundred steps from zero memory: error feedback lets the magnitudes pile up just below
     the threshold (a twelve-bit bucket around it comes to hold several per cent of all elements), the
     range of finely counted keys narrows step by step, and its counts go to several slotted copies.
@@ -565,7 +615,10 @@ def test_long_run_into_the_piled_up_state(gu):
     offsets = np.concatenate([[2], 2 + np.cumsum(sizes)]).tolist()
     numel = offsets[-1] + 1
     ks = [1_500, 1, 200, 30]
-    ctx = binding.scalecom_init(numel, n, torch.float32, len(sizes), gu.DEV)
+    if route == "long":
+        offsets, ks = gu.long_layout(offsets, ks)
+        numel += gu.BALLAST
+    ctx = binding.scalecom_init(numel, n, torch.float32, len(ks), gu.DEV)
     mem = [torch.zeros(numel, device=gu.DEV) for _ in range(n)]
     ref = [np.zeros(numel, np.float32) for _ in range(n)]
     pool = [[((rng.standard_normal(numel) + 0.5 * rng.standard_normal(numel)) * 1e-3).astype(np.float32)
@@ -609,8 +662,9 @@ def test_long_run_bf16_flat(gu):
     ctx.close()
 
 
+@pytest.mark.parametrize("route", ["short", "long"])
 @pytest.mark.parametrize("seed", range(6))
-def test_randomized_long_runs(gu, seed):
+def test_randomized_long_runs(gu, seed, route):
     """120 steps on a random layout (tensors of one and of several supertiles, any learner count,
     rate, beta, lr, gradient type): the ranges of the predicted pass adapt while the magnitudes pile
     up, and every step's index set and reduced values are compared."""
@@ -623,6 +677,9 @@ def test_randomized_long_runs(gu, seed):
     numel = offsets[-1] + int(rng.integers(0, 3))
     rate = int(rng.choice([25, 100, 400]))
     ks = [max(1, s // rate) for s in sizes]
+    if route == "long":
+        offsets, ks = gu.long_layout(offsets, ks)
+        numel, nt = numel + gu.BALLAST, nt + gu.BALLAST
     bf16 = bool(rng.integers(0, 2))
     beta = float(rng.choice([0.1, 0.3, 1.0]))
     lr = float(rng.choice([0.1, 1.0]))
@@ -638,7 +695,7 @@ def test_randomized_long_runs(gu, seed):
             gs.append(g.to(torch.bfloat16) if bf16 else g)
         pool_dev.append(gs)
     pool = [[gu.to_host(g) for g in gs] for gs in pool_dev]
-    what = f"seed {seed} sizes={sizes} ks={ks} n={n} bf16={bf16} beta={beta} lr={lr}"
+    what = f"seed {seed} sizes={sizes} ks={ks[:8]} n={n} bf16={bf16} beta={beta} lr={lr} {route}"
     for step in range(120):
         idx, red = ctx.scalecom_step_layers(mem, pool_dev[step % 4], offsets, ks, beta, lr, step)
         want_idx, want_red = oracle.step_layers(ref, pool[step % 4], offsets, ks, beta, lr, step)
@@ -649,8 +706,9 @@ def test_randomized_long_runs(gu, seed):
     ctx.close()
 
 
+@pytest.mark.parametrize("route", ["short", "long"])
 @pytest.mark.parametrize("spread", [0.1, 0.9, 30.0])
-def test_learners_whose_gradients_differ_in_scale(gu, spread):
+def test_learners_whose_gradients_differ_in_scale(gu, spread, route):
     """Learners on differently distributed data: learner i's gradients are scaled by a factor of its
     own (up to 1 + spread), so the leaders' thresholds differ from step to step by as much, and a
     prediction has to follow each leader's own history.  Tensors of one and of several supertiles;
@@ -661,7 +719,10 @@ def test_learners_whose_gradients_differ_in_scale(gu, spread):
     offsets = np.concatenate([[1], 1 + np.cumsum(sizes)]).tolist()
     numel = offsets[-1]
     ks = [1_200, 50, 300]
-    ctx = binding.scalecom_init(numel, n, torch.float32, len(sizes), gu.DEV)
+    if route == "long":
+        offsets, ks = gu.long_layout(offsets, ks)
+        numel += gu.BALLAST
+    ctx = binding.scalecom_init(numel, n, torch.float32, len(ks), gu.DEV)
     mem = [torch.zeros(numel, device=gu.DEV) for _ in range(n)]
     ref = [np.zeros(numel, np.float32) for _ in range(n)]
     scale = [1.0 + spread * i / (n - 1) for i in range(n)]
@@ -680,8 +741,9 @@ def test_learners_whose_gradients_differ_in_scale(gu, spread):
     ctx.close()
 
 
+@pytest.mark.parametrize("route", ["short", "long"])
 @pytest.mark.parametrize("sigma", [0.05, 0.3])
-def test_gradient_norm_that_changes_from_step_to_step(gu, sigma):
+def test_gradient_norm_that_changes_from_step_to_step(gu, sigma, route):
     """Every step's gradients carry a random common factor (log-normal, applied through lr), as the
     gradient norm of a minibatch does: while the memories are small the threshold follows it, so
     the range of finely counted keys grows beyond one twelve-bit bucket (coarser counts, the open
@@ -692,7 +754,10 @@ def test_gradient_norm_that_changes_from_step_to_step(gu, sigma):
     offsets = np.concatenate([[3], 3 + np.cumsum(sizes)]).tolist()
     numel = offsets[-1] + 2
     ks = [500, 200, 60, 2_800]
-    ctx = binding.scalecom_init(numel, n, torch.float32, len(sizes), gu.DEV)
+    if route == "long":
+        offsets, ks = gu.long_layout(offsets, ks)
+        numel += gu.BALLAST
+    ctx = binding.scalecom_init(numel, n, torch.float32, len(ks), gu.DEV)
     mem = [torch.zeros(numel, device=gu.DEV) for _ in range(n)]
     ref = [np.zeros(numel, np.float32) for _ in range(n)]
     pool = [[((rng.standard_normal(numel) + 0.5 * rng.standard_normal(numel)) * 1e-3).astype(np.float32)

@@ -64,6 +64,26 @@ def test_segments_anywhere(gu):
         ctx.close()
 
 
+@pytest.mark.parametrize("n,sizes,dtype", [
+    (2, [220_001] * 5, torch.float32), (5, [219_999] * 5, torch.bfloat16),          # more than 1024 parts of 1024 positions
+    (2, [400_001] * 6, torch.float32), (3, [399_998] * 6, torch.bfloat16),          # more than 512 parts of 2048
+])
+def test_many_parts(gu, n, sizes, dtype):
+    """So many blocks that the step is launched with registers for six waves per SIMD."""
+    offsets = [2]
+    for s in sizes:
+        offsets.append(offsets[-1] + s)
+    ks, numel = [s // 100 for s in sizes], offsets[-1]
+    ctx = binding.scalecom_init(numel, n, dtype, len(ks), gu.DEV, k_max=sum(ks))
+    mem = [_normal(numel, 31 * i + n, 2e-4).to(gu.DEV) for i in range(n)]
+    ref = [m.cpu().numpy().copy() for m in mem]
+    for step in range(3):
+        grad = [_normal(numel, 500 + 50 * step + i).to(gu.DEV).to(dtype) for i in range(n)]
+        print(f"[short] many parts n={n} numel={numel} step={step}", flush=True)
+        gu.compare_step(ctx, mem, grad, ref, step, 0.5, 0.25, offsets=offsets, ks=ks, what=f"many parts n={n}")
+    ctx.close()
+
+
 @pytest.mark.parametrize("kind", ["equal", "half_zero", "two_values", "dense", "jumps"])
 def test_columns_of_any_size(gu, kind):
     """More keys in the threshold's column than one thread each can rank (256), than one wave can search
@@ -196,6 +216,41 @@ def test_chunks_in_one_launch(gu, chunk):
         ctx.close()
 
 
+@pytest.mark.parametrize("chunk", [4, 5, 25, 63, 84, 100, 112, 126, 127, 155, 170, 254, 255, 450, 509, 510, 1000, 1022])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_winners_first(gu, chunk, dtype):
+    """Eight learners of 4 M positions are too much for one launch: the winners first, in groups of one tile (chunk 4 to 84),
+    two (100, 155) and four (112 to 127), blocks of the update with up to 257 chunks, and maxima by atomics (lanes idle, or few
+    chunks per group); equal magnitudes inside chunks, whole vector and tensors at odd starts."""
+    n, numel = 8, 4_000_003
+    gen = torch.Generator(device=gu.DEV).manual_seed(chunk)
+    mem = [torch.round(torch.randn(numel, device=gu.DEV, generator=gen) * 4) for _ in range(n)]
+    ref = [m.cpu().numpy().copy() for m in mem]
+    offsets = [3, 3 + 70_001, 3 + 70_001, 70_005, 2_000_000, numel - 2]
+    chunks = [chunk] * (len(offsets) - 1)
+    ctx = binding.scalecom_init(numel, n, dtype, len(chunks), gu.DEV)
+    for step in range(2):
+        grad = [torch.round(torch.randn(numel, device=gu.DEV, generator=gen) * 8).to(dtype) for _ in range(n)]
+        print(f"[chunk] winners first chunk={chunk} {dtype} step={step}", flush=True)
+        if step == 0:
+            gu.compare_step(ctx, mem, grad, ref, 3, 0.25, 0.5, chunk=chunk, what=f"winners chunk={chunk}")
+        else:
+            gu.compare_step(ctx, mem, grad, ref, 6, 0.25, 0.5, offsets=offsets, chunks=chunks, what=f"winners per tensor chunk={chunk}")
+    ctx.close()
+
+
+@pytest.mark.parametrize("n,numel,chunk", [(2, 400_003, 1000), (8, 300_001, 600), (4, 500_001, 900), (64, 20_001, 25), (33, 9_001, 500)])
+def test_chunks_with_little_data(gu, n, numel, chunk):
+    """Little data: winners first in groups of few chunks too, and one launch with many learners."""
+    ctx = binding.scalecom_init(numel, n, torch.float32, 1, gu.DEV)
+    mem = [_normal(numel, 3 * i, 1.0).to(gu.DEV) for i in range(n)]
+    ref = [m.cpu().numpy().copy() for m in mem]
+    for step in range(2):
+        grad = [_normal(numel, 90 * step + i, 1.0).to(gu.DEV) for i in range(n)]
+        gu.compare_step(ctx, mem, grad, ref, step + n - 1, 0.5, 0.5, chunk=chunk, what=f"chunk={chunk} n={n}")
+    ctx.close()
+
+
 def test_chunks_per_layer_in_one_launch(gu):
     """Chunk sizes that differ from tensor to tensor, tensors shorter than a chunk, at starts that are no
     multiple of four; elements outside the tensors keep their bits."""
@@ -231,13 +286,16 @@ def test_cosine_distance_at_any_alignment(gu, numel):
     ctx.close()
 
 
-@pytest.mark.parametrize("n", [1, 2, 16, 17])
+@pytest.mark.parametrize("n", [1, 2, 16, 17, 64])
 def test_hamming_distance_repeated(gu, n):
     """The diagnostic keeps thresholds of its own: called again and again between steps, with gradients whose
     scale jumps, on a flat vector and on tensors at odd starts, with more learners than a block has waves."""
     import oracle
     layouts = [([0, 50_001], [500]), ([3, 20_000, 20_000, 20_007, 61_003], [200, 0, 7, 410])]
-    if n == 2:                                                  # too long for the short path
+    if n == 64:                                                 # a block of the sum takes 64 KB of LDS
+        layouts = [([0, 9_001], [90])]
+    if n == 2:                                                  # parts of 8192 positions; too long for the short path
+        layouts += [([5, 1_100_005, 1_105_006, 1_800_003], [11_000, 50, 7_000])]
         layouts += [([0, 2_200_003], [22_000]), ([1, 2_300_000, 4_300_001, 4_300_300], [23_000, 5_000, 3])]
     for offsets, ks in layouts:
         numel = offsets[-1] + 2
