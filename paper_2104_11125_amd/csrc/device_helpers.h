@@ -145,11 +145,13 @@ __device__ __forceinline__ float4 accumulate4(const float4& m, const float4& g, 
 }
 
 // The leader's (mem, grad) at the 4 positions of this lane (zeros where outside the segment).
-template <typename G>
+// TOGETHER: one branch for both, so that they are in flight together, at the price of the guarded code twice; for kernels
+// that wait for little else.
+template <bool TOGETHER = false, typename G>
 __device__ __forceinline__ void leader_load(const float* mem, const G* grad, int64_t p0, int64_t begin, int64_t end,
                                             float4& m, float4& g)
 {
-    if (p0 >= begin && p0 + 3 < end) {                      // (one branch for both: they are in flight together)
+    if (TOGETHER && p0 >= begin && p0 + 3 < end) {
         m = load4(mem + p0);
         g = load4(grad + p0);
         return;
@@ -157,8 +159,9 @@ __device__ __forceinline__ void leader_load(const float* mem, const G* grad, int
     m = make_float4(0, 0, 0, 0);
     g = m;
     if (p0 >= end || p0 + 3 < begin) return;
-    m = load_guarded(mem, p0, begin, end, false);
-    g = load_guarded(grad, p0, begin, end, false);
+    const bool full = !TOGETHER && p0 >= begin && p0 + 3 < end;
+    m = load_guarded(mem, p0, begin, end, full);
+    g = load_guarded(grad, p0, begin, end, full);
 }
 
 // Magnitude keys of x = fma(lr, grad, mem) (Alg. 1 line 6) for those 4 positions; ok[c] tells
@@ -175,12 +178,12 @@ __device__ __forceinline__ void keys_from(const float4& m, const float4& g, floa
     for (int c = 0; c < 4; ++c) ok[c] = (p0 + c >= begin) && (p0 + c < end);
 }
 
-template <typename G>
+template <bool TOGETHER = false, typename G>
 __device__ __forceinline__ void leader_keys(const float* mem, const G* grad, float lr, int64_t p0, int64_t begin,
                                             int64_t end, uint32_t key[4], bool ok[4])
 {
     float4 m, g;
-    leader_load(mem, grad, p0, begin, end, m, g);
+    leader_load<TOGETHER>(mem, grad, p0, begin, end, m, g);
     keys_from(m, g, lr, p0, begin, end, key, ok);
 }
 
@@ -199,8 +202,12 @@ __device__ __forceinline__ uint32_t predicted_t24(uint32_t last, uint32_t growth
 
 __device__ __forceinline__ uint32_t predicted_t24(const uint32_t* pred, const uint32_t* lead_mine, int seg)
 {
-    const uint32_t mine = lead_mine ? lead_mine[seg] : 0u;
-    return predicted_t24(pred[1], mine != 0u ? pred[4] : 0u, mine);
+    uint32_t t24 = pred[1];
+    if (lead_mine) {                                        // (the growth only where it is needed)
+        const uint32_t mine = lead_mine[seg];
+        if (mine != 0u) t24 = predicted_t24(t24, pred[4], mine);
+    }
+    return t24;
 }
 
 // Records the threshold a step found (by one thread, for the next steps' predictions).

@@ -181,7 +181,7 @@ __device__ __forceinline__ uint32_t short_sample(const float* __restrict__ mem, 
     if (g < groups) {
         uint32_t key[4];
         bool ok[4];
-        leader_keys(mem, grad, lr, first + g * kVec, begin, end, key, ok);
+        leader_keys<true>(mem, grad, lr, first + g * kVec, begin, end, key, ok);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             if (!ok[c]) continue;
@@ -205,7 +205,7 @@ __device__ __forceinline__ uint32_t short_sample(const float* __restrict__ mem, 
 // Is the expectation far off?  Every wave looks at the same 16 groups of four positions, one in each of 16 equal stretches of the
 // segment (at equal distances they would share a memory channel), so all waves of all blocks come to the same answer without a word
 // between them.  Far off: many more of the 64 keys above the near columns than the index set's share, or hardly any down to the
-// end of column kShortBulk, where the last step had `below`.  m, g: every group in four lanes.  Costs 0.2 us a step.
+// end of column kShortBulk, where the last step had `below`.  m, g: every group in four lanes.  Costs 0.3 us a step.
 constexpr int kShortCheckGroups = 16, kShortCheckParts = 32;  // (segments of few parts do without: a long column is read by few blocks)
 
 __device__ __forceinline__ bool short_far_off(const float4& m, const float4& g, float lr, const PartDesc& d, const ShortCols& cols,
@@ -257,7 +257,7 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
     const float4 sm = cached4(s_mem), sg = cached4(s_grad);
     float4 m[R], g[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) leader_load(mem, grad, static_cast<int64_t>(d.a0) + (r * T + t) * kVec, begin, end, m[r], g[r]);
+    for (int r = 0; r < R; ++r) leader_load<true>(mem, grad, static_cast<int64_t>(d.a0) + (r * T + t) * kVec, begin, end, m[r], g[r]);
     // the prediction's words in one access (a trip for each of them took as long as the part's loads)
     static_assert(kPredWords == 8 && kPredShortWidth == 5 && kPredShortCalm == 6 && kPredShortTrust == 7, "two groups of four");
     const uint4* pred = reinterpret_cast<const uint4*>(preds + static_cast<size_t>(d.seg) * kPredWords);
@@ -857,7 +857,7 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
     const uint32_t k = static_cast<uint32_t>(d.k);
     float4 lm, lg;
     const ShortFound f = short_search<T, P>(lds, d, used, counts, keys, [&]() {
-        leader_load(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), static_cast<int64_t>(d.a0) + t * kVec, begin, end, lm, lg);
+        leader_load<true>(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), static_cast<int64_t>(d.a0) + t * kVec, begin, end, lm, lg);
     });
     short_record(d, used[d.seg], f, preds, lead_mine, stats);
     const uint32_t T_key = f.T_key, q = f.q;
@@ -906,7 +906,7 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
             eq_rank += eq[c] ? 1u : 0u;
         }
         if (r + 1 < R)                                      // the next row's, while this one is updated
-            leader_load(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), p0 + T * kVec, begin, end, lm, lg);
+            leader_load<true>(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), p0 + T * kVec, begin, end, lm, lg);
         if (p0 >= end || p0 + 3 < begin) continue;          // none of the four positions (no barrier until the next row)
         const bool full = p0 >= begin && p0 + 3 < end;
         float4 sum = make_float4(0, 0, 0, 0);
@@ -983,8 +983,8 @@ k_short_overlap(const float* __restrict__ mem, const G* __restrict__ grad, float
         const int64_t p0 = static_cast<int64_t>(d.a0) + (r * T + t) * kVec;
         uint32_t ka[4], kb[4];
         bool ok[4];
-        leader_keys(mem, grad, lr, p0, begin, end, ka, ok);
-        leader_keys(sum, static_cast<const NoGrad*>(nullptr), 0.0f, p0, begin, end, kb, ok);
+        leader_keys<true>(mem, grad, lr, p0, begin, end, ka, ok);
+        leader_keys<true>(sum, static_cast<const NoGrad*>(nullptr), 0.0f, p0, begin, end, kb, ok);
         uint32_t rank_a = run_a, rank_b = run_b, n_a = 0, n_b = 0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
