@@ -267,17 +267,21 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
     const uint32_t trust = pred_hi.w & 0xffffffu;
     uint32_t have = width == 0u ? kShortNone : (ShortTrust(trust).sampling() ? kShortDoubted : kShortExpected);
     if (t < kShortCols) cnt[t] = mixed[t] = 0u;
-    if (have == kShortExpected) {                           // block-uniform
-        mid = (predicted_t24(pred_lo.y, pred_hi.x, lead) << kBits2) | (kBins2 / 2);
+    uint32_t note = pred_hi.z;                              // calm steps; if the expectation is not used, its top 24 bits and width
+    if (width != 0u) {                                      // block-uniform
+        const uint32_t t24 = predicted_t24(pred_lo.y, pred_hi.x, lead);
+        mid = (t24 << kBits2) | (kBins2 / 2);
         width = width < kShortWidthMin ? kShortWidthMin : (width > kShortWidthMax ? kShortWidthMax : width);
-        if (check && short_far_off(sm, sg, lr, d, ShortCols(mid, width), pred_hi.w >> 24)) have = kShortDoubted;   // in all blocks
+        if (have == kShortExpected && check && short_far_off(sm, sg, lr, d, ShortCols(mid, width), pred_hi.w >> 24))
+            have = kShortDoubted;                           // in all blocks
+        if (have == kShortDoubted) note = t24 | width << 24;
     }
     if (have != kShortExpected) {
         width = kShortWidthFirst;
         mid = d.k > 0 ? short_sample<G, T>(mem, grad, lr, d, stage, wave_tot, res) : 0u;
     }
     if (blockIdx.x == static_cast<uint32_t>(d.part_first) && t == 0)
-        used[d.seg] = make_uint4(mid, width, have | trust << 2, pred_hi.z);
+        used[d.seg] = make_uint4(mid, width, have | trust << 2, note);
     if (stats && blockIdx.x == 0 && t == 0) atomicAdd(&stats[kStatSteps], 1ull);
 
     const ShortCols cols(mid, width);
@@ -793,9 +797,11 @@ __device__ __forceinline__ void short_record(const PartDesc& d, const uint4& u, 
     uint32_t* pred = preds + static_cast<size_t>(d.seg) * kPredWords;
     const uint32_t have = u.z & 3u;
     bool held = !f.missed;
-    if (have == kShortDoubted) {                             // would the expectation have held?
-        const ShortCols cols((predicted_t24(pred, lead_mine, d.seg) << kBits2) | (kBins2 / 2), kShortWidthFirst);
-        held = f.T_key < cols.end(1) && f.T_key >= cols.end(kShortBulk - 1);
+    uint32_t learned = u.y;                                 // width to go on from
+    if (have == kShortDoubted) {                            // would it have been in or next to the narrow columns, with their width?
+        learned = u.w >> 24;
+        const ShortCols cols(((u.w & 0xffffffu) << kBits2) | (kBins2 / 2), learned);
+        held = f.T_key < cols.end(kShortAbove - 1) + cols.span() && f.T_key >= cols.end(kShortBelow + 3);
     }
     pred[kPredShortTrust] = ShortTrust(u.z >> 2).next(held, f.n_scan > kShortLong && have == kShortExpected) |
                             static_cast<uint32_t>(64.0f * static_cast<float>(f.n_near) / static_cast<float>(f.n_valid)) << 24;
@@ -807,9 +813,12 @@ __device__ __forceinline__ void short_record(const PartDesc& d, const uint4& u, 
     want = want > k / 4u ? want : k / 4u;
     want = want > 64u ? want : 64u;
     const bool middle = col >= kShortFirstBin + kShortBins / 4 && col < kShortBelow - kShortBins / 4;
-    uint32_t width = u.y, calm = middle ? u.w + 1u : 0u;
+    uint32_t width = learned, calm = middle ? u.w + 1u : 0u;
     const uint32_t crowd = f.n_scan > f.n_same ? f.n_scan - f.n_same : 0u;
-    if (middle && crowd > kShortColumnMax) {
+    if (have == kShortDoubted) {                            // (the columns were the sample's)
+        width += held ? 0u : 1u;
+        calm = 0u;
+    } else if (middle && crowd > kShortColumnMax) {
         uint32_t less = 32u - static_cast<uint32_t>(__clz(static_cast<int>(crowd / kShortColumnMax)));
         less = less < 4u ? less : 4u;
         width = width > less + kShortWidthMin ? width - less : kShortWidthMin;
