@@ -26,7 +26,8 @@ per `rate` consecutive elements) instead of the exact top-k.
 
 Prints ONE JSON line.  `value` is gradient elements per second (n_learners * numel / step
 time).  `roofline` is for the dominant kernel (the all-learner pass k_update, or the one in its
-place: k_update_chunks with chunk-wise selection, k_short_step on the short tiny configuration), timed with HIP
+place: k_update_chunks or k_chunk_step with chunk-wise selection, k_short_step on the short tiny configuration, whose
+k_update_avg_ms is that kernel's time), timed with HIP
 events recorded by the library on its own stream inside the timed region.  `cpu_baseline` is
 the single-threaded CPU oracle on a bounded sample of the same workload.
 """

@@ -277,7 +277,8 @@ scalecom_status scalecom_layer_ks(int n_tensors, const double* flops_per_gradien
  *   counts_out [host] uint64[SCALECOM_N_STATS]:
  *     [SCALECOM_STAT_MISSED]        the threshold fell outside the expected range: two more passes
  *                                   over the leader's vector in that step (on short layouts, up to
- *                                   2 M elements or 8 M in several tensors: a longer search)
+ *                                   2 M elements or 8 M in several tensors: a longer search, or
+ *                                   a sample in the expectation's place)
  *     [SCALECOM_STAT_NO_PREDICTION] nothing was expected yet (first step of a layout): same cost
  *     [SCALECOM_STAT_FULL_MODE]     so many equal or clustered magnitudes at the threshold that the
  *                                   last two search levels were passes over the leader's vector too
@@ -306,6 +307,9 @@ scalecom_status scalecom_selection_stats(scalecom_ctx* ctx, uint64_t* counts_out
  *   2  per-tile member counts, prefix sums, output slot of every tile, ties resolved
  *   3  all-learner pass: accumulate, low-pass memory update, members' values staged (Eq. 3, 5)
  *   4  sum of the staged values over learners (Alg. 1 line 10)
+ * A step on a short layout (up to 2 M elements, or 8 M in several tensors with small ones among them) has two kernels: phase 0 is the first,
+ * phases 1, 2 and 4 hold none, phase 3 is the second (search, all-learner pass and sum).  The chunk-wise step in one launch
+ * is all phase 3; otherwise phase 0 of a chunk-wise step finds the winners, phase 1 holds no kernel and phase 2 one or none.
  *
  * scalecom_timing_begin: of the following calls of scalecom_step* on this context, every
  * `every`-th (the first, the (every + 1)-th, ...; every >= 1) records phase boundaries, until

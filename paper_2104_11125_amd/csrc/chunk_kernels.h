@@ -150,7 +150,7 @@ k_chunk_step(const LearnerPtrs lp, int n_learners, int leader, float lr, float b
 // the same groups as above), straight to idx_out; no atomics in memory and nothing to clear.  Bound by the vector ALU
 // before memory, so the reduction is left to LDS: a maximum per chunk, then the lowest position among the holders (one
 // atomic per lane and run each, in words of the wave's own).  A reduction inside the ALU per chunk took 43 us at
-// 25.6 M elements and chunk 112, and 52 us at 19.6 M with chunks of 25, 50 and 400; a scan over the lanes 41 and 39.
+// 25.6 M elements and chunk 112, and 52 us at 20.6 M with chunks of 25, 50 and 400; a scan over the lanes 41 and 39.
 constexpr int kChunkGroupMax = 256;              // chunks of a group at most (1021 positions, chunks of 4)
 
 template <typename G, int Q>
