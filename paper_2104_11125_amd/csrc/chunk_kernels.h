@@ -6,6 +6,7 @@
 
 #include "device_helpers.h"
 #include "geometry.h"
+#include "update_kernels.h"
 
 namespace {
 
@@ -237,12 +238,11 @@ k_chunk_winners(const float* __restrict__ mem, const G* __restrict__ grad, float
 template <typename G>
 __global__ void __launch_bounds__(kBlock)
 k_update_chunks(LearnerPtrs lp, float lr, float beta, float one_minus_beta, const StDesc* __restrict__ sts, int n_st,
-                const int32_t* __restrict__ idx, float* __restrict__ vals, int64_t k_total, int learner0)
+                const int32_t* __restrict__ idx, float* __restrict__ vals, int64_t k_total)
 {
-    const int learner = learner0 + blockIdx.x;
-    const int group = blockIdx.y + blockIdx.z * gridDim.y;
+    const int learner = blockIdx.y;
+    const int group = update_group(n_st);
     const int st = group / kUpdateBlocksPerSuper;
-    if (st >= n_st) return;                                 // padding of the 3-d grid (whole block)
     const StDesc d = sts[st];
     const uint32_t begin = static_cast<uint32_t>(d.begin), end = static_cast<uint32_t>(d.end);
     const uint32_t blk0 = static_cast<uint32_t>(d.a0) + static_cast<uint32_t>(group % kUpdateBlocksPerSuper) * kWaves * kWaveTile;

@@ -33,13 +33,13 @@
 //               takes levels 1, 2 and this step as full leader passes instead of the list)
 //   scan, slots prefix sums of the counts over tiles: first output slot of every wave tile;
 //               keys equal to T become members in position order until q are taken
-//   update      every learner (eight per launch), one (learner, 1024 positions) pair per block: one read of
+//   update      every learner, one (learner, 1024 positions) pair per block: one read of
 //               (mem, grad), one write of mem (Eq. 5); members also store x_i into a small
 //               [learner][slot] staging array and learner 0 writes the index (Eq. 3)
 //   reduce      reduced[t] = x_0[t] + x_1[t] + ... in learner order  (Alg. 1 line 10)
 //
 // In the steady state (predictions hold) the leader's vector is read exactly once before the
-// all-learner pass, and 8 kernels make a step (up to 8 learners and 84 M elements).  No kernel reads what another block of the same
+// all-learner pass, and 8 kernels make a step (up to 84 M elements).  No kernel reads what another block of the same
 // launch wrote, so there are no fences or waits between blocks.  The prediction only decides how much work is
 // done, never what is selected.  The output is ascending by position and deterministic.
 // Nothing here is a dense contraction, so there is no MFMA; the kernels are bound by HBM traffic
@@ -528,15 +528,9 @@ void launch_update_reduce(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learne
     const uint64_t* sel_mask = reinterpret_cast<const uint64_t*>(ws + l.sel_mask);
     const uint32_t* tile_slot = reinterpret_cast<const uint32_t*>(ws + l.tile_slot);
     float* vals = reinterpret_cast<float*>(ws + l.vals);
-    // groups of 4 wave tiles over grid y and z (y is limited to 65535); surplus groups find no supertile
-    const int64_t groups = static_cast<int64_t>(n_st) * kUpdateBlocksPerSuper;
-    const unsigned gz = static_cast<unsigned>((groups + 65534) / 65535);
-    const unsigned gy = static_cast<unsigned>((groups + gz - 1) / gz);
-    for (int l0 = 0; l0 < n_learners; l0 += kUpdateLearnersPerLaunch) {
-        const int nl = std::min(kUpdateLearnersPerLaunch, n_learners - l0);
-        k_update<G><<<dim3(nl, gy, gz), kBlock, 0, s>>>(lp, lr, beta, 1.0f - beta, sts, n_st, sel_mask, tile_slot, vals,
-                                                       k_total, idx_out, l0, clear_from, l0 == 0 ? clear_words : 0);
-    }
+    k_update<G><<<dim3(static_cast<unsigned>(n_st) * kUpdateBlocksPerSuper, n_learners), kBlock, 0, s>>>(
+        lp, lr, beta, 1.0f - beta, sts, n_st, sel_mask, tile_slot, vals, k_total, idx_out, clear_from,
+        clear_words);
     mark(4);
     if (k_total > 0)
         k_reduce<<<static_cast<unsigned>((k_total + kBlock - 1) / kBlock), kBlock, 0, s>>>(vals, n_learners, k_total,
@@ -746,8 +740,7 @@ scalecom_status launch_step(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_lear
 }
 
 // Is the whole chunk-wise step in one launch the faster way?  It reads the leader once instead of twice and saves two
-// launches and, beyond eight learners, one per further eight, but moves everything at a rate that falls with the idle lanes of its
-// tiles: 5.0 to 5.2 TB/s where 88 to 98 % of one tile are in use (chunks of 25, 84, 112), 4.6 to 5.1 with two (100, 155), 4.5 to 4.9 at 78 %
+// launches, but moves everything at a rate that falls with the idle lanes of its tiles: 5.0 to 5.2 TB/s where 88 to 98 % of one tile are in use (chunks of 25, 84, 112), 4.6 to 5.1 with two (100, 155), 4.5 to 4.9 at 78 %
 // (200, 400), 3.9 at 66 % (170, 340), 3.0 at 50 % (255), against 6.5 of the all-learner pass.  One launch against the best of the others, us:
 // 3 x 30 M elements, chunk 25 208 against 226, 155 235 / 225, 200 224 / 223, 255 363 / 221; 4 x 11.4 M, 112 105 / 113, 155 112 / 112;
 // 6 x 5.1 M, 25 87 / 78; 8 x 3.3 M, 25 73 / 65; 8 x 1 M, 25 23 / 25, 200 25 / 27, 255 35 / 27; 2 x 100 M, 155 460 / 526, 170 615 / 515;
@@ -758,8 +751,7 @@ bool chunks_in_one_launch(const ChunkPlan& plan, int n_learners, int64_t numel, 
     const double rate = plan.tiles == 1 ? std::min(5.1, 5.9 * plan.use) : std::min(4.8, 5.7 * plan.use);
     const double all = static_cast<double>(n_learners) * static_cast<double>(numel) * (8 + grad_bytes);
     const double leader = static_cast<double>(numel) * (4 + grad_bytes);
-    const int more_launches = (n_learners - 1) / kUpdateLearnersPerLaunch;
-    return all * (1.0 / rate - 1.0 / 6.5) * 1e-6 < leader / 4.8 * 1e-6 + 7.0 + 3.0 * more_launches;
+    return all * (1.0 / rate - 1.0 / 6.5) * 1e-6 < leader / 4.8 * 1e-6 + 7.0;
 }
 
 // If not, are the winners first, in groups of up to `tiles_max` tiles, faster than the maxima by atomics (one launch more)?  With less
@@ -833,14 +825,8 @@ scalecom_status launch_chunked(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
         mark(2);
         mark(3);
         float* vals = reinterpret_cast<float*>(ws + l.vals);
-        const int64_t blocks = static_cast<int64_t>(ctx->n_st) * kUpdateBlocksPerSuper;
-        const unsigned gz = static_cast<unsigned>((blocks + 65534) / 65535);
-        const unsigned gy = static_cast<unsigned>((blocks + gz - 1) / gz);
-        for (int l0 = 0; l0 < n_learners; l0 += kUpdateLearnersPerLaunch) {
-            const int nl = std::min(kUpdateLearnersPerLaunch, n_learners - l0);
-            k_update_chunks<G><<<dim3(nl, gy, gz), kBlock, 0, s>>>(lp, lr, beta, 1.0f - beta, sts, ctx->n_st, idx_out, vals,
-                                                                  k_total, l0);
-        }
+        k_update_chunks<G><<<dim3(static_cast<unsigned>(ctx->n_st) * kUpdateBlocksPerSuper, n_learners), kBlock, 0, s>>>(
+            lp, lr, beta, 1.0f - beta, sts, ctx->n_st, idx_out, vals, k_total);
         mark(4);
         k_reduce<<<static_cast<unsigned>((k_total + kBlock - 1) / kBlock), kBlock, 0, s>>>(vals, n_learners, k_total, red_out);
         mark(5);

@@ -9,8 +9,22 @@
 
 namespace {
 
-// The all-learner pass, one (learner, 4 wave tiles) pair per block and consecutive blocks on
-// consecutive learners: accumulate (Alg. 1 line 6), low-pass memory update with the residual
+// The group of 4 wave tiles that a block of the all-learner pass works on; grid = (groups, learners).  One learner after the
+// other, and of each learner an eighth of the vector on each XCD (blocks go to the XCDs in turn): every XCD streams two
+// arrays at a time, and its eighth of the masks stays in its L2.  With the learners side by side instead, eight to a
+// launch, only eight of them (one per XCD) reached the same rate: 2 reads and 1 write as a bare kernel, float, TB/s, side by
+// side / this order: 25.6 M x 8 6.61 / 6.61, x 7 6.35 / 6.60, x 3 6.41 / 6.55, 110 M x 6 5.50 / 6.13, x 3 6.19 / 6.56.  Neighbouring groups
+// on neighbouring XCDs: 6.35 to 6.40 there, and bfloat16 no difference; whole steps, us, side by side / neighbouring / this order:
+// 6 x 14 M 233 / 212 / 210, 16 x 2.5 M 116 / 114 / 110, 2 x 4 M 52 / 51 / 50, 8 x 10 M bfloat16 169 / 170 / 166, 8 x 3.5 M 88 / 88 / 86, 8 x 25.6 M
+// 448 / 450 / 450.
+static_assert(kUpdateBlocksPerSuper == kXcds, "the groups divide evenly");
+__device__ __forceinline__ int update_group(int n_st)
+{
+    return static_cast<int>((blockIdx.x % kXcds) * static_cast<uint32_t>(n_st) + blockIdx.x / kXcds);
+}
+
+// The all-learner pass, one (learner, 4 wave tiles) pair per block: accumulate (Alg. 1 line 6), low-pass memory
+// update with the residual
 // zeroed on the index set (Eq. 5), and for members the learner's own value x_i (Eq. 3) into
 // vals[learner][slot].  Membership and slots come from the leader's bitmask and prefix
 // counts, so no learner's block reads another learner's data.
@@ -84,22 +98,19 @@ template <typename G>
 __global__ void __launch_bounds__(kBlock)
 k_update(LearnerPtrs lp, float lr, float beta, float one_minus_beta, const StDesc* __restrict__ sts, int n_st,
          const uint64_t* __restrict__ sel_mask, const uint32_t* __restrict__ tile_slot, float* __restrict__ vals,
-         int64_t k_total, int32_t* __restrict__ idx_out, int learner0, uint32_t* __restrict__ clear_from,
+         int64_t k_total, int32_t* __restrict__ idx_out, uint32_t* __restrict__ clear_from,
          size_t clear_words)
 {
-    // grid = (learners, groups of 4 wave tiles split over y and z): x runs fastest, so blocks that
-    // are scheduled together work on the same positions of different learners
-    const int learner = learner0 + blockIdx.x;
-    const int group = blockIdx.y + blockIdx.z * gridDim.y;
+    const int learner = blockIdx.y;
+    const int group = update_group(n_st);
     // The selection's per-step counters and histograms have been read for the last time before this
     // kernel starts; the blocks of its first learner zero them on the way, so that the next step finds
     // them clean and no step pays for a clearing launch.
-    if (clear_words != 0 && blockIdx.x == 0) {              // block-uniform
-        const size_t stride = static_cast<size_t>(gridDim.y) * gridDim.z * kBlock;
+    if (clear_words != 0 && learner == 0) {                 // block-uniform
+        const size_t stride = static_cast<size_t>(gridDim.x) * kBlock;
         for (size_t i = static_cast<size_t>(group) * kBlock + threadIdx.x; i < clear_words; i += stride) clear_from[i] = 0u;
     }
     const int st = group / kUpdateBlocksPerSuper;
-    if (st >= n_st) return;                                 // padding of the 3-d grid (whole block)
     // the wave's index is the same in all of its lanes: say so, and everything derived from it
     // (mask words, counts) stays in scalar registers
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
