@@ -146,18 +146,21 @@ k_chunk_step(const LearnerPtrs lp, int n_learners, int leader, float lr, float b
     }
 }
 
-// The same for layouts with more data, where reading the leader once more costs less than blocks whose positions do not
-// start on whole kilobytes: the winners first, one wave per group of whole chunks (at most 256 * Q - 3 positions,
-// the same groups as above), straight to idx_out; no atomics in memory and nothing to clear.  Bound by the vector ALU
-// before memory, so the reduction is left to LDS: a maximum per chunk, then the lowest position among the holders (one
-// atomic per lane and run each, in words of the wave's own).  A reduction inside the ALU per chunk took 43 us at
-// 25.6 M elements and chunk 112, and 52 us at 20.6 M with chunks of 25, 50 and 400; a scan over the lanes 41 and 39.
+// The same for layouts with more data, where blocks of all learners, whose positions do not start on whole kilobytes, cost more than
+// further launches: the leader by itself first, one wave per group of whole chunks (at most 256 * Q - 3 positions,
+// the same groups as above).  A wave's chunks are nobody else's, so it finds their winners, updates the leader's memory
+// in the same pass and leaves the winners in idx_out and the leader's values there in vals; the leader is read once.  No atomics in memory
+// and nothing to clear.  Bound by memory (25.6 M, chunk 112: 55 us, 5.6 TB/s, with one tile per wave, 62 with four, whose registers leave fewer
+// waves; without any work in LDS 54) once the reduction is left to LDS: a maximum per chunk, then the lowest position among the holders (one
+// atomic per lane and run each, in words of the wave's own).  Where its positions begin makes no difference: groups laid on whole 128-byte lines, or an eighth of
+// the vector per XCD, took as long.  8 x 25.6 M, us a step, winners / winners and memory in this pass: 420 / 387, 3 x 30 M 205 / 179,
+// 1 x 30 M 74 (one launch) / 64.
 constexpr int kChunkGroupMax = 256;              // chunks of a group at most (1021 positions, chunks of 4)
 
 template <typename G, int Q>
 __global__ void __launch_bounds__(kBlock)
-k_chunk_winners(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const StDesc* __restrict__ sts, int n_st,
-                int32_t* __restrict__ idx_out)
+k_chunk_lead(float* __restrict__ mem, const G* __restrict__ grad, float lr, float beta, float one_minus_beta,
+             const StDesc* __restrict__ sts, int n_st, int32_t* __restrict__ idx_out, float* __restrict__ vals)
 {
     constexpr int kMost = Q == 4 ? kChunkGroupMax : 64 * Q;
     __shared__ uint32_t key_max[kWaves][kMost], pos_min[kWaves][kMost];
@@ -167,16 +170,16 @@ k_chunk_winners(const float* __restrict__ mem, const G* __restrict__ grad, float
     const StDesc d = sts[st];
     ChunkGroup<Q> c;
     if (!c.find(d, blockIdx.x * kWaves + wave)) return;     // whole wave
-    float4 m[Q], g[Q];
+    float4 m[Q], x[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const uint32_t p0 = c.base + static_cast<uint32_t>(q * kWaveTile + lane * kVec);
         m[q] = make_float4(0, 0, 0, 0);
-        g[q] = m[q];
+        x[q] = m[q];
         if (p0 < c.hi) {
             const bool whole = p0 >= c.begin && p0 + 3 < c.end;
             m[q] = load_guarded(mem, p0, c.begin, c.end, whole);
-            g[q] = load_guarded(grad, p0, c.begin, c.end, whole);
+            x[q] = load_guarded(grad, p0, c.begin, c.end, whole);
         }
     }
     for (uint32_t j = lane; j < c.n; j += kLanes) {
@@ -186,25 +189,27 @@ k_chunk_winners(const float* __restrict__ mem, const G* __restrict__ grad, float
     wave_lds_fence();
     // A lane's elements belong to chunk j0 up to element nb, then to the next one.  Keys fit 31 bits, so -1 stands for
     // an element outside the group.
-    int32_t key[Q][4];
+    auto key_of = [&](int q, int e) {
+        const uint32_t p = c.base + static_cast<uint32_t>(q * kWaveTile + lane * kVec + e);
+        const float v = e == 0 ? x[q].x : e == 1 ? x[q].y : e == 2 ? x[q].z : x[q].w;
+        return p >= c.lo && p < c.hi ? static_cast<int32_t>(magnitude_key(v)) : -1;
+    };
     uint32_t j0[Q], nb[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const uint32_t p0 = c.base + static_cast<uint32_t>(q * kWaveTile + lane * kVec);
-        const float4 x = accumulate4(m[q], g[q], lr);
-        const float xv[4] = {x.x, x.y, x.z, x.w};
+        x[q] = accumulate4(m[q], x[q], lr);
         const uint32_t rel = p0 > c.lo ? p0 - c.lo : 0u;
         j0[q] = (rel * c.recip) >> 22;
         nb[q] = c.lo + (j0[q] + 1u) * c.ch - p0;            // (at least 1; lane 0 may begin up to 3 before lo)
         int32_t head = -1, tail = -1;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const bool in = p0 + e >= c.lo && p0 + e < c.hi;
-            key[q][e] = in ? static_cast<int32_t>(magnitude_key(xv[e])) : -1;
+            const int32_t key = key_of(q, e);
             if (static_cast<uint32_t>(e) < nb[q])
-                head = key[q][e] > head ? key[q][e] : head;
+                head = key > head ? key : head;
             else
-                tail = key[q][e] > tail ? key[q][e] : tail;
+                tail = key > tail ? key : tail;
         }
         if (head >= 0) atomicMax(&key_max[wave][j0[q]], static_cast<uint32_t>(head));
         if (tail >= 0) atomicMax(&key_max[wave][j0[q] + 1u], static_cast<uint32_t>(tail));
@@ -220,27 +225,44 @@ k_chunk_winners(const float* __restrict__ mem, const G* __restrict__ grad, float
 #pragma unroll
         for (int e = 3; e >= 0; --e) {
             if (static_cast<uint32_t>(e) < nb[q])
-                at0 = key[q][e] == best0 ? p0 + e : at0;
+                at0 = key_of(q, e) == best0 ? p0 + e : at0;
             else
-                at1 = key[q][e] == best1 ? p0 + e : at1;
+                at1 = key_of(q, e) == best1 ? p0 + e : at1;
         }
         if (at0 != 0xffffffffu) atomicMin(&pos_min[wave][j0[q]], at0);
         if (at1 != 0xffffffffu) atomicMin(&pos_min[wave][j0[q] + 1u], at1);
     }
     wave_lds_fence();
-    for (uint32_t j = lane; j < c.n; j += kLanes)
-        idx_out[static_cast<uint32_t>(c.out_base) + c.first + j] = static_cast<int32_t>(pos_min[wave][j]);
+    const uint32_t slot0 = static_cast<uint32_t>(c.out_base) + c.first;
+    for (uint32_t j = lane; j < c.n; j += kLanes) idx_out[slot0 + j] = static_cast<int32_t>(pos_min[wave][j]);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint32_t p0 = c.base + static_cast<uint32_t>(q * kWaveTile + lane * kVec);
+        if (p0 >= c.hi) continue;
+        const bool two = nb[q] < 4u && p0 + nb[q] < c.hi;
+        const uint32_t w0 = pos_min[wave][j0[q]], w1 = two ? pos_min[wave][j0[q] + 1u] : 0xffffffffu;
+        const float xv[4] = {x[q].x, x[q].y, x[q].z, x[q].w}, mv[4] = {m[q].x, m[q].y, m[q].z, m[q].w};
+        float out[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool sel = p0 + e == w0 || p0 + e == w1;
+            if (sel) vals[slot0 + j0[q] + (p0 + e == w0 ? 0u : 1u)] = xv[e];
+            out[e] = fmaf(beta, sel ? 0.0f : xv[e], one_minus_beta * mv[e]);   // Eq. 5
+        }
+        store_guarded(mem, p0, c.lo, c.hi, p0 >= c.lo && p0 + 3 < c.hi, make_float4(out[0], out[1], out[2], out[3]));
+    }
 }
 
-// The all-learner pass with the winners at hand: k_update's blocks and order, but an element is a member if
+// The other learners then, with the winners at hand: k_update's blocks and order, but an element is a member if
 // its chunk's entry of idx_out names it, and the chunk is the slot.  (The masks and slots per wave tile that
 // k_update reads would take one more launch.)  For chunks of 4 to 1021 elements.
 template <typename G>
 __global__ void __launch_bounds__(kBlock)
 k_update_chunks(LearnerPtrs lp, float lr, float beta, float one_minus_beta, const StDesc* __restrict__ sts, int n_st,
-                const int32_t* __restrict__ idx, float* __restrict__ vals, int64_t k_total)
+                const int32_t* __restrict__ idx, float* __restrict__ vals, int64_t k_total, int leader)
 {
-    const int learner = blockIdx.y;
+    int learner = blockIdx.y;
+    learner += learner >= leader ? 1 : 0;                   // (the leader's memory is updated already)
     const int group = update_group(n_st);
     const int st = group / kUpdateBlocksPerSuper;
     const StDesc d = sts[st];

@@ -47,8 +47,8 @@
 // Short layouts (see short_parts) take two kernels instead: `short_collect` sorts the leader's keys by their
 // distance from the expected threshold, `short_step` searches, updates and sums (short_kernels.h).
 // The chunk-wise selector (scalecom_step_chunked, scalecom_step_layers_chunked) needs no search: the whole step in
-// one launch (chunk_step), or the winners (chunk_winners, then update_chunks and reduce), or chunk_select +
-// chunk_marks in place of everything before `update` (see chunk_plan, chunks_in_one_launch).
+// one launch (chunk_step), or the leader's winners and memory in one pass (chunk_lead), then the other learners
+// (update_chunks) and reduce, or chunk_select + chunk_marks in place of everything before `update` (see chunk_plan, chunks_in_one_launch).
 
 #include <hip/hip_runtime.h>
 
@@ -208,15 +208,13 @@ bool sizes_ok(int64_t numel_max, int n_tensors_max, int n_learners_max, int64_t 
 
 }  // namespace
 
-// How a layout's chunk-wise step runs (elements per chunk clamped to the segment's length):
-// with groups of whole chunks of at most 256 * tiles - 3 positions, per_st of them per supertile, in one
-// launch (k_chunk_step, up to two tiles) or two and the sum over learners (k_chunk_winners); tiles = 0: chunks of
-// no suitable size for that, one more launch.
+// Groups of whole chunks, at most 256 * tiles - 3 positions each, for a layout's chunk-wise step (elements per chunk clamped to the
+// segment's length): in one launch (k_chunk_step, up to two tiles), or the leader's winners and memory first
+// (k_chunk_lead), the other learners and the sum after; tiles = 0: chunks of no suitable size, maxima by atomics.
 struct ChunkPlan {
-    int tiles = 0, per_st = 0;
+    int tiles = 0, per_st = 0;   // per_st: groups per supertile
     int max_chunks = 0;          // chunks of a group at most
     double use = 0.0;            // share of the tiles' lanes that hold a position
-    bool crowded = false;        // most positions lie in groups of so few chunks that their maxima wait for each other
 };
 
 struct scalecom_ctx {
@@ -234,7 +232,7 @@ struct scalecom_ctx {
     bool cached_chunked = false;
     int n_st = 0, n_chunks = 0, n_hblocks = 0, n_small = 0;
     int short_threads = 0, short_rows = 0, n_parts = 0;   // the layout's ShortPlan
-    ChunkPlan chunk_one, chunk_two[2];       // the layout's chunk-wise step in one launch; the winners first, up to four tiles and up to two
+    ChunkPlan chunk_one, chunk_lead;      // the layout's chunk-wise step in one launch, and with the leader first
     // segments of one supertile are searched by a kernel of their own, on a second stream beside the
     // leader pass (contexts for more than one tensor only)
     hipStream_t side = nullptr;
@@ -333,18 +331,15 @@ ShortPlan short_parts(const WsLayout& l, int n_tensors, const int64_t* offsets)
     return ShortPlan{};
 }
 
-// The number of tiles, up to tiles_max, with which the groups' positions leave the fewest lanes of their tiles idle
-// (25 positions per chunk fill 98 % of one tile, 100 fill 78 % of one and 98 % of two, 400 fill 78 % of two or four),
-// and none if that is less than `enough` of them.
-ChunkPlan chunk_plan(int n_tensors, const SegDesc* segs, int tiles_max, double enough)
+// The smallest number of tiles, up to tiles_max, that holds the layout's chunks; two instead of one if that fills more of the lanes by
+// `gain` (25 positions per chunk fill 98 % of either, 100 fill 78 % of one and 98 % of two, 200 fill 78 % of either, 155 61 % and 91 %).
+ChunkPlan chunk_plan(int n_tensors, const SegDesc* segs, int tiles_max, double gain)
 {
     ChunkPlan best{};
-    double best_use = enough;
     for (int tiles = 1; tiles <= tiles_max; tiles *= 2) {
         const int64_t positions = 256 * tiles - 3;
-        const int64_t few = tiles == 4 ? 8 : tiles;          // (see winners_first)
         int64_t per_st = 1, max_chunks = 1;
-        double used = 0.0, lanes = 0.0, in_few = 0.0;        // positions, those that their groups' tiles have room for, those in groups of few chunks
+        double used = 0.0, lanes = 0.0;                      // positions, those that their groups' tiles have room for
         bool fits = true;
         for (int s = 0; s < n_tensors && fits; ++s) {
             if (segs[s].end == segs[s].begin) continue;
@@ -358,12 +353,9 @@ ChunkPlan chunk_plan(int n_tensors, const SegDesc* segs, int tiles_max, double e
             const double len = segs[s].end - segs[s].begin;
             used += len;
             lanes += len * (256.0 * tiles) / static_cast<double>(per_group * ch);
-            if (per_group < few) in_few += len;
         }
-        if (fits && lanes > 0.0 && used / lanes > best_use + (best.tiles > 0 ? 0.03 : 0.0)) {
-            best = ChunkPlan{tiles, static_cast<int>(per_st), static_cast<int>(max_chunks), used / lanes, 2.0 * in_few > used};
-            best_use = used / lanes;
-        }
+        if (fits && lanes > 0.0 && (best.tiles == 0 || (tiles == 2 && used / lanes > best.use + gain)))
+            best = ChunkPlan{tiles, static_cast<int>(per_st), static_cast<int>(max_chunks), used / lanes};
     }
     return best;
 }
@@ -496,8 +488,10 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
     ctx->short_threads = plan.threads;
     ctx->short_rows = plan.rows;
     ctx->n_parts = plan.n_parts;
-    ctx->chunk_one = sel_chunks ? chunk_plan(n_tensors, segs, 2, 0.0) : ChunkPlan{};
-    for (int m = 0; m < 2; ++m) ctx->chunk_two[m] = sel_chunks ? chunk_plan(n_tensors, segs, m == 0 ? 4 : 2, 0.85) : ChunkPlan{};
+    ctx->chunk_one = sel_chunks ? chunk_plan(n_tensors, segs, 2, 0.03) : ChunkPlan{};
+    // (with the leader first, us, one / two / four tiles: 3 x 30 M, 112 179 / 187 / 188, 155 196 / 189 / 203, 200 179 / 196 / 192, 255 - / 190 / 199;
+    // 8 x 25.6 M, 100 388 / 389 / 394, 400 - / 400 / 411)
+    ctx->chunk_lead = sel_chunks ? chunk_plan(n_tensors, segs, 4, 0.2) : ChunkPlan{};
     ctx->cached_offsets.assign(offsets, offsets + n_tensors + 1);
     ctx->cached_ks.assign(ks, ks + n_tensors);
     ctx->cached_chunks = ch;
@@ -739,28 +733,18 @@ scalecom_status launch_step(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_lear
     return SCALECOM_OK;
 }
 
-// Is the whole chunk-wise step in one launch the faster way?  It reads the leader once instead of twice and saves two
-// launches, but moves everything at a rate that falls with the idle lanes of its tiles: 5.0 to 5.2 TB/s where 88 to 98 % of one tile are in use (chunks of 25, 84, 112), 4.6 to 5.1 with two (100, 155), 4.5 to 4.9 at 78 %
-// (200, 400), 3.9 at 66 % (170, 340), 3.0 at 50 % (255), against 6.5 of the all-learner pass.  One launch against the best of the others, us:
-// 3 x 30 M elements, chunk 25 208 against 226, 155 235 / 225, 200 224 / 223, 255 363 / 221; 4 x 11.4 M, 112 105 / 113, 155 112 / 112;
-// 6 x 5.1 M, 25 87 / 78; 8 x 3.3 M, 25 73 / 65; 8 x 1 M, 25 23 / 25, 200 25 / 27, 255 35 / 27; 2 x 100 M, 155 460 / 526, 170 615 / 515;
-// 64 x 0.2 M, 25 46 / 75.
+// Is the whole chunk-wise step in one launch the faster way?  It saves two launches and some of the sum over learners, but moves everything
+// at a rate that falls with the idle lanes of its tiles: 5.0 to 5.2 TB/s where 88 to 98 % of one tile are in use (chunks of 25, 84, 112),
+// 4.6 to 5.1 with two (100, 155), 4.5 to 4.9 at 78 % (200, 400), 3.9 at 66 % (170, 340), 3.0 at 50 % (255), where the leader first
+// moves the leader's share at 5.0 to 5.6 and the others' at 6.5.  One launch against the leader first, us: 8 x 0.3 M, chunk 112 10 / 16; 8 x 1 M, 25 23.7 / 24.1,
+// 112 23.1 / 23.3, 200 25.7 / 23.5, 255 35 / 25; 3 x 3 M, 112 23.8 / 25.4, 155 26.5 / 26.3, 200 25.7 / 25.1; 1 x 3 M, 112 10.7 / 10.8; 2 x 10 M, 112 50.5 / 47.5;
+// 8 x 3 M, 25 64 / 55; 64 x 0.2 M, 25 45 / 51, 255 48 / 51.
 bool chunks_in_one_launch(const ChunkPlan& plan, int n_learners, int64_t numel, int grad_bytes)
 {
     if (plan.tiles < 1) return false;
     const double rate = plan.tiles == 1 ? std::min(5.1, 5.9 * plan.use) : std::min(4.8, 5.7 * plan.use);
-    const double all = static_cast<double>(n_learners) * static_cast<double>(numel) * (8 + grad_bytes);
-    const double leader = static_cast<double>(numel) * (4 + grad_bytes);
-    return all * (1.0 / rate - 1.0 / 6.5) * 1e-6 < leader / 4.8 * 1e-6 + 7.0;
-}
-
-// If not, are the winners first, in groups of up to `tiles_max` tiles, faster than the maxima by atomics (one launch more)?  With less
-// than 85 % of the lanes in use they are not (8 x 10^9 elements, chunk 400, 14.2 ms a step against 13.6), nor with few chunks per
-// group, whose words in LDS all lanes then wait for (four tiles: 30 M, chunk 255 113 us against 103, 1000 112 / 98, but 112 107 / 110;
-// two tiles: 4 x 5.3 M, 450 58.0 / 57.2) -- except where a launch counts for more than the pass (8 x 0.3 M, 1000 17.2 / 20.5; 1 x 3 M 19.7 / 18.1).
-bool winners_first(const ChunkPlan& plan, int n_learners, int64_t numel)
-{
-    return plan.tiles > 0 && (!plan.crowded || (numel <= 1'000'000 && n_learners * numel <= 3'000'000));
+    const double leader = static_cast<double>(numel) * (8 + grad_bytes), all = n_learners * leader;
+    return all * (1.0 / rate - 1.0 / 6.5) * 1e-6 < leader * 0.03e-6 + 4.8 + 0.1 * n_learners;
 }
 
 // One step with the chunk-wise selector: leader pass (per-chunk maxima), marks, then the same
@@ -809,24 +793,27 @@ scalecom_status launch_chunked(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
         SC_HIP(ctx, hipGetLastError());
         return SCALECOM_OK;
     }
-    const ChunkPlan& two = winners_first(ctx->chunk_two[0], n_learners, extent) ? ctx->chunk_two[0] : ctx->chunk_two[1];
-    if (winners_first(two, n_learners, extent)) {
+    if (ctx->chunk_lead.tiles > 0) {
+        const ChunkPlan& plan = ctx->chunk_lead;
         const unsigned sz = static_cast<unsigned>((ctx->n_st + 65534) / 65535);
-        const dim3 groups((two.per_st + kWaves - 1) / kWaves, (ctx->n_st + sz - 1) / sz, sz);
-        const float* memL = lp.mem[leader];
-        const G* gradL = static_cast<const G*>(lp.grad[leader]);
-        if (two.tiles == 1)
-            k_chunk_winners<G, 1><<<groups, kBlock, 0, s>>>(memL, gradL, lr, sts, ctx->n_st, idx_out);
-        else if (two.tiles == 2)
-            k_chunk_winners<G, 2><<<groups, kBlock, 0, s>>>(memL, gradL, lr, sts, ctx->n_st, idx_out);
+        const dim3 groups((plan.per_st + kWaves - 1) / kWaves, (ctx->n_st + sz - 1) / sz, sz);
+        float* vals = reinterpret_cast<float*>(ws + l.vals);
+        auto lead = [&](auto kernel) {
+            kernel<<<groups, kBlock, 0, s>>>(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), lr, beta, 1.0f - beta, sts,
+                                             ctx->n_st, idx_out, vals + static_cast<size_t>(leader) * static_cast<size_t>(k_total));
+        };
+        if (plan.tiles == 1)
+            lead(k_chunk_lead<G, 1>);
+        else if (plan.tiles == 2)
+            lead(k_chunk_lead<G, 2>);
         else
-            k_chunk_winners<G, 4><<<groups, kBlock, 0, s>>>(memL, gradL, lr, sts, ctx->n_st, idx_out);
+            lead(k_chunk_lead<G, 4>);
         mark(1);
         mark(2);
         mark(3);
-        float* vals = reinterpret_cast<float*>(ws + l.vals);
-        k_update_chunks<G><<<dim3(static_cast<unsigned>(ctx->n_st) * kUpdateBlocksPerSuper, n_learners), kBlock, 0, s>>>(
-            lp, lr, beta, 1.0f - beta, sts, ctx->n_st, idx_out, vals, k_total);
+        if (n_learners > 1)
+            k_update_chunks<G><<<dim3(static_cast<unsigned>(ctx->n_st) * kUpdateBlocksPerSuper, n_learners - 1), kBlock, 0, s>>>(
+                lp, lr, beta, 1.0f - beta, sts, ctx->n_st, idx_out, vals, k_total, leader);
         mark(4);
         k_reduce<<<static_cast<unsigned>((k_total + kBlock - 1) / kBlock), kBlock, 0, s>>>(vals, n_learners, k_total, red_out);
         mark(5);

@@ -251,6 +251,31 @@ def test_chunks_with_little_data(gu, n, numel, chunk):
     ctx.close()
 
 
+@pytest.mark.parametrize("chunk", [25, 112, 253, 254, 255, 509, 510, 1021])
+@pytest.mark.parametrize("n", [1, 2, 5])
+def test_leader_updated_with_its_winners(gu, n, chunk):
+    """The leader first, its memory updated in the pass that finds its winners: every learner as leader (first, middle, last, the only
+    one), chunks at the edges of one, two and four tiles, equal magnitudes and zeros of both signs, values that are not finite on members and
+    beside them, plain error feedback; with tensors that start and end inside a group of four positions."""
+    numel = max(48_000_000 // n, 17_000_000) if chunk < 200 and n < 5 else 4_000_001
+    gen = torch.Generator(device=gu.DEV).manual_seed(chunk + n)
+    mem = [torch.round(torch.randn(numel, device=gu.DEV, generator=gen) * 2) * 0.5 for _ in range(n)]
+    grad = [torch.round(torch.randn(numel, device=gu.DEV, generator=gen) * 4) for _ in range(n)]
+    for i in range(n):
+        for at, v in ((7, float("nan")), (8, float("inf")), (chunk + 1, -float("inf")), (numel - 1, float("nan")), (3 * chunk, 3e38)):
+            grad[i][at] = v
+        grad[i][numel // 2:numel // 2 + 2 * chunk] = 0.0
+        mem[i][numel // 2:numel // 2 + 2 * chunk] = -0.0
+    ref = [m.cpu().numpy().copy() for m in mem]
+    offsets = [1, 1 + 5 * chunk, numel // 3 + 2, numel - 3]
+    ctx = binding.scalecom_init(numel, n, torch.float32, 3, gu.DEV)
+    for step in range(n):
+        print(f"[chunk] leader first n={n} numel={numel} chunk={chunk} step={step}", flush=True)
+        gu.compare_step(ctx, mem, grad, ref, step, 1.0 if step == 0 else 0.25, 0.5, chunk=chunk, what=f"leader first chunk={chunk}")
+    gu.compare_step(ctx, mem, grad, ref, n - 1, 0.25, 0.5, offsets=offsets, chunks=[chunk] * 3, what=f"leader first per tensor chunk={chunk}")
+    ctx.close()
+
+
 def test_chunks_per_layer_in_one_launch(gu):
     """Chunk sizes that differ from tensor to tensor, tensors shorter than a chunk, at starts that are no
     multiple of four; elements outside the tensors keep their bits."""
