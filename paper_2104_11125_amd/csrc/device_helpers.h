@@ -35,6 +35,19 @@ __device__ __forceinline__ float4 load4(const uint16_t* p)
     r.w = __uint_as_float(v.y & 0xffff0000u);
     return r;
 }
+// load4 in two halves, for gradients that are widened long after they were requested (widening waits for them).
+template <typename G> struct StreamedAs { using type = vf4_t; };
+template <> struct StreamedAs<uint16_t> { using type = vu2_t; };
+template <typename G> using Streamed = typename StreamedAs<G>::type;
+__device__ __forceinline__ vf4_t stream4(const float* p) { return __builtin_nontemporal_load(reinterpret_cast<const vf4_t*>(p)); }
+__device__ __forceinline__ vu2_t stream4(const uint16_t* p) { return __builtin_nontemporal_load(reinterpret_cast<const vu2_t*>(p)); }
+__device__ __forceinline__ float4 widen4(const vf4_t& v) { return make_float4(v.x, v.y, v.z, v.w); }
+__device__ __forceinline__ float4 widen4(const vu2_t& v)
+{
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16),
+                       __uint_as_float(v.y & 0xffff0000u));
+}
+
 __device__ __forceinline__ void store4(float* p, const float4& v)
 {
     vf4_t w;

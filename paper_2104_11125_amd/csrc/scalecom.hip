@@ -673,8 +673,8 @@ void launch_short_as(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learners, f
         kernel<<<ctx->n_parts, T, 0, ctx->stream>>>(lp, n_learners, leader, lr, beta, 1.0f - beta, parts, preds, lead_mine, used,
                                                     counts, keys, idx_out, red_out, stats);
     };
-    // more waves than four per SIMD on 256 compute units: registers for six (blocks of 1024 threads are few)
-    if (T < 1024 && ctx->n_parts * (T / kLanes) > 256 * 4 * 4)
+    // few learners and more waves than four per SIMD on 256 compute units: registers for six (blocks of 1024 threads are few)
+    if (T < 1024 && n_learners < 6 && ctx->n_parts * (T / kLanes) > 256 * 4 * 4)
         step(k_short_step<G, T, R, T < 1024 ? 6 : 4>);
     else
         step(k_short_step<G, T, R, 4>);

@@ -506,11 +506,12 @@ struct ShortFound {
 };
 
 // The search for the segment of a block's part, by all T threads; ends with a barrier.  `request` is called
-// once the counts have been requested, for loads that nothing here waits for.
-template <int T, int P, typename F>
+// once the counts have been requested, `ahead` once the usual step's last keys have been: for loads that nothing here waits for
+// (loads return in the order of their requests).
+template <int T, int P, typename F, typename A>
 __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartDesc& d, const uint4* __restrict__ used,
                                                    const uint16_t* __restrict__ counts, const uint32_t* __restrict__ keys,
-                                                   F&& request)
+                                                   F&& request, A&& ahead)
 {
     constexpr int W = T / kLanes;
     uint32_t* hist = lds.hist;
@@ -586,8 +587,9 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
     // every branch from here on is block-uniform: k, the totals and `used` are the same in all threads
     bool missed = false;
     if (k == 0) {
-        // no member
+        ahead();                                            // no member
     } else if (no_search) {
+        ahead();
         // the k-th largest key is 0, or every position is a member: no key has to be looked at
         T_key = 0u;
         q = k > n_listed ? k - n_listed : 0u;
@@ -609,6 +611,7 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
         uint32_t early_key[4];                              // (most parts have fewer)
 #pragma unroll
         for (int j = 0; j < 4; ++j) early_key[j] = static_cast<uint32_t>(j) < n_mine ? src[j] : 0u;
+        ahead();
         __syncthreads();
 #pragma unroll
         for (int w = 0; w < W; ++w) at += w < wave ? wave_tot[w] : 0u;
@@ -768,6 +771,7 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
             });
         }
         n_scan = lds.n_scan;                                // (added up behind the first level's barrier)
+        ahead();
     }
     {
         const uint32_t g = wave_sum(gt_mine), e = wave_sum(eq_mine);
@@ -847,9 +851,11 @@ __device__ __forceinline__ void short_record(const PartDesc& d, const uint4& u, 
 // The update walks the learners one after the other with one position group per thread: at these
 // sizes that is as fast as one learner per block (4 M elements in all: 16 us either way; 28 M: 57 us
 // against 53 us), and the sums over learners stay in registers.
-//   OCC: waves per SIMD that the registers are kept for, 4 or 6.  Layouts of several tensors have more blocks than the chip runs at once (60 tensors, 1213 blocks
-// of 512 threads: 46 us a step with 99 registers, 42 with 79); with fewer blocks the registers hold more
-// loads in flight (8 x 262 147, 129 blocks: 18.4 us against 19.3).
+//   OCC: waves per SIMD that the registers are kept for, 4 or 6.  Layouts of several tensors have more blocks than the chip runs at once: with few
+// learners six hide more of each other's searches (60 tensors, 1213 blocks of 512 threads, 4 learners bfloat16 41.0 us a step with four, 39.4 with six;
+// 150 tensors x 3 37.2 / 36.8; but 60 x 8 63.1 / 65.0, 200 x 8 52.2 / 54.0, 30 x 6 33.2 / 34.0).  With four the registers hold the first
+// learners' loads of the block's only row while it searches: blocks that are all on the chip at once search together
+// and leave memory idle meanwhile (4 x 1 M 22.9 -> 20.1 us, 3 x 200 003 13.5 -> 12.4, 8 x 300 000 17.0 -> 15.7; of two rows the first: no gain).
 template <typename G, int T, int R, int OCC>
 __global__ void __launch_bounds__(T, OCC)
 k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, float one_minus_beta,
@@ -858,6 +864,8 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
              int32_t* __restrict__ idx_out, float* __restrict__ red_out, unsigned long long* __restrict__ stats)
 {
     constexpr int W = T / kLanes, P = T * kVec * R;
+    constexpr int kAtOnce = T <= 512 && OCC <= 4 ? 8 : 4;   // learners whose loads are in flight together
+    constexpr bool kAhead = OCC <= 4 && R == 1;
     __shared__ ShortLds<T> lds;
     __shared__ uint32_t in_row[2][2][W];                    // of two rows in turn: members for sure / ties
     const PartDesc d = parts[blockIdx.x];
@@ -865,8 +873,21 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
     const int64_t begin = d.begin, end = d.end;
     const uint32_t k = static_cast<uint32_t>(d.k);
     float4 lm, lg;
+    float4 m[kAtOnce];
+    Streamed<G> g[kAtOnce];
+    auto load_one = [&](int j, int i, int64_t p0) {         // for lanes whose four positions all belong to the segment
+        m[j] = load4(lp.mem[i] + p0);
+        g[j] = stream4(static_cast<const G*>(lp.grad[i]) + p0);
+    };
+    const int64_t first = static_cast<int64_t>(d.a0) + t * kVec;
     const ShortFound f = short_search<T, P>(lds, d, used, counts, keys, [&]() {
-        leader_load<true>(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), static_cast<int64_t>(d.a0) + t * kVec, begin, end, lm, lg);
+        leader_load<true>(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), first, begin, end, lm, lg);
+    }, [&]() {
+        if (kAhead && first >= begin && first + 3 < end) {
+#pragma unroll
+            for (int j = 0; j < kAtOnce; ++j)
+                if (j < n_learners) load_one(j, j, first);  // uniform
+        }
     });
     short_record(d, used[d.seg], f, preds, lead_mine, stats);
     const uint32_t T_key = f.T_key, q = f.q;
@@ -938,16 +959,17 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
         };
         if (full) {
             int i = 0;
-            constexpr int kAtOnce = 4;                      // learners whose loads are in flight together
+            if (kAhead) {
+#pragma unroll
+                for (int j = 0; j < kAtOnce; ++j)
+                    if (j < n_learners) learner(j, m[j], widen4(g[j]));
+                i = kAtOnce;
+            }
             for (; i + kAtOnce <= n_learners; i += kAtOnce) {
-                float4 m[kAtOnce], g[kAtOnce];
 #pragma unroll
-                for (int j = 0; j < kAtOnce; ++j) {
-                    m[j] = load4(lp.mem[i + j] + p0);
-                    g[j] = load4(static_cast<const G*>(lp.grad[i + j]) + p0);
-                }
+                for (int j = 0; j < kAtOnce; ++j) load_one(j, i + j, p0);
 #pragma unroll
-                for (int j = 0; j < kAtOnce; ++j) learner(i + j, m[j], g[j]);
+                for (int j = 0; j < kAtOnce; ++j) learner(i + j, m[j], widen4(g[j]));
             }
             for (; i < n_learners; ++i) learner(i, load4(lp.mem[i] + p0), load4(static_cast<const G*>(lp.grad[i]) + p0));
         } else {
@@ -981,10 +1003,10 @@ k_short_overlap(const float* __restrict__ mem, const G* __restrict__ grad, float
     if (d.k == 0) return;                                   // whole block: nothing in common
     const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
     const int64_t begin = d.begin, end = d.end;
-    const ShortFound fa = short_search<T, P>(lds, d, a.used, a.counts, a.keys, []() {});
+    const ShortFound fa = short_search<T, P>(lds, d, a.used, a.counts, a.keys, []() {}, []() {});
     short_record(d, a.used[d.seg], fa, a.preds, a.lead_mine, nullptr);
     __syncthreads();                                        // the search's words are used again
-    const ShortFound fb = short_search<T, P>(lds, d, b.used, b.counts, b.keys, []() {});
+    const ShortFound fb = short_search<T, P>(lds, d, b.used, b.counts, b.keys, []() {}, []() {});
     short_record(d, b.used[d.seg], fb, b.preds, b.lead_mine, nullptr);
     uint32_t run_a = fa.eq_before, run_b = fb.eq_before, both = 0;
 #pragma unroll 1
