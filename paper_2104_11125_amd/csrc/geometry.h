@@ -18,12 +18,20 @@ constexpr int kSuper = kWaveTile * kTilesPerSuper;   // 8192 positions
 constexpr int kBlock = 256;                      // threads per block in the streaming kernels
 constexpr int kWaves = kBlock / kLanes;          // 4
 constexpr int kUpdateBlocksPerSuper = kTilesPerSuper / kWaves;   // update: one wave tile per wave
-constexpr int kXcds = 8;                         // blocks of a launch go to them in turn
 constexpr int kChunk = 1024;                     // supertiles per chunk of the prefix scan
 constexpr int kOwnScanMaxSt = 10240;             // up to this many supertiles k_slots scans the supertile totals itself
 constexpr int kManySupertiles = 32768;           // beyond: one wave per supertile means several rounds of waves on the chip
 constexpr int kSlotsBatch = 4;                   // supertiles per wave of the slot kernel then
 constexpr int kSlotsOwnScanBlock = 1024;         // threads of its blocks then (16 waves = 16 supertiles)
+
+// Blocks of a launch go to the 8 XCDs in turn.  The piece of work for the b-th of n blocks with which every XCD gets an eighth
+// of consecutive pieces.
+constexpr int kXcds = 8;
+__host__ __device__ constexpr uint32_t piece_by_xcd(uint32_t b, uint32_t n)
+{
+    const uint32_t xcd = b % kXcds, less = n / kXcds, more = n % kXcds;
+    return xcd * less + (xcd < more ? xcd : more) + b / kXcds;
+}
 
 constexpr int kBits0 = 12, kBits1 = 12, kBits2 = 7;          // 31-bit key = 12 + 12 + 7
 constexpr int kBins0 = 1 << kBits0, kBins1 = 1 << kBits1, kBins2 = 1 << kBits2;

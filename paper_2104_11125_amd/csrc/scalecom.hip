@@ -309,6 +309,13 @@ struct ShortPlan {
     int64_t part() const { return static_cast<int64_t>(threads) * rows * kVec; }
 };
 
+// The part for the b-th block of a short layout: an eighth of the parts per XCD where they are many or large (us a step, parts in turn / by
+// XCD: 200 tensors x 8 52.5 / 50.7, 150 x 3 37.0 / 36.4, 2 x 2 M 28.1 / 27.7; but smaller vectors, 4 x 1 M, 20.1 / 20.5, 2 x 0.5 M 13.8 / 14.1).
+__host__ __device__ constexpr uint32_t short_piece(int rows, uint32_t n_parts, uint32_t b)
+{
+    return rows == 2 || n_parts > static_cast<uint32_t>(kShortSegParts) ? piece_by_xcd(b, n_parts) : b;
+}
+
 ShortPlan short_parts(const WsLayout& l, int n_tensors, const int64_t* offsets)
 {
     const int64_t total = offsets[n_tensors] - offsets[0];
@@ -440,16 +447,18 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
         PartDesc* parts = reinterpret_cast<PartDesc*>(
             ctx->pinned + sm_off + align_up(sizeof(HistBlock) * static_cast<size_t>(ctx->n_tensors_max), 256));
         const int64_t part = plan.part();
+        std::vector<PartDesc> sorted(static_cast<size_t>(plan.n_parts));
         int32_t n = 0;
         for (int s = 0; s < n_tensors; ++s) {
             if (segs[s].end == segs[s].begin) continue;
             const int64_t a_first = segs[s].begin & ~(kVec - 1);
             const int32_t count = static_cast<int32_t>((segs[s].end - a_first + part - 1) / part);
             for (int32_t j = 0; j < count; ++j)
-                parts[n + j] = PartDesc{s, static_cast<int32_t>(a_first + j * part), segs[s].begin, segs[s].end,
-                                        segs[s].k, segs[s].out_base, n, count};
+                sorted[n + j] = PartDesc{s, static_cast<int32_t>(a_first + j * part), segs[s].begin, segs[s].end,
+                                         segs[s].k, segs[s].out_base, n, count};
             n += count;
         }
+        for (int32_t j = 0; j < n; ++j) parts[j] = sorted[short_piece(plan.rows, static_cast<uint32_t>(n), static_cast<uint32_t>(j))];
         SC_HIP(ctx, hipMemcpyAsync(ctx->ws + ctx->lay.parts, parts, sizeof(PartDesc) * plan.n_parts, hipMemcpyHostToDevice,
                                    ctx->stream));
     }
@@ -1051,7 +1060,7 @@ scalecom_status static_fail(scalecom_status st, const std::string& msg)
 __global__ void __launch_bounds__(kBlock)
 k_flat_tables(SegDesc* __restrict__ segs, StDesc* __restrict__ sts, ChunkDesc* __restrict__ chunks,
               HistBlock* __restrict__ hblocks, PartDesc* __restrict__ parts, int32_t numel, int32_t k, int32_t n_st,
-              int32_t n_ch, int32_t per_block, int32_t n_hb, int32_t n_parts, int32_t part)
+              int32_t n_ch, int32_t per_block, int32_t n_hb, int32_t n_parts, int32_t part, int rows)
 {
     const int32_t i = blockIdx.x * kBlock + threadIdx.x;
     if (i == 0) segs[0] = SegDesc{0, numel, k, 0, 0, n_st, 0, n_ch, 0, 0};
@@ -1061,7 +1070,8 @@ k_flat_tables(SegDesc* __restrict__ segs, StDesc* __restrict__ sts, ChunkDesc* _
         const int32_t lo = i * per_block, hi = lo + per_block < n_st ? lo + per_block : n_st;
         hblocks[i] = HistBlock{0, lo, hi, i == 0 ? 1 : 0, lo * kSuper, 0, numel, 0};
     }
-    if (i < n_parts) parts[i] = PartDesc{0, i * part, 0, numel, k, 0, 0, n_parts};
+    if (i < n_parts)
+        parts[i] = PartDesc{0, static_cast<int32_t>(short_piece(rows, n_parts, i)) * part, 0, numel, k, 0, 0, n_parts};
 }
 
 
@@ -1200,7 +1210,7 @@ scalecom_status scalecom_step_static(int device, void* hip_stream, float* const*
             reinterpret_cast<SegDesc*>(slot.ptr + l.segs), reinterpret_cast<StDesc*>(slot.ptr + l.sts),
             reinterpret_cast<ChunkDesc*>(slot.ptr + l.chunks), reinterpret_cast<HistBlock*>(slot.ptr + l.hblocks),
             reinterpret_cast<PartDesc*>(slot.ptr + l.parts), static_cast<int32_t>(numel), static_cast<int32_t>(k), n_st, n_ch,
-            per_block, n_hb, plan.n_parts, static_cast<int32_t>(plan.part()));
+            per_block, n_hb, plan.n_parts, static_cast<int32_t>(plan.part()), plan.rows);
         k_init<<<1, kBlock, 0, ctx->stream>>>(reinterpret_cast<uint32_t*>(slot.ptr + l.preds),
                                               (kPredWords + static_cast<size_t>(kStaticLearnersMax)));
         k_init<<<1, kBlock, 0, ctx->stream>>>(reinterpret_cast<uint32_t*>(slot.ptr + l.stats),

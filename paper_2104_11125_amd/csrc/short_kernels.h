@@ -224,6 +224,13 @@ __device__ __forceinline__ bool short_far_off(const float4& m, const float4& g, 
     return static_cast<float>(above) > 4.0f * (2.0f * share + 8.0f) || 8u * near < 4u * below;
 }
 
+// The index of a block's part among all parts (the table of parts is in the order of the blocks).
+template <int P>
+__device__ __forceinline__ int short_part_index(const PartDesc& d)
+{
+    return d.part_first + (d.a0 - (d.begin & ~(kVec - 1))) / P;
+}
+
 // One block per part: R rows of four consecutive positions per thread.  The loads of the part are
 // requested before anything else is looked at.
 template <typename G, int T, int R>
@@ -240,6 +247,7 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
     __shared__ uint32_t cnt[kShortCols], first[kShortCols], mixed[kShortCols];
     __shared__ uint64_t heavy;
     const PartDesc d = parts[blockIdx.x];
+    const uint32_t part_index = static_cast<uint32_t>(short_part_index<P>(d));
     const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
     const int64_t begin = d.begin, end = d.end;
     // (without a branch, or the compiler waits for these loads before it requests the part's; any valid address where they are not used)
@@ -280,9 +288,9 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
         width = kShortWidthFirst;
         mid = d.k > 0 ? short_sample<G, T>(mem, grad, lr, d, stage, wave_tot, res) : 0u;
     }
-    if (blockIdx.x == static_cast<uint32_t>(d.part_first) && t == 0)
+    if (part_index == static_cast<uint32_t>(d.part_first) && t == 0)
         used[d.seg] = make_uint4(mid, width, have | trust << 2, note);
-    if (stats && blockIdx.x == 0 && t == 0) atomicAdd(&stats[kStatSteps], 1ull);
+    if (stats && part_index == 0 && t == 0) atomicAdd(&stats[kStatSteps], 1ull);
 
     const ShortCols cols(mid, width);
     uint32_t key[4 * R], col[4 * R], rank[4 * R];
@@ -338,7 +346,7 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
         // a sample's threshold is at most 0.9 spans below the narrow columns)
         const uint64_t many = __builtin_amdgcn_ballot_w64(lane < kShortBelow + 6 && n >= static_cast<uint32_t>(P / 32));
         if (lane == 0) heavy = many;
-        counts[static_cast<size_t>(blockIdx.x) * kShortCols + lane] = static_cast<uint16_t>(lane <= kShortListed ? run : n);
+        counts[static_cast<size_t>(part_index) * kShortCols + lane] = static_cast<uint16_t>(lane <= kShortListed ? run : n);
     }
     __syncthreads();
     // through LDS, so that they leave with full-width stores (scattered 4-byte stores took longer than the rest)
@@ -348,7 +356,7 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
     const uint32_t n_listed = first[kShortListed + 1];
     const uint64_t many = heavy;
     __syncthreads();
-    uint32_t* slice = keys + static_cast<size_t>(blockIdx.x) * P;
+    uint32_t* slice = keys + static_cast<size_t>(part_index) * P;
 #pragma unroll
     for (int r = 0; r < R; ++r) {                           // (what lies past the count is never read)
         const uint32_t at = static_cast<uint32_t>(r * T + t) * kVec;
@@ -365,7 +373,7 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
         uint32_t four = 0;
         for (int j = 0; j < 32 && left != 0; j += 8, left &= left - 1) four |= static_cast<uint32_t>(__ffsll(static_cast<long long>(left))) << j;
         if (lane == 0)
-            *reinterpret_cast<uint32_t*>(counts + static_cast<size_t>(blockIdx.x) * kShortCols + kShortEqual) = four;
+            *reinterpret_cast<uint32_t*>(counts + static_cast<size_t>(part_index) * kShortCols + kShortEqual) = four;
     }
 }
 
@@ -520,7 +528,7 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
     uint32_t* res = lds.res;
     unsigned long long* found = lds.found;
     const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
-    const int mine = static_cast<int>(blockIdx.x) - d.part_first, n_parts = d.n_parts;
+    const int mine = short_part_index<P>(d) - d.part_first, n_parts = d.n_parts;
     const uint32_t k = static_cast<uint32_t>(d.k);
 
     // The counts of all parts, requested at once: eight lanes per part, eight parts per wave and turn.
@@ -796,8 +804,8 @@ __device__ __forceinline__ void short_record(const PartDesc& d, const uint4& u, 
                                              uint32_t* __restrict__ lead_mine, unsigned long long* __restrict__ stats)
 {
     const uint32_t k = static_cast<uint32_t>(d.k);
-    const int mine = static_cast<int>(blockIdx.x) - d.part_first, col = f.col;
-    if (mine != 0 || threadIdx.x != 0 || k == 0 || f.T_key == 0xffffffffu) return;
+    const int col = f.col;
+    if (d.a0 > d.begin || threadIdx.x != 0 || k == 0 || f.T_key == 0xffffffffu) return;
     uint32_t* pred = preds + static_cast<size_t>(d.seg) * kPredWords;
     const uint32_t have = u.z & 3u;
     bool held = !f.missed;
