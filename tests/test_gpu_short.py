@@ -311,6 +311,33 @@ def test_cosine_distance_at_any_alignment(gu, numel):
     ctx.close()
 
 
+@pytest.mark.parametrize("n", [12, 13, 16, 24, 25])
+@pytest.mark.parametrize("route", ["short", "long"])
+def test_sum_over_learners_one_and_two_tiles_per_block(gu, n, route):
+    """The sum over learners around the learner counts that take two tiles per block: tensors that end on, just before and just behind one and
+    two tiles, at starts that are no multiple of four."""
+    import oracle
+    for first, sizes in ((0, [512]), (3, [1021]), (1, [255]), (2, [256, 513, 7, 4_000])):
+        offsets = [first]
+        for size in sizes:
+            offsets.append(offsets[-1] + size)
+        ks = [max(1, size // 20) for size in sizes]
+        numel = offsets[-1] + 2 + gu.BALLAST
+        call_offsets, call_ks = gu.long_layout(offsets, ks) if route == "long" else (offsets, ks)
+        ctx = binding.scalecom_init(numel, n, torch.float32, len(call_ks), gu.DEV)
+        mem = [_normal(numel, 5 * i, 1.0).to(gu.DEV) for i in range(n)]
+        grad = [_normal(numel, 77 + i, 1.0).to(gu.DEV) for i in range(n)]
+        print(f"[hamming] n={n} {route} sizes={sizes}", flush=True)
+        d = ctx.scalecom_hamming_distance(mem, grad, call_offsets, call_ks, 0.7, 1)
+        torch.cuda.synchronize()
+        for s, k in enumerate(ks):
+            a, b = offsets[s], offsets[s + 1]
+            want = oracle.hamming_distance([np.ascontiguousarray(m.cpu().numpy()[a:b]) for m in mem],
+                                           [np.ascontiguousarray(g.cpu().numpy()[a:b]) for g in grad], k, 0.7, 1)
+            assert int(d[s]) == want, (sizes, s)
+        ctx.close()
+
+
 @pytest.mark.parametrize("n", [1, 2, 16, 17, 64])
 def test_hamming_distance_repeated(gu, n):
     """The diagnostic keeps thresholds of its own: called again and again between steps, with gradients whose
