@@ -24,60 +24,60 @@ k_apply_update(float* __restrict__ theta, int64_t numel, const int32_t* __restri
 // Similarity diagnostics (Sec. 3) --------------------------------------------------------------
 // y[p] = sum over learners 0..n-1, left to right, of x_i[p] = fma(lr, grad_i[p], mem_i[p]): the
 // all-reduced error-feedback gradient whose top-k is the "true top-k" (times n, which does not
-// change the order of magnitudes).  Bound by the read of all (mem, grad): a block takes Q wave tiles, one wave per
-// learner (the pattern that moves most bytes, see k_update), and adds the learners up through LDS; one thread per
-// four positions and all learners took 303 us at 8 x 25.6 M, one per position 333 us, two tiles 304, one tile 282 (6.2 TB/s; an eighth of
-// the tiles per XCD 300).  Blocks of 16 learners are the exception: 16 x 20 M 5.2 TB/s with one tile, 6.6 with two.
+// change the order of magnitudes).  Bound by the read of all (mem, grad): a block takes one wave tile, one wave per
+// learner (the pattern that moves most bytes, see k_update) or, from ten learners on, per two of them (A), and adds the learners up
+// through LDS.  us a call, A = 1 / 2: 16 x 20 M 746 / 604 (5.2 TB/s with blocks of 16 waves), 12 x 20 M 491 / 474, 64 x 4 M 424 / 421, but 8 x 25.6 M 415 / 419,
+// 6 x 30 M 407 / 411.  At 8 x 25.6 M the kernel takes 282 us (6.2 TB/s); one thread per four positions and all learners 303, one per position 333,
+// two tiles per block 304, four learners per wave 300, an eighth of the tiles per XCD 300.
 // The first threads zero `clear_words` words from `clear_from` on the way: the selection's scratch
 // zone, which the selection before this kernel has used and the one after it expects clean.
 constexpr int kSumWaves = 16;                    // waves of a block at most: further learners take turns
 
-template <typename G, int Q>
+template <typename G, int A>
 __global__ void __launch_bounds__(kSumWaves * kLanes)
-k_sum_x(const LearnerPtrs lp, int n_learners, float lr, int64_t begin, int64_t end, int64_t n_groups, float* __restrict__ y,
+k_sum_x(const LearnerPtrs lp, int n_learners, float lr, int64_t begin, int64_t end, int64_t n_tiles, float* __restrict__ y,
         uint32_t* __restrict__ clear_from, size_t clear_words)
 {
-    extern __shared__ float4 sum_lds[];                     // [tile][learner][lane]
-    const int64_t group = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
-    for (size_t i = static_cast<size_t>(group) * blockDim.x + threadIdx.x; i < clear_words;
+    extern __shared__ float4 sum_lds[];                     // [learner][lane]
+    const int64_t tile = static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x;
+    for (size_t i = static_cast<size_t>(tile) * blockDim.x + threadIdx.x; i < clear_words;
          i += static_cast<size_t>(gridDim.x) * gridDim.y * blockDim.x)
         clear_from[i] = 0u;
-    if (group >= n_groups) return;                          // whole block
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes), lane = threadIdx.x % kLanes, waves = blockDim.x / kLanes;
-    const int64_t p0 = (begin & ~static_cast<int64_t>(kVec - 1)) + group * (Q * kWaveTile) + lane * kVec;
-    const bool inside = p0 - lane * kVec >= begin && p0 - lane * kVec + Q * kWaveTile <= end;   // whole block
-    for (int i = wave; i < n_learners; i += waves) {
-        float4 m[Q], g[Q];
+    if (tile >= n_tiles) return;                            // whole block
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes), lane = threadIdx.x % kLanes;
+    const int waves = static_cast<int>(blockDim.x) / kLanes;
+    const int64_t p0 = (begin & ~static_cast<int64_t>(kVec - 1)) + tile * kWaveTile + lane * kVec;
+    const bool full = p0 >= begin && p0 + 3 < end;
+    for (int i0 = wave; i0 < n_learners; i0 += A * waves) {
+        float4 m[A], g[A];
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const int64_t p = p0 + q * kWaveTile;
-            if (inside) {
-                m[q] = load4(lp.mem[i] + p);
-                g[q] = load4(static_cast<const G*>(lp.grad[i]) + p);
+        for (int a = 0; a < A; ++a) {
+            const int i = i0 + a * waves < n_learners ? i0 + a * waves : i0;   // (the last turn's second learner may be the first again)
+            if (full) {
+                m[a] = load4(lp.mem[i] + p0);
+                g[a] = load4(static_cast<const G*>(lp.grad[i]) + p0);
             } else {
-                leader_load(lp.mem[i], static_cast<const G*>(lp.grad[i]), p, begin, end, m[q], g[q]);
+                leader_load(lp.mem[i], static_cast<const G*>(lp.grad[i]), p0, begin, end, m[a], g[a]);
             }
         }
 #pragma unroll
-        for (int q = 0; q < Q; ++q) sum_lds[(q * n_learners + i) * kLanes + lane] = accumulate4(m[q], g[q], lr);
+        for (int a = 0; a < A; ++a)
+            if (i0 + a * waves < n_learners) sum_lds[(i0 + a * waves) * kLanes + lane] = accumulate4(m[a], g[a], lr);
     }
     __syncthreads();
-    for (int q = wave; q < Q; q += waves) {
-        const int64_t p = p0 + q * kWaveTile;
-        if (p >= end) return;
-        float4 acc = sum_lds[q * n_learners * kLanes + lane];
-        for (int i = 1; i < n_learners; ++i) {
-            const float4 x = sum_lds[(q * n_learners + i) * kLanes + lane];
-            acc.x += x.x;
-            acc.y += x.y;
-            acc.z += x.z;
-            acc.w += x.w;
-        }
-        if (p >= begin && p + 3 < end)                      // (kept in the caches: the selection that follows reads it)
-            *reinterpret_cast<float4*>(y + p) = acc;
-        else
-            store_guarded(y, p, begin, end, false, acc);
+    if (wave != 0 || p0 >= end) return;
+    float4 acc = sum_lds[lane];
+    for (int i = 1; i < n_learners; ++i) {
+        const float4 x = sum_lds[i * kLanes + lane];
+        acc.x += x.x;
+        acc.y += x.y;
+        acc.z += x.z;
+        acc.w += x.w;
     }
+    if (full)                                               // (kept in the caches: the selection that follows reads it)
+        *reinterpret_cast<float4*>(y + p0) = acc;
+    else
+        store_guarded(y, p0, begin, end, false, acc);
 }
 
 // What the diagnostic's two selections start from, per tensor: d = k; for the leader's vector the prediction

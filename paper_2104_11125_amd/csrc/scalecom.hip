@@ -982,16 +982,15 @@ scalecom_status launch_hamming(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
     k_diag_begin<<<(n_tensors + kBlock - 1) / kBlock, kBlock, 0, s>>>(
         segs, n_tensors, preds, preds + (kPredWords + static_cast<size_t>(leader)) * nt, preds_a, lead_a, d_out, is_short);
     auto sum_x = [&](size_t clear_words) {
-        auto launch = [&](auto kernel, int64_t q) {         // q tiles per block
-            const int64_t group = q * kWaveTile, n_groups = (end - (begin & ~static_cast<int64_t>(kVec - 1)) + group - 1) / group;
-            const unsigned gx = static_cast<unsigned>(std::min<int64_t>(n_groups, 1 << 20));
-            const dim3 grid(gx, static_cast<unsigned>((n_groups + gx - 1) / gx));
-            kernel<<<grid, std::min(n_learners, kSumWaves) * kLanes, q * sizeof(float4) * kLanes * n_learners, s>>>(
-                lp, n_learners, lr, begin, end, n_groups, y, zone, clear_words);
+        const int64_t tiles = (end - (begin & ~static_cast<int64_t>(kVec - 1)) + kWaveTile - 1) / kWaveTile;
+        const unsigned gx = static_cast<unsigned>(std::min<int64_t>(tiles, 1 << 20));
+        const dim3 grid(gx, static_cast<unsigned>((tiles + gx - 1) / gx));
+        auto launch = [&](auto kernel, int at_once) {       // learners that a wave reads at once
+            const int waves = std::min((n_learners + at_once - 1) / at_once, kSumWaves);
+            kernel<<<grid, waves * kLanes, sizeof(float4) * kLanes * n_learners, s>>>(lp, n_learners, lr, begin, end, tiles, y, zone,
+                                                                                     clear_words);
         };
-        // us a call, one tile / two: 16 x 20 M 747 / 629, bfloat16 635 / 544, 16 x 5 M 236 / 217, 16 x 0.5 M 50 / 48, 24 x 10 M 486 / 468; but
-        // 8 x 25.6 M 414 / 434, 12 x 20 M 491 / 520, 32 x 8 M 456 / 471, 64 x 4 M 424 / 461
-        if (n_learners >= 13 && n_learners <= 24)
+        if (n_learners >= 10)                               // (see k_sum_x; 9 x 20 M 377 / 382)
             launch(k_sum_x<G, 2>, 2);
         else
             launch(k_sum_x<G, 1>, 1);

@@ -311,11 +311,11 @@ def test_cosine_distance_at_any_alignment(gu, numel):
     ctx.close()
 
 
-@pytest.mark.parametrize("n", [12, 13, 16, 24, 25])
+@pytest.mark.parametrize("n", [9, 10, 16, 31, 33])
 @pytest.mark.parametrize("route", ["short", "long"])
-def test_sum_over_learners_one_and_two_tiles_per_block(gu, n, route):
-    """The sum over learners around the learner counts that take two tiles per block: tensors that end on, just before and just behind one and
-    two tiles, at starts that are no multiple of four."""
+def test_sum_over_learners_one_and_two_per_wave(gu, n, route):
+    """The sum over learners around the learner counts from which a wave reads two of them at once, an even and an odd number, more than one
+    turn of the waves: tensors that end on, just before and just behind whole tiles, at starts that are no multiple of four."""
     import oracle
     for first, sizes in ((0, [512]), (3, [1021]), (1, [255]), (2, [256, 513, 7, 4_000])):
         offsets = [first]
