@@ -26,7 +26,7 @@ per `rate` consecutive elements) instead of the exact top-k.
 
 Prints ONE JSON line.  `value` is gradient elements per second (n_learners * numel / step
 time).  `roofline` is for the dominant kernel (the all-learner pass k_update, or the one in its
-place: k_update_chunks or k_chunk_step with chunk-wise selection, k_short_step on the short tiny configuration, whose
+place: k_chunk_lead and k_update_chunks, or k_chunk_step, with chunk-wise selection, k_short_step on the short tiny configuration, whose
 k_update_avg_ms is that kernel's time), timed with HIP
 events recorded by the library on its own stream inside the timed region.  `cpu_baseline` is
 the single-threaded CPU oracle on a bounded sample of the same workload.
@@ -407,9 +407,8 @@ def main():
             "algorithmic_bytes_per_launch": r["fused_bytes"],
             "avg_launch_ms": r["fused_ms"],
             "launches_timed": r["launches_timed"],
-            # the pass goes over 8 learners per kernel launch; with more learners the figures above (bytes,
-            # duration, traffic) are those of one step's launches together
-            "kernel_launches_per_pass": -(-w.n_learners // 8),
+            # one launch for all learners
+            "kernel_launches_per_pass": 1,
         },
         "step_roofline": {
             "algorithmic_bytes_per_step": r["step_bytes"],

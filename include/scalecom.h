@@ -309,7 +309,8 @@ scalecom_status scalecom_selection_stats(scalecom_ctx* ctx, uint64_t* counts_out
  *   4  sum of the staged values over learners (Alg. 1 line 10)
  * A step on a short layout (up to 2 M elements, or 8 M in several tensors with small ones among them) has two kernels: phase 0 is the first,
  * phases 1, 2 and 4 hold none, phase 3 is the second (search, all-learner pass and sum).  The chunk-wise step in one launch
- * is all phase 3; otherwise phase 0 of a chunk-wise step finds the winners, phase 1 holds no kernel and phase 2 one or none.
+ * is all phase 3; with the leader first everything but the sum is phase 3 (the leader's winners and memory, then the other learners); otherwise
+ * phase 0 of a chunk-wise step finds the winners, phase 1 holds no kernel and phase 2 one.
  *
  * scalecom_timing_begin: of the following calls of scalecom_step* on this context, every
  * `every`-th (the first, the (every + 1)-th, ...; every >= 1) records phase boundaries, until

@@ -804,6 +804,9 @@ scalecom_status launch_chunked(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
     }
     if (ctx->chunk_lead.tiles > 0) {
         const ChunkPlan& plan = ctx->chunk_lead;
+        mark(1);
+        mark(2);
+        mark(3);
         const unsigned sz = static_cast<unsigned>((ctx->n_st + 65534) / 65535);
         const dim3 groups((plan.per_st + kWaves - 1) / kWaves, (ctx->n_st + sz - 1) / sz, sz);
         float* vals = reinterpret_cast<float*>(ws + l.vals);
@@ -817,9 +820,6 @@ scalecom_status launch_chunked(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
             lead(k_chunk_lead<G, 2>);
         else
             lead(k_chunk_lead<G, 4>);
-        mark(1);
-        mark(2);
-        mark(3);
         if (n_learners > 1)
             k_update_chunks<G><<<dim3(static_cast<unsigned>(ctx->n_st) * kUpdateBlocksPerSuper, n_learners - 1), kBlock, 0, s>>>(
                 lp, lr, beta, 1.0f - beta, sts, ctx->n_st, idx_out, vals, k_total, leader);
