@@ -407,8 +407,8 @@ def main():
             "algorithmic_bytes_per_launch": r["fused_bytes"],
             "avg_launch_ms": r["fused_ms"],
             "launches_timed": r["launches_timed"],
-            # one launch for all learners
-            "kernel_launches_per_pass": 1,
+            # one launch for all learners (chunk-wise: one or two, by the layout)
+            "kernel_launches_per_pass": 1 if args.select == "exact" else None,
         },
         "step_roofline": {
             "algorithmic_bytes_per_step": r["step_bytes"],
