@@ -311,7 +311,7 @@ struct ShortPlan {
 
 // The part for the b-th block of a short layout: an eighth of the parts per XCD where they are many or large (us a step, parts in turn / by
 // XCD: 200 tensors x 8 52.5 / 50.7, 150 x 3 37.0 / 36.4, 2 x 2 M 28.1 / 27.7; but smaller vectors, 4 x 1 M, 20.1 / 20.5, 2 x 0.5 M 13.8 / 14.1).
-__host__ __device__ constexpr uint32_t short_piece(int rows, uint32_t n_parts, uint32_t b)
+constexpr uint32_t short_piece(int rows, uint32_t n_parts, uint32_t b)
 {
     return rows == 2 || n_parts > static_cast<uint32_t>(kShortSegParts) ? piece_by_xcd(b, n_parts) : b;
 }
@@ -1038,6 +1038,7 @@ constexpr int64_t kStaticNumelMax = SCALECOM_STATIC_NUMEL_MAX;
 constexpr int kStaticLearnersMax = SCALECOM_STATIC_LEARNERS_MAX;
 constexpr int64_t kStaticKMax = SCALECOM_STATIC_K_MAX;
 constexpr int64_t kStaticShortMax = 1 << 20;      // longer vectors take the long path: four bytes per position are kept for the short one
+static_assert(kStaticShortMax <= kShortSegParts * kShortPartMax / 2, "parts of one row and no more of them than a segment may have: their blocks are in the order of the parts");
 constexpr WsLayout kStaticLayout = layout_for(kStaticNumelMax, 1, kStaticLearnersMax, kStaticKMax, kStaticShortMax, false);
 constexpr size_t kStaticBytes = kStaticLayout.total;
 static_assert(kStaticBytes <= (size_t{16} << 20), "the static workspace stays modest");
@@ -1067,7 +1068,7 @@ scalecom_status static_fail(scalecom_status st, const std::string& msg)
 __global__ void __launch_bounds__(kBlock)
 k_flat_tables(SegDesc* __restrict__ segs, StDesc* __restrict__ sts, ChunkDesc* __restrict__ chunks,
               HistBlock* __restrict__ hblocks, PartDesc* __restrict__ parts, int32_t numel, int32_t k, int32_t n_st,
-              int32_t n_ch, int32_t per_block, int32_t n_hb, int32_t n_parts, int32_t part, int rows)
+              int32_t n_ch, int32_t per_block, int32_t n_hb, int32_t n_parts, int32_t part)
 {
     const int32_t i = blockIdx.x * kBlock + threadIdx.x;
     if (i == 0) segs[0] = SegDesc{0, numel, k, 0, 0, n_st, 0, n_ch, 0, 0};
@@ -1077,8 +1078,7 @@ k_flat_tables(SegDesc* __restrict__ segs, StDesc* __restrict__ sts, ChunkDesc* _
         const int32_t lo = i * per_block, hi = lo + per_block < n_st ? lo + per_block : n_st;
         hblocks[i] = HistBlock{0, lo, hi, i == 0 ? 1 : 0, lo * kSuper, 0, numel, 0};
     }
-    if (i < n_parts)
-        parts[i] = PartDesc{0, static_cast<int32_t>(short_piece(rows, n_parts, i)) * part, 0, numel, k, 0, 0, n_parts};
+    if (i < n_parts) parts[i] = PartDesc{0, i * part, 0, numel, k, 0, 0, n_parts};
 }
 
 
@@ -1217,7 +1217,7 @@ scalecom_status scalecom_step_static(int device, void* hip_stream, float* const*
             reinterpret_cast<SegDesc*>(slot.ptr + l.segs), reinterpret_cast<StDesc*>(slot.ptr + l.sts),
             reinterpret_cast<ChunkDesc*>(slot.ptr + l.chunks), reinterpret_cast<HistBlock*>(slot.ptr + l.hblocks),
             reinterpret_cast<PartDesc*>(slot.ptr + l.parts), static_cast<int32_t>(numel), static_cast<int32_t>(k), n_st, n_ch,
-            per_block, n_hb, plan.n_parts, static_cast<int32_t>(plan.part()), plan.rows);
+            per_block, n_hb, plan.n_parts, static_cast<int32_t>(plan.part()));
         k_init<<<1, kBlock, 0, ctx->stream>>>(reinterpret_cast<uint32_t*>(slot.ptr + l.preds),
                                               (kPredWords + static_cast<size_t>(kStaticLearnersMax)));
         k_init<<<1, kBlock, 0, ctx->stream>>>(reinterpret_cast<uint32_t*>(slot.ptr + l.stats),
