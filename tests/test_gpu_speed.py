@@ -82,6 +82,33 @@ def test_tensors_of_equal_size_against_one_vector(n, tensors, size, factor):
         ctx.close()
 
 
+@pytest.mark.parametrize("select,n,count,size,large,factor", [
+    ("exact", 16, 600, 64, [100_000] * 10, 1.12), ("exact", 16, 1000, 50, [50_000] * 10, 1.12),   # short layouts
+])
+def test_small_tensors_side_by_side(select, n, count, size, large, factor):
+    """Many small tensors in front of the large ones: no slower than with the same tensors mixed, whose parts, chunks and
+    supertiles every one of the chip's XCDs gets a like number of."""
+    grad, calls, keep, per = None, [], [], count // len(large)
+    for sizes in ([size] * (per * len(large)) + large, [s for l in large for s in [size] * per + [l]]):
+        offsets = [0]
+        for s in sizes:
+            offsets.append(offsets[-1] + s)
+        numel, ks = offsets[-1], [-(-s // 100) for s in sizes]
+        grad = grad or [_normal(numel, i) for i in range(n)]
+        ctx = binding.scalecom_init(numel, n, torch.float32, len(sizes), DEV, k_max=sum(ks))
+        mem = [torch.zeros(numel, device=DEV) for _ in range(n)]
+        idx, red = torch.empty(sum(ks), dtype=torch.int32, device=DEV), torch.empty(sum(ks), device=DEV)
+        keep.append(ctx)
+        step = ctx.scalecom_step_layers if select == "exact" else ctx.scalecom_step_layers_chunked
+        sel = ks if select == "exact" else [100] * len(sizes)
+        calls.append(lambda t, f=step, m=mem, o=offsets, s=sel, i=idx, r=red: f(m, grad, o, s, 0.1, 0.1, t, i, r))
+    got, base = _times(calls)
+    print(f"[speed] {select} {count} x {size} + {len(large)} x {large[0]}, {n} learners: {got:.1f} us, mixed: {base:.1f} us", flush=True)
+    assert got <= factor * base
+    for ctx in keep:
+        ctx.close()
+
+
 @pytest.mark.parametrize("numel,kind", [(200_003, "drop"), (1_048_576, "equal"), (1_048_576, "drop"), (2_097_152, "equal"),
                                         (2_097_152, "sign"), (2_097_152, "two"), (2_097_152, "near"), (2_097_152, "drop")])
 def test_ties_and_jumps_on_short_layouts(numel, kind):
