@@ -451,21 +451,29 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
                                          segs[s].k, segs[s].out_base, n, count};
             n += count;
         }
-        // The order of the blocks.  Where parts are many or large, an eighth of the parts that are filled by three quarters or more to
-        // each XCD (the parts of a segment read the same counts), and the others in turn behind them, or an XCD
-        // whose eighth holds the full parts works while the rest wait.  us a step, parts in turn / an eighth of all per XCD / this order: 60 tensors
-        // of 20 000 x 8 learners 31.3 / 29.7 / 29.7, 2 of 1 M x 16 95 / 95 / 90; 600 of 64 and one of 1 M x 4 40 / 62 / 40, x 16 67 / 132 / 69,
-        // 1200 of 700 and 100 of 2000 x 16 55 / 62 / 55.  Smaller vectors gain nothing (4 x 1 M 20.1 / 20.5, 2 x 0.5 M 13.8 / 14.1).
+        // The order of the blocks.  Where parts are many or large, an eighth of them to each XCD (a segment's parts read the same counts), as long as no
+        // eighth holds much more than the others; else an eighth of the parts that are filled by three quarters or more, and the others in turn behind
+        // them.  us a step, f32, parts in turn / eighths of all / of the filled ones: even layouts, 60 tensors of 20 000 x 8 learners 31.7 / 29.5 / 29.7, 120 of 64 to
+        // 50 000 x 4 20.6 / 17.4 / 19.2 (fullest eighth 1.04 of its share); 300 of 3000 before 3 of 400 000 x 8 58.2 / 59.7 / 55.6 (1.15), 600 of 64 and one of 1 M
+        // x 16 67 / 123 / 71 (3.3), 1200 of 700 and 100 of 2000 x 8 35.6 / 38.7 / 35.3 (1.5).  Smaller vectors gain nothing (4 x 1 M 20.1 / 20.5, 2 x 0.5 M 13.8 / 14.1).
         const bool by_xcd = plan.rows == 2 || n > kShortSegParts;
-        int32_t full[kShortPartsMax], rest[kShortPartsMax];
-        uint32_t n_full = 0, n_rest = 0;
+        auto held = [&](int32_t j) { return std::min<int64_t>(sorted[j].end, sorted[j].a0 + part) - std::max(sorted[j].begin, sorted[j].a0); };
+        int64_t most = 0, all = 0;
+        for (int32_t x = 0, j = 0; x < kXcds; ++x) {
+            int64_t eighth = 0;
+            for (int32_t i = (n + kXcds - 1 - x) / kXcds; i > 0; --i) eighth += held(j++);
+            most = std::max(most, eighth);
+            all += eighth;
+        }
+        const bool even = 10 * kXcds * most <= 11 * all;
+        int32_t first[kShortPartsMax], then[kShortPartsMax];
+        uint32_t n_first = 0, n_then = 0;
         for (int32_t j = 0; j < n; ++j) {
-            const PartDesc& d = sorted[j];
-            const int64_t held = std::min<int64_t>(d.end, d.a0 + part) - std::max(d.begin, d.a0);
-            if (by_xcd && 4 * held >= 3 * part) full[n_full++] = j; else rest[n_rest++] = j;
+            const bool filled = 4 * held(j) >= 3 * part;
+            if (by_xcd && (even || filled)) first[n_first++] = j; else then[n_then++] = j;
         }
         for (uint32_t b = 0; b < static_cast<uint32_t>(n); ++b)
-            parts[b] = sorted[b < n_full ? full[piece_by_xcd(b, n_full)] : rest[b - n_full]];
+            parts[b] = sorted[b < n_first ? first[piece_by_xcd(b, n_first)] : then[b - n_first]];
         SC_HIP(ctx, hipMemcpyAsync(ctx->ws + ctx->lay.parts, parts, sizeof(PartDesc) * plan.n_parts, hipMemcpyHostToDevice,
                                    ctx->stream));
     }
