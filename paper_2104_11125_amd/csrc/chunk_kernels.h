@@ -262,11 +262,11 @@ k_chunk_lead(float* __restrict__ mem, const G* __restrict__ grad, float lr, floa
 template <typename G>
 __global__ void __launch_bounds__(kBlock)
 k_update_chunks(LearnerPtrs lp, float lr, float beta, float one_minus_beta, const StDesc* __restrict__ sts, int n_st,
-                const int32_t* __restrict__ idx, float* __restrict__ vals, int64_t k_total, int leader)
+                const int32_t* __restrict__ idx, float* __restrict__ vals, int64_t k_total, int leader, bool eighths)
 {
     int learner = blockIdx.y;
     learner += learner >= leader ? 1 : 0;                   // (the leader's memory is updated already)
-    const int group = update_group(n_st);
+    const int group = update_group(n_st, eighths);
     const int st = group / kUpdateBlocksPerSuper;
     const StDesc d = sts[st];
     const uint32_t begin = static_cast<uint32_t>(d.begin), end = static_cast<uint32_t>(d.end);

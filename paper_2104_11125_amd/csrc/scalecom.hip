@@ -231,6 +231,7 @@ struct scalecom_ctx {
     std::vector<int64_t> cached_offsets, cached_ks, cached_chunks;
     bool cached_chunked = false;
     int n_st = 0, n_chunks = 0, n_hblocks = 0, n_small = 0;
+    bool eighths = true;             // eighths of the layout's supertiles hold alike (see ensure_tables)
     int short_threads = 0, short_rows = 0, n_parts = 0;   // the layout's ShortPlan
     ChunkPlan chunk_one, chunk_lead;      // the layout's chunk-wise step in one launch, and with the leader first
     // segments of one supertile are searched by a kernel of their own, on a second stream beside the
@@ -505,6 +506,15 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
     ctx->scratch_clean = false;
     SC_HIP(ctx, hipEventRecord(ctx->upload_done, ctx->stream));
     ctx->upload_pending = true;
+    // Whether the all-learner pass gives each XCD an eighth of the supertiles (see update_kernels.h): if these hold alike (10 % over the mean at most).
+    int64_t held[kXcds] = {}, most = 0, all = 0;
+    for (int64_t j = 0; j < n_st; ++j)
+        held[j * kXcds / n_st] += std::min<int64_t>(sts[j].end, static_cast<int64_t>(sts[j].a0) + kSuper) - std::max(sts[j].begin, sts[j].a0);
+    for (int64_t h : held) {
+        most = std::max(most, h);
+        all += h;
+    }
+    ctx->eighths = n_tensors == 1 || 10 * kXcds * most <= 11 * all;
     ctx->n_st = static_cast<int>(n_st);
     ctx->n_chunks = static_cast<int>(n_ch);
     ctx->n_hblocks = static_cast<int>(n_hb);
@@ -532,7 +542,7 @@ bool timed_step(scalecom_ctx* ctx)
 
 // The all-learner pass and the sum over learners, shared by the exact and the chunk-wise selector:
 // both leave the membership mask and the first output slot of every wave tile behind.
-// The first launch of the pass also zeroes `clear_words` words from `clear_from`: the selection's
+// The blocks of its first learner also zero `clear_words` words from `clear_from`: the selection's
 // per-step scratch, which nothing reads any more at that point, so that the next step finds it clean.
 template <typename G, typename Mark>
 void launch_update_reduce(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learners, int64_t k_total, float beta, float lr,
@@ -548,7 +558,7 @@ void launch_update_reduce(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learne
     float* vals = reinterpret_cast<float*>(ws + l.vals);
     k_update<G><<<dim3(static_cast<unsigned>(n_st) * kUpdateBlocksPerSuper, n_learners), kBlock, 0, s>>>(
         lp, lr, beta, 1.0f - beta, sts, n_st, sel_mask, tile_slot, vals, k_total, idx_out, clear_from,
-        clear_words);
+        clear_words, ctx->eighths);
     mark(4);
     if (k_total > 0)
         k_reduce<<<static_cast<unsigned>((k_total + kBlock - 1) / kBlock), kBlock, 0, s>>>(vals, n_learners, k_total,
@@ -837,7 +847,7 @@ scalecom_status launch_chunked(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
             lead(k_chunk_lead<G, 4>);
         if (n_learners > 1)
             k_update_chunks<G><<<dim3(static_cast<unsigned>(ctx->n_st) * kUpdateBlocksPerSuper, n_learners - 1), kBlock, 0, s>>>(
-                lp, lr, beta, 1.0f - beta, sts, ctx->n_st, idx_out, vals, k_total, leader);
+                lp, lr, beta, 1.0f - beta, sts, ctx->n_st, idx_out, vals, k_total, leader, ctx->eighths);
         mark(4);
         k_reduce<<<static_cast<unsigned>((k_total + kBlock - 1) / kBlock), kBlock, 0, s>>>(vals, n_learners, k_total, red_out);
         mark(5);

@@ -11,16 +11,23 @@ namespace {
 
 // The group of 4 wave tiles that a block of the all-learner pass works on; grid = (groups, learners).  One learner after the
 // other, and of each learner an eighth of the vector on each XCD (blocks go to the XCDs in turn): every XCD streams two
-// arrays at a time, and its eighth of the masks stays in its L2.  With the learners side by side instead, eight to a
+// arrays at a time, and its eighth of the masks stays in its L2 as long as it fits (110 M positions: 1.7 MB, traffic 1.003 of what the pass cannot do
+// without; 10^9: 16 MB against 4 MB of L2, read again for each learner, 1.03).  With the learners side by side instead, eight to a
 // launch, only eight of them (one per XCD) reached the same rate: 2 reads and 1 write as a bare kernel, float, TB/s, side by
 // side / this order: 25.6 M x 8 6.61 / 6.61, x 7 6.35 / 6.60, x 3 6.41 / 6.55, 110 M x 6 5.50 / 6.13, x 3 6.19 / 6.56.  Neighbouring groups
 // on neighbouring XCDs: 6.35 to 6.40 there, and bfloat16 no difference; whole steps, us, side by side / neighbouring / this order:
 // 6 x 14 M 233 / 212 / 210, 16 x 2.5 M 116 / 114 / 110, 2 x 4 M 52 / 51 / 50, 8 x 10 M bfloat16 169 / 170 / 166, 8 x 3.5 M 88 / 88 / 86, 8 x 25.6 M
 // 448 / 450 / 450.
+// Where the eighths do not hold alike (small tensors side by side, of which each takes a supertile), whole supertiles go to the XCDs in turn, the last up to
+// seven group by group.  Eighths / in turn, chunk-wise steps, us: 20 000 tensors of 64 and one of 30 M x 8 1688 / 1192, 600 of 64 and one of 3 M x 8 84 / 69, 3000 of 300
+// and 10 of 1 M x 16 646 / 532; but alike, 2000 of 9000 x 8 292 / 335, 8 x 25 M exact 445 / 460.
 static_assert(kUpdateBlocksPerSuper == kXcds, "the groups divide evenly");
-__device__ __forceinline__ int update_group(int n_st)
+__device__ __forceinline__ int update_group(int n_st, bool eighths)
 {
-    return static_cast<int>((blockIdx.x % kXcds) * static_cast<uint32_t>(n_st) + blockIdx.x / kXcds);
+    const uint32_t b = blockIdx.x, n = static_cast<uint32_t>(n_st) * kXcds;
+    if (eighths) return static_cast<int>((b % kXcds) * static_cast<uint32_t>(n_st) + b / kXcds);
+    if (b >= n / (kXcds * kXcds) * (kXcds * kXcds)) return static_cast<int>(b);
+    return static_cast<int>(b / (kXcds * kXcds) * (kXcds * kXcds) + b % kXcds * kXcds + b / kXcds % kXcds);
 }
 
 // The all-learner pass, one (learner, 4 wave tiles) pair per block: accumulate (Alg. 1 line 6), low-pass memory
@@ -99,10 +106,10 @@ __global__ void __launch_bounds__(kBlock)
 k_update(LearnerPtrs lp, float lr, float beta, float one_minus_beta, const StDesc* __restrict__ sts, int n_st,
          const uint64_t* __restrict__ sel_mask, const uint32_t* __restrict__ tile_slot, float* __restrict__ vals,
          int64_t k_total, int32_t* __restrict__ idx_out, uint32_t* __restrict__ clear_from,
-         size_t clear_words)
+         size_t clear_words, bool eighths)
 {
     const int learner = blockIdx.y;
-    const int group = update_group(n_st);
+    const int group = update_group(n_st, eighths);
     // The selection's per-step counters and histograms have been read for the last time before this
     // kernel starts; the blocks of its first learner zero them on the way, so that the next step finds
     // them clean and no step pays for a clearing launch.

@@ -276,6 +276,30 @@ def test_leader_updated_with_its_winners(gu, n, chunk):
     ctx.close()
 
 
+@pytest.mark.parametrize("count", [296, 301, 303])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_supertiles_in_turn(gu, count, dtype):
+    """Small tensors side by side in front of a large one, so that the eighths of the supertiles do not hold alike: the all-learner pass takes whole supertiles
+    in turn, of a number that eight divides and of others; per tensor exact, and chunk-wise with the leader first (and two chunk sizes)."""
+    sizes = [64] * count + [3_000_001, 70]                       # 367 supertiles and one
+    offsets = [2]
+    for s in sizes:
+        offsets.append(offsets[-1] + s)
+    n, numel, ks = 8, offsets[-1] + 3, [max(1, s // 100) for s in sizes]
+    gen = torch.Generator(device=gu.DEV).manual_seed(count)
+    ctx = binding.scalecom_init(numel, n, dtype, len(sizes), gu.DEV)
+    mem = [torch.randn(numel, device=gu.DEV, generator=gen) for _ in range(n)]
+    ref = [m.cpu().numpy().copy() for m in mem]
+    for step, chunk in enumerate((None, 200, 201)):
+        grad = [torch.randn(numel, device=gu.DEV, generator=gen).to(dtype) for _ in range(n)]
+        print(f"[order] {count} + 2 tensors {dtype} chunk={chunk}", flush=True)
+        if chunk is None:
+            gu.compare_step(ctx, mem, grad, ref, step, 0.25, 0.5, offsets=offsets, ks=ks, what="in turn")
+        else:
+            gu.compare_step(ctx, mem, grad, ref, step, 0.25, 0.5, offsets=offsets, chunks=[chunk] * len(sizes), what=f"in turn chunk={chunk}")
+    ctx.close()
+
+
 def test_chunks_per_layer_in_one_launch(gu):
     """Chunk sizes that differ from tensor to tensor, tensors shorter than a chunk, at starts that are no
     multiple of four; elements outside the tensors keep their bits."""
