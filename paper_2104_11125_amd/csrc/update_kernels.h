@@ -124,6 +124,10 @@ k_update(LearnerPtrs lp, float lr, float beta, float one_minus_beta, const StDes
     const int lane = threadIdx.x % kLanes;
     const int wt0 = (group % kUpdateBlocksPerSuper) * kWaves;   // the block's first wave tile
     const StDesc d = sts[st];
+    const int64_t blk0 = static_cast<int64_t>(d.a0) + wt0 * kWaveTile;
+    // Nothing left of a short supertile (whole block): known before its masks are read, which one learner after the other would each fetch again
+    // (10 000 tensors of 1000, us a step, without / with this line: 3 learners 611 / 541, 8 learners 1108 / 876).
+    if (blk0 >= d.end) return;
 
     // membership of the block's 4 tiles (128 bytes) and the block's first output slot: small,
     // cache-resident, issued together with the streaming loads so that nothing waits on a
@@ -156,7 +160,6 @@ k_update(LearnerPtrs lp, float lr, float beta, float one_minus_beta, const StDes
     float* my_vals = vals + static_cast<size_t>(learner) * static_cast<size_t>(k_total);
     int32_t* my_idx = learner == 0 ? idx_out : nullptr;    // one learner's blocks write the positions
     const uint32_t rel0 = static_cast<uint32_t>((wt0 + wave) * kWaveTile + lane * kVec);
-    const int64_t blk0 = static_cast<int64_t>(d.a0) + wt0 * kWaveTile;
     __shared__ float stage_val[kWaves * kWaveTile];
     __shared__ int32_t stage_pos[kWaves * kWaveTile];
     if (blk0 >= d.begin && blk0 + kWaves * kWaveTile <= d.end)

@@ -110,6 +110,25 @@ def test_small_tensors_side_by_side(select, n, count, size, large, factor):
         ctx.close()
 
 
+def test_further_learners_on_short_supertiles():
+    """Tensors of 1000, an eighth of a supertile each: seven more learners cost little more than the step of one, whose search takes most of the time."""
+    count, size = 10_000, 1000
+    numel, offsets, ks = count * size, [t * size for t in range(count + 1)], [size // 100] * count
+    grad = [_normal(numel, i) for i in range(8)]
+    idx, red = torch.empty(sum(ks), dtype=torch.int32, device=DEV), torch.empty(sum(ks), device=DEV)
+    calls, keep = [], []
+    for n in (8, 1):
+        ctx = binding.scalecom_init(numel, n, torch.float32, count, DEV, k_max=sum(ks))
+        mem = [torch.zeros(numel, device=DEV) for _ in range(n)]
+        keep.append(ctx)
+        calls.append(lambda t, c=ctx, m=mem, n=n: c.scalecom_step_layers(m, grad[:n], offsets, ks, 0.1, 0.1, t, idx, red))
+    got, base = _times(calls)
+    print(f"[speed] {count} x {size}: 8 learners {got:.1f} us, 1 learner {base:.1f} us", flush=True)
+    assert got <= 2.3 * base
+    for ctx in keep:
+        ctx.close()
+
+
 @pytest.mark.parametrize("numel,kind", [(200_003, "drop"), (1_048_576, "equal"), (1_048_576, "drop"), (2_097_152, "equal"),
                                         (2_097_152, "sign"), (2_097_152, "two"), (2_097_152, "near"), (2_097_152, "drop")])
 def test_ties_and_jumps_on_short_layouts(numel, kind):
