@@ -267,6 +267,7 @@ k_update_chunks(LearnerPtrs lp, float lr, float beta, float one_minus_beta, cons
     int learner = blockIdx.y;
     learner += learner >= leader ? 1 : 0;                   // (the leader's memory is updated already)
     const int group = update_group(n_st, eighths);
+    if (group < 0) return;
     const int st = group / kUpdateBlocksPerSuper;
     const StDesc d = sts[st];
     const uint32_t begin = static_cast<uint32_t>(d.begin), end = static_cast<uint32_t>(d.end);

@@ -556,9 +556,8 @@ void launch_update_reduce(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learne
     const uint64_t* sel_mask = reinterpret_cast<const uint64_t*>(ws + l.sel_mask);
     const uint32_t* tile_slot = reinterpret_cast<const uint32_t*>(ws + l.tile_slot);
     float* vals = reinterpret_cast<float*>(ws + l.vals);
-    k_update<G><<<dim3(static_cast<unsigned>(n_st) * kUpdateBlocksPerSuper, n_learners), kBlock, 0, s>>>(
-        lp, lr, beta, 1.0f - beta, sts, n_st, sel_mask, tile_slot, vals, k_total, idx_out, clear_from,
-        clear_words, ctx->eighths);
+    k_update<G><<<update_grid(n_st, n_learners), kBlock, 0, s>>>(lp, lr, beta, 1.0f - beta, sts, n_st, sel_mask, tile_slot, vals,
+                                                                 k_total, idx_out, clear_from, clear_words, ctx->eighths);
     mark(4);
     if (k_total > 0)
         k_reduce<<<static_cast<unsigned>((k_total + kBlock - 1) / kBlock), kBlock, 0, s>>>(vals, n_learners, k_total,
@@ -846,7 +845,7 @@ scalecom_status launch_chunked(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
         else
             lead(k_chunk_lead<G, 4>);
         if (n_learners > 1)
-            k_update_chunks<G><<<dim3(static_cast<unsigned>(ctx->n_st) * kUpdateBlocksPerSuper, n_learners - 1), kBlock, 0, s>>>(
+            k_update_chunks<G><<<update_grid(ctx->n_st, n_learners - 1), kBlock, 0, s>>>(
                 lp, lr, beta, 1.0f - beta, sts, ctx->n_st, idx_out, vals, k_total, leader, ctx->eighths);
         mark(4);
         k_reduce<<<static_cast<unsigned>((k_total + kBlock - 1) / kBlock), kBlock, 0, s>>>(vals, n_learners, k_total, red_out);

@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "device_helpers.h"
 #include "geometry.h"
 
@@ -22,9 +24,18 @@ namespace {
 // seven group by group.  Eighths / in turn, chunk-wise steps, us: 20 000 tensors of 64 and one of 30 M x 8 1688 / 1192, 600 of 64 and one of 3 M x 8 84 / 69, 3000 of 300
 // and 10 of 1 M x 16 646 / 532; but alike, 2000 of 9000 x 8 292 / 335, 8 x 25 M exact 445 / 460.
 static_assert(kUpdateBlocksPerSuper == kXcds, "the groups divide evenly");
+constexpr uint32_t kUpdateGridX = 1u << 22;      // groups in x at most, as a launch has less than 2^32 threads there; the others in z
+inline dim3 update_grid(int n_st, int n_learners)
+{
+    const uint32_t groups = static_cast<uint32_t>(n_st) * kUpdateBlocksPerSuper;
+    return dim3(std::min(groups, kUpdateGridX), static_cast<uint32_t>(n_learners), (groups + kUpdateGridX - 1) / kUpdateGridX);
+}
+
+// -1: padding of the grid (whole block)
 __device__ __forceinline__ int update_group(int n_st, bool eighths)
 {
-    const uint32_t b = blockIdx.x, n = static_cast<uint32_t>(n_st) * kXcds;
+    const uint32_t b = blockIdx.x + blockIdx.z * gridDim.x, n = static_cast<uint32_t>(n_st) * kXcds;
+    if (b >= n) return -1;
     if (eighths) return static_cast<int>((b % kXcds) * static_cast<uint32_t>(n_st) + b / kXcds);
     if (b >= n / (kXcds * kXcds) * (kXcds * kXcds)) return static_cast<int>(b);
     return static_cast<int>(b / (kXcds * kXcds) * (kXcds * kXcds) + b % kXcds * kXcds + b / kXcds % kXcds);
@@ -110,11 +121,12 @@ k_update(LearnerPtrs lp, float lr, float beta, float one_minus_beta, const StDes
 {
     const int learner = blockIdx.y;
     const int group = update_group(n_st, eighths);
+    if (group < 0) return;
     // The selection's per-step counters and histograms have been read for the last time before this
     // kernel starts; the blocks of its first learner zero them on the way, so that the next step finds
     // them clean and no step pays for a clearing launch.
     if (clear_words != 0 && learner == 0) {                 // block-uniform
-        const size_t stride = static_cast<size_t>(gridDim.x) * kBlock;
+        const size_t stride = static_cast<size_t>(n_st) * kUpdateBlocksPerSuper * kBlock;
         for (size_t i = static_cast<size_t>(group) * kBlock + threadIdx.x; i < clear_words; i += stride) clear_from[i] = 0u;
     }
     const int st = group / kUpdateBlocksPerSuper;

@@ -331,6 +331,23 @@ def test_maximum_size_chunked_full(gu):
     _streamed_parity(gu, _maximum_size_workload(), step=0, seed=960, chunk=400)
 
 
+def test_two_million_tensors(gu):
+    """More supertiles than one launch has threads for in x (2^21): 2 097 160 tensors of four positions, chunk-wise with maxima by atomics (chunks of three)."""
+    torch.cuda.empty_cache()
+    tensors, n = (1 << 21) + 8, 2
+    numel, offsets, chunks = 4 * tensors, np.arange(0, 4 * tensors + 1, 4).tolist(), [3] * tensors
+    ctx = binding.scalecom_init(numel, n, torch.float32, tensors, gu.DEV, k_max=2 * tensors)   # (a workspace of 137 GB)
+    gen = torch.Generator(device=gu.DEV).manual_seed(5)
+    mem = [torch.randn(numel, device=gu.DEV, generator=gen) for _ in range(n)]
+    ref = [m.cpu().numpy().copy() for m in mem]
+    grad = [torch.randn(numel, device=gu.DEV, generator=gen) for _ in range(n)]
+    print(f"[full] {tensors} tensors", flush=True)
+    gu.compare_step(ctx, mem, grad, ref, 1, 0.25, 0.5, offsets=offsets, chunks=chunks, what="two million tensors")
+    ctx.close()
+    del ctx
+    torch.cuda.empty_cache()
+
+
 def test_large_vector_fallback_paths(gu):
     """Blocks of the search-level kernels that hold several supertiles each (more than 2048
     supertiles) on every path of the selection: no prediction, prediction and fine counts hit,
