@@ -60,14 +60,13 @@ k_chunk_step(const LearnerPtrs lp, int n_learners, int leader, float lr, float b
     extern __shared__ unsigned long long chunk_lds[];
     unsigned long long* best = chunk_lds;
     float* xs = reinterpret_cast<float*>(chunk_lds + max_chunks);
-    // the supertile's group: an eighth of the groups per XCD (3 x 3 M, chunk 112, 24.1 -> 23.2 us; 4 x 1 M 12.8 -> 12.4)
-    const uint32_t lin = blockIdx.x + (blockIdx.y + blockIdx.z * gridDim.y) * gridDim.x;
-    const uint32_t n_groups = gridDim.x * static_cast<uint32_t>(n_st);
-    if (lin >= n_groups) return;                            // padding of the 3-d grid (whole block)
-    const uint32_t piece = piece_by_xcd(lin, n_groups);
-    const StDesc d = sts[piece / gridDim.x];
+    // (groups in turn: an eighth of them per XCD is faster on some vectors, 3 x 3 M, chunk 112 24.1 -> 23.2 us, 2 x 8 M, 25 41.6 -> 38.3, slower on
+    // others, 4 x 3.75 M, 25 38.7 -> 42.1, 500 35.7 -> 42.3, and up to twice as slow where small tensors lie side by side)
+    const int st = static_cast<int>(blockIdx.y + blockIdx.z * gridDim.y);
+    if (st >= n_st) return;                                 // padding of the 3-d grid (whole block)
+    const StDesc d = sts[st];
     ChunkGroup<Q> grp;
-    if (!grp.find(d, piece % gridDim.x)) return;            // whole block
+    if (!grp.find(d, blockIdx.x)) return;                   // whole block
     const uint32_t begin = grp.begin, end = grp.end, recip = grp.recip, cf = grp.first, n_ch = grp.n;
     const uint32_t lo = grp.lo, hi = grp.hi, base = grp.base;
 

@@ -85,6 +85,7 @@ def test_tensors_of_equal_size_against_one_vector(n, tensors, size, factor):
 @pytest.mark.parametrize("select,n,count,size,large,factor", [
     ("exact", 16, 600, 64, [100_000] * 10, 1.12), ("exact", 16, 1000, 50, [50_000] * 10, 1.12),   # short layouts
     ("exact", 3, 20000, 64, [3_000_000] * 10, 1.12), ("chunk", 8, 20000, 64, [3_000_000] * 10, 1.2),   # the all-learner pass
+    ("chunk", 3, 600, 64, [300_000] * 10, 1.2),                                                   # the chunk-wise step in one launch
 ])
 def test_small_tensors_side_by_side(select, n, count, size, large, factor):
     """Many small tensors in front of the large ones: no slower than with the same tensors mixed, whose parts, chunks and
