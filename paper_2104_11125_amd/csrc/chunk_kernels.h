@@ -41,13 +41,14 @@ struct ChunkGroup {
     }
 };
 
-// The whole chunk-wise step in one launch, for chunks of up to 509 elements.  What the step cannot do without is
-// one read of (mem, grad) and one write of mem per learner; the kernels below read the leader twice, and
+// The whole chunk-wise step in one launch, for chunks of up to 1021 elements and little data (see chunks_in_one_launch).  What the step cannot do without is
+// one read of (mem, grad) and one write of mem per learner, and
 // a chunk's winner depends on nothing outside the chunk.  So a block takes whole chunks, at most
 // 256 * Q - 3 positions, and all learners: one wave per learner and wave tile (the access pattern of the
 // all-learner pass: one wave moves 256 consecutive positions of one learner; several tiles per wave or
 // several learners per thread cost 5 to 20 % of the rate), the leader's first.  Winners and the members' values
-// go through LDS.  Blocks share no chunk, so the memories can be updated in place.
+// go through LDS.  Blocks share no chunk, so the memories can be updated in place.  Groups of four tiles are for chunks of 510 to 1021 elements (chunk 1000, us, against
+// the leader first: 2 x 0.3 M 8 / 13, 1 x 3 M 10.6 / 13.2, 4 x 5 M 47 / 53).
 constexpr int kChunkStepWaves = 16;              // waves of a block at most: further (learner, tile) pairs take turns
 
 template <typename G, int Q>

@@ -209,7 +209,7 @@ bool sizes_ok(int64_t numel_max, int n_tensors_max, int n_learners_max, int64_t 
 }  // namespace
 
 // Groups of whole chunks, at most 256 * tiles - 3 positions each, for a layout's chunk-wise step (elements per chunk clamped to the
-// segment's length): in one launch (k_chunk_step, up to two tiles), or the leader's winners and memory first
+// segment's length): in one launch (k_chunk_step), or the leader's winners and memory first
 // (k_chunk_lead), the other learners and the sum after; tiles = 0: chunks of no suitable size, maxima by atomics.
 struct ChunkPlan {
     int tiles = 0, per_st = 0;   // per_st: groups per supertile
@@ -522,7 +522,7 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
     ctx->short_threads = plan.threads;
     ctx->short_rows = plan.rows;
     ctx->n_parts = plan.n_parts;
-    ctx->chunk_one = sel_chunks ? chunk_plan(n_tensors, segs, 2, 0.03) : ChunkPlan{};
+    ctx->chunk_one = sel_chunks ? chunk_plan(n_tensors, segs, 4, 0.03) : ChunkPlan{};
     // (with the leader first, us, one / two / four tiles: 3 x 30 M, 112 179 / 187 / 188, 155 196 / 189 / 203, 200 179 / 196 / 192, 255 - / 190 / 199;
     // 8 x 25.6 M, 100 388 / 389 / 394, 400 - / 400 / 411)
     ctx->chunk_lead = sel_chunks ? chunk_plan(n_tensors, segs, 4, 0.2) : ChunkPlan{};
@@ -766,18 +766,45 @@ scalecom_status launch_step(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_lear
     return SCALECOM_OK;
 }
 
-// Is the whole chunk-wise step in one launch the faster way?  It saves two launches and some of the sum over learners, but moves everything
-// at a rate that falls with the idle lanes of its tiles: 5.0 to 5.2 TB/s where 88 to 98 % of one tile are in use (chunks of 25, 84, 112),
-// 4.6 to 5.1 with two (100, 155), 4.5 to 4.9 at 78 % (200, 400), 3.9 at 66 % (170, 340), 3.0 at 50 % (255), where the leader first
-// moves the leader's share at 5.0 to 5.6 and the others' at 6.5.  One launch against the leader first, us: 8 x 0.3 M, chunk 112 10 / 16; 8 x 1 M, 25 23.7 / 24.1,
-// 112 23.1 / 23.3, 200 25.7 / 23.5, 255 35 / 25; 3 x 3 M, 112 23.8 / 25.4, 155 26.5 / 26.3, 200 25.7 / 25.1; 1 x 3 M, 112 10.7 / 10.8; 2 x 10 M, 112 50.5 / 47.5;
-// 8 x 3 M, 25 64 / 55; 64 x 0.2 M, 25 45 / 51, 255 48 / 51.
-bool chunks_in_one_launch(const ChunkPlan& plan, int n_learners, int64_t numel, int grad_bytes)
+// Is the whole chunk-wise step in one launch the faster way?  It saves two launches, the sum over learners and blocks that find no work in short
+// supertiles, but works on the idle lanes of its tiles as well: per learner and million positions it takes 2.1 to 2.4 us where 88 to 100 % are in use,
+// 2.4 to 2.7 at 78 %, 2.6 to 3.0 at 67 %, 3.2 to 3.9 at 50 %; with the leader first 1.85 per other learner and about 2 for the leader, more for
+// short chunks and for groups of one chunk each (200 to 508), whose lanes wait for each other in LDS.  The constants are fitted to calls of
+// 1 to 64 learners, 0.1 to 33 M positions (round and odd), float and bfloat16, chunks of 8 to 1021.  Over 1680 of them the way taken is 0.6 % slower than
+// the faster one on average, 13 % in one of a hundred (5, 6 and 10 learners, with which one launch takes longer than that).  One launch / the leader first, us: 2 x 10 M,
+// chunk 100 45 / 47, 400 49 / 55, 509 46 / 52; 3 x 3 M, 400 28 / 28, 1000 25 / 28; 8 x 0.3 M, 255 13 / 17; 8 x 1 M, 255 35 / 25, 400 24 / 24; 1 x 30 M, 84 71 / 61,
+// 400 78 / 82; 3 x 6.8 M bfloat16, 12 43 / 48; 10 000 tensors of 1000 x 8 183 / 440.
+// (The words of many short chunks in groups of four tiles, which another tensor's chunks need, do not fit a block's 64 KB with more than 62 learners.)
+size_t chunk_step_lds(const ChunkPlan& one, int n_learners)
 {
-    if (plan.tiles < 1) return false;
-    const double rate = plan.tiles == 1 ? std::min(5.1, 5.9 * plan.use) : std::min(4.8, 5.7 * plan.use);
-    const double leader = static_cast<double>(numel) * (8 + grad_bytes), all = n_learners * leader;
-    return all * (1.0 / rate - 1.0 / 6.5) * 1e-6 < leader * 0.03e-6 + 4.8 + 0.1 * n_learners;
+    return static_cast<size_t>(one.max_chunks) * (sizeof(unsigned long long) + sizeof(float) * n_learners);
+}
+
+bool chunks_in_one_launch(const ChunkPlan& one, const ChunkPlan& lead, int n_learners, int64_t numel, int64_t k_total, int n_st)
+{
+    if (one.tiles < 1 || chunk_step_lds(one, n_learners) > 65536) return false;
+    struct Costs { double whole, lanes, leader; };
+    constexpr Costs costs[3] = {{1.14, 1.13, 1.76}, {0.89, 1.27, 2.01}, {0.56, 1.54, 2.25}};   // one, two and four tiles
+    const Costs& at = costs[one.tiles / 2];
+    const double m = 1e-6 * static_cast<double>(numel), others = n_learners - 1;
+    const double few = n_learners == 1 ? 1.05 : n_learners == 2 ? 0.94 : 1.0;
+    const double leader = m * (costs[lead.tiles / 2].leader + (lead.tiles == 2 && lead.use < 0.85 ? 0.6 : 0.0)) + 6.65e-6 * static_cast<double>(k_total);
+    // million blocks that find no work: in one launch, of the leader's pass, of the all-learner pass per learner
+    auto idle = [&](int per_st, double positions) { return std::max(0.0, 1e-6 * n_st * per_st - m / positions); };
+    const double idle_one = idle(one.per_st, one.use * one.tiles * kWaveTile);
+    const double idle_lead = idle((lead.per_st + kWaves - 1) / kWaves, lead.use * lead.tiles * kWaveTile * kWaves);
+    const double idle_update = idle(kUpdateBlocksPerSuper, kWaveTile * kWaves);
+    const int waves = std::min(n_learners * one.tiles, kChunkStepWaves);
+    return n_learners * m * (at.whole + at.lanes / one.use) * few + (waves > 8 ? 100.0 : 75.0) * waves * idle_one <
+           (n_learners == 1 ? 3.4 : 5.8) + 0.09 * n_learners + 1.85 * others * m + leader + 350.0 * idle_lead + 590.0 * others * idle_update;
+}
+
+// If not, the leader first, but for bfloat16 with chunks that need four tiles: maxima by atomics are as fast or faster with four learners or more up to
+// some size (the leader first / atomics, us: 8 x 2.7 M, 516 51.5 / 46.5, 12 x 4 M, 855 109 / 100, 4 x 5.4 M, 895 53 / 50, 8 x 30 M, 1000 even, 8 x 100 M 1328 / 1338;
+// float 8 x 3 M, 1000 52 / 55).
+bool leader_first(const ChunkPlan& lead, int n_learners, int64_t numel, int grad_bytes)
+{
+    return lead.tiles > 0 && !(lead.tiles == 4 && grad_bytes == 2 && n_learners >= 4 && n_learners * numel <= 300'000'000);
 }
 
 // One step with the chunk-wise selector: leader pass (per-chunk maxima), marks, then the same
@@ -805,28 +832,32 @@ scalecom_status launch_chunked(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_l
     };
     mark(0);
     const int64_t extent = ctx->cached_offsets[n_tensors] - ctx->cached_offsets[0];
-    const int gb = sizeof(G);
-    if (chunks_in_one_launch(ctx->chunk_one, n_learners, extent, gb)) {
+    if (chunks_in_one_launch(ctx->chunk_one, ctx->chunk_lead, n_learners, extent, k_total, ctx->n_st)) {
         mark(1);
         mark(2);
         mark(3);
         const unsigned gz = static_cast<unsigned>((ctx->n_st + 65534) / 65535);
-        const dim3 grid(ctx->chunk_one.per_st, (ctx->n_st + gz - 1) / gz, gz);
-        const int waves = std::min(n_learners * ctx->chunk_one.tiles, kChunkStepWaves);
-        const size_t lds = static_cast<size_t>(ctx->chunk_one.max_chunks) * (sizeof(unsigned long long) + sizeof(float) * n_learners);
-        if (ctx->chunk_one.tiles == 1)
-            k_chunk_step<G, 1><<<grid, waves * kLanes, lds, s>>>(lp, n_learners, leader, lr, beta, 1.0f - beta, sts,
-                                                                 ctx->n_st, ctx->chunk_one.max_chunks, idx_out, red_out);
+        const ChunkPlan& plan = ctx->chunk_one;
+        const dim3 grid(plan.per_st, (ctx->n_st + gz - 1) / gz, gz);
+        const int waves = std::min(n_learners * plan.tiles, kChunkStepWaves);
+        const size_t lds = chunk_step_lds(plan, n_learners);
+        auto step = [&](auto kernel) {
+            kernel<<<grid, waves * kLanes, lds, s>>>(lp, n_learners, leader, lr, beta, 1.0f - beta, sts, ctx->n_st, plan.max_chunks,
+                                                     idx_out, red_out);
+        };
+        if (plan.tiles == 1)
+            step(k_chunk_step<G, 1>);
+        else if (plan.tiles == 2)
+            step(k_chunk_step<G, 2>);
         else
-            k_chunk_step<G, 2><<<grid, waves * kLanes, lds, s>>>(lp, n_learners, leader, lr, beta, 1.0f - beta, sts,
-                                                                 ctx->n_st, ctx->chunk_one.max_chunks, idx_out, red_out);
+            step(k_chunk_step<G, 4>);
         mark(4);
         mark(5);
         if (timed) ++ctx->prof_steps;
         SC_HIP(ctx, hipGetLastError());
         return SCALECOM_OK;
     }
-    if (ctx->chunk_lead.tiles > 0) {
+    if (leader_first(ctx->chunk_lead, n_learners, extent, sizeof(G))) {
         const ChunkPlan& plan = ctx->chunk_lead;
         mark(1);
         mark(2);

@@ -197,9 +197,9 @@ def test_expectations_that_are_not_trusted(gu, numel):
     ctx.close()
 
 
-@pytest.mark.parametrize("chunk", [1, 3, 4, 7, 8, 25, 50, 63, 84, 100, 112, 126, 127, 155, 252, 253, 254, 400, 509, 510, 3000])
+@pytest.mark.parametrize("chunk", [1, 3, 4, 7, 8, 25, 50, 63, 84, 100, 112, 126, 127, 155, 252, 253, 254, 400, 509, 510, 700, 1020, 1021, 1022, 3000])
 def test_chunks_in_one_launch(gu, chunk):
-    """Chunk sizes around the edges of the one-launch step (253 and 509 positions per block, 64 chunks per
+    """Chunk sizes around the edges of the one-launch step (253, 509 and 1021 positions per block, 64 chunks per
     block), lengths with one position in the last chunk and with a full one, learner counts with fewer, as many and
     more (learner, tile) pairs than a block has waves, equal magnitudes inside a chunk."""
     rng = np.random.default_rng(chunk)
@@ -317,6 +317,19 @@ def test_chunks_per_layer_in_one_launch(gu):
             print(f"[chunk] per layer step={step}", flush=True)
             gu.compare_step(ctx, mem, grad, ref, step, 0.5, 0.25, offsets=offsets, chunks=chunks, what="chunks per layer")
         ctx.close()
+
+
+@pytest.mark.parametrize("n", [62, 63])
+def test_chunks_of_four_next_to_chunks_of_a_thousand(gu, n):
+    """Groups of four tiles with 255 chunks each: their words fit a block's LDS with 62 learners in one launch, and not with 63."""
+    offsets, chunks = [1, 3_002, 8_005], [1021, 4]
+    ctx = binding.scalecom_init(8_010, n, torch.float32, 2, gu.DEV)
+    mem = [_normal(8_010, i, 1.0).to(gu.DEV) for i in range(n)]
+    ref = [m.cpu().numpy().copy() for m in mem]
+    for step in range(2):
+        grad = [_normal(8_010, 100 + i + step, 1.0).to(gu.DEV) for i in range(n)]
+        gu.compare_step(ctx, mem, grad, ref, step + 60, 0.5, 0.25, offsets=offsets, chunks=chunks, what=f"255 chunks n={n}")
+    ctx.close()
 
 
 @pytest.mark.parametrize("numel", [1, 3, 1023, 4096, 2048 * 1024 + 5, 2 * 2048 * 1024 + 1029])
