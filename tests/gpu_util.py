@@ -82,6 +82,23 @@ def compare_step(ctx, mem_dev, grad_dev, mem_ref, step, beta, lr, k=None, offset
     return idx, red
 
 
+def chunk_route(ctx, mem, grad, offsets, chunks):
+    """The way a chunk-wise step on these buffers takes, seen from what it leaves in the workspace: nothing if it is one launch, the staged values of all
+    learners (one run of words) with the leader first, the masks in front of them too if the maxima are found by atomics.  The memories are copied."""
+    mem = [m.clone() for m in mem]
+    k_total = sum(-(-(b - a) // c) for a, b, c in zip(offsets, offsets[1:], chunks))
+    words = ctx.workspace[:ctx.workspace.numel() // 4 * 4].view(torch.int32)
+    ctx.scalecom_step_layers_chunked(mem, grad, offsets, chunks, 0.5, 1.0, 0)      # (tables uploaded, scratch cleared)
+    torch.cuda.synchronize()
+    before = words.clone()
+    ctx.scalecom_step_layers_chunked(mem, [g.flip(0) for g in grad], offsets, chunks, 0.5, 3.0, 0)
+    torch.cuda.synchronize()
+    changed = torch.nonzero(words != before).flatten()
+    if changed.numel() == 0:
+        return "one launch"
+    return "leader first" if int(changed[-1] - changed[0]) < len(mem) * k_total else "atomics"
+
+
 def run_workload(w: workloads.Workload, steps=None, what=None):
     """The workload's recipe for `steps` iterations, memory carried, all outputs compared."""
     steps = w.steps if steps is None else steps

@@ -42,9 +42,23 @@ def test_many_learners(gu):
 
 @pytest.mark.parametrize("n", [8, 9, 17])
 def test_learner_counts_around_the_launch_size(gu, n):
-    """The all-learner pass goes over eight learners per launch: one launch exactly, one more for a
-    single learner, and two full ones plus one; long enough for leaders out of every launch."""
+    """As many learners as a short step has in flight at once (eight), one more, and two such turns plus one; every learner as leader."""
     gu.run_workload(workloads.scaled(workloads.by_name("tiny"), 30_011, n_learners=n, steps=n + 2))
+
+
+@pytest.mark.parametrize("n", [8, 9, 17, 64])
+def test_learner_counts_on_the_long_path(gu, n):
+    """The all-learner pass with all learners in one launch: few and many, the first, a middle and the last one as leader."""
+    numel = 30_011
+    offsets, ks = gu.long_layout([0, numel], [300])
+    gen = torch.Generator(device=gu.DEV).manual_seed(n)
+    ctx = binding.scalecom_init(offsets[-1], n, torch.float32, len(ks), gu.DEV, k_max=300)
+    mem = [torch.randn(offsets[-1], device=gu.DEV, generator=gen) for _ in range(n)]
+    ref = [m.cpu().numpy().copy() for m in mem]
+    for step in (0, n // 2, n - 1):
+        grad = [torch.randn(offsets[-1], device=gu.DEV, generator=gen) for _ in range(n)]
+        gu.compare_step(ctx, mem, grad, ref, step, 0.25, 0.5, offsets=offsets, ks=ks, what=f"long path n={n}")
+    ctx.close()
 
 
 def test_single_learner(gu):

@@ -211,53 +211,60 @@ def test_chunks_in_one_launch(gu, chunk):
         for step in range(2):
             grad = [torch.from_numpy(np.round(rng.standard_normal(numel) * 8).astype(np.float32)).to(gu.DEV).to(dtype)
                     for _ in range(n)]
+            if step == 0 and chunk > 1:                          # (chunks of one: the masks never change)
+                assert gu.chunk_route(ctx, mem, grad, [0, numel], [chunk]) == ("one launch" if 4 <= chunk <= 1021 else "atomics")
             print(f"[chunk] chunk={chunk} n={n} numel={numel} step={step}", flush=True)
             gu.compare_step(ctx, mem, grad, ref, step + n // 2, 0.25, 0.5, chunk=chunk, what=f"chunk={chunk} n={n} numel={numel}")
         ctx.close()
 
 
-@pytest.mark.parametrize("chunk", [4, 5, 25, 63, 84, 100, 112, 126, 127, 155, 170, 254, 255, 450, 509, 510, 1000, 1022])
+@pytest.mark.parametrize("chunk", [1, 3, 4, 5, 25, 63, 84, 100, 112, 126, 127, 155, 170, 254, 255, 450, 509, 510, 1000, 1022, 2000])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_winners_first(gu, chunk, dtype):
-    """Eight learners of 4 M positions are too much for one launch: the winners first, in groups of one tile (chunk 4 to 84),
-    two (100, 155) and four (112 to 127), blocks of the update with up to 257 chunks, and maxima by atomics (lanes idle, or few
-    chunks per group); equal magnitudes inside chunks, whole vector and tensors at odd starts."""
+    """Eight learners of 4 M positions are too much for one launch: the leader first in groups of one tile, two (100, 155, 170, 254 to 509) and four (510, 1000),
+    blocks of the update with up to 257 chunks; maxima by atomics for shorter and longer chunks, and from 510 on with bfloat16;
+    equal magnitudes inside chunks, whole vector and tensors at odd starts."""
     n, numel = 8, 4_000_003
     gen = torch.Generator(device=gu.DEV).manual_seed(chunk)
     mem = [torch.round(torch.randn(numel, device=gu.DEV, generator=gen) * 4) for _ in range(n)]
     ref = [m.cpu().numpy().copy() for m in mem]
     offsets = [3, 3 + 70_001, 3 + 70_001, 70_005, 2_000_000, numel - 2]
     chunks = [chunk] * (len(offsets) - 1)
+    route = "leader first" if 4 <= chunk <= (1021 if dtype == torch.float32 else 509) else "atomics"
     ctx = binding.scalecom_init(numel, n, dtype, len(chunks), gu.DEV)
     for step in range(2):
         grad = [torch.round(torch.randn(numel, device=gu.DEV, generator=gen) * 8).to(dtype) for _ in range(n)]
-        print(f"[chunk] winners first chunk={chunk} {dtype} step={step}", flush=True)
+        print(f"[chunk] much data chunk={chunk} {dtype} step={step}", flush=True)
         if step == 0:
-            gu.compare_step(ctx, mem, grad, ref, 3, 0.25, 0.5, chunk=chunk, what=f"winners chunk={chunk}")
+            assert chunk == 1 or gu.chunk_route(ctx, mem, grad, [0, numel], [chunk]) == route   # (chunks of one: the masks never change)
+            gu.compare_step(ctx, mem, grad, ref, 3, 0.25, 0.5, chunk=chunk, what=f"much data chunk={chunk}")
         else:
-            gu.compare_step(ctx, mem, grad, ref, 6, 0.25, 0.5, offsets=offsets, chunks=chunks, what=f"winners per tensor chunk={chunk}")
+            assert chunk == 1 or gu.chunk_route(ctx, mem, grad, offsets, chunks) == route
+            gu.compare_step(ctx, mem, grad, ref, 6, 0.25, 0.5, offsets=offsets, chunks=chunks, what=f"much data per tensor chunk={chunk}")
     ctx.close()
 
 
 @pytest.mark.parametrize("n,numel,chunk", [(2, 400_003, 1000), (8, 300_001, 600), (4, 500_001, 900), (64, 20_001, 25), (33, 9_001, 500)])
 def test_chunks_with_little_data(gu, n, numel, chunk):
-    """Little data: winners first in groups of few chunks too, and one launch with many learners."""
+    """Little data in one launch: groups of four tiles with one chunk or two, and many learners."""
     ctx = binding.scalecom_init(numel, n, torch.float32, 1, gu.DEV)
     mem = [_normal(numel, 3 * i, 1.0).to(gu.DEV) for i in range(n)]
     ref = [m.cpu().numpy().copy() for m in mem]
     for step in range(2):
         grad = [_normal(numel, 90 * step + i, 1.0).to(gu.DEV) for i in range(n)]
+        assert step == 1 or gu.chunk_route(ctx, mem, grad, [0, numel], [chunk]) == "one launch"
         gu.compare_step(ctx, mem, grad, ref, step + n - 1, 0.5, 0.5, chunk=chunk, what=f"chunk={chunk} n={n}")
     ctx.close()
 
 
-@pytest.mark.parametrize("chunk", [25, 112, 253, 254, 255, 509, 510, 1021])
+@pytest.mark.parametrize("chunk", [25, 112, 253, 254, 255, 509, 510, 700, 1021])
 @pytest.mark.parametrize("n", [1, 2, 5])
 def test_leader_updated_with_its_winners(gu, n, chunk):
     """The leader first, its memory updated in the pass that finds its winners: every learner as leader (first, middle, last, the only
-    one), chunks at the edges of one, two and four tiles, equal magnitudes and zeros of both signs, values that are not finite on members and
+    one), chunks at the edges of one, two and four tiles (with one or two learners those that fill four are always one launch, 700 are not), equal magnitudes
+    and zeros of both signs, values that are not finite on members and
     beside them, plain error feedback; with tensors that start and end inside a group of four positions."""
-    numel = max(48_000_000 // n, 17_000_000) if chunk < 200 and n < 5 else 4_000_001
+    numel = {1: 24_000_001, 2: 40_000_001, 5: 10_000_001}[n]
     gen = torch.Generator(device=gu.DEV).manual_seed(chunk + n)
     mem = [torch.round(torch.randn(numel, device=gu.DEV, generator=gen) * 2) * 0.5 for _ in range(n)]
     grad = [torch.round(torch.randn(numel, device=gu.DEV, generator=gen) * 4) for _ in range(n)]
@@ -268,11 +275,30 @@ def test_leader_updated_with_its_winners(gu, n, chunk):
         mem[i][numel // 2:numel // 2 + 2 * chunk] = -0.0
     ref = [m.cpu().numpy().copy() for m in mem]
     offsets = [1, 1 + 5 * chunk, numel // 3 + 2, numel - 3]
-    ctx = binding.scalecom_init(numel, n, torch.float32, 3, gu.DEV)
+    ctx = binding.scalecom_init(numel, n, torch.float32, 3, gu.DEV, k_max=numel // chunk + 3)
+    route = "one launch" if n < 3 and chunk in (510, 1021) else "leader first"
+    assert gu.chunk_route(ctx, mem, grad, [0, numel], [chunk]) == route
+    assert gu.chunk_route(ctx, mem, grad, offsets, [chunk] * 3) == route
     for step in range(n):
         print(f"[chunk] leader first n={n} numel={numel} chunk={chunk} step={step}", flush=True)
         gu.compare_step(ctx, mem, grad, ref, step, 1.0 if step == 0 else 0.25, 0.5, chunk=chunk, what=f"leader first chunk={chunk}")
     gu.compare_step(ctx, mem, grad, ref, n - 1, 0.25, 0.5, offsets=offsets, chunks=[chunk] * 3, what=f"leader first per tensor chunk={chunk}")
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [9, 17])
+def test_leader_first_with_many_learners(gu, n):
+    """More learners than a launch of the all-learner pass once took (eight), with the first, a middle and the last one as leader."""
+    numel, chunk = 3_000_001, 112
+    gen = torch.Generator(device=gu.DEV).manual_seed(n)
+    mem = [torch.randn(numel, device=gu.DEV, generator=gen) for _ in range(n)]
+    ref = [m.cpu().numpy().copy() for m in mem]
+    ctx = binding.scalecom_init(numel, n, torch.float32, 1, gu.DEV, k_max=numel // chunk + 1)
+    for step in (0, n // 2, n - 1):
+        grad = [torch.randn(numel, device=gu.DEV, generator=gen) for _ in range(n)]
+        print(f"[chunk] many learners n={n} step={step}", flush=True)
+        assert step > 0 or gu.chunk_route(ctx, mem, grad, [0, numel], [chunk]) == "leader first"
+        gu.compare_step(ctx, mem, grad, ref, step, 0.25, 0.5, chunk=chunk, what=f"many learners n={n}")
     ctx.close()
 
 
@@ -296,6 +322,7 @@ def test_supertiles_in_turn(gu, count, dtype):
         if chunk is None:
             gu.compare_step(ctx, mem, grad, ref, step, 0.25, 0.5, offsets=offsets, ks=ks, what="in turn")
         else:
+            assert gu.chunk_route(ctx, mem, grad, offsets, [chunk] * len(sizes)) == "leader first"
             gu.compare_step(ctx, mem, grad, ref, step, 0.25, 0.5, offsets=offsets, chunks=[chunk] * len(sizes), what=f"in turn chunk={chunk}")
     ctx.close()
 
@@ -328,6 +355,7 @@ def test_chunks_of_four_next_to_chunks_of_a_thousand(gu, n):
     ref = [m.cpu().numpy().copy() for m in mem]
     for step in range(2):
         grad = [_normal(8_010, 100 + i + step, 1.0).to(gu.DEV) for i in range(n)]
+        assert gu.chunk_route(ctx, mem, grad, offsets, chunks) == ("one launch" if n == 62 else "leader first")
         gu.compare_step(ctx, mem, grad, ref, step + 60, 0.5, 0.25, offsets=offsets, chunks=chunks, what=f"255 chunks n={n}")
     ctx.close()
 
