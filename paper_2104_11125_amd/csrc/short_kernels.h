@@ -881,20 +881,19 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
     const int64_t begin = d.begin, end = d.end;
     const uint32_t k = static_cast<uint32_t>(d.k);
     float4 lm, lg;
-    float4 m[kAtOnce];
+    float4 m[kAtOnce];                                      // the first learners'
     Streamed<G> g[kAtOnce];
-    auto load_one = [&](int j, int i, int64_t p0) {         // for lanes whose four positions all belong to the segment
-        m[j] = load4(lp.mem[i] + p0);
-        g[j] = stream4(static_cast<const G*>(lp.grad[i]) + p0);
-    };
     const int64_t first = static_cast<int64_t>(d.a0) + t * kVec;
     const ShortFound f = short_search<T, P>(lds, d, used, counts, keys, [&]() {
         leader_load<true>(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), first, begin, end, lm, lg);
     }, [&]() {
         if (kAhead && first >= begin && first + 3 < end) {
 #pragma unroll
-            for (int j = 0; j < kAtOnce; ++j)
-                if (j < n_learners) load_one(j, j, first);  // uniform
+            for (int j = 0; j < kAtOnce; ++j) {
+                if (j >= n_learners) continue;              // uniform
+                m[j] = load4(lp.mem[j] + first);
+                g[j] = stream4(static_cast<const G*>(lp.grad[j]) + first);
+            }
         }
     });
     short_record(d, used[d.seg], f, preds, lead_mine, stats);
@@ -973,13 +972,19 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
                     if (j < n_learners) learner(j, m[j], widen4(g[j]));
                 i = kAtOnce;
             }
-            for (; i + kAtOnce <= n_learners; i += kAtOnce) {
+            for (; i < n_learners; i += kAtOnce) {          // (registers of the turn's own: kept for the next row they cost one learner 6 %)
+                float4 m[kAtOnce];
+                Streamed<G> g[kAtOnce];
 #pragma unroll
-                for (int j = 0; j < kAtOnce; ++j) load_one(j, i + j, p0);
+                for (int j = 0; j < kAtOnce; ++j) {
+                    if (i + j >= n_learners) continue;      // uniform
+                    m[j] = load4(lp.mem[i + j] + p0);
+                    g[j] = stream4(static_cast<const G*>(lp.grad[i + j]) + p0);
+                }
 #pragma unroll
-                for (int j = 0; j < kAtOnce; ++j) learner(i + j, m[j], widen4(g[j]));
+                for (int j = 0; j < kAtOnce; ++j)
+                    if (i + j < n_learners) learner(i + j, m[j], widen4(g[j]));
             }
-            for (; i < n_learners; ++i) learner(i, load4(lp.mem[i] + p0), load4(static_cast<const G*>(lp.grad[i]) + p0));
         } else {
             for (int i = 0; i < n_learners; ++i)
                 learner(i, load_guarded(lp.mem[i], p0, begin, end, false),
