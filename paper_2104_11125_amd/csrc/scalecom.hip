@@ -233,6 +233,7 @@ struct scalecom_ctx {
     int n_st = 0, n_chunks = 0, n_hblocks = 0, n_small = 0;
     bool eighths = true;             // eighths of the layout's supertiles hold alike (see ensure_tables)
     int short_threads = 0, short_rows = 0, n_parts = 0;   // the layout's ShortPlan
+    bool short_by_eighths = false;   // its steps' blocks: see short_eighths
     ChunkPlan chunk_one, chunk_lead;      // the layout's chunk-wise step in one launch, and with the leader first
     // segments of one supertile are searched by a kernel of their own, on a second stream beside the
     // leader pass (contexts for more than one tensor only)
@@ -330,6 +331,25 @@ ShortPlan short_parts(const WsLayout& l, int n_tensors, const int64_t* offsets)
         }
     }
     return ShortPlan{};
+}
+
+// Does a short step give each XCD an eighth of the parts (a segment's blocks read the same counts), or go over them in turn?  Eighths where the parts are many and
+// of one row, as long as no eighth holds more than 1.1 times its share.  us a step, f32, in turn / eighths: 67 tensors, 0.45 M x 5 18.1 / 15.4, 51 tensors, 0.5 M x 32
+// 56.8 / 52.0, 44 tensors, 1.3 M x 3 23.5 / 19.6, 148 tensors, 2.5 M x 2 47.9 / 41.6; from there on even.  Fewer parts gain nothing (4 x 1 M 20.1 / 20.5), nor do those of two rows, where the long searches of
+// a large segment's blocks on one or two XCDs cost more (22 tensors, 2 M x 3 41.5 / 47.1); where eighths do not hold alike, 600 tensors of 64 and one of 1 M x 16 67 / 123.
+// The diagnostic, nearly all search, goes over the parts in turn: 23 tensors, 7.3 M x 2 220 / 279, 33 tensors, 2.1 M x 8 91 / 106.
+bool short_eighths(const ShortPlan& plan, const PartDesc* parts)
+{
+    if (plan.rows > 1 || plan.n_parts <= kShortSegParts) return false;
+    int64_t most = 0, all = 0;
+    for (int32_t x = 0, j = 0; x < kXcds; ++x) {
+        int64_t eighth = 0;
+        for (int32_t i = (plan.n_parts + kXcds - 1 - x) / kXcds; i > 0; --i, ++j)
+            eighth += std::min<int64_t>(parts[j].end, parts[j].a0 + plan.part()) - std::max(parts[j].begin, parts[j].a0);
+        most = std::max(most, eighth);
+        all += eighth;
+    }
+    return 10 * kXcds * most <= 11 * all;
 }
 
 // The smallest number of tiles, up to tiles_max, that holds the layout's chunks; two instead of one if that fills more of the lanes by
@@ -437,44 +457,22 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
         if (count == 1 && ks[s] > 0 && ctx->side) small[n_small++] = hblocks[n_hb - 1];
     }
     const ShortPlan plan = sel_chunks ? ShortPlan{} : short_parts(ctx->lay, n_tensors, offsets);
+    bool short_by_eighths = false;
     if (plan.threads > 0) {
         PartDesc* parts = reinterpret_cast<PartDesc*>(
             ctx->pinned + sm_off + align_up(sizeof(HistBlock) * static_cast<size_t>(ctx->n_tensors_max), 256));
         const int64_t part = plan.part();
-        PartDesc sorted[kShortPartsMax];                     // (50 KB with the two lists below)
         int32_t n = 0;
         for (int s = 0; s < n_tensors; ++s) {
             if (segs[s].end == segs[s].begin) continue;
             const int64_t a_first = segs[s].begin & ~(kVec - 1);
             const int32_t count = static_cast<int32_t>((segs[s].end - a_first + part - 1) / part);
             for (int32_t j = 0; j < count; ++j)
-                sorted[n + j] = PartDesc{s, static_cast<int32_t>(a_first + j * part), segs[s].begin, segs[s].end,
-                                         segs[s].k, segs[s].out_base, n, count};
+                parts[n + j] = PartDesc{s, static_cast<int32_t>(a_first + j * part), segs[s].begin, segs[s].end,
+                                        segs[s].k, segs[s].out_base, n, count};
             n += count;
         }
-        // The order of the blocks.  Where parts are many or large, an eighth of them to each XCD (a segment's parts read the same counts), as long as no
-        // eighth holds much more than the others; else an eighth of the parts that are filled by three quarters or more, and the others in turn behind
-        // them.  us a step, f32, parts in turn / eighths of all / of the filled ones: even layouts, 60 tensors of 20 000 x 8 learners 31.7 / 29.5 / 29.7, 120 of 64 to
-        // 50 000 x 4 20.6 / 17.4 / 19.2 (fullest eighth 1.04 of its share); 300 of 3000 before 3 of 400 000 x 8 58.2 / 59.7 / 55.6 (1.15), 600 of 64 and one of 1 M
-        // x 16 67 / 123 / 71 (3.3), 1200 of 700 and 100 of 2000 x 8 35.6 / 38.7 / 35.3 (1.5).  Smaller vectors gain nothing (4 x 1 M 20.1 / 20.5, 2 x 0.5 M 13.8 / 14.1).
-        const bool by_xcd = plan.rows == 2 || n > kShortSegParts;
-        auto held = [&](int32_t j) { return std::min<int64_t>(sorted[j].end, sorted[j].a0 + part) - std::max(sorted[j].begin, sorted[j].a0); };
-        int64_t most = 0, all = 0;
-        for (int32_t x = 0, j = 0; x < kXcds; ++x) {
-            int64_t eighth = 0;
-            for (int32_t i = (n + kXcds - 1 - x) / kXcds; i > 0; --i) eighth += held(j++);
-            most = std::max(most, eighth);
-            all += eighth;
-        }
-        const bool even = 10 * kXcds * most <= 11 * all;
-        int32_t first[kShortPartsMax], then[kShortPartsMax];
-        uint32_t n_first = 0, n_then = 0;
-        for (int32_t j = 0; j < n; ++j) {
-            const bool filled = 4 * held(j) >= 3 * part;
-            if (by_xcd && (even || filled)) first[n_first++] = j; else then[n_then++] = j;
-        }
-        for (uint32_t b = 0; b < static_cast<uint32_t>(n); ++b)
-            parts[b] = sorted[b < n_first ? first[piece_by_xcd(b, n_first)] : then[b - n_first]];
+        short_by_eighths = short_eighths(plan, parts);
         SC_HIP(ctx, hipMemcpyAsync(ctx->ws + ctx->lay.parts, parts, sizeof(PartDesc) * plan.n_parts, hipMemcpyHostToDevice,
                                    ctx->stream));
     }
@@ -522,6 +520,7 @@ scalecom_status ensure_tables(scalecom_ctx* ctx, int n_tensors, const int64_t* o
     ctx->short_threads = plan.threads;
     ctx->short_rows = plan.rows;
     ctx->n_parts = plan.n_parts;
+    ctx->short_by_eighths = short_by_eighths;
     ctx->chunk_one = sel_chunks ? chunk_plan(n_tensors, segs, 4, 0.03) : ChunkPlan{};
     // (with the leader first, us, one / two / four tiles: 3 x 30 M, 112 179 / 187 / 188, 155 196 / 189 / 203, 200 179 / 196 / 192, 255 - / 190 / 199;
     // 8 x 25.6 M, 100 388 / 389 / 394, 400 - / 400 / 411)
@@ -698,12 +697,13 @@ void launch_short_as(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learners, f
     uint32_t* keys = reinterpret_cast<uint32_t*>(ws + l.short_path.keys);
     unsigned long long* stats = reinterpret_cast<unsigned long long*>(ws + l.stats);
     k_short_collect<G, T, R><<<ctx->n_parts, T, 0, ctx->stream>>>(lp.mem[leader], static_cast<const G*>(lp.grad[leader]), lr,
-                                                               parts, preds, lead_mine, used, counts, keys, stats);
+                                                               parts, ctx->short_by_eighths, preds, lead_mine, used, counts, keys,
+                                                               stats);
     mark(1);
     mark(2);
     mark(3);
     auto step = [&](auto kernel) {
-        kernel<<<ctx->n_parts, T, 0, ctx->stream>>>(lp, n_learners, leader, lr, beta, 1.0f - beta, parts, preds, lead_mine, used,
+        kernel<<<ctx->n_parts, T, 0, ctx->stream>>>(lp, n_learners, leader, lr, beta, 1.0f - beta, parts, ctx->short_by_eighths, preds, lead_mine, used,
                                                     counts, keys, idx_out, red_out, stats);
     };
     // few learners and more waves than four per SIMD on 256 compute units: registers for six (blocks of 1024 threads are few)
@@ -807,8 +807,8 @@ bool leader_first(const ChunkPlan& lead, int n_learners, int64_t numel, int grad
     return lead.tiles > 0 && !(lead.tiles == 4 && grad_bytes == 2 && n_learners >= 4 && n_learners * numel <= 300'000'000);
 }
 
-// One step with the chunk-wise selector: leader pass (per-chunk maxima), marks, then the same
-// all-learner pass and reduction as the exact path.
+// One step with the chunk-wise selector, the way chosen by the two rules above: one launch; or the leader's winners and memory, the
+// other learners, the sum; or maxima by atomics, marks, then the same all-learner pass and reduction as the exact path.
 template <typename G>
 scalecom_status launch_chunked(scalecom_ctx* ctx, const LearnerPtrs& lp, int n_learners, int n_tensors, int64_t k_total,
                                float beta, float lr, int leader, int32_t* idx_out, float* red_out)
@@ -1093,7 +1093,6 @@ constexpr int64_t kStaticNumelMax = SCALECOM_STATIC_NUMEL_MAX;
 constexpr int kStaticLearnersMax = SCALECOM_STATIC_LEARNERS_MAX;
 constexpr int64_t kStaticKMax = SCALECOM_STATIC_K_MAX;
 constexpr int64_t kStaticShortMax = 1 << 20;      // longer vectors take the long path: four bytes per position are kept for the short one
-static_assert(kStaticShortMax <= kShortSegParts * kShortPartMax / 2, "parts of one row and no more of them than a segment may have: their blocks are in the order of the parts");
 constexpr WsLayout kStaticLayout = layout_for(kStaticNumelMax, 1, kStaticLearnersMax, kStaticKMax, kStaticShortMax, false);
 constexpr size_t kStaticBytes = kStaticLayout.total;
 static_assert(kStaticBytes <= (size_t{16} << 20), "the static workspace stays modest");

@@ -224,18 +224,17 @@ __device__ __forceinline__ bool short_far_off(const float4& m, const float4& g, 
     return static_cast<float>(above) > 4.0f * (2.0f * share + 8.0f) || 8u * near < 4u * below;
 }
 
-// The index of a block's part among all parts (the table of parts is in the order of the blocks).
-template <int P>
-__device__ __forceinline__ int short_part_index(const PartDesc& d)
+// The part that a block works on: an eighth of them on each XCD, or all in turn (see short_eighths).
+__device__ __forceinline__ uint32_t short_piece(bool eighths)
 {
-    return d.part_first + (d.a0 - (d.begin & ~(kVec - 1))) / P;
+    return eighths ? piece_by_xcd(blockIdx.x, gridDim.x) : blockIdx.x;
 }
 
 // One block per part: R rows of four consecutive positions per thread.  The loads of the part are
 // requested before anything else is looked at.
 template <typename G, int T, int R>
 __device__ __forceinline__ void
-short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const PartDesc* __restrict__ parts,
+short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const PartDesc* __restrict__ parts, uint32_t part_index,
               const uint32_t* __restrict__ preds, const uint32_t* __restrict__ lead_mine, uint4* __restrict__ used,
               uint16_t* __restrict__ counts, uint32_t* __restrict__ keys, unsigned long long* __restrict__ stats)
 {
@@ -246,8 +245,7 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
     __shared__ uint32_t res[2];
     __shared__ uint32_t cnt[kShortCols], first[kShortCols], mixed[kShortCols];
     __shared__ uint64_t heavy;
-    const PartDesc d = parts[blockIdx.x];
-    const uint32_t part_index = static_cast<uint32_t>(short_part_index<P>(d));
+    const PartDesc d = parts[part_index];
     const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
     const int64_t begin = d.begin, end = d.end;
     // (without a branch, or the compiler waits for these loads before it requests the part's; any valid address where they are not used)
@@ -379,11 +377,11 @@ short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float l
 
 template <typename G, int T, int R>
 __global__ void __launch_bounds__(T)
-k_short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const PartDesc* __restrict__ parts,
+k_short_collect(const float* __restrict__ mem, const G* __restrict__ grad, float lr, const PartDesc* __restrict__ parts, bool eighths,
                 const uint32_t* __restrict__ preds, const uint32_t* __restrict__ lead_mine, uint4* __restrict__ used,
                 uint16_t* __restrict__ counts, uint32_t* __restrict__ keys, unsigned long long* __restrict__ stats)
 {
-    short_collect<G, T, R>(mem, grad, lr, parts, preds, lead_mine, used, counts, keys, stats);
+    short_collect<G, T, R>(mem, grad, lr, parts, short_piece(eighths), preds, lead_mine, used, counts, keys, stats);
 }
 
 // What k_short_collect leaves of one vector, and where its expectations are kept.
@@ -402,9 +400,9 @@ k_short_collect_two(const float* __restrict__ mem, const G* __restrict__ grad, f
                     const PartDesc* __restrict__ parts, ShortVector a, ShortVector b)
 {
     if (blockIdx.y == 0)
-        short_collect<G, T, R>(mem, grad, lr, parts, a.preds, a.lead_mine, a.used, a.counts, a.keys, nullptr);
+        short_collect<G, T, R>(mem, grad, lr, parts, blockIdx.x, a.preds, a.lead_mine, a.used, a.counts, a.keys, nullptr);
     else
-        short_collect<NoGrad, T, R>(sum, nullptr, 0.0f, parts, b.preds, b.lead_mine, b.used, b.counts, b.keys, nullptr);
+        short_collect<NoGrad, T, R>(sum, nullptr, 0.0f, parts, blockIdx.x, b.preds, b.lead_mine, b.used, b.counts, b.keys, nullptr);
 }
 
 // The listed keys of a segment's parts [0, n_parts), words [from[p], to[p]) of part p's slice, to `f`
@@ -528,7 +526,7 @@ __device__ __forceinline__ ShortFound short_search(ShortLds<T>& lds, const PartD
     uint32_t* res = lds.res;
     unsigned long long* found = lds.found;
     const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
-    const int mine = short_part_index<P>(d) - d.part_first, n_parts = d.n_parts;
+    const int mine = (d.a0 - (d.begin & ~(kVec - 1))) / P, n_parts = d.n_parts;
     const uint32_t k = static_cast<uint32_t>(d.k);
 
     // The counts of all parts, requested at once: eight lanes per part, eight parts per wave and turn.
@@ -867,7 +865,7 @@ __device__ __forceinline__ void short_record(const PartDesc& d, const uint4& u, 
 template <typename G, int T, int R, int OCC>
 __global__ void __launch_bounds__(T, OCC)
 k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, float one_minus_beta,
-             const PartDesc* __restrict__ parts, uint32_t* __restrict__ preds, uint32_t* __restrict__ lead_mine,
+             const PartDesc* __restrict__ parts, bool eighths, uint32_t* __restrict__ preds, uint32_t* __restrict__ lead_mine,
              const uint4* __restrict__ used, const uint16_t* __restrict__ counts, const uint32_t* __restrict__ keys,
              int32_t* __restrict__ idx_out, float* __restrict__ red_out, unsigned long long* __restrict__ stats)
 {
@@ -876,7 +874,7 @@ k_short_step(LearnerPtrs lp, int n_learners, int leader, float lr, float beta, f
     constexpr bool kAhead = OCC <= 4 && R == 1;
     __shared__ ShortLds<T> lds;
     __shared__ uint32_t in_row[2][2][W];                    // of two rows in turn: members for sure / ties
-    const PartDesc d = parts[blockIdx.x];
+    const PartDesc d = parts[short_piece(eighths)];
     const int t = threadIdx.x, lane = t % kLanes, wave = __builtin_amdgcn_readfirstlane(t / kLanes);
     const int64_t begin = d.begin, end = d.end;
     const uint32_t k = static_cast<uint32_t>(d.k);

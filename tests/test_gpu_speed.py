@@ -133,6 +133,35 @@ def test_further_learners_on_short_supertiles():
         ctx.close()
 
 
+@pytest.mark.parametrize("n,large,others,factor", [
+    (2, 1_750_000, [262_144] * 21, 1.1), (8, 880_000, [60_000] * 20, 1.38), (2, 880_000, [4_000] * 300, 1.38),
+])
+def test_diagnostic_with_one_large_tensor(n, large, others, factor):
+    """Every block searches its tensor's index set, the longer the more parts that has.  One large tensor beside smaller ones, against as many positions in
+    tensors of one size: 1.01, 1.23 and 1.24 times the time with its parts spread over the chip, 1.01, 1.53 and 1.56 with all of them on one or two XCDs."""
+    numel = large + sum(others)
+    count = len(others) + 1
+    grad = [_normal(numel, i) for i in range(n)]
+    calls, keep = [], []
+    for sizes in ([large] + others, [numel // count] * count):
+        offsets = [0]
+        for s in sizes:
+            offsets.append(offsets[-1] + s)
+        ks = [-(-s // 50) for s in sizes]
+        ctx = binding.scalecom_init(numel, n, torch.float32, count, DEV, k_max=sum(ks))
+        mem = [torch.zeros(numel, device=DEV) for _ in range(n)]
+        d = torch.empty(count, dtype=torch.int32, device=DEV)
+        for t in range(2 * n):
+            ctx.scalecom_step_layers(mem, grad, offsets, ks, 0.1, 0.1, t)
+        keep.append(ctx)
+        calls.append(lambda t, c=ctx, mem=mem, o=offsets, ks=ks, d=d: c.scalecom_hamming_distance(mem, grad, o, ks, 0.1, t, d))
+    got, base = _times(calls)
+    print(f"[speed] diagnostic {large} + {len(others)} tensors, {n} learners: {got:.1f} us, equal: {base:.1f} us, {got / base:.3f}", flush=True)
+    assert got <= factor * base
+    for ctx in keep:
+        ctx.close()
+
+
 @pytest.mark.parametrize("numel,kind", [(200_003, "drop"), (1_048_576, "equal"), (1_048_576, "drop"), (2_097_152, "equal"),
                                         (2_097_152, "sign"), (2_097_152, "two"), (2_097_152, "near"), (2_097_152, "drop")])
 def test_ties_and_jumps_on_short_layouts(numel, kind):
