@@ -27,8 +27,9 @@ k_apply_update(float* __restrict__ theta, int64_t numel, const int32_t* __restri
 // change the order of magnitudes).  Bound by the read of all (mem, grad): a block takes one wave tile, one wave per
 // learner (the pattern that moves most bytes, see k_update) or, from ten learners on, per two of them (A), and adds the learners up
 // through LDS.  us a call, A = 1 / 2: 16 x 20 M 746 / 604 (5.2 TB/s with blocks of 16 waves), 12 x 20 M 491 / 474, 64 x 4 M 424 / 421, but 8 x 25.6 M 415 / 419,
-// 6 x 30 M 407 / 411.  At 8 x 25.6 M the kernel takes 282 us (6.2 TB/s); one thread per four positions and all learners 303, one per position 333,
-// two tiles per block 304, four learners per wave 300, an eighth of the tiles per XCD 300.
+// 6 x 30 M 407 / 411.  At 8 x 25.6 M the kernel takes 281 us at best (6.2 TB/s; 299 on average over the 100 calls of another
+// run); beside the 281: one thread per four positions and all learners 303, one per position 333, two tiles per block 304, four learners per wave 300, an
+// eighth of the tiles per XCD 300.
 // The first threads zero `clear_words` words from `clear_from` on the way: the selection's scratch
 // zone, which the selection before this kernel has used and the one after it expects clean.
 constexpr int kSumWaves = 16;                    // waves of a block at most: further learners take turns
