@@ -858,7 +858,7 @@ __device__ __forceinline__ void short_record(const PartDesc& d, const uint4& u, 
 // sizes that is as fast as one learner per block (4 M elements in all: 16 us either way; 28 M: 57 us
 // against 53 us), and the sums over learners stay in registers.
 //   OCC: waves per SIMD that the registers are kept for, 4 or 6.  Layouts of several tensors have more blocks than the chip runs at once: with few
-// learners six hide more of each other's searches (60 tensors, 1213 blocks of 512 threads, 4 learners bfloat16 41.0 us a step with four, 39.4 with six;
+// learners six hide more of each other's searches (60 tensors, 1183 blocks of 512 threads, 4 learners bfloat16 41.0 us a step with four, 39.4 with six;
 // 150 tensors x 3 37.2 / 36.8; but 60 x 8 63.1 / 65.0, 200 x 8 52.2 / 54.0, 30 x 6 33.2 / 34.0).  With four the registers hold the first
 // learners' loads of the block's only row while it searches: blocks that are all on the chip at once search together
 // and leave memory idle meanwhile (4 x 1 M 22.9 -> 20.1 us, 3 x 200 003 13.5 -> 12.4, 8 x 300 000 17.0 -> 15.7; of two rows the first: no gain).
